@@ -1,22 +1,24 @@
-"""Thin ctypes binding of liboptireduce_hip.so: argument marshalling only.
+"""Thin binding of liboptireduce_hip.so: argument marshalling only (ctypes; natively where kernels are enqueued).
 
 Every function has the name and argument order of its C entry point in include/optireduce.h and
 takes torch tensors that already live on the GPU (torch is used for device memory and streams,
 nothing else).  A non-zero status raises OptiReduceError.  There is no CPU fallback: if the
-library is not built, importing this module raises.
+library or the native marshalling module is not built, importing this module raises.
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
 
-import torch
+import torch  # noqa: F401  (its libraries have to be loaded before the native module)
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "liboptireduce_hip.so")
 if not os.path.exists(_LIB_PATH):
     raise ImportError(
         "liboptireduce_hip.so is not built (%s); run `python -m paper_2310_06993_amd.build`" % _LIB_PATH)
 lib = C.CDLL(_LIB_PATH)
+
+from . import _calls  # noqa: E402
 
 _u64, _int, _p, _sz = C.c_uint64, C.c_int, C.c_void_p, C.c_size_t
 
@@ -99,12 +101,6 @@ def _ptr(t):
     return t.data_ptr()
 
 
-def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
-
-
 def _check(status, where):
     if status != OR_OK:
         raise OptiReduceError(status, where)
@@ -127,95 +123,21 @@ def or_time_next_call(start_event, stop_event):
     _check(lib.or_time_next_call(start_event, stop_event), "or_time_next_call")
 
 
-def or_rht_encode(grad, n, block_log2, seed, out, stream=None):
-    _check(lib.or_rht_encode(_ptr(grad), n, block_log2, seed, _ptr(out), _stream(stream)), "or_rht_encode")
+# The entry points that enqueue kernels, marshalled natively (csrc/calls.cpp): same names and argument order as the C
+# ones, device pointers are tensors or None, a workspace carries its own size, `count_out`, `workspace`, `totals` (of
+# or_reduce_decode_batched) and `stream` may be left out.  `stream`: None (the current stream), a torch stream or a raw
+# handle.  Descriptor arrays are those of make_buckets / make_stage_buckets; `totals` an int64 device tensor of n_buckets
+# entries (or_received_total: one entry).
+from ._calls import (  # noqa: E402
+    or_finalize, or_finalize_bf16, or_finalize_decode, or_finalize_decode_batched, or_finalize_decode_bf16, or_fused_path,
+    or_fused_path_batched, or_fused_path_batched_monitored, or_fused_path_bf16, or_fused_path_bf16_static, or_masked_reduce,
+    or_masked_reduce_batched, or_masked_reduce_bf16, or_masked_reduce_pairs, or_received_total, or_reduce_decode,
+    or_reduce_decode_batched, or_reduce_decode_bf16, or_rht_decode, or_rht_decode_at, or_rht_decode_bf16,
+    or_rht_decode_masked, or_rht_decode_masked_bf16, or_rht_encode, or_rht_encode_at, or_rht_encode_bf16)
 
-
-def or_rht_encode_at(grad, n, block_log2, seed, base_index, out, stream=None):
-    _check(lib.or_rht_encode_at(_ptr(grad), n, block_log2, seed, base_index, _ptr(out), _stream(stream)),
-           "or_rht_encode_at")
-
-
-def or_rht_encode_bf16(grad, n, block_log2, seed, base_index, out, stream=None):
-    _check(lib.or_rht_encode_bf16(_ptr(grad), n, block_log2, seed, base_index, _ptr(out), _stream(stream)),
-           "or_rht_encode_bf16")
-
-
-def or_masked_reduce(shards, masks, N, shard_len, sum_out, count_out, stream=None):
-    _check(lib.or_masked_reduce(_ptr(shards), _ptr(masks), N, shard_len, _ptr(sum_out), _ptr(count_out),
-                                _stream(stream)), "or_masked_reduce")
-
-
-def or_masked_reduce_bf16(shards, masks, N, shard_len, sum_out, count_out, stream=None):
-    _check(lib.or_masked_reduce_bf16(_ptr(shards), _ptr(masks), N, shard_len, _ptr(sum_out), _ptr(count_out),
-                                     _stream(stream)), "or_masked_reduce_bf16")
-
-
-def or_rht_decode(agg, n, block_log2, seed, out, stream=None):
-    _check(lib.or_rht_decode(_ptr(agg), n, block_log2, seed, _ptr(out), _stream(stream)), "or_rht_decode")
-
-
-def or_rht_decode_at(agg, n, block_log2, seed, base_index, out, stream=None):
-    _check(lib.or_rht_decode_at(_ptr(agg), n, block_log2, seed, base_index, _ptr(out), _stream(stream)),
-           "or_rht_decode_at")
-
-
-def or_rht_decode_bf16(agg, n, block_log2, seed, base_index, out, stream=None):
-    _check(lib.or_rht_decode_bf16(_ptr(agg), n, block_log2, seed, base_index, _ptr(out), _stream(stream)),
-           "or_rht_decode_bf16")
-
-
-def or_finalize_decode(total, count, n, block_log2, seed, base_index, out, stream=None):
-    _check(lib.or_finalize_decode(_ptr(total), _ptr(count), n, block_log2, seed, base_index, _ptr(out),
-                                  _stream(stream)), "or_finalize_decode")
-
-
-def or_finalize_decode_bf16(total, count, n, block_log2, seed, base_index, out, stream=None):
-    _check(lib.or_finalize_decode_bf16(_ptr(total), _ptr(count), n, block_log2, seed, base_index, _ptr(out),
-                                       _stream(stream)), "or_finalize_decode_bf16")
-
-
-def _ws(workspace):
-    if workspace is None:
-        return None, 0
-    return _ptr(workspace), workspace.numel() * workspace.element_size()
-
-
-def or_reduce_decode(shards, masks, N, shard_len, block_log2, seed, base_index, out, count_out=None,
-                     workspace=None, stream=None):
-    w, wb = _ws(workspace)
-    _check(lib.or_reduce_decode(_ptr(shards), _ptr(masks), N, shard_len, block_log2, seed, base_index, _ptr(out),
-                                _ptr(count_out), w, wb, _stream(stream)), "or_reduce_decode")
-
-
-def or_reduce_decode_bf16(shards, masks, N, shard_len, block_log2, seed, base_index, out, count_out=None,
-                          workspace=None, stream=None):
-    w, wb = _ws(workspace)
-    _check(lib.or_reduce_decode_bf16(_ptr(shards), _ptr(masks), N, shard_len, block_log2, seed, base_index,
-                                     _ptr(out), _ptr(count_out), w, wb, _stream(stream)), "or_reduce_decode_bf16")
-
-
-def or_fused_path(grads, masks, N, shard_len, block_log2, seed, base_index, out, count_out=None, workspace=None,
-                  stream=None):
-    w, wb = _ws(workspace)
-    _check(lib.or_fused_path(_ptr(grads), _ptr(masks), N, shard_len, block_log2, seed, base_index, _ptr(out),
-                             _ptr(count_out), w, wb, _stream(stream)), "or_fused_path")
-
-
-def or_fused_path_bf16(grads, masks, N, shard_len, block_log2, seed, base_index, out, count_out=None,
-                       workspace=None, stream=None):
-    w, wb = _ws(workspace)
-    _check(lib.or_fused_path_bf16(_ptr(grads), _ptr(masks), N, shard_len, block_log2, seed, base_index, _ptr(out),
-                                  _ptr(count_out), w, wb, _stream(stream)), "or_fused_path_bf16")
-
+_calls.bind({name: C.cast(getattr(lib, name), _p).value for name in _SIGS}, _check, lambda o: C.cast(o, _p).value)
 
 OR_STATIC_MAX_SHARD_LEN = 4194304
-
-
-def or_fused_path_bf16_static(grads, masks, N, shard_len, block_log2, seed, base_index, out, count_out=None,
-                              stream=None):
-    _check(lib.or_fused_path_bf16_static(_ptr(grads), _ptr(masks), N, shard_len, block_log2, seed, base_index,
-                                         _ptr(out), _ptr(count_out), _stream(stream)), "or_fused_path_bf16_static")
 
 
 def make_buckets(items):
@@ -228,26 +150,6 @@ def make_buckets(items):
     return arr
 
 
-def or_fused_path_batched(buckets, n_buckets, N, block_log2, bf16, workspace=None, stream=None):
-    w, wb = _ws(workspace)
-    _check(lib.or_fused_path_batched(C.cast(buckets, _p), n_buckets, N, block_log2, int(bool(bf16)), w, wb,
-                                     _stream(stream)), "or_fused_path_batched")
-
-
-def or_fused_path_batched_monitored(buckets, n_buckets, N, block_log2, bf16, totals, workspace=None, stream=None):
-    """totals: an int64 device tensor of n_buckets entries, or None."""
-    w, wb = _ws(workspace)
-    _check(lib.or_fused_path_batched_monitored(C.cast(buckets, _p), n_buckets, N, block_log2, int(bool(bf16)),
-                                               _ptr(totals), w, wb, _stream(stream)),
-           "or_fused_path_batched_monitored")
-
-
-def or_reduce_decode_batched(buckets, n_buckets, N, block_log2, bf16, totals=None, workspace=None, stream=None):
-    w, wb = _ws(workspace)
-    _check(lib.or_reduce_decode_batched(C.cast(buckets, _p), n_buckets, N, block_log2, int(bool(bf16)),
-                                        _ptr(totals), w, wb, _stream(stream)), "or_reduce_decode_batched")
-
-
 def make_stage_buckets(items):
     """items: iterable of (shards, masks, sum, count, out, shard_len, seed, base_index) with device tensors
     (or None where the call ignores the field) -> a host array of or_stage_bucket."""
@@ -258,48 +160,9 @@ def make_stage_buckets(items):
     return arr
 
 
-def or_masked_reduce_batched(buckets, n_buckets, N, bf16, stream=None):
-    _check(lib.or_masked_reduce_batched(C.cast(buckets, _p), n_buckets, N, int(bool(bf16)), _stream(stream)),
-           "or_masked_reduce_batched")
-
-
-def or_finalize_decode_batched(buckets, n_buckets, block_log2, bf16, stream=None):
-    _check(lib.or_finalize_decode_batched(C.cast(buckets, _p), n_buckets, block_log2, int(bool(bf16)),
-                                          _stream(stream)), "or_finalize_decode_batched")
-
-
-def or_finalize(total, count, shard_len, mean_out, stream=None):
-    _check(lib.or_finalize(_ptr(total), _ptr(count), shard_len, _ptr(mean_out), _stream(stream)), "or_finalize")
-
-
-def or_finalize_bf16(total, count, shard_len, mean_out, stream=None):
-    _check(lib.or_finalize_bf16(_ptr(total), _ptr(count), shard_len, _ptr(mean_out), _stream(stream)),
-           "or_finalize_bf16")
-
-
-def or_received_total(count, shard_len, total_out, stream=None):
-    """total_out: a one-element int64 device tensor."""
-    _check(lib.or_received_total(_ptr(count), shard_len, _ptr(total_out), _stream(stream)), "or_received_total")
-
-
 def or_loss_decision(received_total, N, shard_len, policy, prev_transform_on):
     """Host arithmetic only.  policy: an or_loss_policy.  Returns (action, transform_on, loss)."""
     act, ton, loss = C.c_int(), C.c_int(), C.c_double()
     _check(lib.or_loss_decision(int(received_total), N, shard_len, C.byref(policy), int(bool(prev_transform_on)),
                                 C.byref(act), C.byref(ton), C.byref(loss)), "or_loss_decision")
     return act.value, ton.value, loss.value
-
-
-def or_rht_decode_masked(agg, mask, n, block_log2, seed, base_index, out, stream=None):
-    _check(lib.or_rht_decode_masked(_ptr(agg), _ptr(mask), n, block_log2, seed, base_index, _ptr(out),
-                                    _stream(stream)), "or_rht_decode_masked")
-
-
-def or_rht_decode_masked_bf16(agg, mask, n, block_log2, seed, base_index, out, stream=None):
-    _check(lib.or_rht_decode_masked_bf16(_ptr(agg), _ptr(mask), n, block_log2, seed, base_index, _ptr(out),
-                                         _stream(stream)), "or_rht_decode_masked_bf16")
-
-
-def or_masked_reduce_pairs(sums, counts, masks, G, shard_len, sum_out, count_out, stream=None):
-    _check(lib.or_masked_reduce_pairs(_ptr(sums), _ptr(counts), _ptr(masks), G, shard_len, _ptr(sum_out),
-                                      _ptr(count_out), _stream(stream)), "or_masked_reduce_pairs")
