@@ -16,7 +16,7 @@ constexpr int K = OR_K;
 typedef Geo<K> G;
 
 #define OR_LAUNCHER_T(name, kernel, threads)                                                 \
-  /* serves output tiles a.unit0 .. a.unit0 + units - 1, one workgroup per tile */          \
+  /* serves output tiles 0 .. units - 1, one workgroup per tile */                           \
   hipError_t name(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {    \
     if (units == 0) return hipSuccess;                                                       \
     if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;                                  \
@@ -33,41 +33,23 @@ typedef Geo<K> G;
     return launch_kernel(kernel, dim3((unsigned)blocks), dim3(G::THREADS), s, pos, a);       \
   }
 
-#define OR_SPLIT_LAUNCHER(name, LAUNCHER, kernel_full, kernel_tail)                          \
-  LAUNCHER(name##_full, kernel_full)                                                         \
-  LAUNCHER(name##_tail, kernel_tail)                                                         \
-  /* a.unit0 = number of leading tiles that need no bounds checks; the rest go to the checked kernel */ \
-  hipError_t name(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {    \
-    const unsigned long long nfull = a.unit0 < units ? a.unit0 : units, ntail = units - nfull; \
-    PathArgs b = a;                                                                          \
-    b.unit0 = 0;                                                                             \
-    if (nfull) {                                                                             \
-      if (hipError_t e = name##_full(b, nfull, s, ntail ? (pos & LAUNCH_FIRST) : pos)) return e; \
-    }                                                                                        \
-    if (ntail) {                                                                             \
-      b.unit0 = nfull;                                                                       \
-      return name##_tail(b, ntail, s, nfull ? (pos & LAUNCH_LAST) : pos);                    \
-    }                                                                                        \
-    return hipSuccess;                                                                       \
-  }
-
 #if OR_K <= 14
-#define OR_ENC(In, Wire, FULL) (k_encode<K, In, Wire, FULL>)
-#define OR_DEC(Out, FIN, FULL, MASKED) (k_decode<K, Out, FIN, FULL, MASKED>)
+#define OR_ENC(In, Wire) (k_encode<K, In, Wire>)
+#define OR_DEC(Out, FIN, MASKED) (k_decode<K, Out, FIN, MASKED>)
 #define OR_XFORM_LAUNCHER OR_LAUNCHER
 #else
-#define OR_ENC(In, Wire, FULL) (k_encode_block<K, In, Wire, FULL>)
-#define OR_DEC(Out, FIN, FULL, MASKED) (k_decode_block<K, Out, FIN, FULL, MASKED>)
+#define OR_ENC(In, Wire) (k_encode_block<K, In, Wire>)
+#define OR_DEC(Out, FIN, MASKED) (k_decode_block<K, Out, FIN, MASKED>)
 #define OR_XFORM_LAUNCHER OR_BLOCK_LAUNCHER
 #endif
-OR_SPLIT_LAUNCHER(enc_f32, OR_XFORM_LAUNCHER, OR_ENC(float, float, true), OR_ENC(float, float, false))
-OR_SPLIT_LAUNCHER(enc_bf16, OR_XFORM_LAUNCHER, OR_ENC(bf16_t, bf16_t, true), OR_ENC(bf16_t, bf16_t, false))
-OR_SPLIT_LAUNCHER(dec_f32, OR_XFORM_LAUNCHER, OR_DEC(float, false, true, false), OR_DEC(float, false, false, false))
-OR_SPLIT_LAUNCHER(dec_bf16, OR_XFORM_LAUNCHER, OR_DEC(bf16_t, false, true, false), OR_DEC(bf16_t, false, false, false))
-OR_SPLIT_LAUNCHER(fdec_f32, OR_XFORM_LAUNCHER, OR_DEC(float, true, true, false), OR_DEC(float, true, false, false))
-OR_SPLIT_LAUNCHER(fdec_bf16, OR_XFORM_LAUNCHER, OR_DEC(bf16_t, true, true, false), OR_DEC(bf16_t, true, false, false))
-OR_SPLIT_LAUNCHER(mdec_f32, OR_XFORM_LAUNCHER, OR_DEC(float, false, true, true), OR_DEC(float, false, false, true))
-OR_SPLIT_LAUNCHER(mdec_bf16, OR_XFORM_LAUNCHER, OR_DEC(bf16_t, false, true, true), OR_DEC(bf16_t, false, false, true))
+OR_XFORM_LAUNCHER(enc_f32, OR_ENC(float, float))
+OR_XFORM_LAUNCHER(enc_bf16, OR_ENC(bf16_t, bf16_t))
+OR_XFORM_LAUNCHER(dec_f32, OR_DEC(float, false, false))
+OR_XFORM_LAUNCHER(dec_bf16, OR_DEC(bf16_t, false, false))
+OR_XFORM_LAUNCHER(fdec_f32, OR_DEC(float, true, false))
+OR_XFORM_LAUNCHER(fdec_bf16, OR_DEC(bf16_t, true, false))
+OR_XFORM_LAUNCHER(mdec_f32, OR_DEC(float, false, true))
+OR_XFORM_LAUNCHER(mdec_bf16, OR_DEC(bf16_t, false, true))
 #if OR_K <= 14
 // reduce+decode of 2^13 and 2^14 blocks keeps 32 entries per lane
 constexpr int KR = (K == 13 || K == 14) ? K + kWide : K;

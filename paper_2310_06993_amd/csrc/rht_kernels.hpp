@@ -42,7 +42,7 @@ struct PathArgs {
   u64 n_pad;               // padded length = vector length on the encoded side; shard_len for reduce/fused
   u64 seed;
   u64 base;                // index of entry 0 in the sign stream
-  u64 unit0;               // first output tile served by this launch
+  u64 unit0;               // encode / decode: number of leading tiles that need no bounds checks
   int N;                   // workers
   int k;                   // block_log2
   float scale;             // 2^(-k/2) rounded to fp32
@@ -105,16 +105,13 @@ __device__ __forceinline__ void across_tiles(float (&v)[PARTS][NR]) {
 }
 
 // Sec. 3.3 encode: out = B^(-1/2) H D x, blockwise; pad of the last block is zero.
-// FULL = true: every tile of this launch lies wholly inside the input and the output (no bounds checks);
-// the host sends the ragged end of a vector to a FULL = false launch of its own, so that the checked
-// accesses do not cost the common case registers.
+// FULL: every access of the tile lies inside the vectors (no bounds checks).  The first a.unit0 tiles of a launch are
+// such tiles, the ragged end takes the checked form, in the same launch: as a launch of its own it cost 2.5 us of host
+// time and a gap on the GPU (25.6 M fp32 entries, 6240 tiles: 40.2 -> 37.5 us; one 4096-entry block: 6.0 -> 3.5 us).
 template <int K, class In, class Wire, bool FULL>
-__global__ __launch_bounds__(Geo<K>::THREADS) void k_encode(PathArgs a) {
+__device__ __forceinline__ void encode_tile(const PathArgs& a, u64 unit, float* xbuf) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R;
-  static_assert(Geo<K>::PARTS == 1, "larger blocks use k_encode_block");
-  __shared__ float xbuf[Geo<K>::Q > 0 ? T : 1];
   const int wave = wave_id(), lane = lane_id(), kt = tile_bits<K>(a.k);
-  const u64 unit = a.unit0 + blockIdx.x;
   float v[R];
   load_tile<K, false, FULL, OR_NT_ENC>((const In*)a.in, unit * T, a.n, wave, lane, v);
   u64 sg[R];
@@ -126,17 +123,21 @@ __global__ __launch_bounds__(Geo<K>::THREADS) void k_encode(PathArgs a) {
   for (int r = 0; r < R; ++r) v[r] *= c;
   store_tile<K, true, FULL>((Wire*)a.out, unit * T, a.n_pad, wave, lane, v);
 }
+template <int K, class In, class Wire>
+__global__ __launch_bounds__(Geo<K>::THREADS) void k_encode(PathArgs a) {
+  static_assert(Geo<K>::PARTS == 1, "larger blocks use k_encode_block");
+  __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
+  if (blockIdx.x < a.unit0) encode_tile<K, In, Wire, true>(a, blockIdx.x, xbuf);
+  else encode_tile<K, In, Wire, false>(a, blockIdx.x, xbuf);
+}
 
-// The same for blocks above 2^14: workgroup x encodes block a.unit0 / PARTS + x (a.unit0 counts tiles).
-// FULL = false: the block is cut short by the end of the input (its pad reads as zero); the output always
-// holds whole blocks.
+// The same for blocks above 2^14: workgroup x encodes block x (a.unit0 counts tiles).  FULL = false: the block is cut
+// short by the end of the input (its pad reads as zero); the output always holds whole blocks.
 template <int K, class In, class Wire, bool FULL>
-__global__ __launch_bounds__(Geo<K>::THREADS) void k_encode_block(PathArgs a) {
+__device__ __forceinline__ void encode_block(const PathArgs& a, float (*xbuf)[Geo<K>::T]) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R, HB = Geo<K>::HB, PARTS = Geo<K>::PARTS;
-  static_assert(PARTS > 1, "blocks above 2^14");
-  __shared__ float xbuf[2][T];   // the registers allow one workgroup per CU anyway: alternate, one barrier per exchange
   const int wave = wave_id(), lane = lane_id(), kt = Geo<K>::KT;
-  const u64 tile0 = a.unit0 + ((u64)blockIdx.x << HB);
+  const u64 tile0 = (u64)blockIdx.x << HB;
   float v[PARTS][R];
 #pragma unroll
   for (int q = 0; q < PARTS; ++q) load_tile<K, false, FULL, OR_NT_ENCB>((const In*)a.in, (tile0 + q) * T, a.n, wave, lane, v[q]);
@@ -153,6 +154,13 @@ __global__ __launch_bounds__(Geo<K>::THREADS) void k_encode_block(PathArgs a) {
     for (int r = 0; r < R; ++r) v[p][r] *= c;
     store_tile<K, true, true>((Wire*)a.out, (tile0 + p) * T, a.n_pad, wave, lane, v[p]);
   }
+}
+template <int K, class In, class Wire>
+__global__ __launch_bounds__(Geo<K>::THREADS) void k_encode_block(PathArgs a) {
+  static_assert(Geo<K>::PARTS > 1, "blocks above 2^14");
+  __shared__ float xbuf[2][Geo<K>::T];   // the registers allow one workgroup per CU anyway: alternate, one barrier per exchange
+  if ((u64)blockIdx.x << Geo<K>::HB < a.unit0) encode_block<K, In, Wire, true>(a, xbuf);
+  else encode_block<K, In, Wire, false>(a, xbuf);
 }
 
 // Mean tile (layout B) for decode: either the mean itself, or sum / count with 0 where count is 0
@@ -180,12 +188,11 @@ __device__ __forceinline__ void load_mean_tile(const PathArgs& a, u64 tile, int 
   }
 }
 
-// Sec. 3.3 / Sec. 4 decode: out = D B^(-1/2) H mean, first n entries kept.
+// Sec. 3.3 / Sec. 4 decode: out = D B^(-1/2) H mean, first n entries kept.  FULL as in encode_tile.
 template <int K, class Out, bool FINALIZE, bool FULL, bool MASKED = false>
-__device__ __forceinline__ void decode_tile(const PathArgs& a, u64 unit) {
+__device__ __forceinline__ void decode_tile(const PathArgs& a, u64 unit, float* xbuf) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R;
   static_assert(Geo<K>::PARTS == 1, "larger blocks use k_decode_block");
-  __shared__ float xbuf[Geo<K>::Q > 0 ? T : 1];
   const int wave = wave_id(), lane = lane_id(), kt = tile_bits<K>(a.k);
   float v[R];
   load_mean_tile<K, FINALIZE, FULL, MASKED>(a, unit, wave, lane, v);
@@ -198,20 +205,20 @@ __device__ __forceinline__ void decode_tile(const PathArgs& a, u64 unit) {
   apply_signs(v, sg);
   store_tile<K, false, FULL>((Out*)a.out, unit * T, a.n, wave, lane, v);
 }
-template <int K, class Out, bool FINALIZE, bool FULL, bool MASKED = false>
+template <int K, class Out, bool FINALIZE, bool MASKED>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_decode(PathArgs a) {
-  decode_tile<K, Out, FINALIZE, FULL, MASKED>(a, a.unit0 + blockIdx.x);
+  __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
+  if (blockIdx.x < a.unit0) decode_tile<K, Out, FINALIZE, true, MASKED>(a, blockIdx.x, xbuf);
+  else decode_tile<K, Out, FINALIZE, false, MASKED>(a, blockIdx.x, xbuf);
 }
 
 // The same for blocks above 2^14 (see k_encode_block).  The input holds whole blocks; FULL = false: the
 // output is cut short inside this block.
-template <int K, class Out, bool FINALIZE, bool FULL, bool MASKED = false>
-__global__ __launch_bounds__(Geo<K>::THREADS) void k_decode_block(PathArgs a) {
+template <int K, class Out, bool FINALIZE, bool FULL, bool MASKED>
+__device__ __forceinline__ void decode_block(const PathArgs& a, float (*xbuf)[Geo<K>::T]) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R, HB = Geo<K>::HB, PARTS = Geo<K>::PARTS;
-  static_assert(PARTS > 1, "blocks above 2^14");
-  __shared__ float xbuf[2][T];
   const int wave = wave_id(), lane = lane_id(), kt = Geo<K>::KT;
-  const u64 tile0 = a.unit0 + ((u64)blockIdx.x << HB);
+  const u64 tile0 = (u64)blockIdx.x << HB;
   float v[PARTS][R];
 #pragma unroll
   for (int q = 0; q < PARTS; ++q) load_mean_tile<K, FINALIZE, true, MASKED>(a, tile0 + q, wave, lane, v[q]);
@@ -227,6 +234,13 @@ __global__ __launch_bounds__(Geo<K>::THREADS) void k_decode_block(PathArgs a) {
     apply_block_signs(v[p], slo, shi, p);
     store_tile<K, false, FULL>((Out*)a.out, (tile0 + p) * T, a.n, wave, lane, v[p]);
   }
+}
+template <int K, class Out, bool FINALIZE, bool MASKED>
+__global__ __launch_bounds__(Geo<K>::THREADS) void k_decode_block(PathArgs a) {
+  static_assert(Geo<K>::PARTS > 1, "blocks above 2^14");
+  __shared__ float xbuf[2][Geo<K>::T];
+  if ((u64)blockIdx.x << Geo<K>::HB < a.unit0) decode_block<K, Out, FINALIZE, true, MASKED>(a, xbuf);
+  else decode_block<K, Out, FINALIZE, false, MASKED>(a, xbuf);
 }
 
 // acc += value where the worker's copy arrived.  Arrivals are counted as `full` (workers whose whole
@@ -666,7 +680,8 @@ template <int K, class Out>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_finalize_decode_batched(BatchArgs ba) {
   PathArgs a;
   const u64 unit = bucket_of(ba, a);
-  decode_tile<K, Out, true, kShardTilesFull<K>, false>(a, unit);
+  __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
+  decode_tile<K, Out, true, kShardTilesFull<K>, false>(a, unit, xbuf);
 }
 
 }  // namespace ordev

@@ -356,30 +356,31 @@ __device__ __forceinline__ void transform_transposed(float (&v)[16], float* ta, 
 // promises e0 + tile <= limit.
 // A tile that may be cut short by `limit` goes through raw buffer accesses: the descriptor covers exactly
 // the valid bytes of the tile, so the hardware range check returns 0 for loads beyond it and drops stores
-// beyond it -- no per-lane compares or exec masks.
+// beyond it -- no per-lane compares or exec masks.  NT selects the nontemporal cache policy there too.
 template <class T>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const T* p, u64 e0, u64 limit) {
   const u64 left = limit > e0 ? (limit - e0) * sizeof(T) : 0;
   const int bytes = left > 0x7FFFFFFFull ? 0x7FFFFFFF : (int)left;
   return __builtin_amdgcn_make_buffer_rsrc((void*)(p + e0), 0, bytes, 0x00020000);
 }
-__device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, int entry, const float*) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, entry * 4, 0, 0));
+constexpr int kBufNt = 2;   // cache policy operand of the buffer instructions: nontemporal
+template <bool NT> __device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, int entry, const float*) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, entry * 4, 0, NT ? kBufNt : 0));
 }
-__device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, int entry, const bf16_t*) {
-  return __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, entry * 2, 0, 0) << 16);
+template <bool NT> __device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, int entry, const bf16_t*) {
+  return __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, entry * 2, 0, NT ? kBufNt : 0) << 16);
 }
-__device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, int entry, const uint8_t*) {
-  return (float)__builtin_amdgcn_raw_buffer_load_b8(r, entry, 0, 0);
+template <bool NT> __device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, int entry, const uint8_t*) {
+  return (float)__builtin_amdgcn_raw_buffer_load_b8(r, entry, 0, NT ? kBufNt : 0);
 }
-__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int entry, float v, float*) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, entry * 4, 0, 0);
+template <bool NT> __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int entry, float v, float*) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, entry * 4, 0, NT ? kBufNt : 0);
 }
-__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int entry, float v, bf16_t*) {
-  __builtin_amdgcn_raw_buffer_store_b16(from_f32<bf16_t>(v).bits, r, entry * 2, 0, 0);
+template <bool NT> __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int entry, float v, bf16_t*) {
+  __builtin_amdgcn_raw_buffer_store_b16(from_f32<bf16_t>(v).bits, r, entry * 2, 0, NT ? kBufNt : 0);
 }
-__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int entry, float v, uint8_t*) {
-  __builtin_amdgcn_raw_buffer_store_b8(from_f32<uint8_t>(v), r, entry, 0, 0);
+template <bool NT> __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int entry, float v, uint8_t*) {
+  __builtin_amdgcn_raw_buffer_store_b8(from_f32<uint8_t>(v), r, entry, 0, NT ? kBufNt : 0);
 }
 
 // NT = true: nontemporal loads, for inputs that are read once.  Measured on MI355X: 4-7 % faster for the
@@ -388,7 +389,7 @@ template <int K, bool LAYOUT_B, bool FULL, bool NT = false, class T>
 __device__ __forceinline__ void load_tile(const T* __restrict__ p, u64 e0, u64 limit, int wave, int lane,
                                           float (&v)[Geo<K>::R]) {
   constexpr int R = Geo<K>::R;
-  if (FULL || e0 + Geo<K>::T <= limit) {
+  if constexpr (FULL) {
     // uniform base (scalar registers) + 32-bit lane offset
     const T* q = p + e0;
     const unsigned l = (unsigned)lane;
@@ -399,7 +400,7 @@ __device__ __forceinline__ void load_tile(const T* __restrict__ p, u64 e0, u64 l
     const __amdgpu_buffer_rsrc_t rs = tile_rsrc(p, e0, limit);
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      v[r] = buf_load(rs, (LAYOUT_B ? off_b<K>(wave, r) : off_a<K>(wave, r)) + lane, (const T*)nullptr);
+      v[r] = buf_load<NT>(rs, (LAYOUT_B ? off_b<K>(wave, r) : off_a<K>(wave, r)) + lane, (const T*)nullptr);
   }
 }
 
@@ -409,7 +410,7 @@ template <int K, bool LAYOUT_B, bool FULL, bool NT = false, class T>
 __device__ __forceinline__ void store_tile(T* __restrict__ p, u64 e0, u64 limit, int wave, int lane,
                                            const float (&v)[Geo<K>::R]) {
   constexpr int R = Geo<K>::R;
-  if (FULL || e0 + Geo<K>::T <= limit) {
+  if constexpr (FULL) {
     T* q = p + e0;
     const unsigned l = (unsigned)lane;
 #pragma unroll
@@ -419,7 +420,7 @@ __device__ __forceinline__ void store_tile(T* __restrict__ p, u64 e0, u64 limit,
     const __amdgpu_buffer_rsrc_t rs = tile_rsrc(p, e0, limit);
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      buf_store(rs, (LAYOUT_B ? off_b<K>(wave, r) : off_a<K>(wave, r)) + lane, v[r], (T*)nullptr);
+      buf_store<NT>(rs, (LAYOUT_B ? off_b<K>(wave, r) : off_a<K>(wave, r)) + lane, v[r], (T*)nullptr);
   }
 }
 
