@@ -1,5 +1,6 @@
 // One block-size class of kernels (compile with -DOR_K=0, 11, 12, ... 16).
 #include "launch_table.hpp"
+#include "rht_fused.hpp"
 #if OR_K > 14
 #include "rht_fused_mx.hpp"
 #endif
@@ -11,6 +12,9 @@
 namespace orhost {
 using namespace ordev;
 
+#ifndef OR_GROUPS_UPTO
+#define OR_GROUPS_UPTO 256
+#endif
 namespace {
 constexpr int K = OR_K;
 typedef Geo<K> G;
@@ -66,29 +70,43 @@ OR_BATCH_LAUNCHER(rdecb_f32, (k_reduce_decode_batched<KR, float>), Geo<KR>::THRE
 OR_BATCH_LAUNCHER(rdecb_bf16, (k_reduce_decode_batched<KR, bf16_t>), Geo<KR>::THREADS)
 OR_BATCH_LAUNCHER(fdecb_f32, (k_finalize_decode_batched<K, float>), G::THREADS)
 OR_BATCH_LAUNCHER(fdecb_bf16, (k_finalize_decode_batched<K, bf16_t>), G::THREADS)
-// The fused kernels come in two forms where a lane holds 16 entries: with a second tile buffer (the next
-// worker's tile travels while this one is transformed), which shortens the chain of dependent steps of a
-// workgroup and wins while a launch puts at most three workgroups on each of the 256 CUs, and without,
-// which wins beyond that (measured on MI355X; same arithmetic, same results).
-// (Tiles of 8 or 16 wavefronts, at most two workgroups on a CU whatever the grid: always the first form.)
-constexpr unsigned long long kPrefetchUpTo = (G::W >= 8) ? ~0ull : 3 * 256;
-constexpr bool kTwoForms = (G::R == 16);
-#define OR_FUSED_LAUNCHER(name, Args, kernel)                                                \
-  hipError_t name(const Args& a, unsigned long long units, hipStream_t s, int pos) {        \
-    if (units == 0) return hipSuccess;                                                       \
-    if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;                                  \
-    if (kTwoForms && units <= kPrefetchUpTo)                                                 \
-      return launch_kernel(kernel<K, OR_FUSED_IN, kTwoForms>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a); \
-    return launch_kernel(kernel<K, OR_FUSED_IN, false>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a); \
+constexpr unsigned long long kGroupsUpTo = OR_GROUPS_UPTO;
+// GROUPS while a launch has at most one tile per CU; beyond, fp32 tiles STREAM (16 registers of entries per worker: the
+// in-order form with two workers in flight), bf16 tiles PAIR (half of that: more workgroups on a CU win)
+template <class In> constexpr int kSmallMode = K <= 12 ? GROUPS : STREAM;
+template <class In> constexpr int kLargeMode = sizeof(In) == 2 ? PAIR : STREAM;
+template <class In>
+hipError_t fused(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  if (units == 0) return hipSuccess;
+  if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;
+  constexpr int SMALL = kSmallMode<In>, LARGE = kLargeMode<In>;
+  if (SMALL != LARGE && units <= kGroupsUpTo)
+    return launch_kernel(k_fused<K, In, SMALL>, dim3((unsigned)units), dim3(kFusedThreads<K> * (SMALL == GROUPS ? kGroups : 1)), s, pos, a);
+  return launch_kernel(k_fused<K, In, LARGE>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
+}
+template <class In>
+hipError_t fused_batched(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  if (units == 0) return hipSuccess;
+  if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;
+  constexpr int SMALL = kSmallMode<In>, LARGE = kLargeMode<In>;
+  if (SMALL != LARGE && units <= kGroupsUpTo)
+    return launch_kernel(k_fused_batched<K, In, SMALL>, dim3((unsigned)units), dim3(kFusedThreads<K> * (SMALL == GROUPS ? kGroups : 1)), s, pos, a);
+  constexpr int SLOTS = kBatchSlots<K, LARGE>;
+  if constexpr (SLOTS == 1) {
+    return launch_kernel(k_fused_batched<K, In, LARGE>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
+  } else {
+    BatchArgs b = a;   // tile_start in workgroups of SLOTS tiles
+    uint32_t groups = 0;
+    for (int j = 0; j < a.n; ++j) {
+      b.tile_start[j] = groups;
+      groups += (a.tile_start[j + 1] - a.tile_start[j] + SLOTS - 1) / SLOTS;
+    }
+    b.tile_start[a.n] = groups;
+    return launch_kernel(k_fused_batched<K, In, LARGE>, dim3(groups), dim3(kFusedThreads<K> * SLOTS), s, pos, b);
   }
-#define OR_FUSED_IN float
-OR_FUSED_LAUNCHER(fus_f32, PathArgs, k_fused)
-OR_FUSED_LAUNCHER(fusb_f32, BatchArgs, k_fused_batched)
-#undef OR_FUSED_IN
-#define OR_FUSED_IN bf16_t
-OR_FUSED_LAUNCHER(fus_bf16, PathArgs, k_fused)
-OR_FUSED_LAUNCHER(fusb_bf16, BatchArgs, k_fused_batched)
-#undef OR_FUSED_IN
+}
+constexpr launch_fn fus_f32 = fused<float>, fus_bf16 = fused<bf16_t>;
+constexpr batch_fn fusb_f32 = fused_batched<float>, fusb_bf16 = fused_batched<bf16_t>;
 #else
 // one workgroup per pair of output tiles; `units` = output tiles of the shard
 #define OR_PAIR_LAUNCHER(name, kernel)                                                       \

@@ -28,21 +28,11 @@
 // factor (index bit 14) joins the two workgroups of a block: the one that finishes first leaves its result in the
 // workspace, the other one adds and subtracts and stores all four tiles.
 #pragma once
-#include "rht_kernels.hpp"
+#include "rht_fused.hpp"
 
 namespace ordev {
 
-typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {   // round to nearest even, lo in bits 0..15
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{lo, hi}, b2));
-}
-__device__ __forceinline__ float bf16_lo(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t p) { return __builtin_bit_cast(float, p & 0xFFFF0000u); }
 
 // Scratch of the pair hand-over (four tiles per block), one pair of words per block; zeroed before the kernel.
 struct PairFlags {
@@ -331,7 +321,6 @@ __global__ __launch_bounds__(1024) void k_fused_mx(PathArgs a) {
     for (int gq = 0; gq < 4; ++gq) {
       const int x = x_lane + arr * 512 + gq * 128;
       const uint32_t nib = ((uint32_t)sb[x >> 3] >> (x & 4)) & 0xFu;
-      typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
       u32x2v o;
       o[0] = pack_bf16x2(v[4 * gq] * c, v[4 * gq + 1] * c) ^ pair_sign_mask<0>(nib);
       o[1] = pack_bf16x2(v[4 * gq + 2] * c, v[4 * gq + 3] * c) ^ pair_sign_mask<1>(nib);

@@ -5,9 +5,6 @@
 
 // Which kernels read their inputs with nontemporal loads (each choice measured on MI355X; ENCB / DECB
 // are the encode / decode kernels for blocks above 2^14 entries, which came out slower with them).
-#ifndef OR_NT_FUSED
-#define OR_NT_FUSED true
-#endif
 #ifndef OR_NT_RDEC
 #define OR_NT_RDEC true
 #endif
@@ -50,8 +47,6 @@ struct PathArgs {
 
 // In the shard kernels a tile can be cut short only when blocks are smaller than a tile (class 0).
 template <int K> constexpr bool kShardTilesFull = (K != 0);
-// LDS buffers for the exchange: two (one barrier per exchange) while they fit several workgroups per CU.
-template <int K> constexpr int kXbufs = (Geo<K>::Q == 0) ? 0 : (Geo<K>::T * 4 <= 16384 ? 2 : 1);
 
 // +1/-1 entry of H_{2^HB}: row `part`, column q
 __device__ __forceinline__ float part_coef(int part, int q) { return (__builtin_popcount(part & q) & 1) ? -1.0f : 1.0f; }
@@ -367,123 +362,6 @@ __global__ __launch_bounds__(Geo<K>::THREADS) void k_reduce_decode(PathArgs a) {
   reduce_decode_tile<K, Wire, Out>(a, blockIdx.x);
 }
 
-// The whole path for one shard held by one node: the raw slices of N workers are encoded, the
-// encoded entries that arrived are summed and counted, the mean is decoded.  The encoded value is
-// rounded to the wire type (identity for fp32) before it is summed, so the result is the one the
-// three separate calls give.  Blocks of up to 2^14 entries (one tile per block).
-//
-// Per worker: sign flip (layout A), transform to layout B, round, add under the received mask.  Tiles of
-// 2, 4, 8 or 16 wavefronts x 16 registers use the transposed transform of rht_tile.hpp, in both directions.
-// PREFETCH: a second tile buffer, so that the next worker's tile is in flight during the transform (the
-// launcher decides from the size of the grid).  Inputs are read once: nontemporal loads.
-template <int K, class In, bool PREFETCH>
-__device__ __forceinline__ void fused_tile(const PathArgs& a, u64 unit) {
-  constexpr int T = Geo<K>::T, NB = kXbufs<K>, R = Geo<K>::R;
-  constexpr bool FULL = kShardTilesFull<K>;
-  static_assert(!PREFETCH || R == 16, "a second tile buffer only with 16 entries per lane");
-  static_assert(Geo<K>::PARTS == 1, "larger blocks use k_fused_pairs");
-  constexpr bool TRANSP = (R == 16 && Geo<K>::Q >= 1);    // transform_transposed, both ways
-  constexpr int XF = TRANSP ? tr_floats<K> : T;
-  constexpr int NBUF = TRANSP ? 2 : NB;
-  __shared__ float xbuf[NBUF ? NBUF : 1][NBUF ? XF : 1];
-  const int wave = wave_id(), lane = lane_id(), kt = tile_bits<K>(a.k);
-  const u64 L = a.n_pad, e0 = unit * T;
-  const In* grads = (const In*)a.in;
-  const float sigma = TRANSP ? tr_sigma(lane) : lane_sigma(lane, kt < 6 ? kt : 6);
-  // a power-of-two scale commutes with rounding to the wire type; any other scale is applied first
-  const bool scale_first = sizeof(In) == 2 && (a.k & 1);
-  float acc[R], va[R];
-  uint32_t cnt[R / 4];
-  int full = 0, flip = 0;
-  const int moff = mask_word_offset<K>(wave, lane);
-  const u64 mrow = L >> 5;
-  // the first worker's tile is requested before the signs are computed, so Philox runs under its latency
-  load_tile<K, false, FULL, OR_NT_FUSED>(grads, e0, L, wave, lane, va);
-  uint32_t ma = load_mask_words<K, FULL>(a.masks, e0, L, moff);
-  u64 sg[R];
-  sign_masks(a.seed, a.base + e0 + (u64)wave * Geo<K>::WAVE_ENTRIES, sg);
-#pragma unroll
-  for (int r = 0; r < R; ++r) acc[r] = 0.0f;
-#pragma unroll
-  for (int r = 0; r < R / 4; ++r) cnt[r] = 0;
-
-  auto encode_and_add = [&](float (&v)[R], uint32_t words) {
-    apply_signs(v, sg);
-    if constexpr (TRANSP) {
-      transform_transposed<K>(v, xbuf[flip], xbuf[flip ^ 1], wave, lane);
-    } else {
-      transform<K, true, NB != 2>(v, xbuf[NB == 2 ? flip : 0], wave, lane, kt);
-    }
-    flip ^= 1;
-    if (sizeof(In) == 2) {
-      if (scale_first) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = round_to<In>(v[r] * a.scale);
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = round_to<In>(v[r]);
-      }
-    }
-    masked_accumulate(v, words, acc, cnt, full);
-  };
-  if constexpr (PREFETCH) {
-    // Two tile buffers: the next worker's tile travels while this one is transformed.  The loads inside
-    // the loop are unconditional (the last one or two workers are handled after it), so that the count
-    // of loads in flight is the same on every path into a wait and the compiler waits for the older
-    // tile only.
-    float vb[R];
-    uint32_t mb;
-    auto request = [&](int i, float (&v)[R], uint32_t& words) {
-      load_tile<K, false, FULL, OR_NT_FUSED>(grads + (u64)i * L, e0, L, wave, lane, v);
-      words = load_mask_words<K, FULL>(a.masks + (u64)i * mrow, e0, L, moff);
-    };
-    int i = 0;
-    for (; i + 2 < a.N; i += 2) {
-      request(i + 1, vb, mb);
-      encode_and_add(va, ma);
-      request(i + 2, va, ma);
-      encode_and_add(vb, mb);
-    }
-    if (i + 1 < a.N) {
-      request(i + 1, vb, mb);
-      encode_and_add(va, ma);
-      encode_and_add(vb, mb);
-    } else {
-      encode_and_add(va, ma);
-    }
-  } else {
-    for (int i = 0; i < a.N; ++i) {
-      encode_and_add(va, ma);
-      if (i + 1 < a.N) {
-        load_tile<K, false, FULL, OR_NT_FUSED>(grads + (u64)(i + 1) * L, e0, L, wave, lane, va);
-        ma = load_mask_words<K, FULL>(a.masks + (u64)(i + 1) * mrow, e0, L, moff);
-      }
-    }
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  store_counts<K, FULL>(a.count_out, e0, L, wave, lane, cnt, full);
-  if (a.total_out) add_arrivals<R>(a.total_out, cnt, full);
-  finalize_mean(acc, cnt, full, sigma * (scale_first ? 1.0f : a.scale));
-  __builtin_amdgcn_sched_barrier(0);
-  if constexpr (TRANSP) {
-    transform_transposed<K>(acc, xbuf[flip], xbuf[flip ^ 1], wave, lane);   // the same code takes layout B to A
-  } else {
-    transform<K, false, NB != 2>(acc, xbuf[NB == 2 ? flip : 0], wave, lane, kt);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  const float c = a.scale * sigma;
-#pragma unroll
-  for (int r = 0; r < R; ++r) acc[r] *= c;
-  apply_signs(acc, sg);
-  store_tile<K, false, FULL, true>((In*)a.out, e0, L, wave, lane, acc);
-}
-
-template <int K, class In, bool PREFETCH>
-__global__ __launch_bounds__(Geo<K>::THREADS) __attribute__((amdgpu_waves_per_eu(Geo<K>::R == 32 ? 4 : 1)))
-void k_fused(PathArgs a) {
-  fused_tile<K, In, PREFETCH>(a, blockIdx.x);
-}
-
 // ---------------------------------------------------------------------------------------------------
 // The fused path for blocks of 2^15 / 2^16 entries (PARTS = 2 / 4 tiles per block).  A workgroup produces
 // TWO output tiles of its block, p_lo = h and p_hi = h + PARTS/2, from one reading of the block's input
@@ -648,9 +526,11 @@ static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments are limited to 4 KB")
 
 // the bucket that workgroup x serves, as the arguments of a single-bucket call; returns the tile inside it
 __device__ __forceinline__ u64 bucket_of(const BatchArgs& ba, PathArgs& a) {
+  // buckets that end at or before tile x: one comparison a lane (a walk over the descriptors was up to 60 dependent
+  // scalar loads ahead of a workgroup's first access)
   const uint32_t x = blockIdx.x;
-  int j = 0;
-  while (j + 1 < ba.n && ba.tile_start[j + 1] <= x) ++j;
+  const int lane = lane_id();
+  const int j = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane + 1 < ba.n && ba.tile_start[lane + 1] <= x));
   a = PathArgs{};
   a.in = ba.b[j].in; a.masks = (const uint32_t*)ba.b[j].aux; a.count_in = (const uint8_t*)ba.b[j].aux;
   a.out = ba.b[j].out; a.count_out = ba.b[j].count_out;
@@ -658,14 +538,6 @@ __device__ __forceinline__ u64 bucket_of(const BatchArgs& ba, PathArgs& a) {
   a.N = ba.N; a.k = ba.k; a.scale = ba.scale;
   a.total_out = ba.totals ? ba.totals + ba.first + j : nullptr;
   return x - ba.tile_start[j];
-}
-
-template <int K, class In, bool PREFETCH>
-__global__ __launch_bounds__(Geo<K>::THREADS) __attribute__((amdgpu_waves_per_eu(Geo<K>::R == 32 ? 4 : 1)))
-void k_fused_batched(BatchArgs ba) {
-  PathArgs a;
-  const u64 unit = bucket_of(ba, a);
-  fused_tile<K, In, PREFETCH>(a, unit);
 }
 
 // The three-call path on several buckets: aggregation + mean + decode of encoded shards, and mean + decode of
