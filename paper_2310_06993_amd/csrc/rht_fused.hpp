@@ -216,6 +216,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void* p, int byt
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, bytes, 0x00020000);
 }
 
+// 16 bytes a lane, `off` bytes past the descriptor's base.  The offset is never handed over in a scalar register: hipcc 7.2
+// puts no wait between such a 16-byte store and a vector instruction that writes its data registers again, and on this
+// chip the new value then reached memory now and then (counts of 8 read back as 8.0f).  Without one it does wait.
+template <int AUX>
+__device__ __forceinline__ void store16(u32x4v x, __amdgpu_buffer_rsrc_t rs, int off) {
+  __builtin_amdgcn_raw_buffer_store_b128(x, rs, off, 0, AUX);
+}
+
 // The workers in the order they are taken: first those that lost something in the tile, then the others, each kind in
 // increasing order.  `marks`: one bit per worker in LDS, set where something is missing; `order`: 256 bytes of LDS (every
 // wavefront writes the same values and reads back its own).  The result holds entry j in byte j / 64 of lane j % 64.
@@ -651,12 +659,12 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
         if constexpr (ES == 4) o[j] = __builtin_bit_cast(uint32_t, acc[4 * q + j]);
         else o[j] = pack_bf16x2(acc[8 * q + 2 * j], acc[8 * q + 2 * j + 1]);
       }
-      __builtin_amdgcn_raw_buffer_store_b128(o, rs, lane * 16, q * 1024, kBufNt);
+      store16<kBufNt>(o, rs, lane * 16 + q * 1024);
     }
   }
   if (a.count_out) {
     const __amdgpu_buffer_rsrc_t rs = rsrc_of(a.count_out + ew, left);
-    __builtin_amdgcn_raw_buffer_store_b128(u32x4v{c4[0], c4[1], c4[2], c4[3]}, rs, lane * 16, 0, kBufNt);
+    store16<kBufNt>(u32x4v{c4[0], c4[1], c4[2], c4[3]}, rs, lane * 16);
   }
 }
 
