@@ -2,6 +2,7 @@
 #include "launch_table.hpp"
 #include "rht_fused.hpp"
 #if OR_K > 14
+#include "rht_encode_block.hpp"
 #include "rht_fused_mx.hpp"
 #endif
 
@@ -47,7 +48,16 @@ typedef Geo<K> G;
 #define OR_XFORM_LAUNCHER OR_BLOCK_LAUNCHER
 #endif
 OR_XFORM_LAUNCHER(enc_f32, OR_ENC(float, float))
-OR_XFORM_LAUNCHER(enc_bf16, OR_ENC(bf16_t, bf16_t))
+#if OR_K <= 14
+OR_LAUNCHER(enc_bf16, OR_ENC(bf16_t, bf16_t))
+#else
+// workgroups that walk over the blocks: as many as 256 CUs hold at a time
+hipError_t enc_bf16(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  const unsigned long long blocks = units >> G::HB, resident = K == 15 ? 512 : 256;
+  if (blocks == 0) return hipSuccess;
+  return launch_kernel(k_encode_block_bf16<K>, dim3((unsigned)(blocks < resident ? blocks : resident)), dim3(1024), s, pos, a);
+}
+#endif
 OR_XFORM_LAUNCHER(dec_f32, OR_DEC(float, false, false))
 OR_XFORM_LAUNCHER(dec_bf16, OR_DEC(bf16_t, false, false))
 OR_XFORM_LAUNCHER(fdec_f32, OR_DEC(float, true, false))

@@ -85,6 +85,29 @@ def test_encode_decode_bf16(b, orc, k):
     assert (to_np(dec) != want).mean() < 0.02
 
 
+@pytest.mark.parametrize("k,blocks,tail", [(16, 1, 1), (16, 2, 0), (16, 3, -1), (16, 258, 0), (16, 513, 16385), (15, 1, 7),
+                                           (15, 514, 0), (15, 515, 1025)])
+def test_encode_bf16_large_blocks_walked_over(b, orc, k, blocks, tail):
+    """The bf16 encode of 2^15 / 2^16 blocks: one block, more blocks than workgroups (256 / 512 of them walk over the
+    blocks), a last block cut short at an odd entry in different tiles and wavefronts, and in place."""
+    B = 1 << k
+    n = blocks * B - (B - tail if tail > 0 else -tail)
+    rng = np.random.default_rng(500 + k + blocks)
+    x = _bf16_bits((rng.standard_normal(n) * 1e-4).astype(np.float32))
+    seed, base = 0xF00DFACE12345678, (1 << 33) + 5 * B
+    enc = torch.full((blocks * B,), float("nan"), dtype=torch.bfloat16, device=dev())
+    xd = _dev_bf16(x)
+    b.or_rht_encode_bf16(xd, n, k, seed, base, enc)
+    want = orc.rht_encode(x, k, seed, base)
+    assert rel_l2(to_np(enc), want) <= TOL["bf16"]
+    assert (to_np(enc) != want).mean() < 0.02      # as above
+    last = slice((blocks - 1) * B, blocks * B)
+    assert rel_l2(to_np(enc[last]), want[last]) <= TOL["bf16"]
+    if tail == 0:
+        b.or_rht_encode_bf16(xd, n, k, seed, base, xd)
+        assert torch.equal(xd.view(torch.int16), enc.view(torch.int16))
+
+
 @pytest.mark.parametrize("k", [6, 10, 12, 14, 16])
 def test_sign_draws_are_bit_exact(b, orc, k):
     # decode of sqrt(B) * e_0 in every block is exactly the sign vector (even k: all values exact)
