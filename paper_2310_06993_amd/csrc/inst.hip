@@ -4,6 +4,7 @@
 #if OR_K > 14
 #include "rht_encode_block.hpp"
 #include "rht_fused_mx.hpp"
+#include "rht_reduce_block.hpp"
 #endif
 
 #ifndef OR_K
@@ -127,6 +128,8 @@ constexpr batch_fn fusb_f32 = fused_batched<float>, fusb_bf16 = fused_batched<bf
     if (grid > 0x7FFFFFFFull) return hipErrorInvalidValue;                                   \
     return launch_kernel(kernel, dim3((unsigned)grid), dim3(G::THREADS), s, pos, a);         \
   }
+OR_BLOCK_LAUNCHER(rdec_f32, (k_reduce_decode_block<K, float>))
+OR_BLOCK_LAUNCHER(rdec_bf16, (k_reduce_decode_block<K, bf16_t>))
 OR_PAIR_LAUNCHER(fus_f32, (k_fused_pairs<K, float>))
 OR_PAIR_LAUNCHER(fus_bf16, (k_fused_mx<K>))
 #endif
@@ -137,12 +140,7 @@ OR_PAIR_LAUNCHER(fus_bf16, (k_fused_mx<K>))
 #define OR_CAT(a, b) OR_CAT2(a, b)
 extern const KernelTable OR_CAT(or_kernel_table_, OR_K) = {
     G::TL, enc_f32, enc_bf16, dec_f32, dec_bf16, fdec_f32, fdec_bf16, mdec_f32, mdec_bf16,
-#if OR_K <= 14
-    rdec_f32, rdec_bf16,
-#else
-    nullptr, nullptr,
-#endif
-    fus_f32, fus_bf16,
+    rdec_f32, rdec_bf16, fus_f32, fus_bf16,
 #if OR_K <= 14
     fusb_f32, fusb_bf16, rdecb_f32, rdecb_bf16, fdecb_f32, fdecb_bf16
 #else

@@ -406,6 +406,13 @@ or_status check_path(const void* in, const uint32_t* masks, int N, u64 L, int k,
   return OR_OK;
 }
 
+// Reduce + decode of blocks above 2^14: one kernel for both, or a reduction and a decode with sum and counts in between?
+// The one kernel moves less, but a workgroup takes a whole block through all workers one after the other, so launches that
+// leave CUs idle pay for every worker.  fp32 2^16, two launches -> one: N = 2, 4 blocks 21.8 -> 17.1 us; N = 8, 48 blocks
+// 42 -> 53, 96 blocks 63 -> 60, 128 blocks 80 -> 65; N = 32, 48 blocks 101 -> 184, 128 blocks 226 -> 224, 256 blocks
+// 423 -> 363.  2^15 and bf16 cross over at the same numbers.
+bool reduce_in_one_kernel(u64 blocks, int N) { return N <= 2 || blocks >= 128; }
+
 // enqueue one checked shard: T = float or uint16_t (bf16 bits).  `allow` = which of this entry point's first /
 // last launches this shard may be (timing events ride on those only); `total`, if not null, is expected to be
 // zero already and receives the number of arrivals.
@@ -463,6 +470,8 @@ or_status run_path(bool fused, const T* in, const uint32_t* masks, int N, u64 L,
     if (hipError_t e = t->fused_f32(a, units, s, 0)) return finish(e);
     return finish(t->decode_f32(d, units, s, last));
   }
+  if (reduce_in_one_kernel(L >> k, N))
+    return finish((bf16 ? t->reduce_decode_bf16 : t->reduce_decode_f32)(a, units, s, first | last));
   uint8_t* cnt = count_out ? count_out : ws_cnt;
   constexpr int VEC = 16 / sizeof(T);
   if (hipError_t e = launch_masked_reduce<T, VEC>(in, masks, N, L, ws_f32, cnt, s, first)) return finish(e);

@@ -6,6 +6,8 @@
 // lane (layout A of rht_fused.hpp) with DEPTH tiles in flight; a wavefront looks at a tile's received bits once and takes
 // the plain additions if nothing is missing in its part.  Counts are not carried along: a wavefront that saw a loss reads
 // the bits of that tile again at the end.
+// fp32, N = 8, 1024 blocks of 2^16: 601 -> 421 us (5.9 TB/s); bf16 367 -> 251; 2048 blocks of 2^15: 591 -> 421, bf16
+// 360 -> 232.
 #pragma once
 #include "rht_encode_block.hpp"
 

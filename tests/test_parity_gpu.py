@@ -645,3 +645,46 @@ def test_seeded_sweep_of_shapes_through_every_route(b, orc):
         for name, out, cnt in (("fused", out_f, cnt_f), ("reduce_decode", out_r, cnt_r), ("three calls", out_3, cnt_3)):
             assert np.array_equal(to_np(cnt), want_count), (tag, name)
             assert rel_l2(to_np(out), want) <= TOL[kind], (tag, name)
+
+
+@pytest.mark.parametrize("k,blocks,N", [(15, 1, 1), (16, 3, 2), (15, 127, 3), (15, 128, 3), (16, 129, 5), (15, 300, 8), (16, 128, 33)])
+@pytest.mark.parametrize("kind", ["f32", "bf16"])
+def test_reduce_decode_blocks_above_one_tile(b, orc, k, blocks, N, kind):
+    """Reduce + decode in one kernel (one or two workers, or from 128 blocks on) and in two, against the separate calls and,
+    block by block, the oracle: packets, single entries, a wavefront's part, a whole tile and nothing at all lost; what did
+    not arrive is NaN; the totals of the batched form; no counts asked for."""
+    B, L = 1 << k, blocks << k
+    f32, dt = kind == "f32", torch.float32 if kind == "f32" else torch.bfloat16
+    gen = torch.Generator(device=dev()).manual_seed(900 + k + blocks + N)
+    bits = torch.rand((N, L // 256), device=dev(), generator=gen).ge_(0.01).bool().repeat_interleave(256, 1)
+    bits[0, :B] = True
+    bits[N - 1, B - 5:B - 4] = False
+    bits[N // 2, L - 1] = False
+    bits[:, L - B:L - B + 1024] = False          # nobody's: the mean is 0 there
+    bits[N - 1, L - B + 16384:L - B + 32768] = False
+    x = torch.randn((N, L), device=dev(), generator=gen).mul_(1e-3).to(dt)
+    x.masked_fill_(~bits, float("nan"))
+    weights = (1 << torch.arange(32, device=dev(), dtype=torch.int64))
+    words = torch.stack([(row.view(-1, 32) * weights).sum(1) for row in bits])
+    md = torch.where(words >= 1 << 31, words - (1 << 32), words).to(torch.int32).contiguous()
+    count_want = bits.sum(0, dtype=torch.int64)
+    seed, base = 0xABCDEF9876543210, (1 << 34) + 3 * B
+    ws = torch.empty(b.or_workspace_bytes(L, k), dtype=torch.uint8, device=dev())
+    out, cnt = torch.full((L,), float("nan"), dtype=dt, device=dev()), torch.full((L,), 255, dtype=torch.uint8, device=dev())
+    call = b.or_reduce_decode if f32 else b.or_reduce_decode_bf16
+    call(x, md, N, L, k, seed, base, out, cnt, ws)
+    assert torch.equal(cnt.long(), count_want)
+    # the separate calls add and decode in the same order; the stages of the transform come in another one
+    total, cnt2, out2 = torch.empty(L, device=dev()), torch.empty_like(cnt), torch.empty_like(out)
+    (b.or_masked_reduce if f32 else b.or_masked_reduce_bf16)(x, md, N, L, total, cnt2)
+    (b.or_finalize_decode if f32 else b.or_finalize_decode_bf16)(total, cnt2, L, k, seed, base, out2)
+    assert rel_l2(to_np(out), to_np(out2)) <= TOL[kind]
+    mean = torch.where(cnt2 > 0, total / cnt2.clamp(min=1), torch.zeros((), device=dev()))
+    for j in {0, blocks // 2, blocks - 1}:
+        part = slice(j * B, (j + 1) * B)
+        want = orc.rht_decode(mean[part].cpu().numpy(), B, k, seed, base + j * B)
+        assert rel_l2(to_np(out[part].float()), want) <= TOL[kind], j
+    again, totals = torch.full_like(out, float("nan")), torch.full((1,), -1, dtype=torch.int64, device=dev())
+    b.or_reduce_decode_batched(b.make_buckets([(x, md, again, None, L, seed, base)]), 1, N, k, not f32, totals, ws)
+    assert torch.equal(again.view(torch.uint8), out.view(torch.uint8))
+    assert totals.item() == count_want.sum().item()
