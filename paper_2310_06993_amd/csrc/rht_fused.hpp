@@ -6,7 +6,7 @@
 // encoded by itself and added under its received bits.  With packet loss that leaves 1 + (workers with a loss in this
 // tile) transforms where there were N, and the bulk of the work is a plain streaming sum: 16 bytes a lane per load, no
 // barrier in between.  The value of an entry is (sum over whole workers, in increasing order, encoded) + (each of the
-// others, in increasing order), whatever the launch looks like.
+// others, in increasing order) in all three modes below.  (Small launches of 2^12 .. 2^14 tiles: rht_fused_each.hpp.)
 //
 // Positions (V entries per 16 bytes: 4 fp32, 8 bf16; VB = log2 V; 16 entries a lane, 1024 a wavefront)
 //   A  as loaded and stored: register bits = entry bits 0 .. VB-1 and VB+6 .. 9, lane = VB .. VB+5, wavefront = 10 ..

@@ -688,3 +688,37 @@ def test_reduce_decode_blocks_above_one_tile(b, orc, k, blocks, N, kind):
     b.or_reduce_decode_batched(b.make_buckets([(x, md, again, None, L, seed, base)]), 1, N, k, not f32, totals, ws)
     assert torch.equal(again.view(torch.uint8), out.view(torch.uint8))
     assert totals.item() == count_want.sum().item()
+
+
+@pytest.mark.parametrize("k,N,tiles", [(10, 3, 5), (10, 4, 256), (10, 6, 513), (11, 6, 512), (11, 5, 257), (12, 7, 256), (12, 8, 256),
+                                       (12, 8, 257), (12, 2, 1025), (12, 4, 513), (13, 8, 384), (13, 8, 385), (13, 2, 2049),
+                                       (13, 9, 3), (14, 4, 512), (14, 4, 513), (14, 5, 1), (14, 1, 1537)])
+@pytest.mark.parametrize("kind", ["f32", "bf16"])
+def test_fused_forms_at_the_edges_of_their_rules(b, orc, k, N, tiles, kind):
+    """Either side of each rule by which the launcher picks a form of the fused kernel: the value, counts and arrival totals
+    of the first, the middle and the last block against the oracle, of the single and the batched call."""
+    B, L = 1 << k, tiles << k
+    rng = np.random.default_rng(7000 + 100 * k + N + tiles)
+    gen = torch.Generator(device=dev()).manual_seed(k + tiles)
+    dt = torch.float32 if kind == "f32" else torch.bfloat16
+    x = torch.randn((N, L), device=dev(), generator=gen).mul_(1e-3).to(dt)
+    words = np.full((N, L // 32), 0xFFFFFFFF, dtype=np.uint32)
+    lost = rng.random((N, L // 256)) < 0.03
+    words.reshape(N, -1, 8)[lost] = 0
+    words[N - 1, 0] &= ~np.uint32(4)
+    words[:, -1] &= np.uint32(0x7FFFFFFF)         # the last entry of all is nobody's
+    md = masks_to_dev(words)
+    seed, base = 0x0123456789ABCDEF, (1 << 33) + 2 * B
+    out, cnt = torch.full((L,), float("nan"), dtype=dt, device=dev()), torch.full((L,), 255, dtype=torch.uint8, device=dev())
+    (b.or_fused_path if kind == "f32" else b.or_fused_path_bf16)(x, md, N, L, k, seed, base, out, cnt, None)
+    for j in {0, tiles // 2, tiles - 1}:
+        part = slice(j * B, (j + 1) * B)
+        want, wcnt = orc.fused_path(to_np(x[:, part].contiguous()), np.ascontiguousarray(words[:, j * B // 32:(j + 1) * B // 32]), k,
+                                    seed, base + j * B)
+        assert np.array_equal(to_np(cnt[part]), wcnt), j
+        assert rel_l2(to_np(out[part]), want) <= TOL[kind], j
+    again, cnt2 = torch.full_like(out, float("nan")), torch.full_like(cnt, 255)
+    totals = torch.full((1,), -1, dtype=torch.int64, device=dev())
+    b.or_fused_path_batched_monitored(b.make_buckets([(x, md, again, cnt2, L, seed, base)]), 1, N, k, kind == "bf16", totals, None)
+    assert torch.equal(again.view(torch.uint8), out.view(torch.uint8)) and torch.equal(cnt2, cnt)
+    assert totals.item() == cnt.long().sum().item()
