@@ -135,10 +135,9 @@ or_status or_reduce_decode_bf16(const uint16_t* shards, const uint32_t* masks, i
 
 /* or_fused_path: the whole path for the shard one node owns, with all N workers' RAW (not yet
  * encoded) slices of that shard resident: encode each slice, keep what arrived, sum and count,
- * mean, decode.  grads: [N][shard_len] raw gradient slices.  bf16: for block_log2 > 14 the encoded
- * value is rounded to bf16 (nearest even) before it is summed, as if it had been stored by
- * or_rht_encode_bf16; up to 14 the sum is taken in fp32 without that rounding, which is nearer to the
- * exact result.  Other arguments as for or_reduce_decode. */
+ * mean, decode.  grads: [N][shard_len] raw gradient slices; the encoded value is rounded to the
+ * wire type (fp32: no-op; bf16: nearest even) before it is summed, as if it had been stored by
+ * or_rht_encode*.  Other arguments as for or_reduce_decode. */
 or_status or_fused_path(const float* grads, const uint32_t* masks, int N, uint64_t shard_len, int block_log2,
                         uint64_t seed, uint64_t base_index, float* out, uint8_t* count_out, void* workspace,
                         size_t workspace_bytes, void* stream);

@@ -80,77 +80,74 @@ OR_BATCH_LAUNCHER(rdecb_bf16, (k_reduce_decode_batched<KR, bf16_t>), Geo<KR>::TH
 OR_BATCH_LAUNCHER(fdecb_f32, (k_finalize_decode_batched<K, float>), G::THREADS)
 OR_BATCH_LAUNCHER(fdecb_bf16, (k_finalize_decode_batched<K, bf16_t>), G::THREADS)
 // GROUPS (tiles up to 2^12) while a launch leaves CUs idle and has the workers for its four groups.  us, 256 tiles, without
-// -> with: fp32 2^12, N = 6 9.5 -> 10.2, N = 8 12.1 -> 11.3; fp32 2^10, N = 2 5.4 -> 6.7, N = 4 with a loss in every tile
-// 7.4 -> 6.6; bf16 2^10, N = 2 6.3 -> 6.1, N = 8 8.1 -> 6.3.  Smaller tiles leave room for more of them: 2^11, N = 8, 512
-// tiles 10.7 -> 9.3, 781 tiles 11.9 -> 15.6; bf16 2^10, N = 8, 1024 tiles 11.6 -> 8.6.
-template <class In>
+// -> with: 2^12, N = 6 9.5 -> 10.2, N = 8 12.1 -> 11.3; 2^10, N = 2 5.4 -> 6.7, N = 4 with a loss in every tile 7.4 -> 6.6.
+// Smaller tiles leave room for more of them: 2^11, N = 8, 512 tiles 10.7 -> 9.3, 781 tiles 11.9 -> 15.6.
 [[maybe_unused]] bool groups_win(unsigned long long tiles, int N) {
-  constexpr bool BF16 = sizeof(In) == 2;
   if (K > 12) return false;
   if (K == 12) return N >= 8 && tiles <= 256;
-  if (N < 6) return (BF16 || N >= 4) && tiles <= 256;
-  return tiles <= (K == 0 && BF16 ? 1024 : 512);
+  if (N < 6) return N >= 4 && tiles <= 256;
+  return tiles <= 512;
 }
-// every worker encoded by itself (rht_fused_each.hpp): fp32 while a launch is short (2^14, N = 4, 1024 tiles 75 -> 70 us; N = 8,
-// 2556 tiles with bursts of loss 272 -> 282), bf16 while the transforms of few workers hide behind the loads (2^13: N = 4, 512
-// tiles 17.1 -> 15.3, 781 tiles 23.0 -> 25.0; N = 8, 256 tiles 17.5 -> 15.5, 512 tiles 23.4 -> 24.3; 2^12: N = 4, 512 tiles
-// 10.1 -> 9.9, N = 2, 1024 tiles 11.2 -> 10.4; 2^14: N = 4, 512 tiles 30.3 -> 29.5, N = 8, 128 tiles 22.9 -> 23.0)
+// every worker encoded by itself (rht_fused_each.hpp): bf16 always, fp32 while a launch is short (2^14, N = 4, 1024 tiles
+// 75 -> 70 us; N = 8, 2556 tiles with bursts of loss 272 -> 282)
 template <class In>
-[[maybe_unused]] bool each_wins(unsigned long long tiles, int N) {
-  if (sizeof(In) == 4) return tiles <= (K == 12 ? 1024 : K == 13 ? 2048 : 1536);
-  if (K == 12) return N <= 4 && tiles * N <= 2048;
-  if (K == 13) return N <= 8 && tiles * N <= 3072;
-  return N <= 4 && tiles <= 512;
+[[maybe_unused]] bool each_wins(unsigned long long tiles) {
+  if (sizeof(In) == 2) return true;
+  return K >= 12 && tiles <= (K == 12 ? 1024 : K == 13 ? 2048 : 1536);
 }
-// otherwise fp32 tiles STREAM (16 registers of entries per worker: the in-order form with two workers in flight); bf16
-// tiles PAIR in larger launches (half of that: more workgroups on a CU win): from 257 tiles on
-template <class In> constexpr int kLargeMode = sizeof(In) == 2 ? PAIR : STREAM;
+// The second tile buffer of those pays up to three workgroups on a CU.  (Tiles of 8 or 16 wavefronts, at most two workgroups
+// on a CU whatever the grid: always.)
+bool prefetch_wins(unsigned long long tiles) { return G::W >= 8 || tiles <= 3 * 256; }
 template <class In>
 hipError_t fused(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
   if (units == 0) return hipSuccess;
   if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  if constexpr (K <= 12) {
-    if (groups_win<In>(units, a.N))
-      return launch_kernel(k_fused<K, In, GROUPS>, dim3((unsigned)units), dim3(kFusedThreads<K> * kGroups), s, pos, a);
+  if constexpr (sizeof(In) == 4 && K <= 12) {
+    if (groups_win(units, a.N))
+      return launch_kernel(k_fused<K, GROUPS>, dim3((unsigned)units), dim3(kFusedThreads<K> * kGroups), s, pos, a);
   }
-  if constexpr (K >= 12) {
-    if (each_wins<In>(units, a.N))
-      return launch_kernel(k_fused_each<K, In>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a);
+  if constexpr (sizeof(In) == 2 || K >= 12) {
+    if (each_wins<In>(units)) {
+      if (sizeof(In) == 4 || prefetch_wins(units))
+        return launch_kernel(k_fused_each<K, In, true>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a);
+      if constexpr (sizeof(In) == 2)
+        return launch_kernel(k_fused_each<K, In, false>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a);
+    }
   }
-  if constexpr (K > 12 && kLargeMode<In> != STREAM) {
-    if (units <= 256) return launch_kernel(k_fused<K, In, STREAM>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
+  if constexpr (sizeof(In) == 4) {
+    return launch_kernel(k_fused<K, STREAM>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
   }
-  return launch_kernel(k_fused<K, In, kLargeMode<In>>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
 }
 template <class In>
 hipError_t fused_batched(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
   if (units == 0) return hipSuccess;
   if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  constexpr int LARGE = kLargeMode<In>;
-  if constexpr (K <= 12) {
-    if (groups_win<In>(units, a.N))
-      return launch_kernel(k_fused_batched<K, In, GROUPS>, dim3((unsigned)units), dim3(kFusedThreads<K> * kGroups), s, pos, a);
+  if constexpr (sizeof(In) == 4 && K <= 12) {
+    if (groups_win(units, a.N))
+      return launch_kernel(k_fused_batched<K, GROUPS>, dim3((unsigned)units), dim3(kFusedThreads<K> * kGroups), s, pos, a);
   }
-  if constexpr (K >= 12) {
-    if (each_wins<In>(units, a.N))
-      return launch_kernel(k_fused_each_batched<K, In>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a);
-  }
-  if constexpr (K > 12 && LARGE != STREAM) {
-    if (units <= 256)
-      return launch_kernel(k_fused_batched<K, In, STREAM>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
-  }
-  constexpr int SLOTS = kBatchSlots<K, LARGE>;
-  if constexpr (SLOTS == 1) {
-    return launch_kernel(k_fused_batched<K, In, LARGE>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
-  } else {
-    BatchArgs b = a;   // tile_start in workgroups of SLOTS tiles
-    uint32_t groups = 0;
-    for (int j = 0; j < a.n; ++j) {
-      b.tile_start[j] = groups;
-      groups += (a.tile_start[j + 1] - a.tile_start[j] + SLOTS - 1) / SLOTS;
+  if constexpr (sizeof(In) == 2 || K >= 12) {
+    if (each_wins<In>(units)) {
+      if (sizeof(In) == 4 || prefetch_wins(units))
+        return launch_kernel(k_fused_each_batched<K, In, true>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a);
+      if constexpr (sizeof(In) == 2)
+        return launch_kernel(k_fused_each_batched<K, In, false>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a);
     }
-    b.tile_start[a.n] = groups;
-    return launch_kernel(k_fused_batched<K, In, LARGE>, dim3(groups), dim3(kFusedThreads<K> * SLOTS), s, pos, b);
+  }
+  if constexpr (sizeof(In) == 4) {
+    constexpr int SLOTS = kBatchSlots<K, STREAM>;
+    if constexpr (SLOTS == 1) {
+      return launch_kernel(k_fused_batched<K, STREAM>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
+    } else {
+      BatchArgs b = a;   // tile_start in workgroups of SLOTS tiles
+      uint32_t groups = 0;
+      for (int j = 0; j < a.n; ++j) {
+        b.tile_start[j] = groups;
+        groups += (a.tile_start[j + 1] - a.tile_start[j] + SLOTS - 1) / SLOTS;
+      }
+      b.tile_start[a.n] = groups;
+      return launch_kernel(k_fused_batched<K, STREAM>, dim3(groups), dim3(kFusedThreads<K> * SLOTS), s, pos, b);
+    }
   }
 }
 constexpr launch_fn fus_f32 = fused<float>, fus_bf16 = fused<bf16_t>;

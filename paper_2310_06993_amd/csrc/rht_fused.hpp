@@ -1,14 +1,15 @@
-// The fused path (OptiReduce Sec. 3.3 encode, Sec. 3.1.1 aggregation, Sec. 3.3 / Sec. 4 decode) for blocks of up to
-// 2^14 entries: one workgroup per tile of T = 2^max(10, k) entries, from N raw slices to the decoded mean.
+// The fused path (OptiReduce Sec. 3.3 encode, Sec. 3.1.1 aggregation, Sec. 3.3 / Sec. 4 decode) of fp32 slices for blocks of
+// up to 2^14 entries: one workgroup per tile of T = 2^max(10, k) entries, from N raw slices to the decoded mean.  (bf16, whose
+// encoded values are rounded worker by worker, and small launches of 2^12 .. 2^14 tiles: rht_fused_each.hpp.)
 //
 // The encode is linear and the signs are the same for every worker, so the workers whose copy of the tile arrived
 // WHOLE are added up first, as they come from memory, and encoded once.  A worker that lost something in the tile is
 // encoded by itself and added under its received bits.  With packet loss that leaves 1 + (workers with a loss in this
 // tile) transforms where there were N, and the bulk of the work is a plain streaming sum: 16 bytes a lane per load, no
 // barrier in between.  The value of an entry is (sum over whole workers, in increasing order, encoded) + (each of the
-// others, in increasing order) in all three modes below.  (Small launches of 2^12 .. 2^14 tiles: rht_fused_each.hpp.)
+// others, in increasing order) in both modes below.
 //
-// Positions (V entries per 16 bytes: 4 fp32, 8 bf16; VB = log2 V; 16 entries a lane, 1024 a wavefront)
+// Positions, also of the bf16 encode and the reduce + decode of larger blocks (V entries per 16 bytes: 4 fp32, 8 bf16; VB = log2 V; 16 entries a lane, 1024 a wavefront)
 //   A  as loaded and stored: register bits = entry bits 0 .. VB-1 and VB+6 .. 9, lane = VB .. VB+5, wavefront = 10 ..
 //   M  register bits = entry bits VB .. VB+3, lane bits (from 0) = VB+4, VB+5, 0 .. VB-1, VB+6 .. 9, wavefront = 10 ..
 //   B  ("wire") lane = entry bits 0 .. 5: a register is 64 consecutive entries, its received bits one lane mask;
@@ -188,7 +189,7 @@ __device__ __forceinline__ float flip_sign(float v, uint32_t bits, int r) {   //
   return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) ^ ((bits << (31 - r)) & 0x80000000u));
 }
 
-// ---- entries as loaded: 16 (C loads of 16 bytes), or 4 (one load of 16 / 8 bytes, where a tile is spread thinner)
+// ---- entries as loaded: 16 (C loads of 16 bytes)
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float bf16_lo(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
@@ -199,17 +200,10 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {   // round
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{lo, hi}, b2));
 }
 template <class In> struct Raw16 { u32x4v q[sizeof(In) == 4 ? 4 : 2]; };
-template <class In> struct Raw4;
-template <> struct Raw4<float> { u32x4v q; };
-template <> struct Raw4<bf16_t> { u32x2v q; };
 
 template <class In> __device__ __forceinline__ float entry_of(const Raw16<In>& x, int r) {
   if constexpr (sizeof(In) == 4) return __builtin_bit_cast(float, (uint32_t)x.q[r >> 2][r & 3]);
   else return r & 1 ? bf16_hi(x.q[r >> 3][(r >> 1) & 3]) : bf16_lo(x.q[r >> 3][(r >> 1) & 3]);
-}
-template <class In> __device__ __forceinline__ float entry_of(const Raw4<In>& x, int r) {
-  if constexpr (sizeof(In) == 4) return __builtin_bit_cast(float, (uint32_t)x.q[r]);
-  else return r & 1 ? bf16_hi(x.q[r >> 1]) : bf16_lo(x.q[r >> 1]);
 }
 // descriptor of `bytes` bytes at p; 0 bytes: loads return zero without touching memory
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void* p, int bytes) {
@@ -242,29 +236,27 @@ __device__ __forceinline__ uint32_t order_workers(const uint32_t* marks, uint8_t
   return (uint32_t)order[lane] | ((uint32_t)order[64 + lane] << 8) | ((uint32_t)order[128 + lane] << 16) | ((uint32_t)order[192 + lane] << 24);
 }
 
-// Three ways to go through the workers; the value of every entry comes from the same operations in the same order.
+// Two ways to go through the workers; the value of every entry comes from the same operations in the same order.
 //   STREAM  in increasing order, two workers' loads in flight ahead of the one in work, whatever their kind.
 //   GROUPS  for launches too small to fill the chip: four times the wavefronts.  The sum over the whole workers is spread
 //           four entries a lane (eight workers' loads in flight at once), then the four groups of W wavefronts encode four
 //           workers side by side (that sum is the last one) and group 0 adds the results in order and decodes.
-//   PAIR    2^14 blocks in launches that put two workgroups on a CU: 64 registers a lane.  The workers with a loss first;
-//           their sum waits in LDS while the whole ones stream by.
-enum FusedMode { STREAM, GROUPS, PAIR };
+enum FusedMode { STREAM, GROUPS };
 constexpr int kGroups = 4;
 
 // SLOTS > 1 (tiles of one wavefront): the workgroup's wavefronts serve SLOTS tiles, for the sake of the arrival totals: one
 // atomic per workgroup.  (Atomics on one 128-byte line take 14 ns each: 32 thousand tiles of a batch spent 300 us on them.)
-template <int K, class In, int MODE, int SLOTS = 1>
+template <int K, int MODE, int SLOTS = 1>
 __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u64 units) {
+  typedef float In;
   typedef FTile<K, In> F;
   constexpr int W = F::W, T = F::T, ES = sizeof(In), G = MODE == GROUPS ? kGroups : 1;
   constexpr bool TWO = MODE == STREAM && K == 14;   // two exchange buffers, one barrier a transform (one workgroup on a CU)
-  constexpr bool COUNTS = MODE != PAIR;             // counts in LDS from the start (PAIR has no room for them)
   static_assert(SLOTS == 1 || (W == 1 && G == 1), "several tiles per workgroup: tiles of one wavefront");
   constexpr int BUFS = MODE == GROUPS ? G : TWO ? 2 : SLOTS;
   __shared__ __align__(16) float xbuf[BUFS][W * F::PART];
   __shared__ __align__(16) float ybuf[G > 1 ? G - 1 : 1][G > 1 ? 1024 * W : 4];   // GROUPS: what groups 1.. hand to group 0
-  __shared__ __align__(16) uint8_t counts[COUNTS ? G * SLOTS : 1][COUNTS ? T : 16];
+  __shared__ __align__(16) uint8_t counts[G * SLOTS][T];
   __shared__ uint32_t marks_all[SLOTS][8];
   __shared__ uint8_t order_all[SLOTS][MODE == STREAM ? 1 : 256];
   __shared__ uint32_t arrived[2];   // arrivals of the workgroup's tiles; how many of its wavefronts have added theirs
@@ -296,11 +288,10 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
 #pragma unroll
     for (int c = 0; c < F::C; ++c) r.q[c] = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, c * 1024, kBufNt));
   };
-  auto request4 = [&](int i, Raw4<In>& r) {   // four entries from 256 grp + 4 lane of the wavefront's part
+  auto request4 = [&](int i, u32x4v& r) {   // four entries from 256 grp + 4 lane of the wavefront's part
     const bool there = i >= 0 && i < N;
     const __amdgpu_buffer_rsrc_t rs = rsrc_of((const In*)a.in + (u64)(there ? i : 0) * L + ew, there ? left * ES : 0);
-    if constexpr (ES == 4) r.q = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, grp * 1024, 0));
-    else r.q = __builtin_bit_cast(u32x2v, __builtin_amdgcn_raw_buffer_load_b64(rs, lane * 8, grp * 512, 0));
+    r = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, grp * 1024, 0));
   };
   auto request_bits = [&](int i) {   // received bits of the lane's 16 entries from 16 lane of the wavefront's part on
     const bool there = i >= 0 && i < N;
@@ -324,7 +315,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   // the received bits are asked for first (answers come in order), then the first workers' entries
   constexpr int U = 8;
   Raw16<In> ra, rb;
-  Raw4<In> q4[MODE == GROUPS ? U : 1];
+  u32x4v q4[MODE == GROUPS ? U : 1];
   uint32_t ma = 0, mb = 0, bits[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) bits[u] = request_bits(grp + u * G);
@@ -360,19 +351,17 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
         if (w >= N) break;
         if (__builtin_amdgcn_ballot_w64(inside && bits[u] != 0xFFFFu) != 0) {
           if (lane == 0) atomicOr(&marks[w >> 5], 1u << (w & 31));
-          if constexpr (COUNTS) count_bits(bits[u]);
+          count_bits(bits[u]);
         } else {
           ++full;
         }
       }
     }
-    if constexpr (COUNTS) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) c4[q] = inside ? c4[q] + (uint32_t)full * 0x01010101u : 0;
-    }
+    for (int q = 0; q < 4; ++q) c4[q] = inside ? c4[q] + (uint32_t)full * 0x01010101u : 0;
   }
   const int own16 = (wave * 64 + lane) * 16;
-  if constexpr (COUNTS) *(uint4*)&counts[SLOTS > 1 ? slot : grp][own16] = make_uint4(c4[0], c4[1], c4[2], c4[3]);
+  *(uint4*)&counts[SLOTS > 1 ? slot : grp][own16] = make_uint4(c4[0], c4[1], c4[2], c4[3]);
   // Sec. 3.4 loss monitoring: the arrivals of this wavefront's lanes, gathered in LDS; one atomic per workgroup
   auto add_arrived = [&]() {
     uint32_t n = 0;
@@ -387,9 +376,9 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
       }
     }
   };
-  if (COUNTS && a.total_out) add_arrived();
+  if (a.total_out) add_arrived();
   tile_barrier<G * W>();
-  if (COUNTS && SLOTS == 1 && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)arrived[0]);
+  if (SLOTS == 1 && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)arrived[0]);
 
   float acc[16], raw[16], v[16];   // sum over the workers with a loss (B), over the whole ones (A); the one in work
 #pragma unroll
@@ -466,51 +455,6 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
       for (int r = 0; r < 16; ++r) acc[r] += raw[r];
     }
     if (TWO) x = xbuf[flip];
-  } else if constexpr (MODE == PAIR) {
-    request(worker(0), ra);
-    if (lossy > 0) {
-      ma = request_words(worker(0));
-      for (int j = 0; j < lossy; ++j) {
-        int lane_t = lane;
-        asm volatile("" : "+v"(lane_t));
-        take_signed(ra);
-        const uint32_t words = ma;
-        request(worker(j + 1), ra);
-        ma = request_words(worker(j + 1));
-        tile_barrier<W>();
-        to_wire<K, In>(v, x, wave, lane_t, k);
-        add_masked(v, words);
-      }
-      if (whole > 0) {
-        tile_barrier<W>();
-#pragma unroll
-        for (int r = 0; r < 16; r += 4) *(f32x4v*)(x + r * 64 * W + (wave * 64 + lane) * 4) = f32x4v{acc[r], acc[r + 1], acc[r + 2], acc[r + 3]};
-      }
-    }
-    if (whole > 0) {
-      clear_raw();
-      for (int j = lossy; j < N; j += 2) {
-        request(worker(j + 1), rb);
-        add_raw(ra);
-        request(worker(j + 2), ra);
-        add_raw(rb);
-      }
-      if (lossy > 0) {
-#pragma unroll
-        for (int r = 0; r < 16; r += 4) {
-          const f32x4v t = *(const f32x4v*)(x + r * 64 * W + (wave * 64 + lane) * 4);
-          acc[r] = t[0]; acc[r + 1] = t[1]; acc[r + 2] = t[2]; acc[r + 3] = t[3];
-        }
-        tile_barrier<W>();
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-      }
-      sign_all(raw);
-      to_wire<K, In>(raw, x, wave, lane, k);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] += raw[r];
-    }
   } else {
     // Items 0 .. lossy - 1 are the workers with a loss, item lossy the sum over the whole ones; round t: items 4 t ..
     // 4 t + 3.  The rounds before the last run while the whole workers' entries are on their way.
@@ -573,7 +517,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
       for (int u = 0; u < U; ++u)
         if (!((lost >> u) & 1)) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) s4[r] += entry_of<In>(q4[u], r);
+          for (int r = 0; r < 4; ++r) s4[r] += __builtin_bit_cast(float, (uint32_t)q4[u][r]);
         }
       if (b + U < N) {
         const uint32_t next = marks_of(b + U) >> ((b + U) & 31);
@@ -593,43 +537,24 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   }
 
   // ---- counts
-  if constexpr (COUNTS) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const uint4 o = *(const uint4*)&counts[SLOTS > 1 ? slot : g][own16];
-      if (g == 0) { c4[0] = o.x; c4[1] = o.y; c4[2] = o.z; c4[3] = o.w; }
-      else { c4[0] += o.x; c4[1] += o.y; c4[2] += o.z; c4[3] += o.w; }
-    }
-    if constexpr (G > 1) *(uint4*)&counts[0][own16] = make_uint4(c4[0], c4[1], c4[2], c4[3]);
-  } else {
-    for (int j = 0; j < lossy; j += 4) {
-      uint32_t p[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) p[u] = request_bits(j + u < lossy ? worker(j + u) : -1);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) count_bits(p[u]);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) c4[q] += (uint32_t)whole * 0x01010101u;
+  for (int g = 0; g < G; ++g) {
+    const uint4 o = *(const uint4*)&counts[SLOTS > 1 ? slot : g][own16];
+    if (g == 0) { c4[0] = o.x; c4[1] = o.y; c4[2] = o.z; c4[3] = o.w; }
+    else { c4[0] += o.x; c4[1] += o.y; c4[2] += o.z; c4[3] += o.w; }
   }
-  if (!COUNTS && a.total_out) add_arrived();
+  if constexpr (G > 1) *(uint4*)&counts[0][own16] = make_uint4(c4[0], c4[1], c4[2], c4[3]);
 
   // ---- mean over what arrived, decode
   const float post = a.scale * wire_sigma<K, In>(wave);
   if (!TWO) tile_barrier<W>();   // every wavefront has read the last exchange
-  if (!COUNTS && SLOTS == 1 && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)arrived[0]);
   if (lossy == 0) {
     const float f = post * __builtin_amdgcn_rcpf((float)N);
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] *= f;
   } else {
     // the counts, one byte an entry, through LDS into B
-    uint8_t* bytes = COUNTS ? counts[slot] : (uint8_t*)x;
-    if constexpr (!COUNTS) {
-      *(uint4*)(bytes + own16) = make_uint4(c4[0], c4[1], c4[2], c4[3]);
-      tile_barrier<W>();
-    }
-    const uint8_t* mine = bytes + wire_wave_entry<K, In>(wave) + lane;
+    const uint8_t* mine = counts[slot] + wire_wave_entry<K, In>(wave) + lane;
     uint32_t n[16], least = 255;
 #pragma unroll
     for (int r = 0; r < 16; ++r) n[r] = mine[F::reg_entry(r)];
@@ -643,7 +568,6 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] = n[r] ? acc[r] * (post * __builtin_amdgcn_rcpf((float)n[r])) : 0.0f;
     }
-    if constexpr (!COUNTS) tile_barrier<W>();
   }
   from_wire<K, In>(acc, x, wave, lane, k);
   const float c = a.scale * load_sigma<K, In>(lane);
@@ -655,10 +579,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
     for (int q = 0; q < F::C; ++q) {
       u32x4v o;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if constexpr (ES == 4) o[j] = __builtin_bit_cast(uint32_t, acc[4 * q + j]);
-        else o[j] = pack_bf16x2(acc[8 * q + 2 * j], acc[8 * q + 2 * j + 1]);
-      }
+      for (int j = 0; j < 4; ++j) o[j] = __builtin_bit_cast(uint32_t, acc[4 * q + j]);
       store16<kBufNt>(o, rs, lane * 16 + q * 1024);
     }
   }
@@ -670,21 +591,20 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
 
 template <int K> constexpr int kFusedThreads = 64 << (K ? K - 10 : 0);
 // VGPRs are capped so that several workgroups fit on a CU: the loads in flight are those of its neighbours too
-template <int K, int MODE> constexpr int kFusedWaves = MODE == PAIR ? (K == 14 ? 8 : 6) : 4;
-template <int K, class In, int MODE>
-__global__ __launch_bounds__(kFusedThreads<K> * (MODE == GROUPS ? kGroups : 1)) __attribute__((amdgpu_waves_per_eu(kFusedWaves<K, MODE>)))
+template <int K, int MODE>
+__global__ __launch_bounds__(kFusedThreads<K> * (MODE == GROUPS ? kGroups : 1)) __attribute__((amdgpu_waves_per_eu(4)))
 void k_fused(PathArgs a) {
-  fused_tile<K, In, MODE>(a, blockIdx.x, gridDim.x);
+  fused_tile<K, MODE>(a, blockIdx.x, gridDim.x);
 }
-// K = 0: a workgroup of the plain forms serves kBatchSlots tiles of one bucket; ba.tile_start counts workgroups
+// K = 0: a workgroup of the plain form serves kBatchSlots tiles of one bucket; ba.tile_start counts workgroups
 template <int K, int MODE> constexpr int kBatchSlots = K == 0 && MODE != GROUPS ? 8 : 1;
-template <int K, class In, int MODE>
-__global__ __launch_bounds__(kFusedThreads<K> * (MODE == GROUPS ? kGroups : kBatchSlots<K, MODE>)) __attribute__((amdgpu_waves_per_eu(kFusedWaves<K, MODE>)))
+template <int K, int MODE>
+__global__ __launch_bounds__(kFusedThreads<K> * (MODE == GROUPS ? kGroups : kBatchSlots<K, MODE>)) __attribute__((amdgpu_waves_per_eu(4)))
 void k_fused_batched(BatchArgs ba) {
-  constexpr int SLOTS = kBatchSlots<K, MODE>, T = FTile<K, In>::T;
+  constexpr int SLOTS = kBatchSlots<K, MODE>, T = FTile<K, float>::T;
   PathArgs a;
   const u64 group = bucket_of(ba, a);
-  fused_tile<K, In, MODE, SLOTS>(a, group * SLOTS, (a.n_pad + T - 1) / T);
+  fused_tile<K, MODE, SLOTS>(a, group * SLOTS, (a.n_pad + T - 1) / T);
 }
 
 }  // namespace ordev

@@ -722,3 +722,35 @@ def test_fused_forms_at_the_edges_of_their_rules(b, orc, k, N, tiles, kind):
     b.or_fused_path_batched_monitored(b.make_buckets([(x, md, again, cnt2, L, seed, base)]), 1, N, k, kind == "bf16", totals, None)
     assert torch.equal(again.view(torch.uint8), out.view(torch.uint8)) and torch.equal(cnt2, cnt)
     assert totals.item() == cnt.long().sum().item()
+
+
+@pytest.mark.parametrize("k,N,tiles", [(5, 3, 3), (8, 8, 5), (9, 5, 770), (10, 8, 6), (10, 4, 1030), (11, 6, 7), (12, 8, 5), (12, 4, 770),
+                                       (13, 16, 3), (13, 3, 390), (14, 8, 3), (14, 5, 514), (15, 8, 2), (16, 8, 2)])
+def test_fused_bf16_rounds_every_worker_to_the_wire_type(b, orc, k, N, tiles):
+    """The bf16 fused path adds what or_rht_encode_bf16 would have stored.  First and last blocks against the oracle, which
+    rounds every worker's encoded value.  fp32 against fp64 arithmetic moves an encoded value (error about 1e-6 of the block's
+    rms) across a rounding boundary (2^-8 apart) in less than 1 of 1000 cases, and such a step moves the mean by less than its
+    own rounding: under 5 % of the results may differ, by a quarter of what leaving the rounding out changes."""
+    L = -(-(tiles << max(k, 10)) // (1 << k)) << k if k > 9 else (tiles * 1024 + 32 * (1 << max(0, k - 5)))
+    L = L >> k << k
+    rng = np.random.default_rng(8000 + 10 * k + N)
+    gen = torch.Generator(device=dev()).manual_seed(k * 100 + N)
+    x = torch.randn((N, L), device=dev(), generator=gen).mul_(1e-3).to(torch.bfloat16)
+    words = rng.integers(0, 2 ** 32, (N, L // 32), dtype=np.uint64).astype(np.uint32) | np.uint32(0x0F0F0F0F)
+    words[rng.random((N, L // 32)) < 0.9] = 0xFFFFFFFF
+    words[0] = 0xFFFFFFFF
+    md = masks_to_dev(words)
+    seed, base = 0x1122334455667788, (1 << 33) + 6 * max(1 << k, 128)
+    out, cnt = torch.full((L,), float("nan"), dtype=torch.bfloat16, device=dev()), torch.empty(L, dtype=torch.uint8, device=dev())
+    b.or_fused_path_bf16(x, md, N, L, k, seed, base, out, cnt, _workspace(b, L, k))
+    B = max(1 << k, 1024)
+    for lo in (0, (L - 1) // B * B):
+        part = slice(lo, min(lo + B, L))
+        raw = to_np(x[:, part].contiguous())
+        mine = np.ascontiguousarray(words[:, part.start // 32:part.stop // 32])
+        want, wcnt = orc.fused_path(raw, mine, k, seed, base + lo)
+        unrounded, _ = orc.fused_path(np.ascontiguousarray(as_f64(raw).astype(np.float32)), mine, k, seed, base + lo)
+        got = to_np(out[part])
+        assert np.array_equal(to_np(cnt[part]), wcnt)
+        assert (got != want).mean() < 0.05, lo
+        assert rel_l2(got, want) < rel_l2(want, _bf16_bits(unrounded)) / 4, lo
