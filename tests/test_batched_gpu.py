@@ -244,3 +244,30 @@ def test_timing_events_span_every_launch_of_a_batched_call(b):
     assert whole > 1.6 * third > 0.0, (whole, third)      # three launches against one; the margin is for a noisy box
     for e in (a, z, a1, z1):
         hip.hipEventDestroy(e)
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16"])
+@pytest.mark.parametrize("k,N,tiles", [(5, 4, 3), (5, 4, 300), (8, 4, 300), (9, 5, 260), (8, 8, 1030), (9, 8, 600), (5, 6, 1030),
+                                       (10, 8, 1030), (11, 4, 9)])
+def test_totals_of_shards_that_end_inside_a_tile(b, k, N, tiles, kind):
+    """Blocks below 2^10 share tiles of 1024 entries and the last tile of a shard may hold a few blocks only: what lies past
+    the end has not arrived.  One bucket and several, in launches on both sides of the rules that pick the kernel, with most
+    workers whole in that tile; totals against the counts, and against N * L minus what was dropped."""
+    dt = torch.float32 if kind == "f32" else torch.bfloat16
+    B, T = 1 << k, max(1 << k, 1024)
+    gen = torch.Generator(device=dev()).manual_seed(k * 1000 + N)
+    lens = [tiles * T + (B if B < T else 0), T + (T - B if B < T else 0), B, 3 * T]
+    for some in (lens[:1], lens):
+        items, dropped = [], []
+        for j, L in enumerate(some):
+            g = (torch.randn((N, L), device=dev(), generator=gen) * 1e-3).to(dt)
+            m = torch.full((N, L // 32), -1, dtype=torch.int32, device=dev())
+            m[N - 1, 0] = -8                     # three entries
+            m[0, -1] = 0x7FFFFFFF                # one, in the last tile
+            dropped.append(4 if L > 0 else 0)
+            out = torch.empty(L, dtype=dt, device=dev())
+            items.append((g, m, out, torch.full((L,), 255, dtype=torch.uint8, device=dev()), L, 5 + j, 0))
+        totals = torch.full((len(some),), -1, dtype=torch.int64, device=dev())
+        b.or_fused_path_batched_monitored(b.make_buckets(items), len(some), N, k, kind == "bf16", totals, None)
+        for j, (_, _, _, cnt, L, _, _) in enumerate(items):
+            assert int(totals[j]) == int(cnt.sum(dtype=torch.int64)) == N * L - dropped[j], (j, L)
