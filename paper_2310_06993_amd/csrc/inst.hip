@@ -79,76 +79,76 @@ OR_BATCH_LAUNCHER(rdecb_f32, (k_reduce_decode_batched<KR, float>), Geo<KR>::THRE
 OR_BATCH_LAUNCHER(rdecb_bf16, (k_reduce_decode_batched<KR, bf16_t>), Geo<KR>::THREADS)
 OR_BATCH_LAUNCHER(fdecb_f32, (k_finalize_decode_batched<K, float>), G::THREADS)
 OR_BATCH_LAUNCHER(fdecb_bf16, (k_finalize_decode_batched<K, bf16_t>), G::THREADS)
-// GROUPS (tiles up to 2^12) while a launch leaves CUs idle and has the workers for its four groups.  us, 256 tiles, without
-// -> with: 2^12, N = 6 9.5 -> 10.2, N = 8 12.1 -> 11.3; 2^10, N = 2 5.4 -> 6.7, N = 4 with a loss in every tile 7.4 -> 6.6.
-// Smaller tiles leave room for more of them: 2^11, N = 8, 512 tiles 10.7 -> 9.3, 781 tiles 11.9 -> 15.6.
+// Which workers are added before they are encoded is a matter of type, block size and number of workers alone: the two ways
+// round differently, and a bucket gives the same bits alone, in a batch and as part of a longer shard.
+//   bf16: every worker is encoded by itself (its encoded value is rounded).
+//   fp32 up to 2^10: the whole workers' sum first (rht_fused.hpp).  us, every worker by itself -> sum first: 2^10, N = 2, 64 tiles
+//     5.8 -> 5.2; N = 8, 780 tiles 16.7 -> 10.1, 12800 tiles 86.8 -> 87.0; a loss in every copy of every tile, N = 8, 2560 tiles
+//     26.0 -> 21.6.
+//   fp32 2^11: from six workers on.  N = 2, 64 tiles 4.9 -> 5.5; N = 4, 64 tiles 6.4 -> 6.7, 780 tiles 10.2 -> 9.6; N = 8, 64 tiles
+//     9.5 -> 7.2, 780 tiles 16.3 -> 13.8, 12800 tiles 167 -> 171.
+//   fp32 2^12 .. 2^14: every worker by itself.  2^12, N = 16: 100 tiles with 5 % loss 19.2 -> 18.2, 780 tiles 41.8 -> 43.3, 6400
+//     tiles 301 -> 312; N = 64, 780 tiles 142 -> 157; 2^13, N = 8: 256 tiles 16.6 -> 20.0, 2560 tiles 133 -> 136; 2^14, N = 8: 256
+//     tiles 29.4 -> 32.6, 2556 tiles 283 -> 292; a loss in every copy: 2^13, 2560 tiles 139 -> 158.  (The sum first wins where nearly
+//     every copy is whole: 2^14, N = 16, 2560 tiles 481 -> 479, N = 32 926 -> 868.)
+constexpr int kSumFirstFrom = K == 0 ? 1 : K == 11 ? 6 : 256;   // workers
+template <class In> constexpr bool kMaySumFirst = sizeof(In) == 4 && kSumFirstFrom <= 255;
+template <class In> constexpr bool kMayEach = sizeof(In) == 2 || kSumFirstFrom > 1;
+// GROUPS while a launch leaves CUs idle and has the workers for its four groups (same bits as STREAM).  us, without -> with:
+// 2^10, 256 tiles, N = 2 5.4 -> 6.7, N = 4 with a loss in every tile 7.4 -> 6.6; 2^11, N = 8, 512 tiles 10.7 -> 9.3, 781 tiles
+// 11.9 -> 15.6.
 [[maybe_unused]] bool groups_win(unsigned long long tiles, int N) {
-  if (K > 12) return false;
-  if (K == 12) return N >= 8 && tiles <= 256;
   if (N < 6) return N >= 4 && tiles <= 256;
   return tiles <= 512;
 }
-// every worker encoded by itself (rht_fused_each.hpp): bf16 always, fp32 while a launch is short (2^14, N = 4, 1024 tiles
-// 75 -> 70 us; N = 8, 2556 tiles with bursts of loss 272 -> 282)
-template <class In>
-[[maybe_unused]] bool each_wins(unsigned long long tiles) {
-  if (sizeof(In) == 2) return true;
-  return K >= 12 && tiles <= (K == 12 ? 1024 : K == 13 ? 2048 : 1536);
-}
-// The second tile buffer of those pays up to three workgroups on a CU.  (Tiles of 8 or 16 wavefronts, at most two workgroups
-// on a CU whatever the grid: always.)
-bool prefetch_wins(unsigned long long tiles) { return G::W >= 8 || tiles <= 3 * 256; }
+// The second tile buffer of k_fused_each (same bits with and without) pays up to three workgroups on a CU.  (Tiles of 8 or 16
+// wavefronts, at most two workgroups on a CU whatever the grid: always.)
+[[maybe_unused]] bool prefetch_wins(unsigned long long tiles) { return G::W >= 8 || tiles <= 3 * 256; }
 template <class In>
 hipError_t fused(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
   if (units == 0) return hipSuccess;
   if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  if constexpr (sizeof(In) == 4 && K <= 12) {
-    if (groups_win(units, a.N))
-      return launch_kernel(k_fused<K, GROUPS>, dim3((unsigned)units), dim3(kFusedThreads<K> * kGroups), s, pos, a);
-  }
-  if constexpr (sizeof(In) == 2 || K >= 12) {
-    if (each_wins<In>(units)) {
-      if (sizeof(In) == 4 || prefetch_wins(units))
-        return launch_kernel(k_fused_each<K, In, true>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a);
-      if constexpr (sizeof(In) == 2)
-        return launch_kernel(k_fused_each<K, In, false>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a);
+  const dim3 grid((unsigned)units);
+  if constexpr (kMaySumFirst<In>) {
+    if (a.N >= kSumFirstFrom) {
+      if (groups_win(units, a.N)) return launch_kernel(k_fused<K, GROUPS>, grid, dim3(kFusedThreads<K> * kGroups), s, pos, a);
+      return launch_kernel(k_fused<K, STREAM>, grid, dim3(kFusedThreads<K>), s, pos, a);
     }
   }
-  if constexpr (sizeof(In) == 4) {
-    return launch_kernel(k_fused<K, STREAM>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
+  if constexpr (kMayEach<In>) {
+    if (prefetch_wins(units)) return launch_kernel(k_fused_each<K, In, true>, grid, dim3(G::THREADS), s, pos, a);
+    if constexpr (G::W < 8) return launch_kernel(k_fused_each<K, In, false>, grid, dim3(G::THREADS), s, pos, a);
   }
+  return hipErrorInvalidValue;   // not reached
 }
 template <class In>
 hipError_t fused_batched(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
   if (units == 0) return hipSuccess;
   if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  if constexpr (sizeof(In) == 4 && K <= 12) {
-    if (groups_win(units, a.N))
-      return launch_kernel(k_fused_batched<K, GROUPS>, dim3((unsigned)units), dim3(kFusedThreads<K> * kGroups), s, pos, a);
-  }
-  if constexpr (sizeof(In) == 2 || K >= 12) {
-    if (each_wins<In>(units)) {
-      if (sizeof(In) == 4 || prefetch_wins(units))
-        return launch_kernel(k_fused_each_batched<K, In, true>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a);
-      if constexpr (sizeof(In) == 2)
-        return launch_kernel(k_fused_each_batched<K, In, false>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a);
-    }
-  }
-  if constexpr (sizeof(In) == 4) {
-    constexpr int SLOTS = kBatchSlots<K, STREAM>;
-    if constexpr (SLOTS == 1) {
-      return launch_kernel(k_fused_batched<K, STREAM>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
-    } else {
-      BatchArgs b = a;   // tile_start in workgroups of SLOTS tiles
-      uint32_t groups = 0;
-      for (int j = 0; j < a.n; ++j) {
-        b.tile_start[j] = groups;
-        groups += (a.tile_start[j + 1] - a.tile_start[j] + SLOTS - 1) / SLOTS;
+  const dim3 grid((unsigned)units);
+  if constexpr (kMaySumFirst<In>) {
+    if (a.N >= kSumFirstFrom) {
+      if (groups_win(units, a.N)) return launch_kernel(k_fused_batched<K, GROUPS>, grid, dim3(kFusedThreads<K> * kGroups), s, pos, a);
+      constexpr int SLOTS = kBatchSlots<K, STREAM>;
+      if constexpr (SLOTS == 1) {
+        return launch_kernel(k_fused_batched<K, STREAM>, grid, dim3(kFusedThreads<K>), s, pos, a);
+      } else {
+        BatchArgs b = a;   // tile_start in workgroups of SLOTS tiles
+        uint32_t groups = 0;
+        for (int j = 0; j < a.n; ++j) {
+          b.tile_start[j] = groups;
+          groups += (a.tile_start[j + 1] - a.tile_start[j] + SLOTS - 1) / SLOTS;
+        }
+        b.tile_start[a.n] = groups;
+        return launch_kernel(k_fused_batched<K, STREAM>, dim3(groups), dim3(kFusedThreads<K> * SLOTS), s, pos, b);
       }
-      b.tile_start[a.n] = groups;
-      return launch_kernel(k_fused_batched<K, STREAM>, dim3(groups), dim3(kFusedThreads<K> * SLOTS), s, pos, b);
     }
   }
+  if constexpr (kMayEach<In>) {
+    if (prefetch_wins(units)) return launch_kernel(k_fused_each_batched<K, In, true>, grid, dim3(G::THREADS), s, pos, a);
+    if constexpr (G::W < 8) return launch_kernel(k_fused_each_batched<K, In, false>, grid, dim3(G::THREADS), s, pos, a);
+  }
+  return hipErrorInvalidValue;   // not reached
 }
 constexpr launch_fn fus_f32 = fused<float>, fus_bf16 = fused<bf16_t>;
 constexpr batch_fn fusb_f32 = fused_batched<float>, fusb_bf16 = fused_batched<bf16_t>;

@@ -1,6 +1,6 @@
 // The fused path (OptiReduce Sec. 3.3 encode, Sec. 3.1.1 aggregation, Sec. 3.3 / Sec. 4 decode) of fp32 slices for blocks of
-// up to 2^14 entries: one workgroup per tile of T = 2^max(10, k) entries, from N raw slices to the decoded mean.  (bf16, whose
-// encoded values are rounded worker by worker, and small launches of 2^12 .. 2^14 tiles: rht_fused_each.hpp.)
+// up to 2^11 entries: one workgroup per tile of T = 2^max(10, k) entries, from N raw slices to the decoded mean.  (bf16, whose
+// encoded values are rounded worker by worker, few workers at 2^11, and 2^12 .. 2^14: rht_fused_each.hpp.)
 //
 // The encode is linear and the signs are the same for every worker, so the workers whose copy of the tile arrived
 // WHOLE are added up first, as they come from memory, and encoded once.  A worker that lost something in the tile is
@@ -14,8 +14,8 @@
 //   M  register bits = entry bits VB .. VB+3, lane bits (from 0) = VB+4, VB+5, 0 .. VB-1, VB+6 .. 9, wavefront = 10 ..
 //   B  ("wire") lane = entry bits 0 .. 5: a register is 64 consecutive entries, its received bits one lane mask;
 //      register bits = the entry bits not transformed in A and M (U0 = VB+4, U1 = VB+5 and the wavefront bits).
-// Every stage runs as a plain add / subtract between registers, except that tiles of 8 / 16 wavefronts have one / two
-// bits more than registers: U0 / U0, U1 are DPP stages on lane bits 0, 1 of M.  Going from A to M stays inside the
+// Every stage runs as a plain add / subtract between registers, except that tiles of 16 wavefronts have two bits more than
+// registers: U0, U1 are DPP stages on lane bits 0, 1 of M.  Going from A to M stays inside the
 // wavefront (no barrier), M to B is the exchange between wavefronts.  Entry e sits in LDS at e + (e >> (VB+4) << VB):
 // the 32 lanes of either half of a wavefront then fall into 32 different banks in M and B.
 #pragma once
@@ -27,15 +27,14 @@ template <int K, class In>
 struct FTile {
   static constexpr int VB = sizeof(In) == 4 ? 2 : 3, V = 1 << VB, C = 16 / V;   // C loads of 16 bytes a lane
   static constexpr int KT = K ? K : 10, T = 1 << KT, Q = KT - 10, W = 1 << Q;
+  static_assert(Q == 0 || Q == 1 || Q == 4, "tiles of 2^10, 2^11 and 2^14 entries");
   static constexpr int U0 = VB + 4, U1 = VB + 5;
   static constexpr int O0 = VB == 2 ? 8 : 6, O1 = 9;     // the bits of 6..9 other than U0, U1
   static constexpr int PART = 1024 + 64;                 // floats of a wavefront's entries in LDS
   static constexpr int ROW = (1 << U0) + V;              // floats from one value of entry bit U0 to the next
   static constexpr int reg_bit(int i) {                  // entry bit that register bit i stands for in B
     return Q == 0 ? (i == 0 ? U0 : i == 1 ? U1 : i == 2 ? O0 : O1)
-         : Q == 1 ? (i == 0 ? U0 : i == 1 ? U1 : i == 2 ? 10 : O0)
-         : Q == 2 ? (i == 0 ? U0 : i == 1 ? U1 : i + 8)
-         : Q == 3 ? (i == 0 ? U1 : i + 9) : i + 10;
+         : Q == 1 ? (i == 0 ? U0 : i == 1 ? U1 : i == 2 ? 10 : O0) : i + 10;
   }
   static constexpr int wave_bit(int i) {                 // and bit i of the wavefront number
     return Q == 1 ? O1 : i == 0 ? O0 : i == 1 ? O1 : i == 2 ? U0 : U1;
@@ -55,20 +54,13 @@ __device__ __forceinline__ int wire_wave_entry(int wave) {
   for (int i = 0; i < FTile<K, In>::Q; ++i) e |= ((wave >> i) & 1) << FTile<K, In>::wave_bit(i);
   return e;
 }
-// the sign that the DPP stages leave: on the entry bits that took one (U0 for 8 wavefronts, U0 and U1 for 16)
+// the sign that the DPP stages leave: on the entry bits that took one (U0 and U1 for 16 wavefronts)
 template <int K, class In>
 __device__ __forceinline__ float wire_sigma(int wave) {
   constexpr int Q = FTile<K, In>::Q;
-  const int odd = Q == 4 ? (wave >> 2) ^ (wave >> 3) : Q == 3 ? wave >> 2 : 0;
+  const int odd = Q == 4 ? (wave >> 2) ^ (wave >> 3) : 0;
   return odd & 1 ? -1.0f : 1.0f;
 }
-template <int K, class In>
-__device__ __forceinline__ float load_sigma(int lane) {
-  constexpr int Q = FTile<K, In>::Q;
-  const int odd = Q == 4 ? (lane >> 4) ^ (lane >> 5) : Q == 3 ? lane >> 4 : 0;
-  return odd & 1 ? -1.0f : 1.0f;
-}
-
 template <int W>
 __device__ __forceinline__ void tile_barrier() {   // tiles of one wavefront need none: its LDS accesses are in order
   if constexpr (W > 1) __syncthreads();
@@ -91,8 +83,10 @@ __device__ __forceinline__ void stages_m(float (&v)[16], int lane, int k) {
   reg_stage<1>(v);
   if (VB == 2 || K || k > VB + 2) reg_stage<2>(v);
   if (K || k > VB + 3) reg_stage<3>(v);
-  if constexpr (Q >= 3) lane_stage<0>(v, lane);
-  if constexpr (Q == 4) lane_stage<1>(v, lane);
+  if constexpr (Q == 4) {
+    lane_stage<0>(v, lane);
+    lane_stage<1>(v, lane);
+  }
 }
 template <int K, class In>
 __device__ __forceinline__ void stages_b(float (&v)[16], int k) {
@@ -251,9 +245,9 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   typedef float In;
   typedef FTile<K, In> F;
   constexpr int W = F::W, T = F::T, ES = sizeof(In), G = MODE == GROUPS ? kGroups : 1;
-  constexpr bool TWO = MODE == STREAM && K == 14;   // two exchange buffers, one barrier a transform (one workgroup on a CU)
+  static_assert(F::Q <= 1, "tiles of one or two wavefronts: no sign from DPP stages");
   static_assert(SLOTS == 1 || (W == 1 && G == 1), "several tiles per workgroup: tiles of one wavefront");
-  constexpr int BUFS = MODE == GROUPS ? G : TWO ? 2 : SLOTS;
+  constexpr int BUFS = MODE == GROUPS ? G : SLOTS;
   __shared__ __align__(16) float xbuf[BUFS][W * F::PART];
   __shared__ __align__(16) float ybuf[G > 1 ? G - 1 : 1][G > 1 ? 1024 * W : 4];   // GROUPS: what groups 1.. hand to group 0
   __shared__ __align__(16) uint8_t counts[G * SLOTS][T];
@@ -423,7 +417,6 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   };
 
   if constexpr (MODE == STREAM) {
-    int flip = 0;
     uint32_t lost32 = 0;
     auto consume = [&](int i, Raw16<In>& r16, uint32_t& m) {
       if ((i & 31) == 0) lost32 = marks_of(i);
@@ -435,9 +428,8 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
       if (lost) {
         int lane_t = lane;   // LDS addresses formed here, not kept in registers all along
         asm volatile("" : "+v"(lane_t));
-        if (!TWO) tile_barrier<W>();
-        to_wire<K, In>(v, TWO ? xbuf[flip] : x, wave, lane_t, k);
-        flip ^= TWO;
+        tile_barrier<W>();
+        to_wire<K, In>(v, x, wave, lane_t, k);
         add_masked(v, words);
       }
     };
@@ -448,13 +440,11 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
     }
     if (whole > 0) {
       sign_all(raw);
-      if (!TWO) tile_barrier<W>();
-      to_wire<K, In>(raw, TWO ? xbuf[flip] : x, wave, lane, k);
-      flip ^= TWO;
+      tile_barrier<W>();
+      to_wire<K, In>(raw, x, wave, lane, k);
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] += raw[r];
     }
-    if (TWO) x = xbuf[flip];
   } else {
     // Items 0 .. lossy - 1 are the workers with a loss, item lossy the sum over the whole ones; round t: items 4 t ..
     // 4 t + 3.  The rounds before the last run while the whole workers' entries are on their way.
@@ -546,8 +536,8 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   if constexpr (G > 1) *(uint4*)&counts[0][own16] = make_uint4(c4[0], c4[1], c4[2], c4[3]);
 
   // ---- mean over what arrived, decode
-  const float post = a.scale * wire_sigma<K, In>(wave);
-  if (!TWO) tile_barrier<W>();   // every wavefront has read the last exchange
+  const float post = a.scale;
+  tile_barrier<W>();   // every wavefront has read the last exchange
   if (lossy == 0) {
     const float f = post * __builtin_amdgcn_rcpf((float)N);
 #pragma unroll
@@ -570,9 +560,8 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
     }
   }
   from_wire<K, In>(acc, x, wave, lane, k);
-  const float c = a.scale * load_sigma<K, In>(lane);
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = flip_sign(acc[r] * c, sg, r);
+  for (int r = 0; r < 16; ++r) acc[r] = flip_sign(acc[r] * a.scale, sg, r);
   {
     const __amdgpu_buffer_rsrc_t rs = rsrc_of((const In*)a.out + ew, left * ES);
 #pragma unroll

@@ -2,8 +2,9 @@
 // transform to layout B, rounding to the wire type (bf16), addition under the received mask; the mean is decoded the same way
 // back.  Tiles of 2, 4, 8 or 16 wavefronts use the transposed transform of rht_tile.hpp, in both directions.
 //
-// bf16: every worker's encoded value is rounded as if it had been stored and sent, so every worker has to be encoded.  fp32
-// of 2^12 .. 2^14: small launches.  (Other fp32 launches: rht_fused.hpp.)
+// bf16: every worker's encoded value is rounded as if it had been stored and sent, so every worker has to be encoded.  fp32: blocks
+// of 2^12 .. 2^14, and few workers at 2^11, where adding up whole workers first costs more at the start and the end of a
+// workgroup than the transforms that it saves (figures at the rule, inst.hip).
 //
 // PREFETCH: a second tile buffer, so that the next worker's tile is in flight during the transform (same arithmetic, same
 // results).  It shortens the chain of dependent steps of a workgroup and wins while a launch puts at most three workgroups on

@@ -557,8 +557,9 @@ def test_two_level_reduce(b, orc, G, M, L):
 @pytest.mark.parametrize("k,kind", [(8, "f32"), (11, "f32"), (12, "f32"), (12, "bf16")])
 def test_fused_forms_on_both_sides_of_the_grid_size_switch(b, orc, k, kind):
     """Launches of up to 768 tiles use the kernel form that prefetches the next worker's tile, larger ones
-    the plain form: same arithmetic, so a shard of 769 tiles must reproduce, bit for bit, what its first 768
-    tiles give as a shard of their own; sampled blocks of the large launch are checked against the oracle."""
+    the plain form (fp32 blocks of 2^8: one form here, the one that sums whole workers first): same arithmetic, so a
+    shard of 769 tiles must reproduce, bit for bit, what its first 768 tiles give as a shard of their own; sampled
+    blocks of the large launch are checked against the oracle."""
     N = 3
     tile = max(1 << k, 1024)
     L_small, L_big = 768 * tile, 769 * tile
@@ -695,8 +696,8 @@ def test_reduce_decode_blocks_above_one_tile(b, orc, k, blocks, N, kind):
                                        (13, 9, 3), (14, 4, 512), (14, 4, 513), (14, 5, 1), (14, 1, 1537)])
 @pytest.mark.parametrize("kind", ["f32", "bf16"])
 def test_fused_forms_at_the_edges_of_their_rules(b, orc, k, N, tiles, kind):
-    """Either side of each rule by which the launcher picks a form of the fused kernel: the value, counts and arrival totals
-    of the first, the middle and the last block against the oracle, of the single and the batched call."""
+    """Sizes at and between the rules by which the launcher picks a form of the fused kernel: the value, counts and arrival
+    totals of the first, the middle and the last block against the oracle, of the single and the batched call."""
     B, L = 1 << k, tiles << k
     rng = np.random.default_rng(7000 + 100 * k + N + tiles)
     gen = torch.Generator(device=dev()).manual_seed(k + tiles)
@@ -754,3 +755,39 @@ def test_fused_bf16_rounds_every_worker_to_the_wire_type(b, orc, k, N, tiles):
         assert np.array_equal(to_np(cnt[part]), wcnt)
         assert (got != want).mean() < 0.05, lo
         assert rel_l2(got, want) < rel_l2(want, _bf16_bits(unrounded)) / 4, lo
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16"])
+@pytest.mark.parametrize("k,N", [(8, 2), (8, 5), (9, 8), (10, 4), (10, 6), (11, 2), (11, 5), (11, 6), (11, 16), (12, 3), (12, 8), (12, 16),
+                                 (13, 4), (13, 8), (14, 4), (14, 9)])
+def test_fused_bits_do_not_depend_on_the_size_of_the_launch(b, k, N, kind):
+    """A shard of any length gives, bit for bit, what its beginning gives as a shard of its own or as a bucket among others:
+    lengths on both sides of every number of tiles at which the launcher changes to another form (256, 512, 768)."""
+    T = max(1 << k, 1024)
+    sizes = (1, 100, 256, 257, 512, 513, 768, 769, 1100, 1700, 2100)
+    gen = torch.Generator(device=dev()).manual_seed(31 * k + N)
+    dt = torch.float32 if kind == "f32" else torch.bfloat16
+    L_all = sizes[-1] * T
+    x = torch.randn((N, L_all), device=dev(), generator=gen).mul_(1e-3).to(dt)
+    m = torch.where(torch.rand((N, L_all // 256), device=dev(), generator=gen) < 0.02, 0, -1).to(torch.int32).repeat_interleave(8, 1)
+    seed, base = 0x55AA55AA12345678, 0
+    call = b.or_fused_path if kind == "f32" else b.or_fused_path_bf16
+
+    def alone(L):
+        out, cnt = torch.full((L,), float("nan"), dtype=dt, device=dev()), torch.full((L,), 255, dtype=torch.uint8, device=dev())
+        call(x[:, :L].contiguous(), m[:, :L // 32].contiguous(), N, L, k, seed, base, out, cnt, None)
+        return out.view(torch.uint8), cnt
+
+    want, count = alone(L_all)
+    es = x.element_size()
+    for tiles in sizes[:-1]:
+        L = tiles * T
+        out, cnt = alone(L)
+        assert torch.equal(out, want[:L * es]) and torch.equal(cnt, count[:L]), tiles
+    # 24 buckets of 100 tiles: a launch of 2400
+    L = 100 * T
+    xs, ms = x[:, :L].contiguous(), m[:, :L // 32].contiguous()
+    outs = torch.full((24, L), float("nan"), dtype=dt, device=dev())
+    b.or_fused_path_batched(b.make_buckets([(xs, ms, outs[j], None, L, seed, base) for j in range(24)]), 24, N, k, kind == "bf16", None)
+    for j in (0, 11, 23):
+        assert torch.equal(outs[j].view(torch.uint8), want[:L * es]), j
