@@ -406,12 +406,19 @@ or_status check_path(const void* in, const uint32_t* masks, int N, u64 L, int k,
   return OR_OK;
 }
 
-// Reduce + decode of blocks above 2^14: one kernel for both, or a reduction and a decode with sum and counts in between?
-// The one kernel moves less, but a workgroup takes a whole block through all workers one after the other, so launches that
-// leave CUs idle pay for every worker.  fp32 2^16, two launches -> one: N = 2, 4 blocks 21.8 -> 17.1 us; N = 8, 48 blocks
-// 42 -> 53, 96 blocks 63 -> 60, 128 blocks 80 -> 65; N = 32, 48 blocks 101 -> 184, 128 blocks 226 -> 224, 256 blocks
-// 423 -> 363.  2^15 and bf16 cross over at the same numbers.
-bool reduce_in_one_kernel(u64 blocks, int N) { return N <= 2 || blocks >= 128; }
+// Reduce + decode of blocks above 2^14: one kernel for both, or a reduction and a decode with sum and counts in between?  The same
+// additions in the same order, so the same bits.  The one kernel moves less, but a workgroup takes a whole block through all
+// workers one after the other, so launches that leave CUs idle pay for every worker.  us, two launches -> one, fp32 2^15 / 2^16,
+// bf16 2^15 / 2^16:  N = 1, 2 blocks 12.2 -> 10.5 / 21.5 -> 19.1, 12.1 -> 10.3 / 21.5 -> 18.8;  N = 2, 16 blocks 14.1 -> 14.7 /
+// 24.5 -> 26.6, 13.9 -> 12.2 / 24.2 -> 23.1, 48 blocks 17.0 -> 15.4 / 31.4 -> 27.1, 16.4 -> 12.8 / 29.4 -> 24.0;  N = 8, 48
+// blocks 22.5 -> 30.6 / 43.1 -> 58.3, 18.5 -> 21.6 / 33.7 -> 41.4, 96 blocks 33.9 -> 33.6 / 64.1 -> 64.2, 25.2 -> 22.6 /
+// 47.2 -> 44.7, 256 blocks 74.7 -> 56.5 / 146 -> 113, 48.8 -> 32.9 / 92.0 -> 69.0;  N = 16, 96 blocks 52.1 -> 58.0 / 100 -> 114,
+// 33.8 -> 35.7 / 65.0 -> 72.7, 128 blocks 67.0 -> 62.2 / 133 -> 125, 42.0 -> 37.3 / 81.4 -> 79.0;  N = 32, 128 blocks 124 -> 114 /
+// 224 -> 229, 67.7 -> 65.8 / 144 -> 141.
+bool reduce_in_one_kernel(u64 blocks, int N, bool bf16) {
+  if (N <= 2) return N == 1 || bf16 || blocks >= 48;
+  return blocks >= (N <= 8 ? 96 : 128);
+}
 
 // enqueue one checked shard: T = float or uint16_t (bf16 bits).  `allow` = which of this entry point's first /
 // last launches this shard may be (timing events ride on those only); `total`, if not null, is expected to be
@@ -470,7 +477,7 @@ or_status run_path(bool fused, const T* in, const uint32_t* masks, int N, u64 L,
     if (hipError_t e = t->fused_f32(a, units, s, 0)) return finish(e);
     return finish(t->decode_f32(d, units, s, last));
   }
-  if (reduce_in_one_kernel(L >> k, N))
+  if (reduce_in_one_kernel(L >> k, N, bf16))
     return finish((bf16 ? t->reduce_decode_bf16 : t->reduce_decode_f32)(a, units, s, first | last));
   uint8_t* cnt = count_out ? count_out : ws_cnt;
   constexpr int VEC = 16 / sizeof(T);

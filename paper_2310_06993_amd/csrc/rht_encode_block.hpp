@@ -34,21 +34,20 @@ __device__ __forceinline__ void block_lane_signs(u64 seed, u64 g, float* x, int 
   __builtin_amdgcn_wave_barrier();
 }
 
-// 16 values of a tile in B as bf16.  Two registers (the entries 2^reg_bit(0) apart) are packed and exchanged with the
-// neighbour lane, so that a lane stores two consecutive entries of one of them: 4 bytes a lane instead of 2.
-template <int K>
-__device__ __forceinline__ void store_wire_bf16(const float (&v)[16], __amdgpu_buffer_rsrc_t rs, int tile_byte, int wave, int lane) {
-  typedef FTile<K, bf16_t> F;
+// 16 registers of 64 consecutive entries each (register r: from entry `first` + r * STEP on) as bf16.  Two registers are packed
+// and exchanged with the neighbour lane, so that a lane stores two consecutive entries of one of them: 4 bytes a lane, not 2.
+template <int STEP>
+__device__ __forceinline__ void store_pairs_bf16(const float (&v)[16], __amdgpu_buffer_rsrc_t rs, int tile_byte, int first, int lane) {
   const int odd = lane & 1;
   const uint32_t pick = odd ? 0x03020706u : 0x05040100u;   // bytes 0..3: our pair, 4..7: the neighbour's
-  const int at = (wire_wave_entry<K, bf16_t>(wave) + (lane & ~1) + odd * F::reg_entry(1)) * 2;
+  const int at = (first + (lane & ~1) + odd * STEP) * 2;
 #pragma unroll
   for (int r = 0; r < 16; r += 2) {
     const uint32_t own = pack_bf16x2(v[r], v[r + 1]);
     const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xf, 0xf, true);   // lane ^ 1
     // even: (own.lo, other.lo); odd: (other.hi, own.hi)
     const uint32_t x = __builtin_amdgcn_perm(other, own, pick);
-    __builtin_amdgcn_raw_buffer_store_b32(x, rs, at, tile_byte + F::reg_entry(r) * 2, kBufNt);
+    __builtin_amdgcn_raw_buffer_store_b32(x, rs, at, tile_byte + r * STEP * 2, kBufNt);
   }
 }
 
@@ -58,6 +57,7 @@ void k_encode_block_bf16(PathArgs a) {
   typedef FTile<14, bf16_t> F;
   constexpr int P = 1 << (K - 14), T = F::T, W = F::W, BUFS = K == 15 ? 1 : 2;
   constexpr bool AHEAD = K == 16;
+  static_assert(F::reg_entry(1) == 1024 && F::reg_entry(8) == 8192, "register bits of B are entry bits 10 .. 13");
   __shared__ __align__(16) float xbuf[BUFS][W * F::PART];
   const int wave = wave_id(), lane = lane_id();
   const u64 full = a.unit0 >> (K - 14), blocks = a.n_pad >> K;   // blocks that lie inside the input; with the cut one
@@ -115,7 +115,7 @@ void k_encode_block_bf16(PathArgs a) {
       flip ^= BUFS - 1;
 #pragma unroll
       for (int r = 0; r < 16; ++r) v[p][r] *= c;
-      store_wire_bf16<14>(v[p], out, p * (T * 2), wave, lane_t);
+      store_pairs_bf16<F::reg_entry(1)>(v[p], out, p * (T * 2), wire_wave_entry<14, bf16_t>(wave), lane_t);
     }
   }
 }

@@ -6,8 +6,9 @@
 // lane (layout A of rht_fused.hpp) with DEPTH tiles in flight; a wavefront looks at a tile's received bits once and takes
 // the plain additions if nothing is missing in its part.  Counts are not carried along: a wavefront that saw a loss reads
 // the bits of that tile again at the end.
-// fp32, N = 8, 1024 blocks of 2^16: 601 -> 421 us (5.9 TB/s); bf16 367 -> 251; 2048 blocks of 2^15: 591 -> 421, bf16
-// 360 -> 232.
+// N = 8, from reduction + decode: 1024 blocks of 2^16 605 -> 427 us (5.8 TB/s), bf16 368 -> 263; 2048 blocks of 2^15 595 -> 426,
+// bf16 360 -> 241.  (With the 2^14 transform of rht_fused.hpp, which needs fewer exchanges and no DPP stages for most bits, 1 to 8 %
+// less from four workers on; its order of stages gave other bits than the two launches that small shards take.)
 #pragma once
 #include "rht_encode_block.hpp"
 
@@ -134,40 +135,38 @@ __global__ __launch_bounds__(1024) void k_reduce_decode_block(PathArgs a) {
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  // ---- decode
+  // ---- decode, by the stages of decode_block in their order: the same bits as from a reduction and a decode of their own.  Each
+  // tile goes through LDS from A to layout B of rht_tile.hpp; the two buffers alternate, one barrier per exchange.
+  uint32_t slo, shi;
+  block_sign_words<K>(a.seed, a.base + ew, slo, shi);
   across_tiles<P, 16>(v);
-  const int wire = wire_wave_entry<14, In>(wave);   // register r in B: 64 entries from wire + reg_entry(r)
-  uint32_t slo, shi;   // lane 16 p + r: their signs in tile p
-  {
-    const u64 g = a.base + e0 + (u64)((lane >> 4) & (P - 1)) * T + (u64)(wire + ((lane & 15) << 10));
-    static_assert(F::reg_entry(1) == 1024 && F::reg_entry(8) == 8192, "register bits of B are entry bits 10 .. 13");
-    const u64 ctr = g >> 7;
-    const u32x4 w = philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), 0u, 0u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
-    slo = (wire & 64) ? w.c : w.a;
-    shi = (wire & 64) ? w.d : w.b;
-  }
-  const float c = a.scale * wire_sigma<14, In>(wave);
+  const float c = a.scale * lane_sigma(lane, 6);
   const __amdgpu_buffer_rsrc_t out = rsrc_of((const In*)a.out + e0, P * T * ES);
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     int lane_t = lane;   // addresses formed here, not kept in registers all along
     asm volatile("" : "+v"(lane_t));
-    to_wire<14, In>(v[p], xbuf[p & 1], wave, lane_t, 14);
+    lds_a<14, In, true>(v[p], xbuf[0], wave, lane_t);
+    __syncthreads();
+    const float* mine = xbuf[0] + F::padded(wave * 64) + lane_t;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[p][r] = mine[F::padded(r << 10)];
+    transform<K, false, false>(v[p], xbuf[1], wave, lane_t, 14);
 #pragma unroll
     for (int r = 0; r < 16; ++r) v[p][r] *= c;
     apply_block_signs(v[p], slo, shi, p);
     if constexpr (ES == 2) {
-      store_wire_bf16<14>(v[p], out, p * (T * ES), wave, lane_t);
+      store_pairs_bf16<64>(v[p], out, p * (T * ES), wave * 1024, lane_t);
     } else {
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v[p][r]), out, (wire + lane_t) * 4, (p * T + F::reg_entry(r)) * 4, kBufNt);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v[p][r]), out, (wave * 1024 + lane_t) * 4, (p * T + r * 64) * 4, kBufNt);
     }
   }
   if (a.total_out) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) total += (uint32_t)__shfl_xor((int)total, o, 64);
-    if (lane == 0) atomicAdd(&arrived, total);
+    if (lane == 0) atomicAdd(&arrived, total);   // zeroed ahead of the barriers above
     __syncthreads();
     if (threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)arrived);
   }
