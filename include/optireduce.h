@@ -15,6 +15,7 @@
  *     several kernels may by then have enqueued the earlier ones, so treat its outputs as undefined.
  *   - Vectors are contiguous.  fp32 data is `float`; bf16 data is passed as uint16_t bit patterns.
  *     Data pointers must be 16-byte aligned, mask pointers 4-byte aligned.
+ *     count_out of or_reduce_decode* and or_fused_path* may lie at any address (16-byte aligned is fastest).
  *   - block_log2 = k selects the transform block B = 2^k, OR_MIN_LOG2 <= k <= OR_MAX_LOG2.
  *   - The random diagonal: entry i of the padded vector (i counted from `base_index` for the first
  *     entry passed) is multiplied by -1 iff bit (i mod 128) of Philox4x32-10(counter = (i div 128,

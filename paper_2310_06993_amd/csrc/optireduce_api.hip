@@ -96,10 +96,15 @@ __device__ __forceinline__ void masked_reduce_at(const Wire* __restrict__ shards
 #pragma unroll
   for (int j = 0; j < VEC; j += 4)
     __builtin_nontemporal_store(f4{acc[j], acc[j + 1], acc[j + 2], acc[j + 3]}, (f4*)(sum_out + e + j));
+  if (((uintptr_t)count_out & 3) == 0) {
 #pragma unroll
-  for (int j = 0; j < VEC; j += 4)
-    __builtin_nontemporal_store(cnt[j] | (cnt[j + 1] << 8) | (cnt[j + 2] << 16) | (cnt[j + 3] << 24),
-                                (uint32_t*)(count_out + e + j));
+    for (int j = 0; j < VEC; j += 4)
+      __builtin_nontemporal_store(cnt[j] | (cnt[j + 1] << 8) | (cnt[j + 2] << 16) | (cnt[j + 3] << 24),
+                                  (uint32_t*)(count_out + e + j));
+  } else {   // or_reduce_decode* takes counts at any address
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) count_out[e + j] = (uint8_t)cnt[j];
+  }
 }
 
 template <class Wire, int VEC>
@@ -197,13 +202,14 @@ __global__ __launch_bounds__(256) void k_received_total(const uint8_t* __restric
                                                         unsigned long long* __restrict__ total) {
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));
   uint32_t acc = 0;
+  const bool wide = ((uintptr_t)count & 15) == 0;   // or_reduce_decode_batched takes counts at any address
   for (u64 e = ((u64)blockIdx.x * 256 + threadIdx.x) * 16; e < L; e += (u64)gridDim.x * 256 * 16) {
-    if (e + 16 <= L) {
+    if (wide && e + 16 <= L) {
       const u4 c = *(const u4*)(count + e);
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_sad_u8(c[j], 0u, acc);
     } else {
-      for (u64 i = e; i < L; ++i) acc += count[i];
+      for (u64 i = e; i < L && i < e + 16; ++i) acc += count[i];
     }
   }
   unsigned long long w = acc;

@@ -574,7 +574,12 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   }
   if (a.count_out) {
     const __amdgpu_buffer_rsrc_t rs = rsrc_of(a.count_out + ew, left);
-    store16<kBufNt>(u32x4v{c4[0], c4[1], c4[2], c4[3]}, rs, lane * 16);
+    if (((uintptr_t)a.count_out & 15) == 0) {
+      store16<kBufNt>(u32x4v{c4[0], c4[1], c4[2], c4[3]}, rs, lane * 16);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) store_counts4(c4[q], rs, lane * 16 + q * 4, 0, false);
+    }
   }
 }
 

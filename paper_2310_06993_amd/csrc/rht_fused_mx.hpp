@@ -288,8 +288,15 @@ __global__ __launch_bounds__(1024) void k_fused_mx(PathArgs a) {
     }
     __syncthreads();
     const u32x4v c_lo = ((const u32x4v*)stage)[threadIdx.x], c_hi = ((const u32x4v*)(stage + T))[threadIdx.x];
-    __builtin_nontemporal_store(c_lo, (u32x4v*)(a.count_out + e_lo) + threadIdx.x);
-    __builtin_nontemporal_store(c_hi, (u32x4v*)(a.count_out + e_hi) + threadIdx.x);
+    if (((uintptr_t)a.count_out & 15) == 0) {
+      __builtin_nontemporal_store(c_lo, (u32x4v*)(a.count_out + e_lo) + threadIdx.x);
+      __builtin_nontemporal_store(c_hi, (u32x4v*)(a.count_out + e_hi) + threadIdx.x);
+    } else {
+      for (int j = 0; j < T; j += 1024) {
+        a.count_out[e_lo + j + threadIdx.x] = stage[j + threadIdx.x];
+        a.count_out[e_hi + j + threadIdx.x] = stage[T + j + threadIdx.x];
+      }
+    }
     __syncthreads();   // the staging area is part of the transform buffers: all reads before anyone transforms again
   };
   const float post = lane_sigma(lane, 4) * (scale_first ? 1.0f : a.scale);   // the sign that the DPP stages leave on a lane

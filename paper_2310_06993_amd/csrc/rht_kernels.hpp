@@ -289,6 +289,17 @@ __device__ __forceinline__ void store_counts(uint8_t* count_out, u64 e0, u64 lim
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// The counts of a path call may lie at any address: the wide stores below are for those aligned to them, else bytes.
+// `aligned`: the same on every lane (it is a property of the call's pointer).
+__device__ __forceinline__ void store_counts4(uint32_t c, __amdgpu_buffer_rsrc_t rs, int off, int tile_off, bool aligned) {
+  if (aligned) {
+    __builtin_amdgcn_raw_buffer_store_b32(c, rs, off, tile_off, kBufNt);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(c >> (8 * j)), rs, off + j, tile_off, kBufNt);
+  }
+}
+
 // mean over what arrived (0 where nothing arrived), times `post`.  The reciprocal of the count comes
 // from v_rcp_f32 (1 ulp), far inside the 1e-6 budget of the path.
 template <int NR>

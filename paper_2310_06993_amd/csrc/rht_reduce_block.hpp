@@ -94,6 +94,7 @@ __global__ __launch_bounds__(1024) void k_reduce_decode_block(PathArgs a) {
 
   // ---- counts, mean over what arrived
   const __amdgpu_buffer_rsrc_t counts = rsrc_of(a.count_out + ew, a.count_out ? (P - 1) * T + 1024 : 0);   // none: stores are dropped
+  const bool counts_aligned = ((uintptr_t)a.count_out & 3) == 0;
   uint32_t total = 0;
 #pragma unroll
   for (int p = 0; p < P; ++p) {
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(1024) void k_reduce_decode_block(PathArgs a) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int e = (4 * q >> F::VB) * 64 * F::V + (4 * q & (F::V - 1));
-      __builtin_amdgcn_raw_buffer_store_b32(c4[q], counts, lane * F::V, p * T + e, kBufNt);
+      store_counts4(c4[q], counts, lane * F::V, p * T + e, counts_aligned);
     }
     __builtin_amdgcn_sched_barrier(0);
   }

@@ -792,3 +792,34 @@ def test_fused_bits_do_not_depend_on_the_size_of_the_launch(b, k, N, kind):
     b.or_fused_path_batched(b.make_buckets([(xs, ms, outs[j], None, L, seed, base) for j in range(24)]), 24, N, k, kind == "bf16", None)
     for j in (0, 11, 23):
         assert torch.equal(outs[j].view(torch.uint8), want[:L * es]), j
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16"])
+@pytest.mark.parametrize("k,N,blocks", [(5, 3, 37), (8, 8, 2100), (10, 2, 3), (10, 8, 700), (11, 8, 5), (11, 8, 600), (12, 5, 7), (14, 3, 2),
+                                        (15, 2, 2), (15, 9, 2), (16, 1, 1), (16, 8, 3)])
+def test_counts_at_any_address(b, k, N, blocks, kind):
+    """count_out of a path call needs no alignment: at odd addresses every form stores the counts that it stores at an aligned
+    one, and nothing before or behind them; values and totals are unchanged."""
+    L = blocks << k
+    dt = torch.float32 if kind == "f32" else torch.bfloat16
+    gen = torch.Generator(device=dev()).manual_seed(17 * k + N)
+    x = torch.randn((N, L), device=dev(), generator=gen).to(dt)
+    m = torch.where(torch.rand((N, L // 32), device=dev(), generator=gen) < 0.1, 0x0F0F0F0F, -1).to(torch.int32)
+    ws = _workspace(b, L, k)
+    bf16 = kind == "bf16"
+    for single, batched in ((b.or_fused_path_bf16 if bf16 else b.or_fused_path, b.or_fused_path_batched_monitored),
+                            (b.or_reduce_decode_bf16 if bf16 else b.or_reduce_decode, b.or_reduce_decode_batched)):
+        want, count = torch.empty(L, dtype=dt, device=dev()), torch.empty(L, dtype=torch.uint8, device=dev())
+        single(x, m, N, L, k, 3, 0, want, count, ws)
+        for off in (1, 2, 4, 8):
+            store = torch.full((L + 32,), 0xA5, dtype=torch.uint8, device=dev())
+            out = torch.empty_like(want)
+            single(x, m, N, L, k, 3, 0, out, store[off:off + L], ws)
+            again, totals = torch.empty_like(want), torch.full((1,), -1, dtype=torch.int64, device=dev())
+            store2 = torch.full_like(store, 0xA5)
+            batched(b.make_buckets([(x, m, again, store2[off:off + L], L, 3, 0)]), 1, N, k, bf16, totals, ws)
+            for s in (store, store2):
+                assert torch.equal(s[off:off + L], count), off
+                assert bool((s[:off] == 0xA5).all()) and bool((s[off + L:] == 0xA5).all()), off
+            assert torch.equal(out, want) and torch.equal(again, want), off
+            assert totals.item() == count.sum(dtype=torch.int64).item(), off
