@@ -275,17 +275,20 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   if (SLOTS > 1 ? lane < 8 : threadIdx.x < 8) marks[lane & 7] = 0;
   if (SLOTS == 1 && threadIdx.x == 0) arrived[0] = 0;
 
-  // ---- loads; no such worker (i < 0 or >= N): zeros, without touching memory
+  // ---- loads; no such worker (i < 0 or >= N): zeros, without touching memory.  The whole offset is in the vector operand, which the
+  // range check covers by any reading of it: what lies past a tile that is cut short (K = 0) is not read
   auto request = [&](int i, Raw16<In>& r) {   // the lane's entries in A
     const bool there = i >= 0 && i < N;
     const __amdgpu_buffer_rsrc_t rs = rsrc_of((const In*)a.in + (u64)(there ? i : 0) * L + ew, there ? left * ES : 0);
 #pragma unroll
-    for (int c = 0; c < F::C; ++c) r.q[c] = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, c * 1024, kBufNt));
+    for (int c = 0; c < F::C; ++c) r.q[c] = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16 + c * 1024, 0, kBufNt));
   };
+  const u64 e4 = ew + (u64)(grp * 256);   // (as a runtime part of the offset: 2 % slower)
+  const int bytes4 = left > grp * 256 ? (left - grp * 256) * ES : 0;
   auto request4 = [&](int i, u32x4v& r) {   // four entries from 256 grp + 4 lane of the wavefront's part
     const bool there = i >= 0 && i < N;
-    const __amdgpu_buffer_rsrc_t rs = rsrc_of((const In*)a.in + (u64)(there ? i : 0) * L + ew, there ? left * ES : 0);
-    r = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, grp * 1024, 0));
+    const __amdgpu_buffer_rsrc_t rs = rsrc_of((const In*)a.in + (u64)(there ? i : 0) * L + e4, there ? bytes4 : 0);
+    r = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, 0, 0));
   };
   auto request_bits = [&](int i) {   // received bits of the lane's 16 entries from 16 lane of the wavefront's part on
     const bool there = i >= 0 && i < N;
