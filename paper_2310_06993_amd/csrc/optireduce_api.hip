@@ -5,7 +5,6 @@
 #include <math.h>
 #include <algorithm>
 #include <mutex>
-#include <vector>
 
 #include "../../include/optireduce.h"
 #include "launch_table.hpp"
@@ -576,41 +575,45 @@ BatchPlan plan_batches(int nonempty) {
   return p;
 }
 
-// No output of one bucket may touch anything of another bucket (the buckets of a launch run concurrently).  The spans
-// of all buckets are gathered, the written ones sorted by address and every span looked up among them: for the 238
-// buckets of a GPT-2-XL-sized gradient the pairwise comparison this replaces took 0.3 ms of the host's time before the
-// first launch, this takes a few microseconds.
-class SpanSet {
- public:
-  explicit SpanSet(size_t spans) {
-    written_.reserve(spans);
-    read_.reserve(spans);
-  }
-  void add(const void* p, u64 bytes, bool written, int owner) {
-    if (p && bytes) (written ? written_ : read_).push_back({(uintptr_t)p, (uintptr_t)p + bytes, owner});
-  }
-  // false: a written span overlaps a span of another owner (what overlaps within one bucket is that bucket's check)
-  bool disjoint() {
-    const auto before = [](const Span& a, const Span& b) { return a.lo < b.lo; };
-    if (!std::is_sorted(written_.begin(), written_.end(), before)) std::sort(written_.begin(), written_.end(), before);
-    for (size_t i = 1; i < written_.size(); ++i)   // written spans of one owner are disjoint already
-      if (written_[i].lo < written_[i - 1].hi) return false;
-    for (const Span& r : read_) {
-      // the first written span that ends behind the start of r
-      auto w = std::upper_bound(written_.begin(), written_.end(), r.lo, [](uintptr_t v, const Span& s) { return v < s.hi; });
-      for (; w != written_.end() && w->lo < r.hi; ++w)
-        if (w->owner != r.owner) return false;
-    }
-    return true;
-  }
-
- private:
+// No output of one bucket may touch anything of another bucket (the buckets of a launch run concurrently).  `each(f)` calls
+// f(pointer, bytes, written, owner) for every span of the call; false: a written span overlaps a span of another owner (what
+// overlaps within one bucket is that bucket's check).  Written spans are sorted by address, kChunk at a time in an array on the
+// stack (nothing is allocated), and every other span is looked up among them: for the 238 buckets of a GPT-2-XL-sized gradient
+// a comparison of all pairs took 0.3 ms of the host's time before the first launch, this takes a few microseconds.
+template <class Each>
+bool spans_disjoint(const Each& each) {
   struct Span {
     uintptr_t lo, hi;
     int owner;
   };
-  std::vector<Span> written_, read_;
-};
+  constexpr size_t kChunk = 1024;   // 24 KB
+  Span w[kChunk];
+  for (size_t first = 0;; first += kChunk) {
+    size_t at = 0, m = 0;
+    each([&](const void* p, u64 bytes, bool written, int owner) {
+      if (!p || !bytes || !written) return;
+      if (at >= first && m < kChunk) w[m++] = {(uintptr_t)p, (uintptr_t)p + bytes, owner};
+      ++at;
+    });
+    const auto before = [](const Span& a, const Span& b) { return a.lo < b.lo; };
+    if (!std::is_sorted(w, w + m, before)) std::sort(w, w + m, before);
+    for (size_t i = 1; i < m; ++i)   // written spans of one owner are disjoint already
+      if (w[i].lo < w[i - 1].hi) return false;
+    bool apart = true;
+    at = 0;
+    each([&](const void* p, u64 bytes, bool written, int owner) {
+      if (!p || !bytes || !apart) return;
+      if (written && at++ < first + kChunk) return;   // compared just now, or with an earlier chunk
+      const uintptr_t lo = (uintptr_t)p, hi = lo + bytes;
+      // the first written span that ends behind the start of this one
+      const Span* s = std::upper_bound(w, w + m, lo, [](uintptr_t v, const Span& x) { return v < x.hi; });
+      for (; s != w + m && s->lo < hi; ++s)
+        if (s->owner != owner) apart = false;
+    });
+    if (!apart) return false;
+    if (m < kChunk) return true;
+  }
+}
 
 hipError_t zero_totals(unsigned long long* totals, int n, hipStream_t s, int pos) {
   return orhost::launch_kernel(k_zero_u64n, dim3((unsigned)((n + 255) / 256)), dim3(256), s, pos, totals, n);
@@ -626,8 +629,6 @@ or_status path_batched_impl(bool fused, const or_bucket* buckets, int n, int N, 
   if (totals && !aligned(totals, 8)) return OR_ERR_ALIGN;
   const u64 es = bf16 ? 2 : 4;
   // ---- every bucket is checked before anything is enqueued
-  SpanSet spans(4 * (size_t)n + 2);
-  spans.add(totals, totals ? (u64)n * 8 : 0, true, -1);
   int nonempty = 0;
   size_t ws_used = 0;
   for (int j = 0; j < n; ++j) {
@@ -636,15 +637,21 @@ or_status path_batched_impl(bool fused, const or_bucket* buckets, int n, int N, 
       return s;
     if (q.shard_len == 0) continue;
     ++nonempty;
-    const u64 L = q.shard_len;
-    spans.add(q.grads, (u64)N * L * es, false, j);
-    spans.add(q.masks, (u64)N * (L / 8), false, j);
-    spans.add(q.out, L * es, true, j);
-    spans.add(q.count_out, L, true, j);
-    ws_used = std::max(ws_used, workspace_bytes(L, k));
+    ws_used = std::max(ws_used, workspace_bytes(q.shard_len, k));
   }
-  spans.add(ws, ws_used, true, -2);
-  if (!spans.disjoint()) return OR_ERR_SHAPE;
+  const bool apart = spans_disjoint([&](auto&& span) {
+    span(totals, totals ? (u64)n * 8 : 0, true, -1);
+    for (int j = 0; j < n; ++j) {
+      const or_bucket& q = buckets[j];
+      const u64 L = q.shard_len;
+      span(q.grads, (u64)N * L * es, false, j);
+      span(q.masks, (u64)N * (L / 8), false, j);
+      span(q.out, L * es, true, j);
+      span(q.count_out, L, true, j);
+    }
+    span(ws, ws_used, true, -2);
+  });
+  if (!apart) return OR_ERR_SHAPE;
   const orhost::KernelTable* t = orhost::table_for_class(class_of(k));
   orhost::batch_fn f = fused ? (bf16 ? t->fused_batched_bf16 : t->fused_batched_f32)
                              : (bf16 ? t->reduce_decode_batched_bf16 : t->reduce_decode_batched_f32);
@@ -741,24 +748,28 @@ or_status stage_batched_impl(bool reduce, const or_stage_bucket* buckets, int n,
   if (n == 0) return OR_OK;
   if (!buckets) return OR_ERR_NULL;
   const u64 es = bf16 ? 2 : 4;
-  SpanSet spans(4 * (size_t)n);
   int nonempty = 0;
   for (int j = 0; j < n; ++j) {
     const or_stage_bucket& q = buckets[j];
     if (or_status s = check_stage_bucket(q, reduce, N, k, es)) return s;
     if (q.shard_len == 0) continue;
     ++nonempty;
-    const u64 L = q.shard_len;
-    if (reduce) {
-      spans.add(q.shards, (u64)N * L * es, false, j);
-      spans.add(q.masks, (u64)N * (L / 8), false, j);
-    } else {
-      spans.add(q.out, L * es, true, j);
-    }
-    spans.add(q.sum, L * 4, reduce, j);
-    spans.add(q.count, L, reduce, j);
   }
-  if (!spans.disjoint()) return OR_ERR_SHAPE;
+  const bool apart = spans_disjoint([&](auto&& span) {
+    for (int j = 0; j < n; ++j) {
+      const or_stage_bucket& q = buckets[j];
+      const u64 L = q.shard_len;
+      if (reduce) {
+        span(q.shards, (u64)N * L * es, false, j);
+        span(q.masks, (u64)N * (L / 8), false, j);
+      } else {
+        span(q.out, L * es, true, j);
+      }
+      span(q.sum, L * 4, reduce, j);
+      span(q.count, L, reduce, j);
+    }
+  });
+  if (!apart) return OR_ERR_SHAPE;
   if (!nonempty) return OR_OK;
   hipStream_t s = (hipStream_t)stream;
   const BatchPlan plan = plan_batches(nonempty);

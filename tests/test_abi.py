@@ -178,3 +178,66 @@ def test_batched_argument_checks(lib):
     assert mr(bad, 1, 4, 0, None) == 4
     bad = (b.or_stage_bucket * 1)(stage(0, base_index=64))
     assert fd(bad, 1, 12, 0, None) == 4
+
+
+def test_batched_checks_allocate_nothing(lib):
+    """An argument error is a status whatever n_buckets says: the first bucket is refused before anything that grows with
+    n_buckets.  (In a process of its own: an allocation that fails inside a C entry ends the process.)"""
+    import subprocess
+    import sys
+    code = ("import ctypes as C\n"
+            "from paper_2310_06993_amd import binding as b\n"
+            "one = (b.or_bucket * 1)(b.or_bucket(grads=(1 << 30) + 4, masks=1 << 31, out=1 << 32, shard_len=4096))\n"
+            "st = (b.or_stage_bucket * 1)(b.or_stage_bucket(shard_len=48))\n"
+            "n = 2 ** 31 - 1\n"
+            "assert b.lib.or_fused_path_batched(one, n, 2, 12, 0, None, 0, None) == 5\n"
+            "assert b.lib.or_masked_reduce_batched(st, n, 2, 0, None) == 4\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, (r.returncode, r.stderr[-500:])
+
+
+def test_overlap_of_many_buckets_against_all_pairs(lib):
+    """The overlap check of the batched calls against a comparison of all pairs: few and many buckets (more written spans than
+    are sorted at a time), spans that touch, that share a byte, that contain each other.  Where nothing overlaps the call gets as
+    far as a launch, which fails without a GPU: not for a machine that has one."""
+    import random
+    import torch
+    from paper_2310_06993_amd import binding as b
+    if torch.cuda.is_available():
+        pytest.skip("would launch on addresses that are none")
+    L, N = 1024, 2
+    seen = set()
+    for n, seed in [(n, s) for n in (2, 3, 40, 257, 520, 800, 1300) for s in range(8)]:
+        rng = random.Random(n * 100 + seed)
+        step = 1 << 15
+        slots = list(range(1, 4 * n + 1))
+        rng.shuffle(slots)
+        items = []
+        for j in range(n):
+            at = [(1 << 40) + step * s for s in slots[4 * j:4 * j + 4]]
+            items.append([at[0], at[1], at[2], at[3] if rng.random() < 0.8 else 0, rng.choice((L, L, L, 0))])
+        sizes = lambda i: (N * i[4] * 4, N * i[4] // 8, i[4] * 4, i[4])
+        for _ in range(rng.choice((0, 0, 1, 2))):   # move a span of one bucket to where one of another begins or ends
+            i, j = rng.sample(range(n), 2)
+            x, y = rng.randrange(4), rng.randrange(4)
+            delta = rng.choice((-16, 0, sizes(items[j])[y] - 16, sizes(items[j])[y], -sizes(items[i])[x] + 16, -sizes(items[i])[x]))
+            if items[i][x] and items[j][y]:
+                items[i][x] = items[j][y] + delta // 16 * 16
+        spans = [(items[j][x], items[j][x] + sizes(items[j])[x], x >= 2, j) for j in range(n) for x in range(4)
+                 if items[j][x] and sizes(items[j])[x]]
+        spans.sort()
+        want = False
+        for a, s in enumerate(spans):
+            for t in spans[a + 1:]:
+                if t[0] >= s[0] + N * L * 4:
+                    break
+                if t[0] < s[1] and s[0] < t[1] and (s[2] or t[2]):
+                    want = True
+        arr = (b.or_bucket * n)(*[b.or_bucket(grads=i[0], masks=i[1], out=i[2], count_out=i[3] or None, shard_len=i[4]) for i in items])
+        got = b.lib.or_fused_path_batched(arr, n, N, 10, 0, None, 0, None)
+        if not any(i[4] for i in items):
+            assert got == 0
+            continue
+        assert got == (4 if want else 7), (n, seed)
+        seen.add(want)
+    assert seen == {True, False}
