@@ -630,14 +630,12 @@ or_status path_batched_impl(bool fused, const or_bucket* buckets, int n, int N, 
   const u64 es = bf16 ? 2 : 4;
   // ---- every bucket is checked before anything is enqueued
   int nonempty = 0;
-  size_t ws_used = 0;
   for (int j = 0; j < n; ++j) {
     const or_bucket& q = buckets[j];
     if (or_status s = check_path(q.grads, q.masks, N, q.shard_len, k, q.base_index, q.out, q.count_out, ws, ws_bytes, (int)es))
       return s;
     if (q.shard_len == 0) continue;
     ++nonempty;
-    ws_used = std::max(ws_used, workspace_bytes(q.shard_len, k));
   }
   const bool apart = spans_disjoint([&](auto&& span) {
     span(totals, totals ? (u64)n * 8 : 0, true, -1);
@@ -649,9 +647,22 @@ or_status path_batched_impl(bool fused, const or_bucket* buckets, int n, int N, 
       span(q.out, L * es, true, j);
       span(q.count_out, L, true, j);
     }
-    span(ws, ws_used, true, -2);
   });
   if (!apart) return OR_ERR_SHAPE;
+  // The buckets share the workspace one after the other: nothing that is read may lie in it, and a bucket's results not in the
+  // part that it or a later one uses.  (What only earlier, longer ones used is free again by then.)
+  u64 ws_used = 0, ws_all = 0;
+  for (int j = 0; j < n; ++j) ws_all = std::max(ws_all, (u64)workspace_bytes(buckets[j].shard_len, k));
+  for (int j = ws_all ? n - 1 : -1; j >= 0; --j) {
+    const or_bucket& q = buckets[j];
+    const u64 L = q.shard_len;
+    if (L == 0) continue;
+    ws_used = std::max(ws_used, (u64)workspace_bytes(L, k));
+    if (ranges_overlap(ws, ws_all, q.grads, (u64)N * L * es) || ranges_overlap(ws, ws_all, q.masks, (u64)N * (L / 8)) ||
+        ranges_overlap(ws, ws_used, q.out, L * es) || (q.count_out && ranges_overlap(ws, ws_used, q.count_out, L)))
+      return OR_ERR_SHAPE;
+  }
+  if (ws_used && totals && ranges_overlap(ws, ws_used, totals, (u64)n * 8)) return OR_ERR_SHAPE;
   const orhost::KernelTable* t = orhost::table_for_class(class_of(k));
   orhost::batch_fn f = fused ? (bf16 ? t->fused_batched_bf16 : t->fused_batched_f32)
                              : (bf16 ? t->reduce_decode_batched_bf16 : t->reduce_decode_batched_f32);

@@ -241,3 +241,34 @@ def test_overlap_of_many_buckets_against_all_pairs(lib):
         assert got == (4 if want else 7), (n, seed)
         seen.add(want)
     assert seen == {True, False}
+
+
+def test_batched_workspace_overlap(lib):
+    """Blocks above 2^14 share the workspace one bucket after the other: inputs may not lie in it, results not in the part that
+    their bucket or a later one uses, but in what only earlier, longer ones use.  (An accepted call fails at its launch without a
+    GPU.)"""
+    import torch
+    from paper_2310_06993_amd import binding as b
+    if torch.cuda.is_available():
+        pytest.skip("would launch on addresses that are none")
+    k, N = 16, 2
+    short, long = 1 << 16, 1 << 18
+    ws, need_short, need_long = 1 << 40, b.or_workspace_bytes(1 << 16, 16), b.or_workspace_bytes(1 << 18, 16)
+
+    def call(lens, totals=None, **moved):
+        arr = (b.or_bucket * len(lens))()
+        for j, L in enumerate(lens):
+            at = (1 << 41) + j * (1 << 30)
+            arr[j] = b.or_bucket(grads=at, masks=at + (1 << 26), out=at + (1 << 27), count_out=at + (1 << 28), shard_len=L)
+        for name, (j, to) in moved.items():
+            setattr(arr[j], name, to)
+        return b.lib.or_fused_path_batched_monitored(arr, len(lens), N, k, 0, totals, ws, need_long, None)
+
+    behind, inside = ws + need_short, ws + need_long - 4096
+    assert call([long, short]) == 7
+    assert call([long, short], out=(1, behind)) == 7 and call([long, short], count_out=(1, behind)) == 7
+    assert call([long, short], out=(1, behind - 256)) == 4
+    assert call([short, long], out=(0, behind)) == 4 and call([short, long, short], masks=(0, inside)) == 4
+    assert call([long, 0, short], grads=(2, ws + need_long - 256)) == 4
+    assert call([long, short], out=(0, inside)) == 4
+    assert call([long, short], totals=inside) == 4 and call([short, short], totals=behind) == 7

@@ -271,3 +271,23 @@ def test_totals_of_shards_that_end_inside_a_tile(b, k, N, tiles, kind):
         b.or_fused_path_batched_monitored(b.make_buckets(items), len(some), N, k, kind == "bf16", totals, None)
         for j, (_, _, _, cnt, L, _, _) in enumerate(items):
             assert int(totals[j]) == int(cnt.sum(dtype=torch.int64)) == N * L - dropped[j], (j, L)
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16"])
+def test_results_in_the_part_of_the_workspace_that_only_an_earlier_bucket_used(b, kind):
+    """A long bucket, then a short one whose results lie behind its own share of the workspace: as with results elsewhere."""
+    k, N = 16, 3
+    dt = torch.float32 if kind == "f32" else torch.bfloat16
+    long, short = 6 << k, 1 << k
+    raw = _random_buckets(N, [long, short], k, dt, seed=5)
+    ws = torch.empty(b.or_workspace_bytes(long, k), dtype=torch.uint8, device=dev())
+    at = b.or_workspace_bytes(short, k)
+    es = raw[0][0].element_size()
+    for call in (b.or_fused_path_batched, lambda *a: b.or_reduce_decode_batched(*a[:5], None, *a[5:])):
+        outs = [torch.empty(L, dtype=dt, device=dev()) for _, _, L, _, _ in raw]
+        call(b.make_buckets([(g, m, o, None, L, seed, base) for (g, m, L, seed, base), o in zip(raw, outs)]), 2, N, k, kind == "bf16", ws)
+        behind = ws[at:at + short * es].view(dt)
+        first = torch.empty_like(outs[0])
+        call(b.make_buckets([(g, m, o, None, L, seed, base) for (g, m, L, seed, base), o in zip(raw, (first, behind))]), 2, N, k,
+             kind == "bf16", ws)
+        assert torch.equal(first, outs[0]) and torch.equal(behind, outs[1])
