@@ -135,7 +135,7 @@ from ._calls import (  # noqa: E402
     or_reduce_decode_batched, or_reduce_decode_bf16, or_rht_decode, or_rht_decode_at, or_rht_decode_bf16,
     or_rht_decode_masked, or_rht_decode_masked_bf16, or_rht_encode, or_rht_encode_at, or_rht_encode_bf16)
 
-_calls.bind({name: C.cast(getattr(lib, name), _p).value for name in _SIGS}, _check, lambda o: C.cast(o, _p).value)
+_calls.bind({name: C.cast(getattr(lib, name), _p).value for name in _SIGS}, _check, C.Array, lambda o: C.cast(o, _p).value)
 
 OR_STATIC_MAX_SHARD_LEN = 4194304
 

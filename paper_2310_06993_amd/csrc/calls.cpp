@@ -16,7 +16,8 @@
 namespace {
 
 PyObject* g_check = nullptr;     // check(status, name): raises for a status other than OR_OK
-PyObject* g_address = nullptr;   // address(obj) -> int or None, for descriptor arrays that offer no buffer
+PyObject* g_array = nullptr;     // ctypes.Array
+PyObject* g_address = nullptr;   // address(obj) -> int or None, for descriptors that are no ctypes array
 PyObject* g_cuda_stream = nullptr;
 
 constexpr int kMaxArgs = 12;
@@ -180,7 +181,8 @@ PyObject* run(const Entry& e, PyObject* const* args, Py_ssize_t nargs, PyObject*
       }
       case 's': ok = stream_arg(o, v[nv]); ++nv; break;
       case 'b':
-        if (PyObject_CheckBuffer(o)) {
+        // (a ctypes pointer offers a buffer too, but that is the pointer itself)
+        if (PyObject_TypeCheck(o, (PyTypeObject*)g_array)) {
           ok = PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) == 0;
           v[nv++] = ok ? (uint64_t)(uintptr_t)view.buf : 0;
         } else {
@@ -218,10 +220,10 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObject* kw
   return nullptr;
 }
 
-// bind(addresses: dict name -> int, check, address)
+// bind(addresses: dict name -> int, check, ctypes.Array, address)
 PyObject* bind(PyObject*, PyObject* args) {
-  PyObject *addresses, *check, *address;
-  if (!PyArg_ParseTuple(args, "O!OO", &PyDict_Type, &addresses, &check, &address)) return nullptr;
+  PyObject *addresses, *check, *array, *address;
+  if (!PyArg_ParseTuple(args, "O!OO!O", &PyDict_Type, &addresses, &check, &PyType_Type, &array, &address)) return nullptr;
   for (Entry& e : g_entries) {
     PyObject* a = PyDict_GetItemString(addresses, e.name);
     if (!a) return PyErr_Format(PyExc_KeyError, "%s", e.name);
@@ -229,10 +231,10 @@ PyObject* bind(PyObject*, PyObject* args) {
     if (!int_arg(a, v)) return nullptr;
     e.fn = (void*)(uintptr_t)v;
   }
-  Py_INCREF(check);
-  Py_INCREF(address);
-  Py_XSETREF(g_check, check);
-  Py_XSETREF(g_address, address);
+  for (auto [global, value] : {std::pair{&g_check, check}, {&g_array, array}, {&g_address, address}}) {
+    Py_INCREF(value);
+    Py_XSETREF(*global, value);
+  }
   Py_RETURN_NONE;
 }
 
