@@ -135,7 +135,25 @@ from ._calls import (  # noqa: E402
     or_reduce_decode_batched, or_reduce_decode_bf16, or_rht_decode, or_rht_decode_at, or_rht_decode_bf16,
     or_rht_decode_masked, or_rht_decode_masked_bf16, or_rht_encode, or_rht_encode_at, or_rht_encode_bf16)
 
-_calls.bind({name: C.cast(getattr(lib, name), _p).value for name in _SIGS}, _check, C.Array, lambda o: C.cast(o, _p).value)
+
+
+def _integer(o, unsigned):
+    """What ctypes makes of an argument that is no int: its own integer of the right type, or _as_parameter_."""
+    kind = _u64 if unsigned else _int
+    while not isinstance(o, kind) and hasattr(o, "_as_parameter_"):
+        o = o._as_parameter_
+    try:
+        return o.value if isinstance(o, kind) else kind(o).value
+    except TypeError as e:
+        raise C.ArgumentError(str(e)) from None
+
+
+def _extent(o, sized):
+    return _ptr(o), o.numel() * o.element_size() if sized else 0
+
+
+_calls.bind({name: C.cast(getattr(lib, name), _p).value for name in _SIGS}, _check, C.Array, lambda o: C.cast(o, _p).value,
+            _integer, _extent)
 
 OR_STATIC_MAX_SHARD_LEN = 4194304
 

@@ -18,6 +18,8 @@ namespace {
 PyObject* g_check = nullptr;     // check(status, name): raises for a status other than OR_OK
 PyObject* g_array = nullptr;     // ctypes.Array
 PyObject* g_address = nullptr;   // address(obj) -> int or None, for descriptors that are no ctypes array
+PyObject* g_integer = nullptr;   // integer(obj, unsigned) -> int, for what is neither an int nor has __index__
+PyObject* g_extent = nullptr;    // extent(obj) -> (address, bytes), for what is no torch tensor but behaves like one
 PyObject* g_cuda_stream = nullptr;
 
 constexpr int kMaxArgs = 12;
@@ -86,29 +88,8 @@ Entry g_entries[] = {
 };
 constexpr int kEntries = sizeof(g_entries) / sizeof(g_entries[0]);
 
-bool tensor_arg(PyObject* o, uint64_t& ptr, uint64_t* bytes) {
-  ptr = 0;
-  if (bytes) *bytes = 0;
-  if (o == Py_None) return true;
-  if (!THPVariable_Check(o)) {
-    PyErr_Format(PyExc_TypeError, "expected a torch tensor, not %.100s", Py_TYPE(o)->tp_name);
-    return false;
-  }
-  const at::Tensor& t = THPVariable_Unpack(o);
-  if (!t.is_cuda()) {
-    PyErr_SetString(PyExc_ValueError, "liboptireduce_hip takes device tensors");
-    return false;
-  }
-  if (!t.is_contiguous()) {
-    PyErr_SetString(PyExc_ValueError, "tensor must be contiguous");
-    return false;
-  }
-  ptr = (uint64_t)(uintptr_t)t.const_data_ptr();
-  if (bytes) *bytes = (uint64_t)t.numel() * t.element_size();
-  return true;
-}
-
-bool int_arg(PyObject* o, uint64_t& v) {
+// an int-like object that has no need of ctypes' rules
+bool index_of(PyObject* o, uint64_t& v) {
   if (PyLong_Check(o)) {
     v = PyLong_AsUnsignedLongLongMask(o);
   } else {
@@ -125,9 +106,42 @@ bool take_int(PyObject* o, uint64_t& v) {
   if (!o) return false;
   bool ok = true;
   if (o == Py_None) v = 0;
-  else ok = int_arg(o, v);
+  else ok = index_of(o, v);
   Py_DECREF(o);
   return ok;
+}
+
+bool int_arg(PyObject* o, bool is_unsigned, uint64_t& v) {
+  if (PyIndex_Check(o)) return index_of(o, v);
+  return take_int(PyObject_CallFunctionObjArgs(g_integer, o, is_unsigned ? Py_True : Py_False, nullptr), v);
+}
+
+bool tensor_arg(PyObject* o, uint64_t& ptr, uint64_t* bytes) {
+  ptr = 0;
+  if (bytes) *bytes = 0;
+  if (o == Py_None) return true;
+  if (!THPVariable_Check(o)) {
+    PyObject* pair = PyObject_CallFunctionObjArgs(g_extent, o, bytes ? Py_True : Py_False, nullptr);
+    if (!pair) return false;
+    unsigned long long p = 0, n = 0;
+    const bool ok = PyArg_ParseTuple(pair, "KK", &p, &n);
+    Py_DECREF(pair);
+    ptr = p;
+    if (bytes) *bytes = n;
+    return ok;
+  }
+  const at::Tensor& t = THPVariable_Unpack(o);
+  if (!t.is_cuda()) {
+    PyErr_SetString(PyExc_ValueError, "liboptireduce_hip takes device tensors");
+    return false;
+  }
+  if (!t.is_contiguous()) {
+    PyErr_SetString(PyExc_ValueError, "tensor must be contiguous");
+    return false;
+  }
+  ptr = (uint64_t)(uintptr_t)t.const_data_ptr();
+  if (bytes) *bytes = (uint64_t)t.numel() * t.element_size();
+  return true;
 }
 
 bool stream_arg(PyObject* o, uint64_t& v) {
@@ -172,7 +186,7 @@ PyObject* run(const Entry& e, PyObject* const* args, Py_ssize_t nargs, PyObject*
       case 't': ok = tensor_arg(o, v[nv], nullptr); ++nv; break;
       case 'w': ok = tensor_arg(o, v[nv], &v[nv + 1]); nv += 2; break;
       case 'i':
-      case 'u': ok = int_arg(o, v[nv]); ++nv; break;
+      case 'u': ok = int_arg(o, e.kinds[i] == 'u', v[nv]); ++nv; break;
       case 'q': {
         const int t = PyObject_IsTrue(o);
         ok = t >= 0;
@@ -220,18 +234,19 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObject* kw
   return nullptr;
 }
 
-// bind(addresses: dict name -> int, check, ctypes.Array, address)
+// bind(addresses: dict name -> int, check, ctypes.Array, address, integer, extent)
 PyObject* bind(PyObject*, PyObject* args) {
-  PyObject *addresses, *check, *array, *address;
-  if (!PyArg_ParseTuple(args, "O!OO!O", &PyDict_Type, &addresses, &check, &PyType_Type, &array, &address)) return nullptr;
+  PyObject *addresses, *check, *array, *address, *integer, *extent;
+  if (!PyArg_ParseTuple(args, "O!OO!OOO", &PyDict_Type, &addresses, &check, &PyType_Type, &array, &address, &integer, &extent))
+    return nullptr;
   for (Entry& e : g_entries) {
     PyObject* a = PyDict_GetItemString(addresses, e.name);
     if (!a) return PyErr_Format(PyExc_KeyError, "%s", e.name);
     uint64_t v;
-    if (!int_arg(a, v)) return nullptr;
+    if (!index_of(a, v)) return nullptr;
     e.fn = (void*)(uintptr_t)v;
   }
-  for (auto [global, value] : {std::pair{&g_check, check}, {&g_array, array}, {&g_address, address}}) {
+  for (auto [global, value] : {std::pair{&g_check, check}, {&g_array, array}, {&g_address, address}, {&g_integer, integer}, {&g_extent, extent}}) {
     Py_INCREF(value);
     Py_XSETREF(*global, value);
   }

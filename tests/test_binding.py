@@ -30,3 +30,56 @@ def test_descriptor_arrays_in_every_form_that_ctypes_casts(arr):
     for form in (arr[0], bytearray(arr), np.frombuffer(bytes(arr), dtype=np.uint8), [1], 1.5):
         with pytest.raises(C.ArgumentError):
             b.or_fused_path_batched(form, 1, 2, 12, 0, None, 1)
+
+
+class _Has:
+    """_as_parameter_, as ctypes looks for it."""
+    def __init__(self, value):
+        self._as_parameter_ = value
+
+
+class _TensorLike:
+    """What the binding needs of a device tensor, without torch."""
+    is_cuda = True
+
+    def __init__(self, contiguous=True):
+        self.contiguous = contiguous
+
+    def is_contiguous(self):
+        return self.contiguous
+
+    def data_ptr(self):
+        return (1 << 20) + 4
+
+    def numel(self):
+        return 3
+
+    def element_size(self):
+        return 2
+
+
+def test_integers_in_every_form_that_ctypes_takes(arr):
+    for one in (1, True, np.int64(1), C.c_int(1), _Has(1), _Has(C.c_int(1))):
+        assert _status(arr, one, 2, 12, 0, None, 1) == BAD_ALIGN, one
+    for bad in (1.0, None, "1", C.c_uint64(1), _Has(1.0), [1]):
+        with pytest.raises(C.ArgumentError):
+            b.or_fused_path_batched(arr, bad, 2, 12, 0, None, 1)
+    for zero in (0, C.c_uint64(0), np.uint64(0), 1 << 64):
+        b.or_rht_encode(None, zero, 10, -1, None, 1)                      # an empty vector
+    with pytest.raises(C.ArgumentError):
+        b.or_rht_encode(None, C.c_int(0), 10, 1, None, 1)
+
+
+def test_tensors_and_what_looks_like_one():
+    with pytest.raises(b.OptiReduceError) as e:
+        b.or_rht_encode(_TensorLike(), 64, 10, 1, _TensorLike(), 1)
+    assert e.value.status == BAD_ALIGN
+    with pytest.raises(ValueError):
+        b.or_rht_encode(_TensorLike(contiguous=False), 64, 10, 1, None, 1)
+    with pytest.raises(AttributeError):
+        b.or_rht_encode("x", 64, 10, 1, None, 1)
+    # a workspace's size is taken from it: 6 bytes are too few
+    one = (b.or_bucket * 1)(b.or_bucket(grads=1 << 30, masks=1 << 31, out=1 << 32, shard_len=1 << 16))
+    with pytest.raises(b.OptiReduceError) as e:
+        b.or_fused_path_batched(one, 1, 2, 16, 0, _TensorLike(), 1)
+    assert e.value.status == 6
