@@ -139,7 +139,7 @@ bool tensor_arg(PyObject* o, uint64_t& ptr, uint64_t* bytes) {
     PyErr_SetString(PyExc_ValueError, "tensor must be contiguous");
     return false;
   }
-  ptr = (uint64_t)(uintptr_t)t.const_data_ptr();
+  ptr = (uint64_t)(uintptr_t)t.mutable_data_ptr();   // as Tensor.data_ptr(): a copy-on-write clone gets storage of its own
   if (bytes) *bytes = (uint64_t)t.numel() * t.element_size();
   return true;
 }
