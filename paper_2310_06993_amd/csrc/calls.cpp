@@ -155,6 +155,18 @@ bool stream_arg(PyObject* o, uint64_t& v) {
   return take_int(PyNumber_Long(o), v);
 }
 
+// held or given up for a scope, whichever way it is left
+struct Buffer {
+  Py_buffer view = {};
+  ~Buffer() {
+    if (view.obj) PyBuffer_Release(&view);
+  }
+};
+struct WithoutGil {
+  PyThreadState* state = PyEval_SaveThread();
+  ~WithoutGil() { PyEval_RestoreThread(state); }
+};
+
 PyObject* run(const Entry& e, PyObject* const* args, Py_ssize_t nargs, PyObject* kwnames) {
   const int n = (int)strlen(e.kinds);
   PyObject* got[kMaxArgs] = {};
@@ -170,7 +182,7 @@ PyObject* run(const Entry& e, PyObject* const* args, Py_ssize_t nargs, PyObject*
   }
   uint64_t v[kMaxArgs + 1];
   int nv = 0;
-  Py_buffer view = {};
+  Buffer buffer;
   bool ok = true;
   for (int i = 0; ok && i < n; ++i) {
     PyObject* o = got[i];
@@ -197,8 +209,8 @@ PyObject* run(const Entry& e, PyObject* const* args, Py_ssize_t nargs, PyObject*
       case 'b':
         // (a ctypes pointer offers a buffer too, but that is the pointer itself)
         if (PyObject_TypeCheck(o, (PyTypeObject*)g_array)) {
-          ok = PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) == 0;
-          v[nv++] = ok ? (uint64_t)(uintptr_t)view.buf : 0;
+          ok = PyObject_GetBuffer(o, &buffer.view, PyBUF_SIMPLE) == 0;
+          v[nv++] = ok ? (uint64_t)(uintptr_t)buffer.view.buf : 0;
         } else {
           ok = take_int(PyObject_CallFunctionObjArgs(g_address, o, nullptr), v[nv]);
           ++nv;
@@ -206,21 +218,14 @@ PyObject* run(const Entry& e, PyObject* const* args, Py_ssize_t nargs, PyObject*
         break;
     }
   }
-  PyObject* result = nullptr;
-  if (ok) {
-    or_status s;
-    Py_BEGIN_ALLOW_THREADS
+  if (!ok) return nullptr;
+  or_status s;
+  {
+    WithoutGil released;
     s = e.call(e.fn, v);
-    Py_END_ALLOW_THREADS
-    if (s == OR_OK) {
-      Py_INCREF(Py_None);
-      result = Py_None;
-    } else {
-      result = PyObject_CallFunction(g_check, "is", (int)s, e.name);
-    }
   }
-  if (view.obj) PyBuffer_Release(&view);
-  return result;
+  if (s == OR_OK) Py_RETURN_NONE;
+  return PyObject_CallFunction(g_check, "is", (int)s, e.name);
 }
 
 template <int I>

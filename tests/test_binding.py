@@ -83,3 +83,16 @@ def test_tensors_and_what_looks_like_one():
     with pytest.raises(b.OptiReduceError) as e:
         b.or_fused_path_batched(one, 1, 2, 16, 0, _TensorLike(), 1)
     assert e.value.status == 6
+
+
+def test_an_error_of_the_runtime_leaves_nothing_held(arr):
+    """No GPU: looking up the current stream raises after the descriptors were taken; they are let go."""
+    import sys
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the stream is there")
+    before = sys.getrefcount(arr)
+    for _ in range(5):
+        with pytest.raises(RuntimeError):
+            b.or_fused_path_batched(arr, 1, 2, 12, 0, None)
+    assert sys.getrefcount(arr) == before
