@@ -254,7 +254,7 @@ def roofline(cfg, L, nbytes, kern):
     N, k = cfg.workers, cfg.block_log2
     adds = (k * (N + 1) / N + 1.0) * N * L
     peak_adds = 256 * 4 * 32 * 2.4e9
-    names = {True: "k_fused (one launch per step)",
+    names = {True: "k_fused%s (one launch per step)" % ("" if cfg.dtype == "f32" and cfg.block_log2 <= 10 else "_each"),
              False: "k_sign_table + k_fused_mx (one step; the fused kernel is 99 % of it)" if cfg.dtype != "f32"
              else "k_sign_table + k_fused_pairs (+ k_decode_block for 2^16 blocks), one step"}
     return {"bound": "hbm", "achieved": nbytes / kern / 1e9, "peak": HBM_PEAK_GBPS, "unit": "GB/s",

@@ -121,32 +121,38 @@ hipError_t fused(const PathArgs& a, unsigned long long units, hipStream_t s, int
   }
   return hipErrorInvalidValue;   // not reached
 }
+// workgroups of SLOTS tiles each; tile_start then counts workgroups
+template <int SLOTS, class Kernel>
+hipError_t launch_slots(Kernel kernel, int tile_threads, const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  if constexpr (SLOTS == 1) return launch_kernel(kernel, dim3((unsigned)units), dim3(tile_threads), s, pos, a);
+  BatchArgs b = a;
+  uint32_t groups = 0;
+  for (int j = 0; j < a.n; ++j) {
+    b.tile_start[j] = groups;
+    groups += (a.tile_start[j + 1] - a.tile_start[j] + SLOTS - 1) / SLOTS;
+  }
+  b.tile_start[a.n] = groups;
+  return launch_kernel(kernel, dim3(groups), dim3(tile_threads * SLOTS), s, pos, b);
+}
+template <class In, int SLOTS>
+hipError_t launch_each(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  if (prefetch_wins(units)) return launch_slots<SLOTS>(k_fused_each_batched<K, In, true, SLOTS>, G::THREADS, a, units, s, pos);
+  if constexpr (G::W < 8) return launch_slots<SLOTS>(k_fused_each_batched<K, In, false, SLOTS>, G::THREADS, a, units, s, pos);
+  return hipErrorInvalidValue;   // not reached
+}
 template <class In>
 hipError_t fused_batched(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
   if (units == 0) return hipSuccess;
   if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)units);
   if constexpr (kMaySumFirst<In>) {
     if (a.N >= kSumFirstFrom) {
-      if (groups_win(units, a.N)) return launch_kernel(k_fused_batched<K, GROUPS>, grid, dim3(kFusedThreads<K> * kGroups), s, pos, a);
-      constexpr int SLOTS = kBatchSlots<K, STREAM>;
-      if constexpr (SLOTS == 1) {
-        return launch_kernel(k_fused_batched<K, STREAM>, grid, dim3(kFusedThreads<K>), s, pos, a);
-      } else {
-        BatchArgs b = a;   // tile_start in workgroups of SLOTS tiles
-        uint32_t groups = 0;
-        for (int j = 0; j < a.n; ++j) {
-          b.tile_start[j] = groups;
-          groups += (a.tile_start[j + 1] - a.tile_start[j] + SLOTS - 1) / SLOTS;
-        }
-        b.tile_start[a.n] = groups;
-        return launch_kernel(k_fused_batched<K, STREAM>, dim3(groups), dim3(kFusedThreads<K> * SLOTS), s, pos, b);
-      }
+      if (groups_win(units, a.N)) return launch_kernel(k_fused_batched<K, GROUPS>, dim3((unsigned)units), dim3(kFusedThreads<K> * kGroups), s, pos, a);
+      return launch_slots<kBatchSlots<K, STREAM>>(k_fused_batched<K, STREAM>, kFusedThreads<K>, a, units, s, pos);
     }
   }
   if constexpr (kMayEach<In>) {
-    if (prefetch_wins(units)) return launch_kernel(k_fused_each_batched<K, In, true>, grid, dim3(G::THREADS), s, pos, a);
-    if constexpr (G::W < 8) return launch_kernel(k_fused_each_batched<K, In, false>, grid, dim3(G::THREADS), s, pos, a);
+    if (kEachSlots<K> > 1 && !a.totals) return launch_each<In, 1>(a, units, s, pos);
+    return launch_each<In, kEachSlots<K>>(a, units, s, pos);
   }
   return hipErrorInvalidValue;   // not reached
 }

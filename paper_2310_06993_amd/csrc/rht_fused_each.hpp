@@ -15,16 +15,15 @@
 
 namespace ordev {
 
-template <int K, class In, bool PREFETCH, bool TOTAL>
-__device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit) {
+// `arrived`: arrivals of the workgroup's tiles, and how many of its wavefronts have added theirs; `tiles`: of this workgroup.  FULL:
+// the tile is not cut short by the end of the shard.
+template <int K, class In, bool PREFETCH, bool TOTAL, int SLOTS, bool FULL>
+__device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit, int wave, int tiles,
+                                                float (*xbuf)[Geo<K>::Q >= 1 ? tr_floats<K> : 1], uint32_t* arrived) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R;
-  constexpr bool FULL = kShardTilesFull<K>;
   constexpr bool TRANSP = Geo<K>::Q >= 1;   // tiles of one wavefront: the plain transform, which needs no LDS there
   static_assert(Geo<K>::PARTS == 1 && R == 16, "blocks of up to 2^14, 16 entries a lane");
-  __shared__ float xbuf[2][TRANSP ? tr_floats<K> : 1];
-  __shared__ uint32_t arrived;
-  if (TOTAL && threadIdx.x == 0) arrived = 0;   // the transforms' barriers lie before and after the additions
-  const int wave = wave_id(), lane = lane_id(), kt = tile_bits<K>(a.k);
+  const int lane = lane_id(), kt = tile_bits<K>(a.k);
   const u64 L = a.n_pad, e0 = unit * T;
   const In* grads = (const In*)a.in;
   const float sigma = TRANSP ? tr_sigma(lane) : lane_sigma(lane, kt < 6 ? kt : 6);
@@ -94,15 +93,16 @@ __device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit) {
   store_counts<K, FULL>(a.count_out, e0, L, wave, lane, cnt, full);
   if constexpr (TOTAL) {   // Sec. 3.4 loss monitoring: gathered in LDS, one atomic per workgroup
     if (a.total_out) {
-      if constexpr (Geo<K>::W == 1) {
-        add_arrivals<R>(a.total_out, cnt, full);
-      } else {
-        uint32_t n = 0;
+      uint32_t n = 0;
 #pragma unroll
-        for (int r = 0; r < R / 4; ++r) n = __builtin_amdgcn_sad_u8(cnt[r], 0u, n);
+      for (int r = 0; r < R / 4; ++r) n = __builtin_amdgcn_sad_u8(cnt[r], 0u, n);
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) n += (uint32_t)__shfl_xor((int)n, o, 64);
-        if (lane == 0) atomicAdd(&arrived, n + (uint32_t)full * (64 * R));
+      for (int o = 32; o > 0; o >>= 1) n += (uint32_t)__shfl_xor((int)n, o, 64);
+      if (lane == 0) {
+        atomicAdd(&arrived[0], n + (uint32_t)full * (64 * R));
+        if constexpr (SLOTS > 1) {
+          if (atomicAdd(&arrived[1], 1u) == (uint32_t)tiles - 1) atomicAdd(a.total_out, (unsigned long long)atomicAdd(&arrived[0], 0u));
+        }
       }
     }
   }
@@ -110,7 +110,7 @@ __device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit) {
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (TRANSP) transform_transposed<K>(acc, xbuf[flip], xbuf[flip ^ 1], wave, lane);   // the same code takes layout B to A
   else transform<K, false>(acc, xbuf[0], wave, lane, kt);
-  if (TOTAL && Geo<K>::W > 1 && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)arrived);
+  if (TOTAL && SLOTS == 1 && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)arrived[0]);
   __builtin_amdgcn_sched_barrier(0);
   const float c = a.scale * sigma;
 #pragma unroll
@@ -119,17 +119,43 @@ __device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit) {
   store_tile<K, false, FULL, true>((In*)a.out, e0, L, wave, lane, acc);
 }
 
+// SLOTS > 1 (tiles of one wavefront): the workgroup's wavefronts serve SLOTS tiles of a bucket, one atomic for all their arrivals
+// (see fused_tile).  K = 0: whether the tile is cut short is decided once, for all accesses (decided at each of them, or with
+// range-checked accesses throughout, the loop over the workers keeps descriptors in vector registers: three times slower).
+template <int K, class In, bool PREFETCH, bool TOTAL, int SLOTS>
+__device__ __forceinline__ void fused_each(const PathArgs& a, u64 first_unit, u64 units) {
+  static_assert(SLOTS == 1 || Geo<K>::W == 1, "several tiles per workgroup: tiles of one wavefront");
+  __shared__ float xbuf[2][Geo<K>::Q >= 1 ? tr_floats<K> : 1];
+  __shared__ uint32_t arrived[2];
+  if (TOTAL && threadIdx.x < 2) arrived[threadIdx.x] = 0;   // the transforms' barriers lie before and after the additions
+  const int slot = SLOTS > 1 ? wave_id() : 0, wave = SLOTS > 1 ? 0 : wave_id();
+  const int tiles = units - first_unit < SLOTS ? (int)(units - first_unit) : SLOTS;
+  if constexpr (SLOTS > 1) {
+    __syncthreads();   // the only one: from here on every wavefront is on its own
+    if (slot >= tiles) return;
+  }
+  const u64 unit = first_unit + slot;
+  if (kShardTilesFull<K> || (unit + 1) * Geo<K>::T <= a.n_pad)
+    fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, true>(a, unit, wave, tiles, xbuf, arrived);
+  else
+    fused_each_tile<K, In, false, TOTAL, SLOTS, false>(a, unit, wave, tiles, xbuf, arrived);
+}
+
 template <int K, class In, bool PREFETCH>
 __global__ __launch_bounds__(Geo<K>::THREADS) __attribute__((amdgpu_waves_per_eu(1)))
 void k_fused_each(PathArgs a) {
-  fused_each_tile<K, In, PREFETCH, false>(a, blockIdx.x);
+  fused_each<K, In, PREFETCH, false, 1>(a, blockIdx.x, gridDim.x);
 }
-template <int K, class In, bool PREFETCH>
-__global__ __launch_bounds__(Geo<K>::THREADS) __attribute__((amdgpu_waves_per_eu(1)))
+// K = 0 with arrival totals: a workgroup serves SLOTS = kEachSlots tiles of one bucket, and ba.tile_start counts workgroups.  us, a
+// workgroup per tile -> eight: 60 x 400 tiles, N = 8, bf16 2^8 200 -> 145 with totals; without them 4 x 100 tiles 15 -> 17.
+template <int K> constexpr int kEachSlots = K == 0 ? 8 : 1;
+template <int K, class In, bool PREFETCH, int SLOTS>
+__global__ __launch_bounds__(Geo<K>::THREADS * SLOTS) __attribute__((amdgpu_waves_per_eu(1)))
 void k_fused_each_batched(BatchArgs ba) {
+  constexpr int T = Geo<K>::T;
   PathArgs a;
-  const u64 unit = bucket_of(ba, a);
-  fused_each_tile<K, In, PREFETCH, true>(a, unit);
+  const u64 group = bucket_of(ba, a);
+  fused_each<K, In, PREFETCH, (SLOTS == kEachSlots<K>), SLOTS>(a, group * SLOTS, (a.n_pad + T - 1) / T);
 }
 
 }  // namespace ordev

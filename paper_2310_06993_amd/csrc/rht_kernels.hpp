@@ -326,7 +326,7 @@ template <int K, class Wire, class Out>
 __device__ __forceinline__ void reduce_decode_tile(const PathArgs& a, u64 unit) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R;
   constexpr bool FULL = kShardTilesFull<K>;
-  static_assert(Geo<K>::PARTS == 1, "blocks above 2^14 go through sum/count in memory");
+  static_assert(Geo<K>::PARTS == 1, "blocks above 2^14: k_reduce_decode_block, or sum and count in memory");
   __shared__ float xbuf[Geo<K>::Q > 0 ? T : 1];
   const int wave = wave_id(), lane = lane_id(), kt = tile_bits<K>(a.k);
   const u64 L = a.n_pad, e0 = unit * T;
