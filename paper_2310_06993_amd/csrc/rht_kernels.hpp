@@ -536,12 +536,20 @@ struct BatchArgs {
 static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
 // the bucket that workgroup x serves, as the arguments of a single-bucket call; returns the tile inside it
+template <bool WALK = false>
 __device__ __forceinline__ u64 bucket_of(const BatchArgs& ba, PathArgs& a) {
   // buckets that end at or before tile x: one comparison a lane (a walk over the descriptors was up to 60 dependent
-  // scalar loads ahead of a workgroup's first access)
+  // scalar loads ahead of a workgroup's first access).  us, walk -> that, 64 buckets: finalize + decode 2^14 19.2 -> 14.7, reduce +
+  // decode bf16 2^11 26.2 -> 17.8; but reduce + decode fp32 with its data in the cache 2^14 37.5 -> 42.6, 2^10 16 buckets 14.5 ->
+  // 17.1 (in memory: the same), which therefore walks
   const uint32_t x = blockIdx.x;
-  const int lane = lane_id();
-  const int j = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane + 1 < ba.n && ba.tile_start[lane + 1] <= x));
+  int j = 0;
+  if constexpr (WALK) {
+    while (j + 1 < ba.n && ba.tile_start[j + 1] <= x) ++j;
+  } else {
+    const int lane = lane_id();
+    j = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane + 1 < ba.n && ba.tile_start[lane + 1] <= x));
+  }
   a = PathArgs{};
   a.in = ba.b[j].in; a.masks = (const uint32_t*)ba.b[j].aux; a.count_in = (const uint8_t*)ba.b[j].aux;
   a.out = ba.b[j].out; a.count_out = ba.b[j].count_out;
@@ -556,7 +564,7 @@ __device__ __forceinline__ u64 bucket_of(const BatchArgs& ba, PathArgs& a) {
 template <int K, class Wire>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_reduce_decode_batched(BatchArgs ba) {
   PathArgs a;
-  const u64 unit = bucket_of(ba, a);
+  const u64 unit = bucket_of<sizeof(Wire) == 4>(ba, a);
   reduce_decode_tile<K, Wire, Wire>(a, unit);
 }
 template <int K, class Out>
