@@ -7,8 +7,8 @@
 // the plain additions if nothing is missing in its part.  Counts are not carried along: a wavefront that saw a loss reads
 // the bits of that tile again at the end.
 // N = 8, from reduction + decode: 1024 blocks of 2^16 605 -> 427 us (5.8 TB/s), bf16 368 -> 263; 2048 blocks of 2^15 595 -> 426,
-// bf16 360 -> 241.  (With the 2^14 transform of rht_fused.hpp, which needs fewer exchanges and no DPP stages for most bits, 1 to 8 %
-// less from four workers on; its order of stages gave other bits than the two launches that small shards take.)
+// bf16 360 -> 241.  (With the 2^14 transform of rht_fused.hpp, which has no DPP stages for most bits and stores from its own
+// layout, 1 to 10 % less from four workers and 256 blocks on; its order of stages gave other bits than the two launches that small shards take.)
 #pragma once
 #include "rht_encode_block.hpp"
 
