@@ -9,6 +9,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <exception>
+#include <string>
 #include <utility>
 
 #include "../../include/optireduce.h"
@@ -259,10 +260,18 @@ PyObject* bind(PyObject*, PyObject* args) {
 }
 
 PyMethodDef g_methods[kEntries + 2];
+std::string g_docs[kEntries];   // the signature, in the form that inspect reads
+
+std::string signature(const Entry& e) {
+  std::string s = std::string(e.name) + "($module";
+  for (int i = 0; e.kinds[i]; ++i) s += std::string(", ") + e.args[i] + (i >= e.required ? "=None" : "");
+  return s + ")\n--\n\n";
+}
 
 template <size_t... I>
 void fill_methods(std::index_sequence<I...>) {
-  ((g_methods[I] = {g_entries[I].name, (PyCFunction)(void (*)(void))entry<(int)I>, METH_FASTCALL | METH_KEYWORDS, nullptr}), ...);
+  ((g_docs[I] = signature(g_entries[I])), ...);
+  ((g_methods[I] = {g_entries[I].name, (PyCFunction)(void (*)(void))entry<(int)I>, METH_FASTCALL | METH_KEYWORDS, g_docs[I].c_str()}), ...);
   g_methods[kEntries] = {"bind", bind, METH_VARARGS, nullptr};
   g_methods[kEntries + 1] = {nullptr, nullptr, 0, nullptr};
 }

@@ -96,3 +96,18 @@ def test_an_error_of_the_runtime_leaves_nothing_held(arr):
         with pytest.raises(RuntimeError):
             b.or_fused_path_batched(arr, 1, 2, 12, 0, None)
     assert sys.getrefcount(arr) == before
+
+
+def test_signatures_can_be_read():
+    """Names, order and defaults of the arguments, as inspect and help() show them."""
+    import inspect
+    show = lambda f: str(inspect.signature(f))
+    assert show(b.or_rht_encode) == "(grad, n, block_log2, seed, out, stream=None)"
+    assert show(b.or_fused_path) == ("(grads, masks, N, shard_len, block_log2, seed, base_index, out, count_out=None, workspace=None, "
+                                     "stream=None)")
+    assert show(b.or_fused_path_batched_monitored) == "(buckets, n_buckets, N, block_log2, bf16, totals, workspace=None, stream=None)"
+    assert show(b.or_reduce_decode_batched) == "(buckets, n_buckets, N, block_log2, bf16, totals=None, workspace=None, stream=None)"
+    assert show(b.or_masked_reduce_pairs) == "(sums, counts, masks, G, shard_len, sum_out, count_out, stream=None)"
+    for name in b._SIGS:
+        if hasattr(b, name):
+            assert inspect.signature(getattr(b, name)) is not None, name
