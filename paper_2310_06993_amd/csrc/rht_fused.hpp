@@ -369,6 +369,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
     if (lane == 0) {
       atomicAdd(&arrived[0], n);
       if constexpr (SLOTS > 1) {
+        __threadfence_block();   // the arrivals before the sign that they are there
         if (atomicAdd(&arrived[1], 1u) == (uint32_t)tiles - 1) atomicAdd(a.total_out, (unsigned long long)atomicAdd(&arrived[0], 0u));
       }
     }

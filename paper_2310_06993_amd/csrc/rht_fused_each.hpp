@@ -101,6 +101,7 @@ __device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit, int
       if (lane == 0) {
         atomicAdd(&arrived[0], n + (uint32_t)full * (64 * R));
         if constexpr (SLOTS > 1) {
+          __threadfence_block();   // the arrivals before the sign that they are there
           if (atomicAdd(&arrived[1], 1u) == (uint32_t)tiles - 1) atomicAdd(a.total_out, (unsigned long long)atomicAdd(&arrived[0], 0u));
         }
       }
