@@ -82,18 +82,19 @@ OR_BATCH_LAUNCHER(fdecb_bf16, (k_finalize_decode_batched<K, bf16_t>), G::THREADS
 // Which workers are added before they are encoded is a matter of type, block size and number of workers alone: the two ways
 // round differently, and a bucket gives the same bits alone, in a batch and as part of a longer shard.
 //   bf16: every worker is encoded by itself (its encoded value is rounded).
-//   fp32 up to 2^10: the whole workers' sum first (rht_fused.hpp).  us, every worker by itself -> sum first: 2^10, N = 2, 64 tiles
-//     5.8 -> 5.2; N = 8, 780 tiles 16.7 -> 10.1, 12800 tiles 86.8 -> 87.0; a loss in every copy of every tile, N = 8, 2560 tiles
-//     26.0 -> 21.6.
+//   fp32 2^10: the whole workers' sum first (rht_fused.hpp).  us, every worker by itself -> sum first: N = 2, 64 tiles 5.8 -> 5.2;
+//     N = 8, 780 tiles 16.7 -> 10.1, 12800 tiles 86.8 -> 87.0; a loss in every copy of every tile, N = 8, 2560 tiles 26.0 -> 21.6.
+//   fp32 below 2^10, where the blocks of a tile are told apart: from six workers on.  2^8: N = 2, 3120
+//     blocks 6.5 -> 6.8; N = 8, 1024 blocks 12.9 -> 7.3, 10240 blocks 22.2 -> 21.7, 51200 blocks 86.6 -> 90.2; N = 32, 3120 blocks
+//     52.9 -> 26.9; a loss in every copy of every tile, N = 8, 3120 blocks 17.4 -> 15.4, 51200 blocks 92.5 -> 96.1.
 //   fp32 2^11: from six workers on.  N = 2, 64 tiles 4.9 -> 5.5; N = 4, 64 tiles 6.4 -> 6.7, 780 tiles 10.2 -> 9.6; N = 8, 64 tiles
 //     9.5 -> 7.2, 780 tiles 16.3 -> 13.8, 12800 tiles 167 -> 171.
 //   fp32 2^12 .. 2^14: every worker by itself.  2^12, N = 16: 100 tiles with 5 % loss 19.2 -> 18.2, 780 tiles 41.8 -> 43.3, 6400
 //     tiles 301 -> 312; N = 64, 780 tiles 142 -> 157; 2^13, N = 8: 256 tiles 16.6 -> 20.0, 2560 tiles 133 -> 136; 2^14, N = 8: 256
 //     tiles 29.4 -> 32.6, 2556 tiles 283 -> 292; a loss in every copy: 2^13, 2560 tiles 139 -> 158.  (The sum first wins where nearly
 //     every copy is whole: 2^14, N = 16, 2560 tiles 481 -> 479, N = 32 926 -> 868.)
-constexpr int kSumFirstFrom = K == 0 ? 1 : K == 11 ? 6 : 256;   // workers
-template <class In> constexpr bool kMaySumFirst = sizeof(In) == 4 && kSumFirstFrom <= 255;
-template <class In> constexpr bool kMayEach = sizeof(In) == 2 || kSumFirstFrom > 1;
+constexpr bool kMaySumFirst = K == 0 || K == 11;
+[[maybe_unused]] bool sum_first_wins(int k, int N) { return k == 10 || (k <= 11 && N >= 6); }
 // GROUPS while a launch leaves CUs idle and has the workers for its four groups (same bits as STREAM).  us, without -> with:
 // 2^10, 256 tiles, N = 2 5.4 -> 6.7, N = 4 with a loss in every tile 7.4 -> 6.6; 2^11, N = 8, 512 tiles 10.7 -> 9.3, 781 tiles
 // 11.9 -> 15.6.
@@ -104,21 +105,25 @@ template <class In> constexpr bool kMayEach = sizeof(In) == 2 || kSumFirstFrom >
 // The second tile buffer of k_fused_each (same bits with and without) pays up to three workgroups on a CU.  (Tiles of 8 or 16
 // wavefronts, at most two workgroups on a CU whatever the grid: always.)
 [[maybe_unused]] bool prefetch_wins(unsigned long long tiles) { return G::W >= 8 || tiles <= 3 * 256; }
+template <bool SPLIT>   // blocks below 2^10, several to a tile
+hipError_t sum_first(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  if (groups_win(units, a.N))
+    return launch_kernel(k_fused<K, GROUPS, SPLIT>, dim3((unsigned)units), dim3(kFusedThreads<K> * kGroups), s, pos, a);
+  return launch_kernel(k_fused<K, STREAM, SPLIT>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
+}
 template <class In>
 hipError_t fused(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
   if (units == 0) return hipSuccess;
   if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;
   const dim3 grid((unsigned)units);
-  if constexpr (kMaySumFirst<In>) {
-    if (a.N >= kSumFirstFrom) {
-      if (groups_win(units, a.N)) return launch_kernel(k_fused<K, GROUPS>, grid, dim3(kFusedThreads<K> * kGroups), s, pos, a);
-      return launch_kernel(k_fused<K, STREAM>, grid, dim3(kFusedThreads<K>), s, pos, a);
+  if constexpr (kMaySumFirst && sizeof(In) == 4) {
+    if (sum_first_wins(a.k, a.N)) {
+      if (K == 0 && a.k < 10) return sum_first<K == 0>(a, units, s, pos);
+      return sum_first<false>(a, units, s, pos);
     }
   }
-  if constexpr (kMayEach<In>) {
-    if (prefetch_wins(units)) return launch_kernel(k_fused_each<K, In, true>, grid, dim3(G::THREADS), s, pos, a);
-    if constexpr (G::W < 8) return launch_kernel(k_fused_each<K, In, false>, grid, dim3(G::THREADS), s, pos, a);
-  }
+  if (prefetch_wins(units)) return launch_kernel(k_fused_each<K, In, true>, grid, dim3(G::THREADS), s, pos, a);
+  if constexpr (G::W < 8) return launch_kernel(k_fused_each<K, In, false>, grid, dim3(G::THREADS), s, pos, a);
   return hipErrorInvalidValue;   // not reached
 }
 // workgroups of SLOTS tiles each; tile_start then counts workgroups
@@ -134,6 +139,12 @@ hipError_t launch_slots(Kernel kernel, int tile_threads, const BatchArgs& a, uns
   b.tile_start[a.n] = groups;
   return launch_kernel(kernel, dim3(groups), dim3(tile_threads * SLOTS), s, pos, b);
 }
+template <bool SPLIT>
+hipError_t sum_first(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  if (groups_win(units, a.N))
+    return launch_kernel(k_fused_batched<K, GROUPS, SPLIT>, dim3((unsigned)units), dim3(kFusedThreads<K> * kGroups), s, pos, a);
+  return launch_slots<kBatchSlots<K, STREAM>>(k_fused_batched<K, STREAM, SPLIT>, kFusedThreads<K>, a, units, s, pos);
+}
 template <class In, int SLOTS>
 hipError_t launch_each(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
   if (prefetch_wins(units)) return launch_slots<SLOTS>(k_fused_each_batched<K, In, true, SLOTS>, G::THREADS, a, units, s, pos);
@@ -144,17 +155,14 @@ template <class In>
 hipError_t fused_batched(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
   if (units == 0) return hipSuccess;
   if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  if constexpr (kMaySumFirst<In>) {
-    if (a.N >= kSumFirstFrom) {
-      if (groups_win(units, a.N)) return launch_kernel(k_fused_batched<K, GROUPS>, dim3((unsigned)units), dim3(kFusedThreads<K> * kGroups), s, pos, a);
-      return launch_slots<kBatchSlots<K, STREAM>>(k_fused_batched<K, STREAM>, kFusedThreads<K>, a, units, s, pos);
+  if constexpr (kMaySumFirst && sizeof(In) == 4) {
+    if (sum_first_wins(a.k, a.N)) {
+      if (K == 0 && a.k < 10) return sum_first<K == 0>(a, units, s, pos);
+      return sum_first<false>(a, units, s, pos);
     }
   }
-  if constexpr (kMayEach<In>) {
-    if (kEachSlots<K> > 1 && !a.totals) return launch_each<In, 1>(a, units, s, pos);
-    return launch_each<In, kEachSlots<K>>(a, units, s, pos);
-  }
-  return hipErrorInvalidValue;   // not reached
+  if (kEachSlots<K> > 1 && !a.totals) return launch_each<In, 1>(a, units, s, pos);
+  return launch_each<In, kEachSlots<K>>(a, units, s, pos);
 }
 constexpr launch_fn fus_f32 = fused<float>, fus_bf16 = fused<bf16_t>;
 constexpr batch_fn fusb_f32 = fused_batched<float>, fusb_bf16 = fused_batched<bf16_t>;

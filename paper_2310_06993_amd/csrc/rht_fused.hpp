@@ -1,13 +1,14 @@
 // The fused path (OptiReduce Sec. 3.3 encode, Sec. 3.1.1 aggregation, Sec. 3.3 / Sec. 4 decode) of fp32 slices for blocks of
 // up to 2^11 entries: one workgroup per tile of T = 2^max(10, k) entries, from N raw slices to the decoded mean.  (bf16, whose
-// encoded values are rounded worker by worker, few workers at 2^11, and 2^12 .. 2^14: rht_fused_each.hpp.)
+// encoded values are rounded worker by worker, few workers at 2^11 and below 2^10, and 2^12 .. 2^14: rht_fused_each.hpp.)
 //
-// The encode is linear and the signs are the same for every worker, so the workers whose copy of the tile arrived
+// The encode is linear and the signs are the same for every worker, so the workers whose copy of the block arrived
 // WHOLE are added up first, as they come from memory, and encoded once.  A worker that lost something in the tile is
 // encoded by itself and added under its received bits.  With packet loss that leaves 1 + (workers with a loss in this
 // tile) transforms where there were N, and the bulk of the work is a plain streaming sum: 16 bytes a lane per load, no
 // barrier in between.  The value of an entry is (sum over whole workers, in increasing order, encoded) + (each of the
-// others, in increasing order) in both modes below.
+// others, in increasing order) in both modes below.  Blocks that share a tile (K = 0) are looked at one by one: a worker that lost
+// something in the tile is encoded with zeros in the blocks that it has whole, so no block's value depends on its neighbours'.
 //
 // Positions, also of the bf16 encode and the reduce + decode of larger blocks (V entries per 16 bytes: 4 fp32, 8 bf16; VB = log2 V; 16 entries a lane, 1024 a wavefront)
 //   A  as loaded and stored: register bits = entry bits 0 .. VB-1 and VB+6 .. 9, lane = VB .. VB+5, wavefront = 10 ..
@@ -212,6 +213,12 @@ __device__ __forceinline__ void store16(u32x4v x, __amdgpu_buffer_rsrc_t rs, int
   __builtin_amdgcn_raw_buffer_store_b128(x, rs, off, 0, AUX);
 }
 
+// One bit per run of 2^log entries (up to 32 of them): the runs of the block of 2^k that run `at` lies in.
+__device__ __forceinline__ uint32_t block_runs(int at, int k, int log) {
+  const int g = 1 << (k - log);
+  return (0xFFFFFFFFu >> (32 - g)) << (at & ~(g - 1));
+}
+
 // The workers in the order they are taken: first those that lost something in the tile, then the others, each kind in
 // increasing order.  `marks`: one bit per worker in LDS, set where something is missing; `order`: 256 bytes of LDS (every
 // wavefront writes the same values and reads back its own).  The result holds entry j in byte j / 64 of lane j % 64.
@@ -240,11 +247,13 @@ constexpr int kGroups = 4;
 
 // SLOTS > 1 (tiles of one wavefront): the workgroup's wavefronts serve SLOTS tiles, for the sake of the arrival totals: one
 // atomic per workgroup.  (Atomics on one 128-byte line take 14 ns each: 32 thousand tiles of a batch spent 300 us on them.)
-template <int K, int MODE, int SLOTS = 1>
+// SPLIT: blocks below 2^10, several to a tile.
+template <int K, int MODE, bool SPLIT, int SLOTS = 1>
 __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u64 units) {
   typedef float In;
   typedef FTile<K, In> F;
   constexpr int W = F::W, T = F::T, ES = sizeof(In), G = MODE == GROUPS ? kGroups : 1;
+  static_assert(!SPLIT || K == 0, "larger blocks are whole tiles");
   static_assert(F::Q <= 1, "tiles of one or two wavefronts: no sign from DPP stages");
   static_assert(SLOTS == 1 || (W == 1 && G == 1), "several tiles per workgroup: tiles of one wavefront");
   constexpr int BUFS = MODE == GROUPS ? G : SLOTS;
@@ -253,6 +262,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   __shared__ __align__(16) uint8_t counts[G * SLOTS][T];
   __shared__ uint32_t marks_all[SLOTS][8];
   __shared__ uint8_t order_all[SLOTS][MODE == STREAM ? 1 : 256];
+  __shared__ uint2 missing16[MODE == GROUPS && SPLIT ? 256 : 1];   // per worker with a loss: the runs of 16 entries that miss something
   __shared__ uint32_t arrived[2];   // arrivals of the workgroup's tiles; how many of its wavefronts have added theirs
   const int wave_all = wave_id(), lane = lane_id();
   const int slot = SLOTS > 1 ? wave_all : 0;
@@ -346,8 +356,9 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
       for (int u = 0; u < U; ++u) {
         const int w = i + u * G;
         if (w >= N) break;
-        if (__builtin_amdgcn_ballot_w64(inside && bits[u] != 0xFFFFu) != 0) {
+        if (const u64 missing = __builtin_amdgcn_ballot_w64(inside && bits[u] != 0xFFFFu)) {
           if (lane == 0) atomicOr(&marks[w >> 5], 1u << (w & 31));
+          if (MODE == GROUPS && SPLIT && lane == 0) missing16[w] = make_uint2((uint32_t)missing, (uint32_t)(missing >> 32));
           count_bits(bits[u]);
         } else {
           ++full;
@@ -389,6 +400,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   auto marks_of = [&](int i) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)marks[i >> 5]); };   // the 32 around worker i
   for (int i = 0; i < N; i += 32) lossy += __builtin_popcount(marks_of(i));
   const int whole = N - lossy;
+  const bool has_sum = whole > 0 || SPLIT;
   const uint32_t ord = MODE == STREAM ? 0 : order_workers(marks, order, N, lossy, lane);
   auto worker = [&](int j) -> int {   // the j-th in order, -1 past the end
     return j < N ? (int)(((uint32_t)__builtin_amdgcn_readlane((int)ord, j & 63) >> (j >> 6 << 3)) & 0xFFu) : -1;
@@ -402,10 +414,6 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
       for (int r = 0; r < 16; ++r) acc[r] += in_mask(mask_of_reg(words, r)) ? y[r] : 0.0f;
     }
   };
-  auto add_raw = [&](const Raw16<In>& y) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) raw[r] += entry_of<In>(y, r);
-  };
   // the signed entries of a worker with a loss.  The shifted copies of the sign bits are formed anew for every worker:
   // kept over the loop they would cost sixteen registers
   auto sign_all = [&](float (&y)[16]) {
@@ -414,10 +422,30 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
 #pragma unroll
     for (int r = 0; r < 16; ++r) y[r] = flip_sign(y[r], s, r);
   };
-  auto take_signed = [&](const Raw16<In>& y) {
+  // SPLIT: all ones where the block of the lane's entries 256 c + 4 lane .. + 3 has a run of 32 entries with its bit in `missing`
+  auto lost_chunk = [&](uint32_t missing, int c) -> int {
+    int at = lane >> 3;   // the masks of runs are formed here, not kept in registers all along
+    asm volatile("" : "+v"(at));
+    return (missing & block_runs(8 * c + at, k, 5)) != 0 ? -1 : 0;
+  };
+  // (lane l of the first 32 of `words`: the received bits of entries 32 l ..)
+  auto runs_missing = [&](uint32_t words) { return (uint32_t)__builtin_amdgcn_ballot_w64(words != 0xFFFFFFFFu); };
+  auto take_signed = [&](const Raw16<In>& y, uint32_t missing) {   // SPLIT: without the blocks that are whole
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = entry_of<In>(y, r);
+    for (int c = 0; c < 4; ++c) {
+      const int lost = SPLIT ? lost_chunk(missing, c) : -1;
+#pragma unroll
+      for (int r = 4 * c; r < 4 * c + 4; ++r) v[r] = __builtin_bit_cast(float, __builtin_bit_cast(int, entry_of<In>(y, r)) & lost);
+    }
     sign_all(v);
+  };
+  auto add_whole = [&](const Raw16<In>& y, uint32_t missing) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int lost = SPLIT ? lost_chunk(missing, c) : 0;
+#pragma unroll
+      for (int r = 4 * c; r < 4 * c + 4; ++r) raw[r] += __builtin_bit_cast(float, __builtin_bit_cast(int, entry_of<In>(y, r)) & ~lost);
+    }
   };
 
   if constexpr (MODE == STREAM) {
@@ -426,7 +454,9 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
       if ((i & 31) == 0) lost32 = marks_of(i);
       const bool lost = (lost32 >> (i & 31)) & 1;
       const uint32_t words = m;
-      if (lost) take_signed(r16); else add_raw(r16);
+      const uint32_t missing = SPLIT && lost ? runs_missing(words) : 0;
+      if (SPLIT || !lost) add_whole(r16, missing);
+      if (lost) take_signed(r16, missing);
       request(i + 2, r16);
       m = request_words(i + 2);
       if (lost) {
@@ -442,7 +472,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
       consume(i, ra, ma);
       if (i + 1 < N) consume(i + 1, rb, mb);
     }
-    if (whole > 0) {
+    if (has_sum) {
       sign_all(raw);
       tile_barrier<W>();
       to_wire<K, In>(raw, x, wave, lane, k);
@@ -450,11 +480,11 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
       for (int r = 0; r < 16; ++r) acc[r] += raw[r];
     }
   } else {
-    // Items 0 .. lossy - 1 are the workers with a loss, item lossy the sum over the whole ones; round t: items 4 t ..
+    // Items 0 .. lossy - 1 are the workers with a loss, item lossy the sum over what is whole; round t: items 4 t ..
     // 4 t + 3.  The rounds before the last run while the whole workers' entries are on their way.
     request(grp < lossy ? worker(grp) : -1, ra);
     ma = request_words(grp < lossy ? worker(grp) : -1);
-    const int items = lossy + (whole > 0), own4 = (wave * 64 + lane) * 4;
+    const int items = lossy + has_sum, own4 = (wave * 64 + lane) * 4;
     auto round = [&](int t) {
       const int item = t * G + grp;
       const bool works = item < items, is_sum = item == lossy;
@@ -464,7 +494,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
           lds_a<K, In, false>(v, x, wave, lane);
           sign_all(v);
         } else {
-          take_signed(ra);
+          take_signed(ra, SPLIT ? runs_missing(words) : 0);
         }
       }
       request(item + G < lossy ? worker(item + G) : -1, ra);
@@ -504,6 +534,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
       }
     };
     float s4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    const uint32_t runs16 = SPLIT ? block_runs((grp & 1) * 16 + (lane >> 2), k, 4) : 0;   // of this lane's four entries, in their half of the tile
     int t = 0;
     for (int b = 0; b < N; b += U) {
       const uint32_t lost = marks_of(b) >> (b & 31);
@@ -512,17 +543,21 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
         if (!((lost >> u) & 1)) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) s4[r] += __builtin_bit_cast(float, (uint32_t)q4[u][r]);
+        } else if (SPLIT) {   // its blocks that are whole
+          const bool lost_here = ((grp < 2 ? missing16[b + u].x : missing16[b + u].y) & runs16) != 0;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s4[r] += lost_here ? 0.0f : __builtin_bit_cast(float, (uint32_t)q4[u][r]);
         }
       if (b + U < N) {
         const uint32_t next = marks_of(b + U) >> ((b + U) & 31);
 #pragma unroll
-        for (int u = 0; u < U; ++u) request4((next >> u) & 1 ? -1 : b + U + u, q4[u]);
+        for (int u = 0; u < U; ++u) request4(!SPLIT && ((next >> u) & 1) ? -1 : b + U + u, q4[u]);
       }
       if (t < lossy / G) round(t++);
     }
     while (t < lossy / G) round(t++);
     if (items > t * G) {
-      if (whole > 0)   // the sum goes to the group that encodes it (behind a barrier since that buffer was last read)
+      if (has_sum)   // the sum goes to the group that encodes it (behind a barrier since that buffer was last read)
         *(f32x4v*)(xbuf[lossy % G] + wave * F::PART + F::padded(grp * 256) + F::padded(lane * 4)) = f32x4v{s4[0], s4[1], s4[2], s4[3]};
       __syncthreads();
       round(t);
@@ -589,20 +624,20 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
 
 template <int K> constexpr int kFusedThreads = 64 << (K ? K - 10 : 0);
 // VGPRs are capped so that several workgroups fit on a CU: the loads in flight are those of its neighbours too
-template <int K, int MODE>
+template <int K, int MODE, bool SPLIT>
 __global__ __launch_bounds__(kFusedThreads<K> * (MODE == GROUPS ? kGroups : 1)) __attribute__((amdgpu_waves_per_eu(4)))
 void k_fused(PathArgs a) {
-  fused_tile<K, MODE>(a, blockIdx.x, gridDim.x);
+  fused_tile<K, MODE, SPLIT>(a, blockIdx.x, gridDim.x);
 }
 // K = 0: a workgroup of the plain form serves kBatchSlots tiles of one bucket; ba.tile_start counts workgroups
 template <int K, int MODE> constexpr int kBatchSlots = K == 0 && MODE != GROUPS ? 8 : 1;
-template <int K, int MODE>
+template <int K, int MODE, bool SPLIT>
 __global__ __launch_bounds__(kFusedThreads<K> * (MODE == GROUPS ? kGroups : kBatchSlots<K, MODE>)) __attribute__((amdgpu_waves_per_eu(4)))
 void k_fused_batched(BatchArgs ba) {
   constexpr int SLOTS = kBatchSlots<K, MODE>, T = FTile<K, float>::T;
   PathArgs a;
   const u64 group = bucket_of(ba, a);
-  fused_tile<K, MODE, SLOTS>(a, group * SLOTS, (a.n_pad + T - 1) / T);
+  fused_tile<K, MODE, SPLIT, SLOTS>(a, group * SLOTS, (a.n_pad + T - 1) / T);
 }
 
 }  // namespace ordev

@@ -3,7 +3,7 @@
 // back.  Tiles of 2, 4, 8 or 16 wavefronts use the transposed transform of rht_tile.hpp, in both directions.
 //
 // bf16: every worker's encoded value is rounded as if it had been stored and sent, so every worker has to be encoded.  fp32: blocks
-// of 2^12 .. 2^14, and few workers at 2^11, where adding up whole workers first costs more at the start and the end of a
+// of 2^12 .. 2^14, and few workers at 2^11 and below 2^10, where adding up whole workers first costs more at the start and the end of a
 // workgroup than the transforms that it saves (figures at the rule, inst.hip).
 //
 // PREFETCH: a second tile buffer, so that the next worker's tile is in flight during the transform (same arithmetic, same

@@ -823,3 +823,45 @@ def test_counts_at_any_address(b, k, N, blocks, kind):
                 assert bool((s[:off] == 0xA5).all()) and bool((s[off + L:] == 0xA5).all()), off
             assert torch.equal(out, want) and torch.equal(again, want), off
             assert totals.item() == count.sum(dtype=torch.int64).item(), off
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16"])
+@pytest.mark.parametrize("k,N,blocks", [(5, 4, 40), (5, 3, 20000), (6, 8, 33), (7, 6, 9), (8, 2, 1200), (8, 8, 50), (8, 16, 4000), (9, 4, 3),
+                                        (9, 8, 2000), (9, 33, 11)])
+def test_fused_bits_do_not_depend_on_the_blocks_around(b, k, N, blocks, kind):
+    """Blocks below 2^10 share tiles of 1024 entries.  Any run of blocks of a shard gives, as a shard of its own, the bits that it has
+    within the shard: cut off at every position within a tile, with losses in some blocks of a tile and none in others."""
+    B, L = 1 << k, blocks << k
+    gen = torch.Generator(device=dev()).manual_seed(70 * k + N)
+    dt = torch.float32 if kind == "f32" else torch.bfloat16
+    x = torch.randn((N, L), device=dev(), generator=gen).mul_(1e-3).to(dt)
+    m = torch.where(torch.rand((N, L // 32), device=dev(), generator=gen) < 0.08 * 32 / B, 0x7FFF0FFF, -1).to(torch.int32)
+    m[:, : B // 32] = 0x0FFFFFFF                                       # a block that everybody lost something of
+    m[0] = -1
+    seed = 0x77AA77AA12345678
+    call = b.or_fused_path if kind == "f32" else b.or_fused_path_bf16
+
+    def run(first, n):
+        out, cnt = torch.full((n << k,), float("nan"), dtype=dt, device=dev()), torch.full((n << k,), 255, dtype=torch.uint8, device=dev())
+        base = (1 << 20) + (first << k)
+        if base % max(B, 128):
+            return None
+        call(x[:, first << k:(first + n) << k].contiguous(), m[:, (first << k) // 32:((first + n) << k) // 32].contiguous(), N, n << k, k, seed,
+             base, out, cnt, None)
+        return out.view(torch.uint8), cnt
+
+    want, count = run(0, blocks)
+    es = x.element_size()
+    per = max(1, 1024 >> k)
+    tried = 0
+    for first, n in [(0, 1), (0, 3), (1, 2), (blocks // 2 // per * per, 1), (blocks - 1, 1)] + [(f, blocks - f) for f in range(1, per, max(1, per // 8))] + \
+            [(0, blocks - f) for f in range(1, per, max(1, per // 8))]:
+        if n < 1 or first + n > blocks:
+            continue
+        got = run(first, n)
+        if got is None:
+            continue
+        tried += 1
+        assert torch.equal(got[0], want[first * B * es:(first + n) * B * es]), (first, n)
+        assert torch.equal(got[1], count[first * B:(first + n) * B]), (first, n)
+    assert tried >= 3
