@@ -34,8 +34,20 @@ __device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit, int
   int full = 0, flip = 0;
   const int moff = mask_word_offset<K>(wave, lane);
   const u64 mrow = L >> 5;
+  static_assert(FULL || Geo<K>::W == 1, "only tiles of one wavefront are cut short");
+  [[maybe_unused]] const int left = FULL ? T : (int)(L - e0);
   auto request = [&](int i, float (&v)[R], uint32_t& words) {
-    load_tile<K, false, FULL, true>(grads + (u64)i * L, e0, L, wave, lane, v);
+    if constexpr (FULL) {
+      load_tile<K, false, true, true>(grads + (u64)i * L, e0, L, wave, lane, v);
+    } else {   // past the end: the last entry again, as a zero (range-checked loads: their descriptors in vector registers, see below)
+      const In* q = grads + (u64)i * L + e0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int e = r * 64 + lane;
+        const float x = to_f32(load_one<true>(&q[e < left ? e : left - 1]));
+        v[r] = e < left ? x : 0.0f;
+      }
+    }
     words = load_mask_words<K, FULL>(a.masks + (u64)i * mrow, e0, L, moff);
   };
   // the first worker's tile is requested before the signs are computed, so Philox runs under its latency
@@ -121,8 +133,9 @@ __device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit, int
 }
 
 // SLOTS > 1 (tiles of one wavefront): the workgroup's wavefronts serve SLOTS tiles of a bucket, one atomic for all their arrivals
-// (see fused_tile).  K = 0: whether the tile is cut short is decided once, for all accesses (decided at each of them, or with
-// range-checked accesses throughout, the loop over the workers keeps descriptors in vector registers: three times slower).
+// (see fused_tile).  K = 0: whether the tile is cut short is decided once, for all accesses.  (With
+// range-checked loads in the loop over the workers the compiler keeps their descriptors in vector registers and makes a loop of
+// every load: launches of whole tiles two to three times slower, one cut tile of 32 workers 48 -> 69 us.)
 template <int K, class In, bool PREFETCH, bool TOTAL, int SLOTS>
 __device__ __forceinline__ void fused_each(const PathArgs& a, u64 first_unit, u64 units) {
   static_assert(SLOTS == 1 || Geo<K>::W == 1, "several tiles per workgroup: tiles of one wavefront");
@@ -136,10 +149,12 @@ __device__ __forceinline__ void fused_each(const PathArgs& a, u64 first_unit, u6
     if (slot >= tiles) return;
   }
   const u64 unit = first_unit + slot;
-  if (kShardTilesFull<K> || (unit + 1) * Geo<K>::T <= a.n_pad)
+  if constexpr (kShardTilesFull<K>) {
     fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, true>(a, unit, wave, tiles, xbuf, arrived);
-  else
-    fused_each_tile<K, In, false, TOTAL, SLOTS, false>(a, unit, wave, tiles, xbuf, arrived);
+  } else {
+    if ((unit + 1) * Geo<K>::T <= a.n_pad) fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, true>(a, unit, wave, tiles, xbuf, arrived);
+    else fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, false>(a, unit, wave, tiles, xbuf, arrived);
+  }
 }
 
 template <int K, class In, bool PREFETCH>
