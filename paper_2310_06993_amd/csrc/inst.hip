@@ -2,9 +2,14 @@
 #include "launch_table.hpp"
 #include "rht_fused.hpp"
 #include "rht_fused_each.hpp"
+#if OR_K >= 11 && OR_K <= 15
+#include "rht_fused_bf16.hpp"
+#endif
 #if OR_K > 14
 #include "rht_encode_block.hpp"
+#if OR_K == 16
 #include "rht_fused_mx.hpp"
+#endif
 #include "rht_reduce_block.hpp"
 #endif
 
@@ -81,7 +86,7 @@ OR_BATCH_LAUNCHER(fdecb_f32, (k_finalize_decode_batched<K, float>), G::THREADS)
 OR_BATCH_LAUNCHER(fdecb_bf16, (k_finalize_decode_batched<K, bf16_t>), G::THREADS)
 // Which workers are added before they are encoded is a matter of type, block size and number of workers alone: the two ways
 // round differently, and a bucket gives the same bits alone, in a batch and as part of a longer shard.
-//   bf16: every worker is encoded by itself (its encoded value is rounded).
+//   bf16: every worker is encoded by itself (its encoded value is rounded); above 2^10 in a kernel of its own (rht_fused_bf16.hpp).
 //   fp32 2^10: the whole workers' sum first (rht_fused.hpp).  us, every worker by itself -> sum first: N = 2, 64 tiles 5.8 -> 5.2;
 //     N = 8, 780 tiles 16.7 -> 10.1, 12800 tiles 86.8 -> 87.0; a loss in every copy of every tile, N = 8, 2560 tiles 26.0 -> 21.6.
 //   fp32 below 2^10, where the blocks of a tile are told apart: from six workers on.  2^8: N = 2, 3120
@@ -164,8 +169,12 @@ hipError_t fused_batched(const BatchArgs& a, unsigned long long units, hipStream
   if (kEachSlots<K> > 1 && !a.totals) return launch_each<In, 1>(a, units, s, pos);
   return launch_each<In, kEachSlots<K>>(a, units, s, pos);
 }
-constexpr launch_fn fus_f32 = fused<float>, fus_bf16 = fused<bf16_t>;
-constexpr batch_fn fusb_f32 = fused_batched<float>, fusb_bf16 = fused_batched<bf16_t>;
+constexpr launch_fn fus_f32 = fused<float>;
+constexpr batch_fn fusb_f32 = fused_batched<float>;
+#if OR_K == 0
+constexpr launch_fn fus_bf16 = fused<bf16_t>;
+constexpr batch_fn fusb_bf16 = fused_batched<bf16_t>;
+#endif
 #else
 // one workgroup per pair of output tiles; `units` = output tiles of the shard
 #define OR_PAIR_LAUNCHER(name, kernel)                                                       \
@@ -179,7 +188,60 @@ constexpr batch_fn fusb_f32 = fused_batched<float>, fusb_bf16 = fused_batched<bf
 OR_BLOCK_LAUNCHER(rdec_f32, (k_reduce_decode_block<K, float>))
 OR_BLOCK_LAUNCHER(rdec_bf16, (k_reduce_decode_block<K, bf16_t>))
 OR_PAIR_LAUNCHER(fus_f32, (k_fused_pairs<K, float>))
+#if OR_K == 16
 OR_PAIR_LAUNCHER(fus_bf16, (k_fused_mx<K>))
+#endif
+#endif
+#if OR_K >= 11 && OR_K <= 15
+// a workgroup per block; `units` and tile_start of the call count tiles (of at most 2^14)
+#if OR_K <= 14
+constexpr int kGroupsBf16 = K == 11 ? 8 : 16 / MTile<K>::W;
+// How many groups of wavefronts encode workers side by side (1: none; the same bits)?  As many as there are workers for, in launches
+// that leave CUs idle or leave room on them.  us, without -> with: 2^11, N = 8, 64 blocks 11.6 -> 6.9, 512 blocks 12.7 -> 9.6 (1024:
+// 13.9 -> 16.6), N = 3, 100 blocks 7.0 -> 6.3, N = 2 6.0 -> 6.1;  2^12, N = 8, 64 blocks 13.2 -> 8.9, 512 blocks 17.1 -> 13.9 with
+// four groups (eight: 18.2), N = 3, 100 blocks 7.8 -> 7.0, N = 2 6.7 -> 6.7;  2^13, N = 8, 64 blocks 15.9 -> 13.0, 512 blocks 20.1 ->
+// 28.7, N = 3, 100 blocks 9.0 -> 9.0;  2^14, N = 32, 2 blocks 65.5 -> 59.1, N = 8, 64 blocks 21.2 -> 20.5, 256 blocks 22.0 -> 23.2,
+// N = 3, 100 blocks 11.7 -> 13.3.
+int groups_bf16(unsigned long long blocks, int N) {
+  int most = kGroupsBf16;
+  if (N < (K <= 12 ? 3 : K == 13 ? 4 : 6)) return 1;
+  if (blocks > (K == 14 ? 128 : 256)) most = K == 11 ? 8 : K == 12 && blocks <= 512 ? 4 : 1;
+  if (blocks > 512) most = 1;
+  int g = 1;
+  while (g < most && g < N) g *= 2;
+  return g;
+}
+template <int G>
+hipError_t launch_groups(int g, const PathArgs& a, unsigned long long blocks, hipStream_t s, int pos) {
+  if constexpr (G > 2) if (g < G) return launch_groups<G / 2>(g, a, blocks, s, pos);
+  return launch_kernel(k_fused_bf16_groups<K, G>, dim3((unsigned)blocks), dim3(MTile<K>::THREADS * G), s, pos, a);
+}
+template <int G>
+hipError_t launch_groups(int g, const BatchArgs& a, unsigned long long blocks, hipStream_t s, int pos) {
+  if constexpr (G > 2) if (g < G) return launch_groups<G / 2>(g, a, blocks, s, pos);
+  return launch_kernel(k_fused_bf16_groups_batched<K, G>, dim3((unsigned)blocks), dim3(MTile<K>::THREADS * G), s, pos, a);
+}
+#endif
+hipError_t fus_bf16(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  const unsigned long long blocks = units >> G::HB;
+  if (blocks == 0) return hipSuccess;
+  if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+#if OR_K <= 14
+  if (const int g = groups_bf16(blocks, a.N); g > 1) return launch_groups<kGroupsBf16>(g, a, blocks, s, pos);
+#endif
+  return launch_kernel(k_fused_bf16<K>, dim3((unsigned)blocks), dim3(MTile<K>::THREADS), s, pos, a);
+}
+hipError_t fusb_bf16(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  const unsigned long long blocks = units >> G::HB;
+  if (blocks == 0) return hipSuccess;
+  if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+#if OR_K <= 14
+  if (const int g = groups_bf16(blocks, a.N); g > 1) return launch_groups<kGroupsBf16>(g, a, blocks, s, pos);
+#endif
+  BatchArgs b = a;
+  for (int j = 0; j <= a.n; ++j) b.tile_start[j] >>= G::HB;
+  return launch_kernel(k_fused_bf16_batched<K>, dim3((unsigned)blocks), dim3(MTile<K>::THREADS), s, pos, b);
+}
 #endif
 }  // namespace
 
@@ -191,6 +253,8 @@ extern const KernelTable OR_CAT(or_kernel_table_, OR_K) = {
     rdec_f32, rdec_bf16, fus_f32, fus_bf16,
 #if OR_K <= 14
     fusb_f32, fusb_bf16, rdecb_f32, rdecb_bf16, fdecb_f32, fdecb_bf16
+#elif OR_K == 15
+    nullptr, fusb_bf16, nullptr, nullptr, nullptr, nullptr
 #else
     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr
 #endif

@@ -452,10 +452,11 @@ or_status run_path(bool fused, const T* in, const uint32_t* masks, int N, u64 L,
   d.out = out; d.n = L; d.n_pad = L; d.seed = seed; d.base = base; d.k = k; d.scale = a.scale;
   d.in = ws_f32;
   d.unit0 = units;   // shards hold whole blocks: no tile of the decode needs bounds checks
+  if (fused && bf16 && k == 15) return finish(t->fused_bf16(a, units, s, first | last));   // a workgroup per block, no workspace
   if (fused && bf16) {
-    // bf16: one kernel does everything.  Workspace: [hand-over slots of the workgroup pairs, 4 L bytes, k = 16 only]
+    // bf16: one kernel does everything.  Workspace: [hand-over slots of the workgroup pairs, 4 L bytes]
     // [sign stream of the shard, L/8 bytes][pair flags, 8 bytes a block]
-    const u64 counters = L >> 7, nflags = k == 16 ? 2 * (L >> 16) : 0;   // one thread per Philox counter
+    const u64 counters = L >> 7, nflags = 2 * (L >> 16);   // one thread per Philox counter
     unsigned* flags = (unsigned*)(ws_cnt + (L / 8 + 255) / 256 * 256);
     const u64 blocks = ((counters > nflags ? counters : nflags) + 255) / 256;
     if (blocks > 0x7FFFFFFFull) return OR_ERR_SHAPE;

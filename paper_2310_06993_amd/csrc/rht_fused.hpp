@@ -636,7 +636,7 @@ __global__ __launch_bounds__(kFusedThreads<K> * (MODE == GROUPS ? kGroups : kBat
 void k_fused_batched(BatchArgs ba) {
   constexpr int SLOTS = kBatchSlots<K, MODE>, T = FTile<K, float>::T;
   PathArgs a;
-  const u64 group = bucket_of(ba, a);
+  const u64 group = bucket_of(ba, a, blockIdx.x);
   fused_tile<K, MODE, SPLIT, SLOTS>(a, group * SLOTS, (a.n_pad + T - 1) / T);
 }
 

@@ -1,10 +1,10 @@
-// The fused path for blocks of up to 2^14 entries with every worker encoded by itself: per worker sign flip (layout A),
+// The fused path for blocks of up to 2^14 entries (bf16: 2^10) with every worker encoded by itself: per worker sign flip (layout A),
 // transform to layout B, rounding to the wire type (bf16), addition under the received mask; the mean is decoded the same way
 // back.  Tiles of 2, 4, 8 or 16 wavefronts use the transposed transform of rht_tile.hpp, in both directions.
 //
-// bf16: every worker's encoded value is rounded as if it had been stored and sent, so every worker has to be encoded.  fp32: blocks
-// of 2^12 .. 2^14, and few workers at 2^11 and below 2^10, where adding up whole workers first costs more at the start and the end of a
-// workgroup than the transforms that it saves (figures at the rule, inst.hip).
+// bf16: every worker's encoded value is rounded as if it had been stored and sent, so every worker has to be encoded (above 2^10:
+// rht_fused_bf16.hpp).  fp32: blocks of 2^12 .. 2^14, and few workers at 2^11 and below 2^10, where adding up whole workers first costs
+// more at the start and the end of a workgroup than the transforms that it saves (figures at the rule, inst.hip).
 //
 // PREFETCH: a second tile buffer, so that the next worker's tile is in flight during the transform (same arithmetic, same
 // results).  It shortens the chain of dependent steps of a workgroup and wins while a launch puts at most three workgroups on
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(Geo<K>::THREADS * SLOTS) __attribute__((amdgpu_wave
 void k_fused_each_batched(BatchArgs ba) {
   constexpr int T = Geo<K>::T;
   PathArgs a;
-  const u64 group = bucket_of(ba, a);
+  const u64 group = bucket_of(ba, a, blockIdx.x);
   fused_each<K, In, PREFETCH, (SLOTS == kEachSlots<K>), SLOTS>(a, group * SLOTS, (a.n_pad + T - 1) / T);
 }
 

@@ -535,14 +535,13 @@ struct BatchArgs {
 
 static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
-// the bucket that workgroup x serves, as the arguments of a single-bucket call; returns the tile inside it
+// the bucket that unit x of the launch lies in, as the arguments of a single-bucket call; returns the tile inside it
 template <bool WALK = false>
-__device__ __forceinline__ u64 bucket_of(const BatchArgs& ba, PathArgs& a) {
+__device__ __forceinline__ u64 bucket_of(const BatchArgs& ba, PathArgs& a, uint32_t x) {
   // buckets that end at or before tile x: one comparison a lane (a walk over the descriptors was up to 60 dependent
   // scalar loads ahead of a workgroup's first access).  us, walk -> that, 64 buckets: finalize + decode 2^14 19.2 -> 14.7, reduce +
   // decode bf16 2^11 26.2 -> 17.8; but reduce + decode fp32 with its data in the cache 2^14 37.5 -> 42.6, 2^10 16 buckets 14.5 ->
   // 17.1 (in memory: the same), which therefore walks
-  const uint32_t x = blockIdx.x;
   int j = 0;
   if constexpr (WALK) {
     while (j + 1 < ba.n && ba.tile_start[j + 1] <= x) ++j;
@@ -564,13 +563,13 @@ __device__ __forceinline__ u64 bucket_of(const BatchArgs& ba, PathArgs& a) {
 template <int K, class Wire>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_reduce_decode_batched(BatchArgs ba) {
   PathArgs a;
-  const u64 unit = bucket_of<sizeof(Wire) == 4>(ba, a);
+  const u64 unit = bucket_of<sizeof(Wire) == 4>(ba, a, blockIdx.x);
   reduce_decode_tile<K, Wire, Wire>(a, unit);
 }
 template <int K, class Out>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_finalize_decode_batched(BatchArgs ba) {
   PathArgs a;
-  const u64 unit = bucket_of(ba, a);
+  const u64 unit = bucket_of(ba, a, blockIdx.x);
   __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
   decode_tile<K, Out, true, kShardTilesFull<K>, false>(a, unit, xbuf);
 }

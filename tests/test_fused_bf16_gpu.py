@@ -1,0 +1,55 @@
+"""The bf16 fused path above 2^10 at the edges of its forms: numbers of workers around the groups that encode side by side, numbers
+of blocks around the rules that choose them, with and without losses."""
+import numpy as np
+import pytest
+import torch
+
+from _util import TOL, dev, masks_to_dev, rel_l2, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def b():
+    import paper_2310_06993_amd.binding as binding
+    return binding
+
+
+def _workspace(b, L, k):
+    n = b.or_workspace_bytes(L, k)
+    return torch.empty(n, dtype=torch.uint8, device=dev()) if n else None
+
+
+@pytest.mark.parametrize("loss", [0.0, 0.02, 0.4])
+@pytest.mark.parametrize("k,N,blocks", [(11, 2, 3), (11, 3, 1), (11, 7, 257), (11, 8, 512), (11, 9, 513), (11, 17, 2), (12, 3, 256),
+                                        (12, 4, 257), (12, 8, 1), (12, 9, 512), (12, 15, 513), (13, 3, 2), (13, 4, 256), (13, 5, 257),
+                                        (13, 255, 1), (14, 5, 3), (14, 6, 128), (14, 7, 129), (14, 33, 1), (15, 1, 2), (15, 6, 3)])
+def test_forms_against_the_oracle(b, orc, k, N, blocks, loss):
+    """First, middle and last block against the oracle, and the same bits and the arrival total from the batched call.  loss 0: the
+    shortcuts for wavefronts and blocks that have everything; 0.4: hardly a run of 32 entries is whole."""
+    B, L = 1 << k, blocks << k
+    rng = np.random.default_rng(100 * k + N + blocks)
+    gen = torch.Generator(device=dev()).manual_seed(k + N)
+    x = torch.randn((N, L), device=dev(), generator=gen).mul_(1e-3).to(torch.bfloat16)
+    words = np.full((N, L // 32), 0xFFFFFFFF, dtype=np.uint32)
+    if loss > 0.1:
+        words &= ~(np.uint32(1) << rng.integers(0, 32, words.shape, dtype=np.uint32))
+        words[:, -1] &= np.uint32(0x7FFFFFFF)        # the last entry of all is nobody's
+    elif loss:
+        words.reshape(N, -1, 8)[rng.random((N, L // 256)) < loss] = 0
+    md = masks_to_dev(words)
+    seed, base = 0x0FEDCBA987654321, (1 << 33) + 4 * B
+    out, cnt = torch.full((L,), float("nan"), dtype=torch.bfloat16, device=dev()), torch.full((L,), 255, dtype=torch.uint8, device=dev())
+    ws = _workspace(b, L, k)
+    b.or_fused_path_bf16(x, md, N, L, k, seed, base, out, cnt, ws)
+    for j in {0, blocks // 2, blocks - 1}:
+        part = slice(j * B, (j + 1) * B)
+        want, wcnt = orc.fused_path(to_np(x[:, part].contiguous()), np.ascontiguousarray(words[:, j * B // 32:(j + 1) * B // 32]), k,
+                                    seed, base + j * B)
+        assert np.array_equal(to_np(cnt[part]), wcnt), j
+        assert rel_l2(to_np(out[part]), want) <= TOL["bf16"], j
+    again, cnt2 = torch.full_like(out, float("nan")), torch.full_like(cnt, 255)
+    totals = torch.full((1,), -1, dtype=torch.int64, device=dev())
+    b.or_fused_path_batched_monitored(b.make_buckets([(x, md, again, cnt2, L, seed, base)]), 1, N, k, True, totals, ws)
+    assert torch.equal(again.view(torch.uint8), out.view(torch.uint8)) and torch.equal(cnt2, cnt)
+    assert totals.item() == cnt.long().sum().item()
