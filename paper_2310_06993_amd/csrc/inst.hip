@@ -8,7 +8,7 @@
 #if OR_K > 14
 #include "rht_encode_block.hpp"
 #if OR_K == 16
-#include "rht_fused_mx.hpp"
+#include "rht_fused_bf16_64k.hpp"
 #endif
 #include "rht_reduce_block.hpp"
 #endif
@@ -188,9 +188,6 @@ constexpr batch_fn fusb_bf16 = fused_batched<bf16_t>;
 OR_BLOCK_LAUNCHER(rdec_f32, (k_reduce_decode_block<K, float>))
 OR_BLOCK_LAUNCHER(rdec_bf16, (k_reduce_decode_block<K, bf16_t>))
 OR_PAIR_LAUNCHER(fus_f32, (k_fused_pairs<K, float>))
-#if OR_K == 16
-OR_PAIR_LAUNCHER(fus_bf16, (k_fused_mx<K>))
-#endif
 #endif
 #if OR_K >= 11 && OR_K <= 15
 // a workgroup per block; `units` and tile_start of the call count tiles (of at most 2^14)
@@ -243,6 +240,33 @@ hipError_t fusb_bf16(const BatchArgs& a, unsigned long long units, hipStream_t s
   return launch_kernel(k_fused_bf16_batched<K>, dim3((unsigned)blocks), dim3(MTile<K>::THREADS), s, pos, b);
 }
 #endif
+#if OR_K == 16
+// A workgroup per block, or two or four that meet in the workspace (the same bits)?  A workgroup takes 7 to 8 us a worker, and takes
+// 4.5 / 3.3 us for a half / a quarter of the encoded values.  us, four / two / one workgroups a block: N = 8, 16
+// blocks 48 / 64 / 91, 64 blocks 52 / 67 / 93, 100 blocks 86 / 68 / 93, 128 blocks 88 / 70 / 94, 160 blocks 122 / 118 / 94;  N = 2, 64
+// blocks 30 / 34 / 39, 128 blocks 44 / 37 / 40;  N = 32, 2 blocks 136 / 190 / 297.
+constexpr unsigned long long kFourSplit = 64, kTwoSplit = 128;
+constexpr unsigned long long kWalkers = 256;   // workgroups that walk over the blocks: one fills a CU
+hipError_t fus_bf16(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  const unsigned long long blocks = units >> G::HB;
+  if (blocks == 0) return hipSuccess;
+  if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+  if (blocks > kTwoSplit) return launch_kernel(k_fused_bf16_64k, dim3((unsigned)(blocks < kWalkers ? blocks : kWalkers)), dim3(512), s, pos, a);
+  const unsigned eights = (unsigned)(blocks + 7) / 8 * 8;
+  if (hipError_t e = blocks <= kFourSplit ? launch_kernel(k_fused_bf16_split_64k<1>, dim3(eights * 4), dim3(512), s, pos & LAUNCH_FIRST, a)
+                                  : launch_kernel(k_fused_bf16_split_64k<2>, dim3(eights * 2), dim3(512), s, pos & LAUNCH_FIRST, a))
+    return e;
+  return launch_kernel(k_decode_64k, dim3((unsigned)blocks), dim3(512), s, pos & LAUNCH_LAST, a);
+}
+hipError_t fusb_bf16(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  const unsigned long long blocks = units >> G::HB;
+  if (blocks == 0) return hipSuccess;
+  if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+  BatchArgs b = a;
+  for (int j = 0; j <= a.n; ++j) b.tile_start[j] >>= G::HB;
+  return launch_kernel(k_fused_bf16_batched_64k, dim3((unsigned)(blocks < kWalkers ? blocks : kWalkers)), dim3(512), s, pos, b);
+}
+#endif
 }  // namespace
 
 #if !defined(__HIP_DEVICE_COMPILE__)
@@ -253,10 +277,8 @@ extern const KernelTable OR_CAT(or_kernel_table_, OR_K) = {
     rdec_f32, rdec_bf16, fus_f32, fus_bf16,
 #if OR_K <= 14
     fusb_f32, fusb_bf16, rdecb_f32, rdecb_bf16, fdecb_f32, fdecb_bf16
-#elif OR_K == 15
-    nullptr, fusb_bf16, nullptr, nullptr, nullptr, nullptr
 #else
-    nullptr, nullptr, nullptr, nullptr, nullptr, nullptr
+    nullptr, fusb_bf16, nullptr, nullptr, nullptr, nullptr
 #endif
 };
 #endif

@@ -183,11 +183,10 @@ __global__ __launch_bounds__(256) void k_zero_u64n(unsigned long long* p, int n)
 
 // Sign bits of n_counters * 128 consecutive entries as a table: the Philox output for counter
 // first_counter + c, 16 bytes, at tab + 16 c -- so bit j of 64-bit word w is the sign of entry 64 w + j
-// counted from the first entry.  The fused kernels for blocks above 2^14 read it with scalar loads.
+// counted from the first entry.  The fp32 fused kernels for blocks above 2^14 read it with scalar loads.
 __global__ __launch_bounds__(256) void k_sign_table(uint4* __restrict__ tab, u64 seed, u64 first_counter,
-                                                    u64 n_counters, unsigned* __restrict__ flags, u64 n_flag_words) {
+                                                    u64 n_counters) {
   const u64 c = (u64)blockIdx.x * 256 + threadIdx.x;
-  if (c < n_flag_words) flags[c] = 0;   // the words of the pair hand-over of the bf16 kernel for 2^16 blocks
   if (c >= n_counters) return;
   const u64 ctr = first_counter + c;
   const ordev::u32x4 w =
@@ -452,28 +451,16 @@ or_status run_path(bool fused, const T* in, const uint32_t* masks, int N, u64 L,
   d.out = out; d.n = L; d.n_pad = L; d.seed = seed; d.base = base; d.k = k; d.scale = a.scale;
   d.in = ws_f32;
   d.unit0 = units;   // shards hold whole blocks: no tile of the decode needs bounds checks
-  if (fused && bf16 && k == 15) return finish(t->fused_bf16(a, units, s, first | last));   // a workgroup per block, no workspace
-  if (fused && bf16) {
-    // bf16: one kernel does everything.  Workspace: [hand-over slots of the workgroup pairs, 4 L bytes]
-    // [sign stream of the shard, L/8 bytes][pair flags, 8 bytes a block]
-    const u64 counters = L >> 7, nflags = 2 * (L >> 16);   // one thread per Philox counter
-    unsigned* flags = (unsigned*)(ws_cnt + (L / 8 + 255) / 256 * 256);
-    const u64 blocks = ((counters > nflags ? counters : nflags) + 255) / 256;
-    if (blocks > 0x7FFFFFFFull) return OR_ERR_SHAPE;
-    if (hipError_t e = orhost::launch_kernel(k_sign_table, dim3((unsigned)blocks), dim3(256), s, first, (uint4*)ws_cnt, seed,
-                                             base >> 7, counters, flags, nflags))
-      return finish(e);
-    a.sign_tab = (const u64*)ws_cnt;
+  if (fused && bf16) {   // one call does everything; 2^16 in launches of few blocks: the means go through the workspace
     a.mean_out = ws_f32;
-    a.count_in = (const uint8_t*)flags;
-    return finish(t->fused_bf16(a, units, s, last));
+    return finish(t->fused_bf16(a, units, s, first | last));
   }
   if (fused) {
     // the sign table takes the part of the workspace that the unfused path uses for counts (L/8 of its L bytes)
     const u64 counters = L >> 7;
     if ((counters + 255) / 256 > 0x7FFFFFFFull) return OR_ERR_SHAPE;
     if (hipError_t e = orhost::launch_kernel(k_sign_table, dim3((unsigned)((counters + 255) / 256)), dim3(256), s,
-                                             first, (uint4*)ws_cnt, seed, base >> 7, counters, (unsigned*)nullptr, (u64)0))
+                                             first, (uint4*)ws_cnt, seed, base >> 7, counters))
       return finish(e);
     a.sign_tab = (const u64*)ws_cnt;
     if (k == 15)   // two tiles per block: the fused kernel decodes as well
@@ -677,7 +664,9 @@ or_status path_batched_impl(bool fused, const or_bucket* buckets, int n, int N, 
   }
   if (!nonempty) return OR_OK;
   int seen = 0;
-  if (!f) {   // blocks above 2^14: one bucket after the other, sharing the workspace in stream order
+  // blocks above 2^14: one bucket after the other, sharing the workspace in stream order.  (A single bucket as if it came alone: few
+  // blocks of 2^16 are split over workgroups that meet in the workspace.)
+  if (!f || (fused && bf16 && k == 16 && nonempty == 1)) {
     for (int j = 0; j < n; ++j) {
       const or_bucket& q = buckets[j];
       if (q.shard_len == 0) continue;

@@ -23,7 +23,8 @@ def _workspace(b, L, k):
 @pytest.mark.parametrize("loss", [0.0, 0.02, 0.4])
 @pytest.mark.parametrize("k,N,blocks", [(11, 2, 3), (11, 3, 1), (11, 7, 257), (11, 8, 512), (11, 9, 513), (11, 17, 2), (12, 3, 256),
                                         (12, 4, 257), (12, 8, 1), (12, 9, 512), (12, 15, 513), (13, 3, 2), (13, 4, 256), (13, 5, 257),
-                                        (13, 255, 1), (14, 5, 3), (14, 6, 128), (14, 7, 129), (14, 33, 1), (15, 1, 2), (15, 6, 3)])
+                                        (13, 255, 1), (14, 5, 3), (14, 6, 128), (14, 7, 129), (14, 33, 1), (15, 1, 2), (15, 6, 3),
+                                        (16, 1, 1), (16, 3, 64), (16, 2, 65), (16, 2, 129), (16, 5, 3), (16, 2, 258), (16, 40, 1)])
 def test_forms_against_the_oracle(b, orc, k, N, blocks, loss):
     """First, middle and last block against the oracle, and the same bits and the arrival total from the batched call.  loss 0: the
     shortcuts for wavefronts and blocks that have everything; 0.4: hardly a run of 32 entries is whole."""
@@ -53,3 +54,33 @@ def test_forms_against_the_oracle(b, orc, k, N, blocks, loss):
     b.or_fused_path_batched_monitored(b.make_buckets([(x, md, again, cnt2, L, seed, base)]), 1, N, k, True, totals, ws)
     assert torch.equal(again.view(torch.uint8), out.view(torch.uint8)) and torch.equal(cnt2, cnt)
     assert totals.item() == cnt.long().sum().item()
+
+
+@pytest.mark.parametrize("k,N", [(15, 3), (16, 2), (16, 5)])
+def test_bits_do_not_depend_on_the_size_of_the_launch(b, k, N):
+    """A shard of blocks of 2^15 / 2^16 gives, bit for bit, what its beginning gives as a shard of its own or as a bucket among
+    others: numbers of blocks on both sides of every change of form, and two rounds of 256 workgroups."""
+    B, sizes = 1 << k, (1, 64, 65, 128, 129, 256, 300)
+    gen = torch.Generator(device=dev()).manual_seed(k + N)
+    x = torch.randn((N, sizes[-1] * B), device=dev(), generator=gen).mul_(1e-3).to(torch.bfloat16)
+    m = torch.where(torch.rand((N, sizes[-1] * B // 2048), device=dev(), generator=gen) < 0.002, 0, -1).to(torch.int32).repeat_interleave(64, 1)
+    seed = 0x55AA55AA12345678
+
+    def alone(L):
+        out, cnt = torch.full((L,), float("nan"), dtype=torch.bfloat16, device=dev()), torch.full((L,), 255, dtype=torch.uint8, device=dev())
+        b.or_fused_path_bf16(x[:, :L].contiguous(), m[:, :L // 32].contiguous(), N, L, k, seed, 0, out, cnt, _workspace(b, L, k))
+        return out.view(torch.uint8), cnt
+
+    want, count = alone(sizes[-1] * B)
+    for blocks in sizes[:-1]:
+        out, cnt = alone(blocks * B)
+        assert torch.equal(out, want[:out.numel()]) and torch.equal(cnt, count[:cnt.numel()]), blocks
+    L = 65 * B
+    xs, ms = x[:, :L].contiguous(), m[:, :L // 32].contiguous()
+    outs, cnts = torch.full((5, L), float("nan"), dtype=torch.bfloat16, device=dev()), torch.full((5, L), 255, dtype=torch.uint8, device=dev())
+    totals = torch.full((5,), -1, dtype=torch.int64, device=dev())
+    b.or_fused_path_batched_monitored(b.make_buckets([(xs, ms, outs[j], cnts[j], L, seed, 0) for j in range(5)]), 5, N, k, True, totals,
+                                      _workspace(b, L, k))
+    for j in range(5):
+        assert torch.equal(outs[j].view(torch.uint8), want[:2 * L]) and torch.equal(cnts[j], count[:L]), j
+        assert totals[j].item() == count[:L].long().sum().item(), j
