@@ -116,6 +116,37 @@ hipError_t sum_first(const PathArgs& a, unsigned long long units, hipStream_t s,
     return launch_kernel(k_fused<K, GROUPS, SPLIT>, dim3((unsigned)units), dim3(kFusedThreads<K> * kGroups), s, pos, a);
   return launch_kernel(k_fused<K, STREAM, SPLIT>, dim3((unsigned)units), dim3(kFusedThreads<K>), s, pos, a);
 }
+// k_fused_each_groups: how many groups of wavefronts encode workers side by side (1: none; the same bits)?  Launches that leave CUs idle,
+// where the shorter chain is worth the trip of the encoded values through LDS.  us, without -> with:
+//   bf16 2^10 and below: 2^10, N = 8, 64 tiles 12.9 -> 6.0, 1024 tiles 16.8 -> 13.3, 2048 tiles 18.8 -> 24.8; N = 32, 1024 tiles 54.9 ->
+//     34.2 with eight groups (sixteen: 44.6); 2^9, N = 16, 50 tiles 22.0 -> 7.5 with sixteen (eight: 8.3); N = 2, 1024 tiles 6.2 -> 6.2
+//   fp32 below 2^10 (two to five workers): N = 4, 1024 tiles 8.3 -> 6.2, 2048 tiles 10.0 -> 7.8; N = 5, 3000 tiles 12.5 -> 16.9
+//   fp32 2^11 (two to five): N = 4, 64 tiles 6.3 -> 5.5, 256 tiles 6.6 -> 5.8; N = 3 5.6 -> 5.5; N = 2 5.0 -> 5.2; N = 5, 300 tiles 8.2 -> 9.4
+//   fp32 2^12: N = 16, 100 tiles 19.4 -> 16.3, 200 tiles 19.5 -> 17.9; N = 32, 8 tiles 34.5 -> 26.3; N = 8, 128 tiles 11.4 -> 10.8, 256 tiles
+//     11.6 -> 12.2; N = 6, 100 tiles 9.4 -> 10.1
+//   fp32 2^13: N = 32, 2 tiles 41.6 -> 48.9; N = 8, 64 tiles 13.9 -> 16.6
+constexpr int kEachGroups = K == 0 ? 16 : K == 11 || K == 12 ? 4 : 1;
+[[maybe_unused]] int each_groups(unsigned long long tiles, int N) {
+  int most = 1;
+  if (K == 0) most = tiles <= 256 ? 16 : tiles <= 1024 ? 8 : 1;
+  if (K == 11 && (N == 3 || N == 4) && tiles <= 256) most = 4;
+  if (K == 12 && tiles <= (N >= 12 ? 200 : 128) && N >= 8) most = 4;
+  int g = 1;
+  while (g < most && g < N) g *= 2;
+  return g;
+}
+// the smallest number of groups that a class launches: no kernels that nothing reaches
+constexpr int kFewestGroups = K == 0 ? 2 : 4;
+template <class In, int GR>
+hipError_t launch_each_groups(int g, const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  if constexpr (GR > kFewestGroups) if (g < GR) return launch_each_groups<In, GR / 2>(g, a, units, s, pos);
+  return launch_kernel(k_fused_each_groups<K, In, GR>, dim3((unsigned)units), dim3(G::THREADS * GR), s, pos, a);
+}
+template <class In, int GR>
+hipError_t launch_each_groups(int g, const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  if constexpr (GR > kFewestGroups) if (g < GR) return launch_each_groups<In, GR / 2>(g, a, units, s, pos);
+  return launch_kernel(k_fused_each_groups_batched<K, In, GR>, dim3((unsigned)units), dim3(G::THREADS * GR), s, pos, a);
+}
 template <class In>
 hipError_t fused(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
   if (units == 0) return hipSuccess;
@@ -127,6 +158,9 @@ hipError_t fused(const PathArgs& a, unsigned long long units, hipStream_t s, int
       return sum_first<false>(a, units, s, pos);
     }
   }
+  constexpr int most = K == 0 && sizeof(In) == 4 ? 8 : kEachGroups;   // fp32 below 2^10: up to five workers
+  if constexpr (most > 1)
+    if (const int g = each_groups(units, a.N); g > 1) return launch_each_groups<In, most>(g, a, units, s, pos);
   if (prefetch_wins(units)) return launch_kernel(k_fused_each<K, In, true>, grid, dim3(G::THREADS), s, pos, a);
   if constexpr (G::W < 8) return launch_kernel(k_fused_each<K, In, false>, grid, dim3(G::THREADS), s, pos, a);
   return hipErrorInvalidValue;   // not reached
@@ -166,6 +200,9 @@ hipError_t fused_batched(const BatchArgs& a, unsigned long long units, hipStream
       return sum_first<false>(a, units, s, pos);
     }
   }
+  constexpr int most = K == 0 && sizeof(In) == 4 ? 8 : kEachGroups;   // fp32 below 2^10: up to five workers
+  if constexpr (most > 1)
+    if (const int g = each_groups(units, a.N); g > 1) return launch_each_groups<In, most>(g, a, units, s, pos);
   if (kEachSlots<K> > 1 && !a.totals) return launch_each<In, 1>(a, units, s, pos);
   return launch_each<In, kEachSlots<K>>(a, units, s, pos);
 }

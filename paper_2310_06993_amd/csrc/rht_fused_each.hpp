@@ -157,6 +157,193 @@ __device__ __forceinline__ void fused_each(const PathArgs& a, u64 first_unit, u6
   }
 }
 
+// For launches that leave CUs idle: G groups of W wavefronts encode G workers side by side.  The encoded values of a round go
+// through LDS, zero where they were lost, and group g adds those of its share of the registers over the workers, in order: the same
+// operations in the same order as above.  Group 0 decodes.  Bound by the chain of rounds: with four wavefronts a SIMD a round of 2^12
+// takes about 1.5 us of vector instructions and 1.6 us of LDS (figures at the rule, inst.hip).
+template <int K, class In, int G, bool TOTAL, bool FULL>
+__device__ __forceinline__ void fused_each_groups_tile(const PathArgs& a, u64 unit, int grp, int wave, float (*x)[Geo<K>::Q >= 1 ? tr_floats<K> : 1024],
+                                                       float (*y)[Geo<K>::Q >= 1 ? tr_floats<K> : 1], uint32_t* arrived, uint32_t* lossy) {
+  constexpr int T = Geo<K>::T, R = Geo<K>::R, W = Geo<K>::W, S = R / G;   // S: registers of a share
+  constexpr bool TRANSP = Geo<K>::Q >= 1;
+  static_assert(Geo<K>::PARTS == 1 && R == 16 && G >= 2 && G <= 16, "blocks of up to 2^14, a share is at least a register");
+  static_assert(FULL || W == 1, "only tiles of one wavefront are cut short");
+  const int lane = lane_id(), kt = tile_bits<K>(a.k), N = a.N;
+  const u64 L = a.n_pad, e0 = unit * T, mrow = L >> 5;
+  const float sigma = TRANSP ? tr_sigma(lane) : lane_sigma(lane, kt < 6 ? kt : 6);
+  const bool scale_first = sizeof(In) == 2 && (a.k & 1);
+  const int moff = mask_word_offset<K>(wave, lane);
+  [[maybe_unused]] const int left = FULL ? T : (int)(L - e0);
+  auto request = [&](int i, float (&v)[R], uint32_t& words) {   // past the last worker: the last one again, not used
+    const int w = i < N ? i : N - 1;
+    const In* p = (const In*)a.in + (u64)w * L;
+    if constexpr (FULL) {
+      load_tile<K, false, true, true>(p, e0, L, wave, lane, v);
+    } else {   // past the end: the last entry again, as a zero
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int e = r * 64 + lane;
+        const float t = to_f32(load_one<true>(&p[e0 + (e < left ? e : left - 1)]));
+        v[r] = e < left ? t : 0.0f;
+      }
+    }
+    words = load_mask_words<K, FULL>(a.masks + (u64)w * mrow, e0, L, moff);
+  };
+  float va[R];
+  uint32_t ma;
+  request(grp, va, ma);
+  u64 sg[R];
+  sign_masks(a.seed, a.base + e0 + (u64)wave * Geo<K>::WAVE_ENTRIES, sg);
+  float acc[S];
+#pragma unroll
+  for (int r = 0; r < S; ++r) acc[r] = 0.0f;
+  constexpr int V = S < 4 ? S : 4;   // values of one access to LDS
+  typedef float values_t __attribute__((ext_vector_type(V)));
+  for (int first = 0; first < N; first += G) {
+    const bool works = first + grp < N;
+    float v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = va[r];
+    const uint32_t words = ma;
+    if (first + G < N) request(first + grp + G, va, ma);
+    apply_signs(v, sg);
+    // (a group without a worker goes through the transform for the sake of its barrier)
+    if constexpr (TRANSP) transform_transposed<K>(v, x[grp], y[grp], wave, lane);
+    else transform<K, true>(v, x[grp], wave, lane, kt);
+    if (works) {
+      if constexpr (sizeof(In) == 2) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = round_to<In>(scale_first ? v[r] * a.scale : v[r]);
+      }
+      if (!all_arrived(words)) {
+        if (lane == 0) *lossy = 1;
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = in_mask(mask_of_reg(words, r)) ? v[r] : 0.0f;
+      }
+      float* to = x[grp] + wave * 1024 + lane * V;   // by access; behind this wavefront's reads of its part of x
+      if constexpr (TRANSP) to = x[grp] + wave * tr_wave<K> + lane * V;
+#pragma unroll
+      for (int j = 0; j < R / V; ++j) {
+        values_t t;
+#pragma unroll
+        for (int d = 0; d < V; ++d) t[d] = v[j * V + d];
+        *(values_t*)(to + j * 64 * V) = t;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (first + g < N) {
+        const float* from = x[g] + wave * (TRANSP ? tr_wave<K> : 1024) + grp * (64 * S) + lane * V;
+#pragma unroll
+        for (int j = 0; j < S / V; ++j) {
+          const values_t t = *(const values_t*)(from + j * 64 * V);
+#pragma unroll
+          for (int d = 0; d < V; ++d) acc[j * V + d] += t[d];
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // ---- counts and mean over what arrived.  The last round ended in a barrier behind which everyone sees `lossy`
+  float* flat = x[0];
+  float* means = flat + G * W * 256;          // by wavefront, register, lane (layout B)
+  static_assert(G * T / 4 + T <= G * (TRANSP ? tr_floats<K> : 1024), "counts and means fit");
+  const float post = sigma * (scale_first ? 1.0f : a.scale);
+  // received bits of 16 entries: half of word lane >> 1 of the wavefront's 32 words, i.e. register lane >> 2, lanes 16 (lane & 3) ..
+  uint32_t c4[4];
+  const uint32_t all = (uint32_t)N * 0x01010101u;
+  const bool inside = FULL || lane * 16 < left;
+  if (*(volatile uint32_t*)lossy == 0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) c4[q] = inside ? all : 0;
+    const float f = post * __builtin_amdgcn_rcpf((float)N);
+#pragma unroll
+    for (int r = 0; r < S; ++r) means[(wave * R + grp * S + r) * 64 + lane] = acc[r] * f;
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) c4[q] = 0;
+    const int off = off_b<K>(wave, lane >> 2) + (lane & 3) * 16;
+    for (int i = grp; i < N; i += G) {
+      const uint32_t bits = inside ? ((const uint16_t*)(a.masks + (u64)i * mrow + (e0 >> 5)))[off >> 4] : 0u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) c4[q] += (((bits >> (4 * q)) & 0xFu) * 0x00204081u) & 0x01010101u;
+    }
+    *(uint4*)(flat + ((grp * W + wave) * 64 + lane) * 4) = make_uint4(c4[0], c4[1], c4[2], c4[3]);
+    __syncthreads();
+    // every wavefront adds up the counts of its part over the groups; group 0 keeps what it stores
+    const uint8_t* bytes = (const uint8_t*)flat + wave * 1024;
+#pragma unroll
+    for (int r = 0; r < S; ++r) {
+      uint32_t n = 0;
+#pragma unroll
+      for (int g = 0; g < G; ++g) n += bytes[g * W * 1024 + (grp * S + r) * 64 + lane];
+      means[(wave * R + grp * S + r) * 64 + lane] = n ? acc[r] * (post * __builtin_amdgcn_rcpf((float)n)) : 0.0f;
+    }
+    if (grp == 0) {
+#pragma unroll
+      for (int g = 1; g < G; ++g) {
+        const uint4 o = *(const uint4*)(flat + ((g * W + wave) * 64 + lane) * 4);
+        c4[0] += o.x; c4[1] += o.y; c4[2] += o.z; c4[3] += o.w;
+      }
+    }
+  }
+  if (grp == 0 && a.count_out) {
+    const int off = off_b<K>(wave, lane >> 2) + (lane & 3) * 16;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.count_out + e0), 0, left, 0x00020000);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) store_counts4(c4[q], rs, off + q * 4, 0, ((uintptr_t)a.count_out & 3) == 0);
+  }
+  if (TOTAL && grp == 0 && a.total_out) {   // Sec. 3.4 loss monitoring: gathered in LDS, one atomic per workgroup
+    uint32_t n = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) n = __builtin_amdgcn_sad_u8(c4[q], 0u, n);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) n += (uint32_t)__shfl_xor((int)n, o, 64);
+    if (lane == 0) atomicAdd(arrived, n);
+  }
+  __syncthreads();
+  if (TOTAL && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)*arrived);
+  if (grp > 0) return;   // (a barrier waits for the wavefronts that are left)
+  float v[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) v[r] = means[(wave * R + r) * 64 + lane];
+  __syncthreads();
+  if constexpr (TRANSP) transform_transposed<K>(v, x[0], y[0], wave, lane);
+  else transform<K, false>(v, x[0], wave, lane, kt);
+  const float c = a.scale * sigma;
+#pragma unroll
+  for (int r = 0; r < R; ++r) v[r] *= c;
+  apply_signs(v, sg);
+  store_tile<K, false, FULL, true>((In*)a.out, e0, L, wave, lane, v);
+}
+template <int K, class In, int G, bool TOTAL>
+__device__ __forceinline__ void fused_each_groups(const PathArgs& a, u64 unit) {
+  constexpr int W = Geo<K>::W;
+  __shared__ __align__(16) float x[G][Geo<K>::Q >= 1 ? tr_floats<K> : 1024];
+  __shared__ __align__(16) float y[G][Geo<K>::Q >= 1 ? tr_floats<K> : 1];
+  __shared__ uint32_t arrived, lossy;
+  const int grp = wave_id() / W, wave = wave_id() % W;
+  if (threadIdx.x == 0) arrived = lossy = 0;
+  __syncthreads();
+  if constexpr (kShardTilesFull<K>) {
+    fused_each_groups_tile<K, In, G, TOTAL, true>(a, unit, grp, wave, x, y, &arrived, &lossy);
+  } else {
+    if ((unit + 1) * Geo<K>::T <= a.n_pad) fused_each_groups_tile<K, In, G, TOTAL, true>(a, unit, grp, wave, x, y, &arrived, &lossy);
+    else fused_each_groups_tile<K, In, G, TOTAL, false>(a, unit, grp, wave, x, y, &arrived, &lossy);
+  }
+}
+template <int K, class In, int G>
+__global__ __launch_bounds__(Geo<K>::THREADS * G) void k_fused_each_groups(PathArgs a) {
+  fused_each_groups<K, In, G, false>(a, blockIdx.x);
+}
+template <int K, class In, int G>
+__global__ __launch_bounds__(Geo<K>::THREADS * G) void k_fused_each_groups_batched(BatchArgs ba) {
+  PathArgs a;
+  const u64 unit = bucket_of(ba, a, blockIdx.x);
+  fused_each_groups<K, In, G, true>(a, unit);
+}
+
 template <int K, class In, bool PREFETCH>
 __global__ __launch_bounds__(Geo<K>::THREADS) __attribute__((amdgpu_waves_per_eu(1)))
 void k_fused_each(PathArgs a) {

@@ -1,4 +1,4 @@
-"""The bf16 fused path above 2^10 at the edges of its forms: numbers of workers around the groups that encode side by side, numbers
+"""The fused path at the edges of the forms for launches of few blocks, and bf16 above 2^10: numbers of workers around the groups that encode side by side, numbers
 of blocks around the rules that choose them, with and without losses."""
 import numpy as np
 import pytest
@@ -84,3 +84,37 @@ def test_bits_do_not_depend_on_the_size_of_the_launch(b, k, N):
     for j in range(5):
         assert torch.equal(outs[j].view(torch.uint8), want[:2 * L]) and torch.equal(cnts[j], count[:L]), j
         assert totals[j].item() == count[:L].long().sum().item(), j
+
+
+@pytest.mark.parametrize("kind,k,N,L", [("bf16", 10, 2, 1024), ("bf16", 10, 9, 257 << 10), ("bf16", 10, 16, 256 << 10), ("bf16", 10, 33, 1024 << 10),
+                                        ("bf16", 10, 3, 1025 << 10), ("bf16", 9, 17, 50 * 512 + 512), ("bf16", 5, 5, 32), ("bf16", 6, 8, 3 * 1024 + 64),
+                                        ("bf16", 7, 255, 1024 + 128), ("f32", 9, 5, 2047 * 512), ("f32", 5, 3, 7 * 1024 + 32), ("f32", 8, 2, 256),
+                                        ("f32", 11, 3, 256 << 11), ("f32", 11, 4, 257 << 11), ("f32", 12, 8, 128 << 12), ("f32", 12, 13, 200 << 12),
+                                        ("f32", 12, 9, 1 << 12), ("f32", 12, 255, 2 << 12)])
+@pytest.mark.parametrize("loss", [0.0, 0.3])
+def test_side_by_side_groups_against_the_oracle(b, orc, kind, k, N, L, loss):
+    """The same for the groups of the stage-by-stage form: whole tiles and tiles cut short, counts at an odd address."""
+    f32, B = kind == "f32", max(1 << k, 1024)
+    rng = np.random.default_rng(k * 1000 + N + L)
+    gen = torch.Generator(device=dev()).manual_seed(k + N)
+    x = torch.randn((N, L), device=dev(), generator=gen).mul_(1e-3).to(torch.float32 if f32 else torch.bfloat16)
+    words = np.full((N, L // 32), 0xFFFFFFFF, dtype=np.uint32)
+    if loss:
+        hit = rng.random(words.shape) < loss
+        words[hit] &= ~(np.uint32(1) << rng.integers(0, 32, int(hit.sum()), dtype=np.uint32))
+        words[:, -1] &= np.uint32(0x7FFFFFFF)        # the last entry of all is nobody's
+    md, seed, base = masks_to_dev(words), 0x0FEDCBA987654321, (1 << 33) + 4 * B
+    out, room = torch.full_like(x[0], float("nan")), torch.full((L + 5,), 255, dtype=torch.uint8, device=dev())
+    cnt = room[5:]
+    (b.or_fused_path if f32 else b.or_fused_path_bf16)(x, md, N, L, k, seed, base, out, cnt, None)
+    for lo in {0, L // 2 // B * B, (L - 1) // B * B}:
+        part = slice(lo, min(lo + B, L))
+        want, wcnt = orc.fused_path(to_np(x[:, part].contiguous()), np.ascontiguousarray(words[:, part.start // 32:part.stop // 32]), k,
+                                    seed, base + lo)
+        assert np.array_equal(to_np(cnt[part]), wcnt), lo
+        assert rel_l2(to_np(out[part]), want) <= TOL[kind], lo
+    again, cnt2 = torch.full_like(out, float("nan")), torch.full((L,), 255, dtype=torch.uint8, device=dev())
+    totals = torch.full((1,), -1, dtype=torch.int64, device=dev())
+    b.or_fused_path_batched_monitored(b.make_buckets([(x, md, again, cnt2, L, seed, base)]), 1, N, k, not f32, totals, None)
+    assert torch.equal(again.view(torch.uint8), out.view(torch.uint8)) and torch.equal(cnt2, cnt)
+    assert totals.item() == cnt2.long().sum().item()
