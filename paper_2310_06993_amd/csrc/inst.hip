@@ -7,6 +7,7 @@
 #endif
 #if OR_K > 14
 #include "rht_encode_block.hpp"
+#include "rht_fused_f32_block.hpp"
 #if OR_K == 16
 #include "rht_fused_bf16_64k.hpp"
 #endif
@@ -213,18 +214,34 @@ constexpr launch_fn fus_bf16 = fused<bf16_t>;
 constexpr batch_fn fusb_bf16 = fused_batched<bf16_t>;
 #endif
 #else
-// one workgroup per pair of output tiles; `units` = output tiles of the shard
-#define OR_PAIR_LAUNCHER(name, kernel)                                                       \
-  hipError_t name(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {    \
-    if (units == 0) return hipSuccess;                                                       \
-    const unsigned long long blocks = units >> G::HB, per = G::PARTS / 2;                    \
-    unsigned long long grid = per == 1 ? blocks : (blocks + 7) / 8 * 8 * per;                \
-    if (grid > 0x7FFFFFFFull) return hipErrorInvalidValue;                                   \
-    return launch_kernel(kernel, dim3((unsigned)grid), dim3(G::THREADS), s, pos, a);         \
-  }
 OR_BLOCK_LAUNCHER(rdec_f32, (k_reduce_decode_block<K, float>))
 OR_BLOCK_LAUNCHER(rdec_bf16, (k_reduce_decode_block<K, bf16_t>))
-OR_PAIR_LAUNCHER(fus_f32, (k_fused_pairs<K, float>))
+// fp32: 2^15 values a workgroup.  2^16: then the means are decoded where they are
+unsigned long long half_grid(unsigned long long blocks) { return K == 15 ? blocks : (blocks + 7) / 8 * 8 * 2; }
+hipError_t fus_f32(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  const unsigned long long blocks = units >> G::HB;
+  if (blocks == 0) return hipSuccess;
+  if (half_grid(blocks) > 0x7FFFFFFFull) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)half_grid(blocks));
+  if (K == 15) return launch_kernel(k_fused_f32_half<K>, grid, dim3(1024), s, pos, a);
+  if (hipError_t e = launch_kernel(k_fused_f32_half<K>, grid, dim3(1024), s, pos & LAUNCH_FIRST, a)) return e;
+  PathArgs d = a;
+  d.in = a.out;
+  d.unit0 = units;   // shards hold whole blocks
+  return dec_f32(d, units, s, pos & LAUNCH_LAST);
+}
+hipError_t fusb_f32(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  const unsigned long long blocks = units >> G::HB;
+  if (blocks == 0) return hipSuccess;
+  if (half_grid(blocks) > 0x7FFFFFFFull) return hipErrorInvalidValue;
+  BatchArgs b = a;
+  for (int j = 0; j <= a.n; ++j) b.tile_start[j] >>= G::HB;
+  const dim3 grid((unsigned)half_grid(blocks));
+  if (K == 15) return launch_kernel(k_fused_f32_half_batched<K>, grid, dim3(1024), s, pos, b);
+  if (hipError_t e = launch_kernel(k_fused_f32_half_batched<K>, grid, dim3(1024), s, pos & LAUNCH_FIRST, b)) return e;
+  if constexpr (K == 16) return launch_kernel(k_decode_block_batched<K>, dim3((unsigned)blocks), dim3(G::THREADS), s, pos & LAUNCH_LAST, b);
+  return hipErrorInvalidValue;   // not reached
+}
 #endif
 #if OR_K >= 11 && OR_K <= 15
 // a workgroup per block; `units` and tile_start of the call count tiles (of at most 2^14)
@@ -315,7 +332,7 @@ extern const KernelTable OR_CAT(or_kernel_table_, OR_K) = {
 #if OR_K <= 14
     fusb_f32, fusb_bf16, rdecb_f32, rdecb_bf16, fdecb_f32, fdecb_bf16
 #else
-    nullptr, fusb_bf16, nullptr, nullptr, nullptr, nullptr
+    fusb_f32, fusb_bf16, nullptr, nullptr, nullptr, nullptr
 #endif
 };
 #endif

@@ -8,9 +8,6 @@
 #ifndef OR_NT_RDEC
 #define OR_NT_RDEC true
 #endif
-#ifndef OR_NT_PAIRS
-#define OR_NT_PAIRS true
-#endif
 #ifndef OR_NT_ENC
 #define OR_NT_ENC true
 #endif
@@ -32,8 +29,7 @@ struct PathArgs {
   const uint32_t* masks;   // [N][L/32]
   void* out;               // result vector
   uint8_t* count_out;      // may be null
-  float* mean_out;         // fused without decode: mean in the encoded domain, fp32
-  const u64* sign_tab;     // fused, blocks above 2^14: sign bits of the shard's entries, 64 per word (see k_fused_pairs)
+  float* mean_out;         // fused bf16 in blocks of 2^16, launches of few blocks: the means on their way to the decode
   unsigned long long* total_out;   // may be null: receives the number of (worker, entry) arrivals (Sec. 3.4 loss monitoring)
   u64 n;                   // valid entries of the input (encode) / output (decode)
   u64 n_pad;               // padded length = vector length on the encoded side; shard_len for reduce/fused
@@ -47,9 +43,6 @@ struct PathArgs {
 
 // In the shard kernels a tile can be cut short only when blocks are smaller than a tile (class 0).
 template <int K> constexpr bool kShardTilesFull = (K != 0);
-
-// +1/-1 entry of H_{2^HB}: row `part`, column q
-__device__ __forceinline__ float part_coef(int part, int q) { return (__builtin_popcount(part & q) & 1) ? -1.0f : 1.0f; }
 
 template <int K>
 __device__ __forceinline__ int tile_bits(int k) { return K ? Geo<K>::KT : k; }
@@ -210,10 +203,10 @@ __global__ __launch_bounds__(Geo<K>::THREADS) void k_decode(PathArgs a) {
 // The same for blocks above 2^14 (see k_encode_block).  The input holds whole blocks; FULL = false: the
 // output is cut short inside this block.
 template <int K, class Out, bool FINALIZE, bool FULL, bool MASKED>
-__device__ __forceinline__ void decode_block(const PathArgs& a, float (*xbuf)[Geo<K>::T]) {
+__device__ __forceinline__ void decode_block(const PathArgs& a, u64 blk, float (*xbuf)[Geo<K>::T]) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R, HB = Geo<K>::HB, PARTS = Geo<K>::PARTS;
   const int wave = wave_id(), lane = lane_id(), kt = Geo<K>::KT;
-  const u64 tile0 = (u64)blockIdx.x << HB;
+  const u64 tile0 = blk << HB;
   float v[PARTS][R];
 #pragma unroll
   for (int q = 0; q < PARTS; ++q) load_mean_tile<K, FINALIZE, true, MASKED>(a, tile0 + q, wave, lane, v[q]);
@@ -234,8 +227,8 @@ template <int K, class Out, bool FINALIZE, bool MASKED>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_decode_block(PathArgs a) {
   static_assert(Geo<K>::PARTS > 1, "blocks above 2^14");
   __shared__ float xbuf[2][Geo<K>::T];
-  if ((u64)blockIdx.x << Geo<K>::HB < a.unit0) decode_block<K, Out, FINALIZE, true, MASKED>(a, xbuf);
-  else decode_block<K, Out, FINALIZE, false, MASKED>(a, xbuf);
+  if ((u64)blockIdx.x << Geo<K>::HB < a.unit0) decode_block<K, Out, FINALIZE, true, MASKED>(a, blockIdx.x, xbuf);
+  else decode_block<K, Out, FINALIZE, false, MASKED>(a, blockIdx.x, xbuf);
 }
 
 // acc += value where the worker's copy arrived.  Arrivals are counted as `full` (workers whose whole
@@ -371,146 +364,6 @@ __device__ __forceinline__ void reduce_decode_tile(const PathArgs& a, u64 unit) 
 template <int K, class Wire, class Out>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_reduce_decode(PathArgs a) {
   reduce_decode_tile<K, Wire, Out>(a, blockIdx.x);
-}
-
-// ---------------------------------------------------------------------------------------------------
-// The fused path for blocks of 2^15 / 2^16 entries (PARTS = 2 / 4 tiles per block).  A workgroup produces
-// TWO output tiles of its block, p_lo = h and p_hi = h + PARTS/2, from one reading of the block's input
-// tiles: with u_q the signed input tiles and H_{2P} = [[H_P, H_P], [H_P, -H_P]],
-//     A = sum_{q <  P/2} H[h][q] u_q,   C = sum_{q >= P/2} H[h][q - P/2] u_q,   p_lo = A + C,  p_hi = A - C,
-// so the +-1 combination costs half the sign flips and adds per output of the one-tile-per-workgroup
-// form, and the inputs are read PARTS/2 times instead of PARTS times.  With four tiles per block it stops at
-// the fp32 mean (layout B) in `mean_out` and k_decode_block finishes; with two it decodes its block itself.
-template <int K, class In>
-__global__ __launch_bounds__(Geo<K>::THREADS) void k_fused_pairs(PathArgs a) {
-  constexpr int T = Geo<K>::T, R = Geo<K>::R, HB = Geo<K>::HB, PARTS = Geo<K>::PARTS, HP = PARTS / 2;
-  static_assert(PARTS == 2 || PARTS == 4, "two or four tiles per block");
-  // bound by the vector ALUs: the transform with lane bits 2..5 turned into register bits (rht_tile.hpp)
-  __shared__ float tbuf[2][tr_floats<K>];   // alternate between the two roles: one barrier per transform
-  int flip = 0;
-  const int wave = wave_id(), lane = lane_id();
-  const u64 L = a.n_pad, nblocks = L >> K;
-  // workgroup -> (block, h); the HP workgroups of a block sit on one XCD, next to each other
-  u64 blk;
-  int h;
-  if constexpr (HP == 1) {
-    blk = blockIdx.x;
-    h = 0;
-  } else {
-    const u64 x = blockIdx.x, slot = x >> 3;
-    h = (int)(slot & (HP - 1));
-    blk = ((slot / HP) << 3) + (x & 7);
-  }
-  if (blk >= nblocks) return;
-  const u64 t0 = blk << HB;                      // first tile of the block
-  const u64 e_lo = (t0 + h) * T, e_hi = (t0 + h + HP) * T;
-  const In* grads = (const In*)a.in;
-  const float sigma = tr_sigma(lane);
-  const bool scale_first = sizeof(In) == 2 && (a.k & 1);
-  const int moff = mask_word_offset<K>(wave, lane);
-  const u64 mrow = L >> 5;
-
-  float acc_lo[R], acc_hi[R];
-  uint32_t cnt_lo[R / 4], cnt_hi[R / 4];
-  int full_lo = 0, full_hi = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) acc_lo[r] = acc_hi[r] = 0.0f;
-#pragma unroll
-  for (int r = 0; r < R / 4; ++r) cnt_lo[r] = cnt_hi[r] = 0;
-
-  // dst (+)= coef * (signed t), t = input tile q.  The sign bits come from a table that a small kernel
-  // wrote before this one (a.sign_tab: bit j of word w = entry 64w + j of the shard): the R words of this
-  // wavefront's registers are scalar loads that land in scalar register pairs and serve as lane masks as
-  // they are.  Forming them from Philox words held in a vector register instead costs two v_readlane per
-  // register and worker -- measured, a fifth of this kernel's vector-ALU time.
-  typedef const u64 __attribute__((address_space(4))) * table_ptr;
-  auto add_signed = [&](float (&dst)[R], const float (&t)[R], int q, float coef, bool first) {
-    table_ptr sg = (table_ptr)(a.sign_tab + ((((t0 + q) * T) + (u64)wave * Geo<K>::WAVE_ENTRIES) >> 6));
-    asm volatile("" : "+s"(sg));   // the words of a tile are loaded where the tile is used, not hoisted
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float ts = in_mask(sg[r]) ? -t[r] : t[r];
-      dst[r] = first ? coef * ts : __builtin_fmaf(coef, ts, dst[r]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  auto finish_tile = [&](float (&v)[R], uint32_t m, float (&acc)[R], uint32_t (&cnt)[R / 4], int& full) {
-    transform_transposed<K>(v, tbuf[flip], tbuf[flip ^ 1], wave, lane);
-    flip ^= 1;
-    if (sizeof(In) == 2) {
-      if (scale_first) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = round_to<In>(v[r] * a.scale);
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = round_to<In>(v[r]);
-      }
-    }
-    masked_accumulate(v, m, acc, cnt, full);
-  };
-
-  for (int i = 0; i < a.N; ++i) {
-    const In* x = grads + (u64)i * L;
-    float A[R], C[R], t[R], w[R];
-    // up to three tiles in flight: u_0 -> A, u_1 -> t (four-tile blocks), u_HP -> C
-    load_tile<K, false, true, OR_NT_PAIRS>(x, t0 * T, L, wave, lane, A);
-    if constexpr (HP == 2) load_tile<K, false, true, OR_NT_PAIRS>(x, (t0 + 1) * T, L, wave, lane, t);
-    load_tile<K, false, true, OR_NT_PAIRS>(x, (t0 + HP) * T, L, wave, lane, C);
-    const uint32_t m_lo = load_mask_words<K, true>(a.masks + (u64)i * mrow, e_lo, L, moff);
-    const uint32_t m_hi = load_mask_words<K, true>(a.masks + (u64)i * mrow, e_hi, L, moff);
-    add_signed(A, A, 0, 1.0f, true);
-    if constexpr (HP == 2) {
-      add_signed(A, t, 1, part_coef(h, 1), false);
-      load_tile<K, false, true, OR_NT_PAIRS>(x, (t0 + HP + 1) * T, L, wave, lane, t);
-    }
-    add_signed(C, C, HP, 1.0f, true);
-    if constexpr (HP == 2) add_signed(C, t, HP + 1, part_coef(h, 1), false);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      w[r] = A[r] + C[r];
-      C[r] = A[r] - C[r];
-    }
-    finish_tile(w, m_lo, acc_lo, cnt_lo, full_lo);
-    finish_tile(C, m_hi, acc_hi, cnt_hi, full_hi);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  const float post = sigma * (scale_first ? 1.0f : a.scale);
-  if (a.total_out) {
-    add_arrivals<R>(a.total_out, cnt_lo, full_lo);
-    add_arrivals<R>(a.total_out, cnt_hi, full_hi);
-  }
-  store_counts<K, true>(a.count_out, e_lo, L, wave, lane, cnt_lo, full_lo);
-  finalize_mean(acc_lo, cnt_lo, full_lo, post);
-  if constexpr (HP == 2) store_tile<K, true, true>(a.mean_out, e_lo, L, wave, lane, acc_lo);
-  store_counts<K, true>(a.count_out, e_hi, L, wave, lane, cnt_hi, full_hi);
-  finalize_mean(acc_hi, cnt_hi, full_hi, post);
-  if constexpr (HP == 2) {
-    store_tile<K, true, true>(a.mean_out, e_hi, L, wave, lane, acc_hi);
-  } else {
-    // Two tiles per block: this workgroup holds the whole mean of its block and decodes it here (no trip of
-    // the mean through memory, no decode launch): the factor across the two tiles, the transform of each
-    // (layout B to layout A), scale, signs from the table (whose words are in layout-A order).
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float s = acc_lo[r] + acc_hi[r];
-      acc_hi[r] = acc_lo[r] - acc_hi[r];
-      acc_lo[r] = s;
-    }
-    const float c = a.scale * sigma;
-    auto decode_tile = [&](float (&v)[R], int q) {
-      transform_transposed<K>(v, tbuf[flip], tbuf[flip ^ 1], wave, lane);
-      flip ^= 1;
-      table_ptr sg = (table_ptr)(a.sign_tab + ((((t0 + q) * T) + (u64)wave * Geo<K>::WAVE_ENTRIES) >> 6));
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const float x = v[r] * c;
-        v[r] = in_mask(sg[r]) ? -x : x;
-      }
-      store_tile<K, false, true, true>((In*)a.out, (t0 + q) * T, L, wave, lane, v);
-    };
-    decode_tile(acc_lo, 0);
-    decode_tile(acc_hi, 1);
-  }
 }
 
 // Several buckets of one launch shape class (same N, block size and type) in ONE launch: small buckets

@@ -56,6 +56,38 @@ def test_forms_against_the_oracle(b, orc, k, N, blocks, loss):
     assert totals.item() == cnt.long().sum().item()
 
 
+@pytest.mark.parametrize("loss", [0.0, 0.01, 0.4])
+@pytest.mark.parametrize("k,N,blocks", [(15, 1, 1), (15, 2, 9), (15, 9, 3), (15, 33, 2), (16, 1, 1), (16, 2, 9), (16, 9, 3), (16, 64, 1), (16, 255, 1)])
+def test_fp32_large_blocks_against_the_oracle(b, orc, k, N, blocks, loss):
+    """fp32 blocks of 2^15 / 2^16, whose whole workers are summed before the encode: none, some and all of the copies whole."""
+    B, L = 1 << k, blocks << k
+    rng = np.random.default_rng(100 * k + N + blocks)
+    gen = torch.Generator(device=dev()).manual_seed(k + N)
+    x = torch.randn((N, L), device=dev(), generator=gen).mul_(1e-3)
+    words = np.full((N, L // 32), 0xFFFFFFFF, dtype=np.uint32)
+    if loss > 0.1:
+        words &= ~(np.uint32(1) << rng.integers(0, 32, words.shape, dtype=np.uint32))
+        words[:, -1] &= np.uint32(0x7FFFFFFF)        # the last entry of all is nobody's
+    elif loss:
+        words[rng.random(N) < 0.5, rng.integers(0, L // 32)] = 0x12345678
+    md, seed, base = masks_to_dev(words), 0x0FEDCBA987654321, (1 << 33) + 4 * B
+    out, room = torch.full((L,), float("nan"), device=dev()), torch.full((L + 3,), 255, dtype=torch.uint8, device=dev())
+    cnt, ws = room[3:], _workspace(b, L, k)
+    b.or_fused_path(x, md, N, L, k, seed, base, out, cnt, ws)
+    for j in {0, blocks // 2, blocks - 1}:
+        part = slice(j * B, (j + 1) * B)
+        want, wcnt = orc.fused_path(to_np(x[:, part].contiguous()), np.ascontiguousarray(words[:, j * B // 32:(j + 1) * B // 32]), k,
+                                    seed, base + j * B)
+        assert np.array_equal(to_np(cnt[part]), wcnt), j
+        assert rel_l2(to_np(out[part]), want) <= TOL["f32"], j
+    again, cnt2 = torch.full((2, L), float("nan"), device=dev()), torch.full((2, L), 255, dtype=torch.uint8, device=dev())
+    totals = torch.full((2,), -1, dtype=torch.int64, device=dev())
+    b.or_fused_path_batched_monitored(b.make_buckets([(x, md, again[j], cnt2[j], L, seed, base) for j in range(2)]), 2, N, k, False, totals, ws)
+    for j in range(2):
+        assert torch.equal(again[j].view(torch.uint8), out.view(torch.uint8)) and torch.equal(cnt2[j], cnt), j
+        assert totals[j].item() == cnt2[j].long().sum().item(), j
+
+
 @pytest.mark.parametrize("k,N", [(15, 3), (16, 2), (16, 5)])
 def test_bits_do_not_depend_on_the_size_of_the_launch(b, k, N):
     """A shard of blocks of 2^15 / 2^16 gives, bit for bit, what its beginning gives as a shard of its own or as a bucket among
