@@ -246,7 +246,7 @@ enum FusedMode { STREAM, GROUPS };
 constexpr int kGroups = 4;
 
 // SLOTS > 1 (tiles of one wavefront): the workgroup's wavefronts serve SLOTS tiles, for the sake of the arrival totals: one
-// atomic per workgroup.  (Atomics on one 128-byte line take 14 ns each: 32 thousand tiles of a batch spent 300 us on them.)
+// atomic per workgroup (add_total).
 // SPLIT: blocks below 2^10, several to a tile.
 template <int K, int MODE, bool SPLIT, int SLOTS = 1>
 __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u64 units) {
@@ -263,12 +263,12 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   __shared__ uint32_t marks_all[SLOTS][8];
   __shared__ uint8_t order_all[SLOTS][MODE == STREAM ? 1 : 256];
   __shared__ uint2 missing16[MODE == GROUPS && SPLIT ? 256 : 1];   // per worker with a loss: the runs of 16 entries that miss something
-  __shared__ uint32_t arrived[2];   // arrivals of the workgroup's tiles; how many of its wavefronts have added theirs
+  __shared__ uint32_t missing[2];   // what the workgroup's tiles miss; how many of its wavefronts have added theirs
   const int wave_all = wave_id(), lane = lane_id();
   const int slot = SLOTS > 1 ? wave_all : 0;
   const int grp = G == 1 ? 0 : wave_all / W, wave = SLOTS > 1 ? 0 : G == 1 ? wave_all : wave_all % W;
   if constexpr (SLOTS > 1) {
-    if (threadIdx.x < 2) arrived[threadIdx.x] = 0;
+    if (threadIdx.x < 2) missing[threadIdx.x] = 0;
     __syncthreads();   // the only one: from here on every wavefront is on its own
   }
   const u64 unit = first_unit + slot;
@@ -283,7 +283,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   const u64 row_bytes = L >> 3;
   float* x = xbuf[SLOTS > 1 ? slot : grp];
   if (SLOTS > 1 ? lane < 8 : threadIdx.x < 8) marks[lane & 7] = 0;
-  if (SLOTS == 1 && threadIdx.x == 0) arrived[0] = 0;
+  if (SLOTS == 1 && threadIdx.x == 0) missing[0] = 0;
 
   // ---- loads; no such worker (i < 0 or >= N): zeros, without touching memory.  The whole offset is in the vector operand, which the
   // range check covers by any reading of it: what lies past a tile that is cut short (K = 0) is not read
@@ -344,6 +344,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   };
   const uint32_t sg = lane_signs<K, In>(a.seed, a.base + ew, x, wave, lane);
   tile_barrier<G * W>();
+  bool lossy_here = false;   // a worker of the group lost something in the wavefront's part
   {
     const bool inside = K || lane * 16 < left;
     int full = 0;   // workers that lost nothing in the wavefront's part
@@ -356,9 +357,10 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
       for (int u = 0; u < U; ++u) {
         const int w = i + u * G;
         if (w >= N) break;
-        if (const u64 missing = __builtin_amdgcn_ballot_w64(inside && bits[u] != 0xFFFFu)) {
+        if (const u64 lost = __builtin_amdgcn_ballot_w64(inside && bits[u] != 0xFFFFu)) {
+          lossy_here = true;
           if (lane == 0) atomicOr(&marks[w >> 5], 1u << (w & 31));
-          if (MODE == GROUPS && SPLIT && lane == 0) missing16[w] = make_uint2((uint32_t)missing, (uint32_t)(missing >> 32));
+          if (MODE == GROUPS && SPLIT && lane == 0) missing16[w] = make_uint2((uint32_t)lost, (uint32_t)(lost >> 32));
           count_bits(bits[u]);
         } else {
           ++full;
@@ -370,24 +372,26 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
   }
   const int own16 = (wave * 64 + lane) * 16;
   *(uint4*)&counts[SLOTS > 1 ? slot : grp][own16] = make_uint4(c4[0], c4[1], c4[2], c4[3]);
-  // Sec. 3.4 loss monitoring: the arrivals of this wavefront's lanes, gathered in LDS; one atomic per workgroup
-  auto add_arrived = [&]() {
-    uint32_t n = 0;
+  // Sec. 3.4 loss monitoring: what this wavefront's lanes miss, gathered in LDS; one atomic per workgroup at most
+  if (a.total_out) {
+    const uint32_t entries = K || left >= 1024 ? 1024u : (uint32_t)left;
+    if (lossy_here) {
+      uint32_t n = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) n = __builtin_amdgcn_sad_u8(c4[q], 0u, n);
+      for (int q = 0; q < 4; ++q) n = __builtin_amdgcn_sad_u8(c4[q], 0u, n);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) n += (uint32_t)__shfl_xor((int)n, o, 64);
-    if (lane == 0) {
-      atomicAdd(&arrived[0], n);
-      if constexpr (SLOTS > 1) {
-        __threadfence_block();   // the arrivals before the sign that they are there
-        if (atomicAdd(&arrived[1], 1u) == (uint32_t)tiles - 1) atomicAdd(a.total_out, (unsigned long long)atomicAdd(&arrived[0], 0u));
+      for (int o = 32; o > 0; o >>= 1) n += (uint32_t)__shfl_xor((int)n, o, 64);
+      if (lane == 0) atomicAdd(&missing[0], (uint32_t)((N - grp + G - 1) / G) * entries - n);   // the group's workers
+    }
+    if constexpr (SLOTS > 1) {
+      if (lane == 0) {
+        __threadfence_block();   // what is missing before the sign that it is there
+        if (atomicAdd(&missing[1], 1u) == (uint32_t)tiles - 1) add_total(a, first_unit == 0, atomicAdd(&missing[0], 0u));
       }
     }
-  };
-  if (a.total_out) add_arrived();
+  }
   tile_barrier<G * W>();
-  if (SLOTS == 1 && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)arrived[0]);
+  if (SLOTS == 1 && a.total_out && threadIdx.x == 0) add_total(a, unit == 0, missing[0]);
 
   float acc[16], raw[16], v[16];   // sum over the workers with a loss (B), over the whole ones (A); the one in work
 #pragma unroll

@@ -190,14 +190,14 @@ __device__ __forceinline__ void mt_store_counts(const PathArgs& a, u64 e0, int w
     for (int q = 0; q < 8; ++q) store_counts4(c8[q], rs, at + q * 4, 0, false);
   }
 }
-// Sec. 3.4 loss monitoring: the wavefront's arrivals, gathered in LDS
-__device__ __forceinline__ void mt_add_arrivals(const uint32_t (&c8)[8], uint32_t* arrived, int lane) {
+// Sec. 3.4 loss monitoring: what the wavefront's 2048 entries miss, gathered in LDS
+__device__ __forceinline__ void mt_add_missing(const uint32_t (&c8)[8], int N, uint32_t* missing, int lane) {
   uint32_t n = 0;
 #pragma unroll
   for (int q = 0; q < 8; ++q) n = __builtin_amdgcn_sad_u8(c8[q], 0u, n);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) n += (uint32_t)__shfl_xor((int)n, o, 64);
-  if (lane == 0) atomicAdd(arrived, n);
+  if (lane == 0) atomicAdd(missing, (uint32_t)N * 2048u - n);
 }
 // the counts of the lane's register r in S2, from the wavefront's counts by word (32 bytes a lane) at `counts`
 __device__ __forceinline__ uint32_t mt_count(const uint8_t* counts, int r, int lane) {
@@ -262,14 +262,14 @@ __device__ __forceinline__ void fused_bf16_tile(const PathArgs& a, u64 unit) {
   typedef MTile<K> M;
   constexpr int W = M::W, T = M::T, R = M::R;
   __shared__ __align__(16) float x[T];
-  __shared__ uint32_t arrived;
+  __shared__ uint32_t missing;
   const int wave = wave_id(), lane = lane_id(), N = a.N;
   const u64 e0 = unit * T, ew = e0 + (u64)wave * 2048;
   InFlight f;
   mt_request<K>(a, e0, 0, wave, lane, f);
   const uint32_t signs = mt_signs(a.seed, a.base + ew, (uint8_t*)(x + wave * 2048), lane);
   Operand h = mt_operand(lane);
-  if (TOTAL && threadIdx.x == 0) arrived = 0;   // behind barriers when it is added to
+  if (TOTAL && threadIdx.x == 0) missing = 0;   // behind barriers when it is added to
 
   float acc[R];
 #pragma unroll
@@ -308,7 +308,7 @@ __device__ __forceinline__ void fused_bf16_tile(const PathArgs& a, u64 unit) {
     mt_recount<K>(a, e0, 0, 1, wave, lane, c8);
   }
   mt_store_counts<K>(a, e0, wave, lane, c8);
-  if (TOTAL && a.total_out) mt_add_arrivals(c8, &arrived, lane);
+  if (TOTAL && a.total_out && !clean) mt_add_missing(c8, N, &missing, lane);
   // ---- mean over what arrived
   const float post = K & 1 ? 1.0f : a.scale;
   if (clean) {
@@ -323,8 +323,8 @@ __device__ __forceinline__ void fused_bf16_tile(const PathArgs& a, u64 unit) {
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = mt_mean(acc[r], mt_count(mine, r, lane), post);
   }
-  lds_barrier<W>();   // the counts are read, the arrivals are there
-  if (TOTAL && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)arrived);
+  lds_barrier<W>();   // the counts are read, what is missing is there
+  if (TOTAL && a.total_out && threadIdx.x == 0) add_total(a, unit == 0, missing);
   __builtin_amdgcn_sched_barrier(0);
   mt_decode<K>(acc, x, wave, lane);
   mt_store(acc, signs, a, ew, lane);
@@ -339,14 +339,14 @@ __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
   constexpr int W = M::W, T = M::T, R = M::R, D = 16 / G;   // D: pairs of a lane and a share
   static_assert(G >= 2 && G <= 16, "a share is at least a pair");
   __shared__ __align__(16) float x[G][T];
-  __shared__ uint32_t arrived, lossy;   // lossy: something was lost somewhere in the block
+  __shared__ uint32_t missing, lossy;   // lossy: something was lost somewhere in the block
   const int wave_all = wave_id(), lane = lane_id(), N = a.N, grp = wave_all / W, wave = wave_all % W;
   const u64 e0 = unit * T, ew = e0 + (u64)wave * 2048;
   InFlight f;
   mt_request<K>(a, e0, grp, wave, lane, f);
   const uint32_t signs = mt_signs(a.seed, a.base + ew, (uint8_t*)(x[grp] + wave * 2048), lane);
   Operand h = mt_operand(lane);
-  if (TOTAL && threadIdx.x == 0) arrived = 0;   // behind barriers when it is added to
+  if (TOTAL && threadIdx.x == 0) missing = 0;   // behind barriers when it is added to
   float acc[2 * D];
 #pragma unroll
   for (int r = 0; r < 2 * D; ++r) acc[r] = 0.0f;
@@ -412,7 +412,7 @@ __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
       for (int q = 0; q < 8; ++q) c8[q] = (uint32_t)N * 0x01010101u;
       mt_store_counts<K>(a, e0, wave, lane, c8);
     }
-    if (TOTAL && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)N * T);
+    if (TOTAL && a.total_out && threadIdx.x == 0) add_total(a, unit == 0, 0);
   } else {   // the group's workers, then all of them
     uint32_t* counts = (uint32_t*)&x[0][0];   // [group][wavefront][lane][8]
     static_assert(G * W * 512 + T <= G * T, "counts and means fit");
@@ -432,10 +432,10 @@ __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
       *(uint4*)(counts + (wave * 64 + lane) * 8) = make_uint4(c8[0], c8[1], c8[2], c8[3]);
       *(uint4*)(counts + (wave * 64 + lane) * 8 + 4) = make_uint4(c8[4], c8[5], c8[6], c8[7]);
       mt_store_counts<K>(a, e0, wave, lane, c8);
-      if (TOTAL && a.total_out) mt_add_arrivals(c8, &arrived, lane);
+      if (TOTAL && a.total_out) mt_add_missing(c8, N, &missing, lane);
     }
     lds_barrier<2>();
-    if (TOTAL && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)arrived);
+    if (TOTAL && a.total_out && threadIdx.x == 0) add_total(a, unit == 0, missing);
 #pragma unroll
     for (int r = 0; r < 2 * D; ++r) {
       const int reg = grp * 2 * D + r;

@@ -15,11 +15,11 @@
 
 namespace ordev {
 
-// `arrived`: arrivals of the workgroup's tiles, and how many of its wavefronts have added theirs; `tiles`: of this workgroup.  FULL:
+// `missing`: what the workgroup's tiles miss, and how many of its wavefronts have added theirs; `tiles`: of this workgroup.  FULL:
 // the tile is not cut short by the end of the shard.
 template <int K, class In, bool PREFETCH, bool TOTAL, int SLOTS, bool FULL>
 __device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit, int wave, int tiles,
-                                                float (*xbuf)[Geo<K>::Q >= 1 ? tr_floats<K> : 1], uint32_t* arrived) {
+                                                float (*xbuf)[Geo<K>::Q >= 1 ? tr_floats<K> : 1], uint32_t* missing) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R;
   constexpr bool TRANSP = Geo<K>::Q >= 1;   // tiles of one wavefront: the plain transform, which needs no LDS there
   static_assert(Geo<K>::PARTS == 1 && R == 16, "blocks of up to 2^14, 16 entries a lane");
@@ -103,18 +103,14 @@ __device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit, int
   }
   __builtin_amdgcn_sched_barrier(0);
   store_counts<K, FULL>(a.count_out, e0, L, wave, lane, cnt, full);
-  if constexpr (TOTAL) {   // Sec. 3.4 loss monitoring: gathered in LDS, one atomic per workgroup
+  if constexpr (TOTAL) {   // Sec. 3.4 loss monitoring: gathered in LDS, one atomic per workgroup at most
     if (a.total_out) {
-      uint32_t n = 0;
-#pragma unroll
-      for (int r = 0; r < R / 4; ++r) n = __builtin_amdgcn_sad_u8(cnt[r], 0u, n);
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) n += (uint32_t)__shfl_xor((int)n, o, 64);
+      const uint32_t n = missing_of<R>(cnt, full, a.N, FULL ? 64 * R : left);
       if (lane == 0) {
-        atomicAdd(&arrived[0], n + (uint32_t)full * (64 * R));
+        if (n) atomicAdd(&missing[0], n);
         if constexpr (SLOTS > 1) {
-          __threadfence_block();   // the arrivals before the sign that they are there
-          if (atomicAdd(&arrived[1], 1u) == (uint32_t)tiles - 1) atomicAdd(a.total_out, (unsigned long long)atomicAdd(&arrived[0], 0u));
+          __threadfence_block();   // what is missing before the sign that it is there
+          if (atomicAdd(&missing[1], 1u) == (uint32_t)tiles - 1) add_total(a, unit < SLOTS, atomicAdd(&missing[0], 0u));
         }
       }
     }
@@ -123,7 +119,7 @@ __device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit, int
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (TRANSP) transform_transposed<K>(acc, xbuf[flip], xbuf[flip ^ 1], wave, lane);   // the same code takes layout B to A
   else transform<K, false>(acc, xbuf[0], wave, lane, kt);
-  if (TOTAL && SLOTS == 1 && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)arrived[0]);
+  if (TOTAL && SLOTS == 1 && a.total_out && threadIdx.x == 0) add_total(a, unit == 0, missing[0]);
   __builtin_amdgcn_sched_barrier(0);
   const float c = a.scale * sigma;
 #pragma unroll
@@ -132,7 +128,7 @@ __device__ __forceinline__ void fused_each_tile(const PathArgs& a, u64 unit, int
   store_tile<K, false, FULL, true>((In*)a.out, e0, L, wave, lane, acc);
 }
 
-// SLOTS > 1 (tiles of one wavefront): the workgroup's wavefronts serve SLOTS tiles of a bucket, one atomic for all their arrivals
+// SLOTS > 1 (tiles of one wavefront): the workgroup's wavefronts serve SLOTS tiles of a bucket, one atomic for all that they miss
 // (see fused_tile).  K = 0: whether the tile is cut short is decided once, for all accesses.  (With
 // range-checked loads in the loop over the workers the compiler keeps their descriptors in vector registers and makes a loop of
 // every load: launches of whole tiles two to three times slower, one cut tile of 32 workers 48 -> 69 us.)
@@ -140,8 +136,8 @@ template <int K, class In, bool PREFETCH, bool TOTAL, int SLOTS>
 __device__ __forceinline__ void fused_each(const PathArgs& a, u64 first_unit, u64 units) {
   static_assert(SLOTS == 1 || Geo<K>::W == 1, "several tiles per workgroup: tiles of one wavefront");
   __shared__ float xbuf[2][Geo<K>::Q >= 1 ? tr_floats<K> : 1];
-  __shared__ uint32_t arrived[2];
-  if (TOTAL && threadIdx.x < 2) arrived[threadIdx.x] = 0;   // the transforms' barriers lie before and after the additions
+  __shared__ uint32_t missing[2];
+  if (TOTAL && threadIdx.x < 2) missing[threadIdx.x] = 0;   // the transforms' barriers lie before and after the additions
   const int slot = SLOTS > 1 ? wave_id() : 0, wave = SLOTS > 1 ? 0 : wave_id();
   const int tiles = units - first_unit < SLOTS ? (int)(units - first_unit) : SLOTS;
   if constexpr (SLOTS > 1) {
@@ -150,10 +146,10 @@ __device__ __forceinline__ void fused_each(const PathArgs& a, u64 first_unit, u6
   }
   const u64 unit = first_unit + slot;
   if constexpr (kShardTilesFull<K>) {
-    fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, true>(a, unit, wave, tiles, xbuf, arrived);
+    fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, true>(a, unit, wave, tiles, xbuf, missing);
   } else {
-    if ((unit + 1) * Geo<K>::T <= a.n_pad) fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, true>(a, unit, wave, tiles, xbuf, arrived);
-    else fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, false>(a, unit, wave, tiles, xbuf, arrived);
+    if ((unit + 1) * Geo<K>::T <= a.n_pad) fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, true>(a, unit, wave, tiles, xbuf, missing);
+    else fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, false>(a, unit, wave, tiles, xbuf, missing);
   }
 }
 
@@ -163,7 +159,7 @@ __device__ __forceinline__ void fused_each(const PathArgs& a, u64 first_unit, u6
 // takes about 1.5 us of vector instructions and 1.6 us of LDS (figures at the rule, inst.hip).
 template <int K, class In, int G, bool TOTAL, bool FULL>
 __device__ __forceinline__ void fused_each_groups_tile(const PathArgs& a, u64 unit, int grp, int wave, float (*x)[Geo<K>::Q >= 1 ? tr_floats<K> : 1024],
-                                                       float (*y)[Geo<K>::Q >= 1 ? tr_floats<K> : 1], uint32_t* arrived, uint32_t* lossy) {
+                                                       float (*y)[Geo<K>::Q >= 1 ? tr_floats<K> : 1], uint32_t* missing, uint32_t* lossy) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R, W = Geo<K>::W, S = R / G;   // S: registers of a share
   constexpr bool TRANSP = Geo<K>::Q >= 1;
   static_assert(Geo<K>::PARTS == 1 && R == 16 && G >= 2 && G <= 16, "blocks of up to 2^14, a share is at least a register");
@@ -294,16 +290,16 @@ __device__ __forceinline__ void fused_each_groups_tile(const PathArgs& a, u64 un
 #pragma unroll
     for (int q = 0; q < 4; ++q) store_counts4(c4[q], rs, off + q * 4, 0, ((uintptr_t)a.count_out & 3) == 0);
   }
-  if (TOTAL && grp == 0 && a.total_out) {   // Sec. 3.4 loss monitoring: gathered in LDS, one atomic per workgroup
+  if (TOTAL && grp == 0 && a.total_out && *(volatile uint32_t*)lossy) {   // Sec. 3.4 loss monitoring: gathered in LDS, one atomic per workgroup at most
     uint32_t n = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) n = __builtin_amdgcn_sad_u8(c4[q], 0u, n);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) n += (uint32_t)__shfl_xor((int)n, o, 64);
-    if (lane == 0) atomicAdd(arrived, n);
+    if (lane == 0) atomicAdd(missing, (uint32_t)N * (FULL ? 1024u : (uint32_t)left) - n);
   }
   __syncthreads();
-  if (TOTAL && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)*arrived);
+  if (TOTAL && a.total_out && threadIdx.x == 0) add_total(a, unit == 0, *missing);
   if (grp > 0) return;   // (a barrier waits for the wavefronts that are left)
   float v[R];
 #pragma unroll
@@ -322,15 +318,15 @@ __device__ __forceinline__ void fused_each_groups(const PathArgs& a, u64 unit) {
   constexpr int W = Geo<K>::W;
   __shared__ __align__(16) float x[G][Geo<K>::Q >= 1 ? tr_floats<K> : 1024];
   __shared__ __align__(16) float y[G][Geo<K>::Q >= 1 ? tr_floats<K> : 1];
-  __shared__ uint32_t arrived, lossy;
+  __shared__ uint32_t missing, lossy;
   const int grp = wave_id() / W, wave = wave_id() % W;
-  if (threadIdx.x == 0) arrived = lossy = 0;
+  if (threadIdx.x == 0) missing = lossy = 0;
   __syncthreads();
   if constexpr (kShardTilesFull<K>) {
-    fused_each_groups_tile<K, In, G, TOTAL, true>(a, unit, grp, wave, x, y, &arrived, &lossy);
+    fused_each_groups_tile<K, In, G, TOTAL, true>(a, unit, grp, wave, x, y, &missing, &lossy);
   } else {
-    if ((unit + 1) * Geo<K>::T <= a.n_pad) fused_each_groups_tile<K, In, G, TOTAL, true>(a, unit, grp, wave, x, y, &arrived, &lossy);
-    else fused_each_groups_tile<K, In, G, TOTAL, false>(a, unit, grp, wave, x, y, &arrived, &lossy);
+    if ((unit + 1) * Geo<K>::T <= a.n_pad) fused_each_groups_tile<K, In, G, TOTAL, true>(a, unit, grp, wave, x, y, &missing, &lossy);
+    else fused_each_groups_tile<K, In, G, TOTAL, false>(a, unit, grp, wave, x, y, &missing, &lossy);
   }
 }
 template <int K, class In, int G>

@@ -101,12 +101,12 @@ __device__ __forceinline__ void fused_f32_half(const PathArgs& a, u64 e0, int h)
   __shared__ __align__(16) float x[kHalf];
   __shared__ uint32_t marks[8];        // one bit per worker: something is missing
   __shared__ uint8_t order[256];
-  __shared__ uint32_t arrived;
+  __shared__ uint32_t missing;
   const int wave = wave_id(), lane = lane_id(), N = a.N;
   const u64 L = a.n_pad, eo = e0 + (u64)h * kHalf;   // eo: first of the workgroup's encoded values
   float* mine = x + wave * 2048;
   if (threadIdx.x < 8) marks[threadIdx.x] = 0;
-  if (TOTAL && threadIdx.x == 0) arrived = 0;
+  if (TOTAL && threadIdx.x == 0) missing = 0;
   lds_barrier<16>();
 
   // ---- who lost something
@@ -195,7 +195,7 @@ __device__ __forceinline__ void fused_f32_half(const PathArgs& a, u64 e0, int h)
     mt_recount<15>(a, eo, 0, 1, wave, lane, c8);
   }
   mt_store_counts<15>(a, eo, wave, lane, c8);
-  if (TOTAL && a.total_out) mt_add_arrivals(c8, &arrived, lane);
+  if (TOTAL && a.total_out && lossy) mt_add_missing(c8, N, &missing, lane);
   if (lossy == 0) {
     const float f = a.scale * __builtin_amdgcn_rcpf((float)N);
 #pragma unroll
@@ -208,8 +208,8 @@ __device__ __forceinline__ void fused_f32_half(const PathArgs& a, u64 e0, int h)
 #pragma unroll
     for (int r = 0; r < 32; ++r) acc[r] = mt_mean(acc[r], mt_count(counts, r, lane), a.scale);
   }
-  lds_barrier<16>();   // the counts are read, the arrivals are there
-  if (TOTAL && a.total_out && threadIdx.x == 0) atomicAdd(a.total_out, (unsigned long long)arrived);
+  lds_barrier<16>();   // the counts are read, what is missing is there
+  if (TOTAL && a.total_out && threadIdx.x == 0) add_total(a, eo == 0, missing);
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (PARTS == 2) {   // the mean, where the decoded block will be
     const __amdgpu_buffer_rsrc_t out = rsrc_of((const float*)a.out + eo + wave * 128, (kHalf - wave * 128) * 4);
