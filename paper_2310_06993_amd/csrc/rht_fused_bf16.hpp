@@ -19,8 +19,8 @@
 // by one -> this: 2^14, N = 8, 2556 blocks, 2 % loss in bursts 230 -> 165 (5.1 TB/s), 5 % in single packets 241 -> 177;  2^15, N = 8,
 // 1280 blocks 258 -> 196;  2^13, N = 8, 5000 blocks 209 -> 153;  2^12, N = 16, 10000 blocks 375 -> 271, N = 2 74 -> 54;  2^11, N = 8,
 // 20000 blocks 195 -> 142.  Two workers in flight instead of one: 164 -> 170.
-// The price is a longer decode in launches of few blocks and two workers, which has half as many wavefronts: 2^12, N = 2, 100 blocks
-// 5.9 -> 6.7.
+// The price is a longer decode, which has half as many wavefronts: with few workers launches of few blocks gain nothing (2^12, N = 2,
+// 129 blocks 5.9 -> 6.0 where both groups decode) or lose (2^12, N = 3, 512 blocks 9.0 -> 9.5; 2^13, N = 3, 65 blocks 8.4 -> 8.9).
 #pragma once
 #include "rht_fused.hpp"
 
@@ -257,6 +257,73 @@ __device__ __forceinline__ void mt_store(const float (&v)[32], uint32_t signs, c
   }
 }
 
+// The decode of one block by two groups of wavefronts, 16 values a lane: the same stages in the same order, so the same bits.  For
+// launches of few blocks and workers, where it is a third of the time: half of the values, and no trip of the means to group 0.
+// Entry bits of the positions (E = K - 1; waves of both groups: e9 .. eK-2 from S3 on):
+//   S2  as encoded    regs e5, eK-4 .. eK-2   lanes e0 .. e4 e6          group eE, waves e7 ..
+//   S3                regs e3 e4 e6 eE        lanes e0 e1 e2 e5 e7 e8
+//   L                 regs e0 e1 e2 e7        lanes e3 e4 e5 e6 e8 eE    (2^13: e8 is left there, the one stage across lanes)
+// x: 2^K floats for S2 -> S3, then 2^K for S3 -> L, inside the wavefront; nobody reads the former any more, and the latter only ahead of
+// the barrier.  `bytes`: the block's signs.
+template <int K>
+__device__ __forceinline__ void mt_decode_shared(float (&v)[16], float* x, const uint8_t* bytes, const PathArgs& a, u64 e0, int grp, int wave,
+                                                 int lane) {
+  static_assert(K >= 11 && K <= 13, "at most one stage more than the registers take");
+  constexpr int E = K - 1, TOP = K - 4;
+  const int all = grp * MTile<K>::W + wave;
+  reg_stages(v, 0, 4);
+  {
+    float* p = x + (lane & 7) * 4 + ((lane >> 3) & 3) + (lane >> 5) * 32 + wave * 128 + (grp << E);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p[MTile<K>::s2_reg(r)] = v[r];
+  }
+  lds_barrier<2>();
+  {
+    const float* p = x + (lane & 7) * 4 + ((lane >> 3) & 1) * 64 + ((lane >> 4) & 1) * 128 + (lane >> 5) * 256 + all * 512;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {   // registers e3 e4 | e6 eE
+      const f32x4v t = *(const f32x4v*)(p + (g & 1) * 32 + ((g >> 1) << E));
+      v[4 * g] = t[0]; v[4 * g + 1] = t[1]; v[4 * g + 2] = t[2]; v[4 * g + 3] = t[3];
+    }
+  }
+  reg_stage<3>(v);
+  reg_stages(v, 0, 3);
+  // from the lowest address bit up: e0 e1 (e2^e3) e5 (e7^e4) (e8^e6) e3 e4 e6 eE
+  float* mine = x + MTile<K>::T + all * 1024;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) mine[(lane ^ ((r & 1) * 4 + ((r >> 1) & 1) * 16 + ((r >> 2) & 1) * 32)) + r * 64] = v[r];
+  __builtin_amdgcn_wave_barrier();
+  {
+    const int at = (lane & 1) * (4 + 64) + ((lane >> 1) & 1) * (16 + 128) + ((lane >> 2) & 1) * 8 + ((((lane >> 3) ^ (lane >> 4)) & 1) * 32) +
+                   ((lane >> 3) & 1) * 256 + (lane >> 5) * 512;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {   // registers e0 e1 | e2 e7
+      const f32x4v t = *(const f32x4v*)(mine + (at ^ ((g & 1) * 4 + (g >> 1) * 16)));
+      v[4 * g] = t[0]; v[4 * g + 1] = t[1]; v[4 * g + 2] = t[2]; v[4 * g + 3] = t[3];
+    }
+  }
+  if constexpr (TOP > 7) reg_stage<3>(v);
+  if constexpr (TOP > 8) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float o = __shfl_xor(v[r], 16, 64);
+      v[r] = lane & 16 ? o - v[r] : v[r] + o;
+    }
+  }
+  reg_stages(v, 0, 3);
+  const int at = (lane & 15) + ((lane >> 4) & 1) * 32 + all * 64 + ((lane >> 5) << (E - 3));   // of 8 entries
+  uint32_t signs = pair_signs((uint32_t)bytes[at] | (uint32_t)bytes[at + 16] << 8);
+  const __amdgpu_buffer_rsrc_t out = rsrc_of((const bf16_t*)a.out + e0, MTile<K>::T * 2);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {   // e7
+    u32x4v o;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) o[d] = pack_bf16x2(v[8 * q + 2 * d] * a.scale, v[8 * q + 2 * d + 1] * a.scale);
+    flip_pairs(o, signs);
+    store16<kBufNt>(o, out, at * 16 + q * 256);
+  }
+}
+
 template <int K, bool TOTAL>
 __device__ __forceinline__ void fused_bf16_tile(const PathArgs& a, u64 unit) {
   typedef MTile<K> M;
@@ -332,19 +399,22 @@ __device__ __forceinline__ void fused_bf16_tile(const PathArgs& a, u64 unit) {
 
 // For launches that leave CUs idle: G groups of W wavefronts encode G workers side by side.  The encoded values go through LDS as
 // the bf16 pairs that they are, and group g adds those of its share of the registers over the workers, in order: the same
-// operations in the same order as above.  Group 0 decodes.
+// operations in the same order as above.  Group 0 decodes; of two groups (up to 2^13) both.
 template <int K, int G, bool TOTAL>
 __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
   typedef MTile<K> M;
   constexpr int W = M::W, T = M::T, R = M::R, D = 16 / G;   // D: pairs of a lane and a share
   static_assert(G >= 2 && G <= 16, "a share is at least a pair");
+  constexpr bool SHARED = G == 2 && K <= 13;
   __shared__ __align__(16) float x[G][T];
+  __shared__ __align__(16) uint8_t sign_bytes[SHARED ? T / 8 : 16];
   __shared__ uint32_t missing, lossy;   // lossy: something was lost somewhere in the block
   const int wave_all = wave_id(), lane = lane_id(), N = a.N, grp = wave_all / W, wave = wave_all % W;
   const u64 e0 = unit * T, ew = e0 + (u64)wave * 2048;
   InFlight f;
   mt_request<K>(a, e0, grp, wave, lane, f);
-  const uint32_t signs = mt_signs(a.seed, a.base + ew, (uint8_t*)(x[grp] + wave * 2048), lane);
+  // (SHARED: both groups write the same bytes to the same place)
+  const uint32_t signs = mt_signs(a.seed, a.base + ew, SHARED ? sign_bytes + wave * 256 : (uint8_t*)(x[grp] + wave * 2048), lane);
   Operand h = mt_operand(lane);
   if (TOTAL && threadIdx.x == 0) missing = 0;   // behind barriers when it is added to
   float acc[2 * D];
@@ -405,7 +475,10 @@ __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
   if (lossy == 0) {
     const float f = post * __builtin_amdgcn_rcpf((float)N);
 #pragma unroll
-    for (int r = 0; r < 2 * D; ++r) means[(wave * R + grp * 2 * D + r) * 64 + lane] = acc[r] * f;
+    for (int r = 0; r < 2 * D; ++r) {
+      if constexpr (SHARED) acc[r] *= f;
+      else means[(wave * R + grp * 2 * D + r) * 64 + lane] = acc[r] * f;
+    }
     if (grp == 0) {
       uint32_t c8[8];
 #pragma unroll
@@ -414,7 +487,7 @@ __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
     }
     if (TOTAL && a.total_out && threadIdx.x == 0) add_total(a, unit == 0, 0);
   } else {   // the group's workers, then all of them
-    uint32_t* counts = (uint32_t*)&x[0][0];   // [group][wavefront][lane][8]
+    uint32_t* counts = (uint32_t*)&x[SHARED ? 1 : 0][0];   // [group][wavefront][lane][8]
     static_assert(G * W * 512 + T <= G * T, "counts and means fit");
     uint32_t c8[8];
     mt_recount<K>(a, e0, grp, G, wave, lane, c8);
@@ -439,8 +512,14 @@ __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
 #pragma unroll
     for (int r = 0; r < 2 * D; ++r) {
       const int reg = grp * 2 * D + r;
-      means[(wave * R + reg) * 64 + lane] = mt_mean(acc[r], mt_count((const uint8_t*)(counts + wave * 512), reg, lane), post);
+      const float m = mt_mean(acc[r], mt_count((const uint8_t*)(counts + wave * 512), reg, lane), post);
+      if constexpr (SHARED) acc[r] = m;
+      else means[(wave * R + reg) * 64 + lane] = m;
     }
+  }
+  if constexpr (SHARED) {
+    mt_decode_shared<K>(acc, &x[0][0], sign_bytes, a, e0, grp, wave, lane);
+    return;
   }
   lds_barrier<2>();
   if (grp > 0) return;   // (a barrier waits for the wavefronts that are left)
