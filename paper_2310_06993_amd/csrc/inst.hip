@@ -204,8 +204,15 @@ hipError_t fused_batched(const BatchArgs& a, unsigned long long units, hipStream
   constexpr int most = K == 0 && sizeof(In) == 4 ? 8 : kEachGroups;   // fp32 below 2^10: up to five workers
   if constexpr (most > 1)
     if (const int g = each_groups(units, a.N); g > 1) return launch_each_groups<In, most>(g, a, units, s, pos);
-  if (kEachSlots<K> > 1 && !a.totals) return launch_each<In, 1>(a, units, s, pos);
-  return launch_each<In, kEachSlots<K>>(a, units, s, pos);
+  // K = 0 with totals, tiles a workgroup: eight share an atomic, four come and go more evenly, which is worth more in launches that
+  // fill the chip.  us, eight -> four: bf16 2^9, N = 2, 2049 / 51201 tiles 15.2 -> 12.2 / 165 -> 145, N = 8, 2049 / 12801 tiles 36.3 ->
+  // 28.4 / 124 -> 104, N = 16, 1025 / 6401 tiles 36.6 -> 40.1 / 128 -> 107;  fp32 2^9, N = 3, 17067 tiles 84 -> 68.  (Two: N = 5, 5 % loss, 3277
+  // tiles 30 -> 37; four 30 -> 31, the one size where eight were better.)
+  if constexpr (K == 0) {
+    if (a.totals && units >= 2048) return launch_each<In, 4>(a, units, s, pos);
+    if (a.totals) return launch_each<In, 8>(a, units, s, pos);
+  }
+  return launch_each<In, 1>(a, units, s, pos);
 }
 constexpr launch_fn fus_f32 = fused<float>;
 constexpr batch_fn fusb_f32 = fused_batched<float>;
@@ -254,7 +261,7 @@ constexpr int kGroupsBf16 = K == 11 ? 8 : 16 / MTile<K>::W;
 // 28.7;  2^14, N = 32, 2 blocks 65.5 -> 59.1, N = 8, 64 blocks 21.2 -> 20.5, 256 blocks 22.0 -> 23.2, N = 3, 100 blocks 11.7 -> 13.3.
 // Two groups, which share the decode too (mt_decode_shared): N = 2, 2^11, 65 blocks 6.0 -> 5.3, 2^12, 17 / 512 blocks 6.6 -> 5.7 / 8.8 ->
 // 7.4 (700: 9.3 -> 9.2), 2^13, 65 / 384 blocks 7.6 -> 7.3 / 9.9 -> 10.9;  N = 3, 2^13, 17 / 384 blocks 8.8 -> 8.7 / 11.6 -> 13.3;  instead of four
-// groups: 2^12, N = 3, 200 / 384 blocks 7.2 / 9.8 -> 9.0, N = 4, 384 / 512 blocks 10.5 / 11.0 -> 9.6 / 9.9, 2^11, N = 3, 384 blocks 7.0 -> 7.5.
+// groups: 2^12, N = 3, 257 / 384 blocks 7.2 / 9.8 -> 7.5 / 9.0, N = 4, 384 / 512 blocks 10.5 / 11.0 -> 9.6 / 9.9, 2^11, N = 3, 384 blocks 7.0 -> 7.5.
 int groups_bf16(unsigned long long blocks, int N) {
   int most = kGroupsBf16;
   if (K <= 13 && N == 2) return blocks <= (K == 13 ? 256 : 512) ? 2 : 1;

@@ -345,16 +345,15 @@ __global__ __launch_bounds__(Geo<K>::THREADS) __attribute__((amdgpu_waves_per_eu
 void k_fused_each(PathArgs a) {
   fused_each<K, In, PREFETCH, false, 1>(a, blockIdx.x, gridDim.x);
 }
-// K = 0 with arrival totals: a workgroup serves SLOTS = kEachSlots tiles of one bucket, and ba.tile_start counts workgroups.  us, a
-// workgroup per tile -> eight: 60 x 400 tiles, N = 8, bf16 2^8 200 -> 145 with totals; without them 4 x 100 tiles 15 -> 17.
-template <int K> constexpr int kEachSlots = K == 0 ? 8 : 1;
+// K = 0 with arrival totals: a workgroup serves SLOTS tiles of one bucket (rule in inst.hip), and ba.tile_start counts workgroups.
+// Without totals a workgroup per tile (4 x 100 tiles, eight a workgroup -> one: 17 -> 15).
 template <int K, class In, bool PREFETCH, int SLOTS>
 __global__ __launch_bounds__(Geo<K>::THREADS * SLOTS) __attribute__((amdgpu_waves_per_eu(1)))
 void k_fused_each_batched(BatchArgs ba) {
   constexpr int T = Geo<K>::T;
   PathArgs a;
   const u64 group = bucket_of(ba, a, blockIdx.x);
-  fused_each<K, In, PREFETCH, (SLOTS == kEachSlots<K>), SLOTS>(a, group * SLOTS, (a.n_pad + T - 1) / T);
+  fused_each<K, In, PREFETCH, (K != 0 || SLOTS > 1), SLOTS>(a, group * SLOTS, (a.n_pad + T - 1) / T);
 }
 
 }  // namespace ordev
