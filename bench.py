@@ -254,12 +254,16 @@ def roofline(cfg, L, nbytes, kern):
     N, k = cfg.workers, cfg.block_log2
     adds = (k * (N + 1) / N + 1.0) * N * L
     peak_adds = 256 * 4 * 32 * 2.4e9
-    names = {True: "k_fused%s (one launch per step)" % ("" if cfg.dtype == "f32" and cfg.block_log2 <= 10 else "_each"),
-             False: "k_sign_table + k_fused_mx (one step; the fused kernel is 99 % of it)" if cfg.dtype != "f32"
-             else "k_sign_table + k_fused_pairs (+ k_decode_block for 2^16 blocks), one step"}
+    if cfg.block_log2 > 14:
+        name = "k_fused_f32_half%s, one step" % (" + k_decode_block" if cfg.block_log2 == 16 else "") if cfg.dtype == "f32" \
+            else "k_fused_bf16%s (one launch per step)" % ("_64k" if cfg.block_log2 == 16 else "")
+    elif cfg.dtype != "f32" and cfg.block_log2 > 10:
+        name = "k_fused_bf16 (one launch per step)"
+    else:
+        name = "k_fused%s (one launch per step)" % ("" if cfg.dtype == "f32" and cfg.block_log2 <= 10 else "_each")
     return {"bound": "hbm", "achieved": nbytes / kern / 1e9, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
             "frac": nbytes / kern / 1e9 / HBM_PEAK_GBPS, "traffic": profiled_traffic(cfg.name),
-            "kernel": names[cfg.block_log2 <= 14], "avg_launch_us": kern * 1e6,
+            "kernel": name, "avg_launch_us": kern * 1e6,
             "ideal_ms_hbm": nbytes / (HBM_PEAK_GBPS * 1e9) * 1e3, "ideal_ms_alu": adds / peak_adds * 1e3,
             "alu": {"algorithmic_fp32_additions": adds, "achieved_Tadd_per_s": adds / kern / 1e12,
                     "peak_Tadd_per_s": peak_adds / 1e12, "frac": adds / kern / peak_adds}}

@@ -218,9 +218,9 @@ or_status or_masked_reduce_pairs(const float* sums, const uint8_t* counts, const
  * to fill the GPU alone.  `buckets` is a HOST array, read before the call returns; the device
  * pointers in it follow the rules of or_fused_path (grads/out are float or bf16 bits per `bf16`).
  * Every bucket is validated before anything is enqueued; no output of one bucket may overlap anything
- * of another bucket (OR_ERR_SHAPE).  Buckets of length 0 are skipped.  For block_log2 > 14 the buckets
- * are run one after the other and `workspace` must cover the largest or_workspace_bytes() among them; no
- * input may overlap it, no output the or_workspace_bytes() of its own or of a later bucket. */
+ * of another bucket (OR_ERR_SHAPE).  Buckets of length 0 are skipped.  For block_log2 > 14 `workspace`
+ * must cover the largest or_workspace_bytes() among the buckets; no input may overlap it, no output the
+ * or_workspace_bytes() of its own or of a later bucket (as if they ran one after the other). */
 typedef struct or_bucket {
   const void* grads;      /* [N][shard_len] raw slices                  */
   const uint32_t* masks;  /* [N][shard_len/32]                          */
