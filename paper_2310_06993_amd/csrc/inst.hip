@@ -4,6 +4,9 @@
 #include "rht_fused_each.hpp"
 #if OR_K >= 11 && OR_K <= 15
 #include "rht_fused_bf16.hpp"
+#if OR_K <= 14
+#include "rht_encode_bf16.hpp"
+#endif
 #endif
 #if OR_K > 14
 #include "rht_encode_block.hpp"
@@ -53,8 +56,10 @@ typedef Geo<K> G;
 #define OR_XFORM_LAUNCHER OR_BLOCK_LAUNCHER
 #endif
 OR_XFORM_LAUNCHER(enc_f32, OR_ENC(float, float))
-#if OR_K <= 14
+#if OR_K == 0
 OR_LAUNCHER(enc_bf16, OR_ENC(bf16_t, bf16_t))
+#elif OR_K <= 14
+OR_LAUNCHER_T(enc_bf16, k_encode_bf16<K>, MTile<K>::THREADS)
 #else
 // workgroups that walk over the blocks: as many as 256 CUs hold at a time
 hipError_t enc_bf16(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {

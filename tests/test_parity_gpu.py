@@ -108,6 +108,29 @@ def test_encode_bf16_large_blocks_walked_over(b, orc, k, blocks, tail):
         assert torch.equal(xd.view(torch.int16), enc.view(torch.int16))
 
 
+@pytest.mark.parametrize("k,blocks,tail", [(11, 1, 1), (11, 1, 0), (11, 7, 2047), (12, 1, 2049), (12, 3, 0), (12, 2, 2048), (13, 2, 4097),
+                                           (13, 5, 6145), (14, 1, 3), (14, 3, 0), (14, 2, 16383), (14, 600, 2047)])
+def test_encode_bf16_middle_blocks(b, orc, k, blocks, tail):
+    """The bf16 encode of 2^11 .. 2^14 blocks: a last block cut short at odd entries and at the edges of the parts of its wavefronts,
+    and in place."""
+    B = 1 << k
+    n = blocks * B - (B - tail if tail else 0)
+    rng = np.random.default_rng(700 + k + blocks + tail)
+    x = _bf16_bits((rng.standard_normal(n) * 1e-4).astype(np.float32))
+    seed, base = 0xF00DFACE12345678, (1 << 33) + 5 * B
+    enc = torch.full((blocks * B,), float("nan"), dtype=torch.bfloat16, device=dev())
+    xd = _dev_bf16(x)
+    b.or_rht_encode_bf16(xd, n, k, seed, base, enc)
+    want = orc.rht_encode(x, k, seed, base)
+    assert rel_l2(to_np(enc), want) <= TOL["bf16"]
+    assert (to_np(enc) != want).mean() < 0.02      # as above
+    last = slice((blocks - 1) * B, blocks * B)
+    assert rel_l2(to_np(enc[last]), want[last]) <= TOL["bf16"]
+    if tail == 0:
+        b.or_rht_encode_bf16(xd, n, k, seed, base, xd)
+        assert torch.equal(xd.view(torch.int16), enc.view(torch.int16))
+
+
 @pytest.mark.parametrize("k", [6, 10, 12, 14, 16])
 def test_sign_draws_are_bit_exact(b, orc, k):
     # decode of sqrt(B) * e_0 in every block is exactly the sign vector (even k: all values exact)
