@@ -2,7 +2,7 @@
 // and exchange as in rht_fused_bf16.hpp.
 //
 // Bound by memory (a large copy: 5.2 TB/s).  us, stages one by one with 2 bytes a lane per access -> this: 2^12, 13.1e6 entries 14.4 ->
-// 11.5 (4.6 TB/s), 210e6 153 -> 130 (6.5 TB/s);  2^11, 210e6 149 -> 131;  2^13 157 -> 130;  2^14, 131e3 4.9 -> 4.1, 13.1e6 15.8 -> 12.0,
+// 11.4 (4.6 TB/s), 210e6 153 -> 130 (6.5 TB/s);  2^11, 210e6 149 -> 131;  2^13 157 -> 130;  2^14, one ragged block 4.6 -> 3.9, 131e3 4.9 -> 4.1, 13.1e6 15.9 -> 12.4,
 // 210e6 167 -> 136.
 #pragma once
 #include "rht_fused_bf16.hpp"
