@@ -14,13 +14,16 @@
 //
 // Bound by a wavefront's own chain: per worker 1400 additions, 330 other vector instructions and 64 products in each of two
 // wavefronts a SIMD, 4.5 us, and 2.3 us of exchange through LDS, which only partly run at the same time (7.0 to 7.5 us).  us, two
-// workgroups a block that read everything twice and met in memory -> this: N = 8, 15317 blocks 5980 - 6400 -> 4800 - 5030 (4.0 TB/s), 2560
-// blocks 970 -> 766, N = 2, 1000 blocks 240 -> 153.
+// workgroups a block that read everything twice and met in memory -> this: N = 8, 15317 blocks 5980 - 6400 -> 4670 - 5030 (4.0 - 4.3 TB/s), 2560
+// blocks 970 -> 738, N = 2, 1000 blocks 240 -> 144.
 //
 // One workgroup is all that fits on a CU, so nothing but the kernel itself runs under its waits for memory.  Three quarters of the
 // next worker's entries are written to LDS by the loads themselves (no registers) from the start of a worker on, the last quarter
 // is asked for once the entries in registers have been used for the last time; and a workgroup walks over blocks, so that this
-// goes on through the decode of a block into the next one.
+// goes on through the decode of a block into the next one.  It does so only while nothing is spilled: the reload of a spilled register
+// waits for everything that was asked for before it.  Hence addresses and constants are formed where they are used (`lane_t`).  us,
+// 44 bytes of scratch a lane -> none: N = 1, 129 blocks 25.0 -> 22.9;  N = 2, 1000 blocks 151 -> 144;  N = 8, 2560 blocks 891 -> 879, nothing
+// lost 766 -> 738;  N = 32, 300 blocks 626 -> 624.
 #pragma once
 #include "rht_fused_bf16.hpp"
 
@@ -117,7 +120,7 @@ __device__ __forceinline__ void decode_64k(float (&acc)[4][32], float* x, u32x4v
 // blocks first, first + step ..  NQ = 1, 2: for launches of few blocks, one block's quarters quarter0 .. quarter0 + NQ - 1 (a quarter
 // or a half of them), up to the mean, which goes to a.mean_out for k_decode_64k: by quarter, wavefront, four registers, lane.
 template <int NQ, class Next>
-__device__ __forceinline__ void fused_bf16_walk_64k(u64 first, u64 blocks, u64 step, int quarter0, bool totals, const Next& next) {
+__device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blocks, uint32_t step, int quarter0, bool totals, const Next& next) {
   constexpr int B = 1 << 16;
   __shared__ __align__(16) float x[1 << 14];
   __shared__ __align__(16) u32x4v stage[8 * kStaged * 64];
@@ -128,7 +131,7 @@ __device__ __forceinline__ void fused_bf16_walk_64k(u64 first, u64 blocks, u64 s
   u32x4v p[16];   // load q: 8 entries from 512 q + 8 lane of the wavefront's part
   auto part_of = [&](const PathArgs& a, u64 blk, int i) { return (const bf16_t*)a.in + (u64)i * a.n_pad + (blk << 16) + (u64)wave * 8192; };
   // The loads that write LDS are out of the compiler's sight, which would
-  // wait for them ahead of every other access to LDS; landed() is the wait for them
+  // wait for them ahead of every other access to LDS; landed() is the only wait for them, whatever was asked for after them
   auto request_staged = [&](const bf16_t* part, int from, int to_q) {
     const u32x4v rs = {(uint32_t)(uintptr_t)part, (uint32_t)((uintptr_t)part >> 32), 16384u, 0x00020000u};
     const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(stage + wave * kStaged * 64);
@@ -138,10 +141,8 @@ __device__ __forceinline__ void fused_bf16_walk_64k(u64 first, u64 blocks, u64 s
                    :: "s"(to + q * 1024), "v"(lane * 16), "s"(rs), "s"(q * 1024) : "memory", "m0");
   };
   u32x4v mw;   // received bits of the worker whose entries are on their way
-  auto landed = [&](bool stores_behind) {   // names what the compiler knows to be in flight: it waits for that here and not behind the loads that follow
-    // (the 16 stores of the block before come after them, and are not waited for)
-    if (stores_behind) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  auto landed = [&]() {   // names what the compiler knows to be in flight: it waits for that here and not behind the loads that follow
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     asm volatile("" : "+v"(p[10]), "+v"(p[11]), "+v"(p[12]), "+v"(p[13]), "+v"(p[14]), "+v"(p[15]), "+v"(mw));
   };
   auto request_rest = [&](const bf16_t* part, int from, int to_q) {   // null: zeros, without touching memory
@@ -167,7 +168,7 @@ __device__ __forceinline__ void fused_bf16_walk_64k(u64 first, u64 blocks, u64 s
     return u32x4v{first, first ^ n1, first ^ n2, first ^ n1 ^ n2};
   };
 
-  for (u64 at = first;; at += step) {
+  for (uint32_t at = first;; at += step) {
     PathArgs a;
     const u64 blk = next(at, a);
     if (at == first) {
@@ -177,7 +178,11 @@ __device__ __forceinline__ void fused_bf16_walk_64k(u64 first, u64 blocks, u64 s
     }
     const int N = a.N;
     const u64 e0 = blk << 16;
-    signs[threadIdx.x] = signs_64k(a.seed, a.base + e0 + (u64)wave * 8192, (uint8_t*)(x + wave * 2048), lane);
+    {
+      int lane_t = lane;   // addresses formed here, not kept in registers all along
+      asm volatile("" : "+v"(lane_t));
+      signs[wave * 64 + lane_t] = signs_64k(a.seed, a.base + e0 + (u64)wave * 8192, (uint8_t*)(x + wave * 2048), lane_t);
+    }
     float acc[NQ][32];
 #pragma unroll
     for (int s = 0; s < NQ; ++s)
@@ -185,10 +190,11 @@ __device__ __forceinline__ void fused_bf16_walk_64k(u64 first, u64 blocks, u64 s
       for (int r = 0; r < 32; ++r) acc[s][r] = 0.0f;
     const bool more = NQ == 4 && at + step < blocks;
     bool clean = true;   // nothing of this wavefront's S2 part was lost so far
-    for (int i = 0; i < N; ++i) {
-      int lane_t = lane;   // addresses formed here, not kept in registers all along
+    int i = 0;
+    do {   // (N >= 1)
+      int lane_t = lane;   // as above
       asm volatile("" : "+v"(lane_t));
-      landed(i == 0 && at != first);
+      landed();
       const bool whole = __builtin_amdgcn_ballot_w64((mw[0] & mw[1] & mw[2] & mw[3]) != 0xFFFFFFFFu) == 0;
       if (!whole) {
         lost[wave * 64 + lane_t] = mw;
@@ -298,7 +304,7 @@ __device__ __forceinline__ void fused_bf16_walk_64k(u64 first, u64 blocks, u64 s
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-    }
+    } while (++i < N);
 
     // ---- counts (a byte for each of the 128 entries of the lane's words) and the mean over what arrived
     const float post = a.scale;
@@ -320,7 +326,8 @@ __device__ __forceinline__ void fused_bf16_walk_64k(u64 first, u64 blocks, u64 s
     };
     uint32_t total = 0;
     if (clean) {
-      const uint32_t c = (uint32_t)N * 0x01010101u;
+      uint32_t c = (uint32_t)N * 0x01010101u;
+      asm volatile("" : "+v"(c));   // here, not ahead of the blocks
       store_counts([&](int) { return u32x4v{c, c, c, c}; });
       total = (uint32_t)N * 128u;
       const float f = post * __builtin_amdgcn_rcpf((float)N);
@@ -377,7 +384,9 @@ __device__ __forceinline__ void fused_bf16_walk_64k(u64 first, u64 blocks, u64 s
 
     if constexpr (NQ == 4) {
       lds_barrier<8>();   // everyone has read what was there
-      decode_64k(acc, x, signs[threadIdx.x], a, e0, wave, lane);
+      int lane_t = lane;
+      asm volatile("" : "+v"(lane_t));
+      decode_64k(acc, x, signs[wave * 64 + lane_t], a, e0, wave, lane_t);
     } else {
       float* to = a.mean_out + e0 + (u64)quarter0 * kQuarterEntries + wave * 2048 + lane * 4;
 #pragma unroll
@@ -391,23 +400,28 @@ __device__ __forceinline__ void fused_bf16_walk_64k(u64 first, u64 blocks, u64 s
 }
 
 static __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_fused_bf16_64k(PathArgs args) {
-  fused_bf16_walk_64k<4>(blockIdx.x, args.n_pad >> 16, gridDim.x, 0, args.total_out != nullptr, [&](u64 at, PathArgs& a) {
+  fused_bf16_walk_64k<4>(blockIdx.x, (uint32_t)(args.n_pad >> 16), gridDim.x, 0, args.total_out != nullptr, [&](uint32_t at, PathArgs& a) {
     a = args;
-    return at;
+    return (u64)at;
   });
 }
 static __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_fused_bf16_batched_64k(BatchArgs ba) {
-  fused_bf16_walk_64k<4>(blockIdx.x, ba.tile_start[ba.n], gridDim.x, 0, ba.totals != nullptr, [&](u64 at, PathArgs& a) { return bucket_of(ba, a, (uint32_t)at); });
+  int j = bucket_index(ba, blockIdx.x);   // onwards from there by scalar loads
+  fused_bf16_walk_64k<4>(blockIdx.x, ba.tile_start[ba.n], gridDim.x, 0, ba.totals != nullptr, [&](uint32_t at, PathArgs& a) {
+    while (j + 1 < ba.n && ba.tile_start[j + 1] <= at) ++j;
+    bucket_args(ba, a, j);
+    return (u64)(at - ba.tile_start[j]);
+  });
 }
 // 4 / NQ workgroups a block, on one XCD (blockIdx modulo 8) next to each other: they read the same entries
 template <int NQ>
 static __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_fused_bf16_split_64k(PathArgs args) {
   const unsigned slot = blockIdx.x >> 3;
-  const u64 blocks = args.n_pad >> 16, blk = (u64)(slot / (4 / NQ)) * 8 + (blockIdx.x & 7);
+  const uint32_t blocks = (uint32_t)(args.n_pad >> 16), blk = slot / (4 / NQ) * 8 + (blockIdx.x & 7);
   if (blk >= blocks) return;
-  fused_bf16_walk_64k<NQ>(blk, blocks, 0, (int)(slot % (4 / NQ)) * NQ, args.total_out != nullptr, [&](u64 at, PathArgs& a) {
+  fused_bf16_walk_64k<NQ>(blk, blocks, 0, (int)(slot % (4 / NQ)) * NQ, args.total_out != nullptr, [&](uint32_t at, PathArgs& a) {
     a = args;
-    return at;
+    return (u64)at;
   });
 }
 static __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_decode_64k(PathArgs a) {

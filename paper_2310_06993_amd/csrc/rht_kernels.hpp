@@ -400,9 +400,18 @@ struct BatchArgs {
 
 static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
-// the bucket that unit x of the launch lies in, as the arguments of a single-bucket call; returns the tile inside it
+// bucket j of the launch as the arguments of a single-bucket call
+__device__ __forceinline__ void bucket_args(const BatchArgs& ba, PathArgs& a, int j) {
+  a = PathArgs{};
+  a.in = ba.b[j].in; a.masks = (const uint32_t*)ba.b[j].aux; a.count_in = (const uint8_t*)ba.b[j].aux;
+  a.out = ba.b[j].out; a.count_out = ba.b[j].count_out;
+  a.n = a.n_pad = ba.b[j].shard_len; a.seed = ba.b[j].seed; a.base = ba.b[j].base;
+  a.N = ba.N; a.k = ba.k; a.scale = ba.scale;
+  a.total_out = ba.totals ? ba.totals + ba.first + j : nullptr;
+}
+// the bucket that unit x of the launch lies in
 template <bool WALK = false>
-__device__ __forceinline__ u64 bucket_of(const BatchArgs& ba, PathArgs& a, uint32_t x) {
+__device__ __forceinline__ int bucket_index(const BatchArgs& ba, uint32_t x) {
   // buckets that end at or before tile x: one comparison a lane (a walk over the descriptors was up to 60 dependent
   // scalar loads ahead of a workgroup's first access).  us, walk -> that, 64 buckets: finalize + decode 2^14 19.2 -> 14.7, reduce +
   // decode bf16 2^11 26.2 -> 17.8; but reduce + decode fp32 with its data in the cache 2^14 37.5 -> 42.6, 2^10 16 buckets 14.5 ->
@@ -414,12 +423,13 @@ __device__ __forceinline__ u64 bucket_of(const BatchArgs& ba, PathArgs& a, uint3
     const int lane = lane_id();
     j = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane + 1 < ba.n && ba.tile_start[lane + 1] <= x));
   }
-  a = PathArgs{};
-  a.in = ba.b[j].in; a.masks = (const uint32_t*)ba.b[j].aux; a.count_in = (const uint8_t*)ba.b[j].aux;
-  a.out = ba.b[j].out; a.count_out = ba.b[j].count_out;
-  a.n = a.n_pad = ba.b[j].shard_len; a.seed = ba.b[j].seed; a.base = ba.b[j].base;
-  a.N = ba.N; a.k = ba.k; a.scale = ba.scale;
-  a.total_out = ba.totals ? ba.totals + ba.first + j : nullptr;
+  return j;
+}
+// its arguments; returns the tile inside it
+template <bool WALK = false>
+__device__ __forceinline__ u64 bucket_of(const BatchArgs& ba, PathArgs& a, uint32_t x) {
+  const int j = bucket_index<WALK>(ba, x);
+  bucket_args(ba, a, j);
   return x - ba.tile_start[j];
 }
 
