@@ -273,6 +273,38 @@ def test_totals_of_shards_that_end_inside_a_tile(b, k, N, tiles, kind):
             assert int(totals[j]) == int(cnt.sum(dtype=torch.int64)) == N * L - dropped[j], (j, L)
 
 
+@pytest.mark.parametrize("kind,k,N", [("bf16", 9, 4), ("bf16", 10, 3), ("bf16", 5, 1), ("f32", 8, 3), ("f32", 9, 5)])
+@pytest.mark.parametrize("tiles", [2047, 2048, 2049, 2050])
+def test_totals_where_tiles_share_a_workgroup(b, kind, k, N, tiles):
+    """Blocks of up to 2^10 with totals, every worker by itself: from 2048 tiles on four of them share a workgroup, below that other
+    forms serve them.  Buckets of 1, 2 and 3 modulo 4 tiles, a bucket of one tile, last tiles cut short where blocks are smaller than a
+    tile; two entries lost in every bucket, and in the largest something in nearly every tile.  Totals against the counts and against
+    what was dropped; results and counts, bit for bit, as from a call for each bucket."""
+    dt = torch.float32 if kind == "f32" else torch.bfloat16
+    B, T, seed = 1 << k, 1024, 0x7777123456789ABC
+    parts = [601, 514, 303, 1]
+    parts.insert(1, tiles - sum(parts))
+    gen = torch.Generator(device=dev()).manual_seed(k * 100 + tiles)
+    items, lost = [], []
+    for j, n in enumerate(parts):
+        L = n * T - (T - B if j % 2 and B < T else 0)
+        g = (torch.randn((N, L), device=dev(), generator=gen) * 1e-3).to(dt)
+        m = torch.full((N, L // 32), -1, dtype=torch.int32, device=dev())
+        m[N - 1, 0] &= -4                        # two entries, at the start
+        if n == max(parts):
+            m[0, 12::24] = 0                     # every 24th run of 32; a tile has 32
+        lost.append(N * L - int(np.unpackbits(to_np(m).view(np.uint8)).sum()))
+        items.append((g, m, torch.full((L,), float("nan"), dtype=dt, device=dev()), torch.full((L,), 255, dtype=torch.uint8, device=dev()), L,
+                      seed + j, j << 20))
+    totals = torch.full((len(parts),), -1, dtype=torch.int64, device=dev())
+    b.or_fused_path_batched_monitored(b.make_buckets(items), len(parts), N, k, kind == "bf16", totals, None)
+    for j, (g, m, out, cnt, L, s, base) in enumerate(items):
+        assert totals[j].item() == N * L - lost[j] == cnt.long().sum().item(), j
+        one, cnt1 = torch.full_like(out, float("nan")), torch.full_like(cnt, 255)
+        (b.or_fused_path if kind == "f32" else b.or_fused_path_bf16)(g, m, N, L, k, s, base, one, cnt1, None)
+        assert torch.equal(one.view(torch.uint8), out.view(torch.uint8)) and torch.equal(cnt1, cnt), j
+
+
 @pytest.mark.parametrize("kind", ["f32", "bf16"])
 def test_results_in_the_part_of_the_workspace_that_only_an_earlier_bucket_used(b, kind):
     """A long bucket, then a short one whose results lie behind its own share of the workspace: as with results elsewhere."""
