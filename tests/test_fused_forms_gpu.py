@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from _util import TOL, dev, masks_to_dev, rel_l2, to_np
+from _util import TOL, as_f64, dev, masks_to_dev, rel_l2, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -18,6 +18,16 @@ def b():
 def _workspace(b, L, k):
     n = b.or_workspace_bytes(L, k)
     return torch.empty(n, dtype=torch.uint8, device=dev()) if n else None
+
+
+def _assert_close(got, want, kind, where):
+    """As a whole, and entry by entry, which a block's norm does not show: two bf16 results of the same value are at most one step apart,
+    2^-7 of the value, twice that with what their encoded values' roundings add (a step of a few among B, spread over the block); fp32
+    results eight times the tolerance's rms."""
+    assert rel_l2(got, want) <= TOL[kind], where
+    g, w = as_f64(got), as_f64(want)
+    rms, step = np.sqrt(np.mean(w * w)), 2.0 ** -6 if kind == "bf16" else 8 * TOL["f32"]
+    assert (np.abs(g - w) <= step * (np.abs(w) + rms)).all(), where
 
 
 @pytest.mark.parametrize("loss", [0.0, 0.02, 0.4])
@@ -49,7 +59,7 @@ def test_forms_against_the_oracle(b, orc, k, N, blocks, loss):
         want, wcnt = orc.fused_path(to_np(x[:, part].contiguous()), np.ascontiguousarray(words[:, j * B // 32:(j + 1) * B // 32]), k,
                                     seed, base + j * B)
         assert np.array_equal(to_np(cnt[part]), wcnt), j
-        assert rel_l2(to_np(out[part]), want) <= TOL["bf16"], j
+        _assert_close(to_np(out[part]), want, "bf16", j)
     again, cnt2 = torch.full_like(out, float("nan")), torch.full_like(cnt, 255)
     totals = torch.full((1,), -1, dtype=torch.int64, device=dev())
     b.or_fused_path_batched_monitored(b.make_buckets([(x, md, again, cnt2, L, seed, base)]), 1, N, k, True, totals, ws)
@@ -80,7 +90,7 @@ def test_fp32_large_blocks_against_the_oracle(b, orc, k, N, blocks, loss):
         want, wcnt = orc.fused_path(to_np(x[:, part].contiguous()), np.ascontiguousarray(words[:, j * B // 32:(j + 1) * B // 32]), k,
                                     seed, base + j * B)
         assert np.array_equal(to_np(cnt[part]), wcnt), j
-        assert rel_l2(to_np(out[part]), want) <= TOL["f32"], j
+        _assert_close(to_np(out[part]), want, "f32", j)
     again, cnt2 = torch.full((2, L), float("nan"), device=dev()), torch.full((2, L), 255, dtype=torch.uint8, device=dev())
     totals = torch.full((2,), -1, dtype=torch.int64, device=dev())
     b.or_fused_path_batched_monitored(b.make_buckets([(x, md, again[j], cnt2[j], L, seed, base) for j in range(2)]), 2, N, k, False, totals, ws)
@@ -145,9 +155,53 @@ def test_side_by_side_groups_against_the_oracle(b, orc, kind, k, N, L, loss):
         want, wcnt = orc.fused_path(to_np(x[:, part].contiguous()), np.ascontiguousarray(words[:, part.start // 32:part.stop // 32]), k,
                                     seed, base + lo)
         assert np.array_equal(to_np(cnt[part]), wcnt), lo
-        assert rel_l2(to_np(out[part]), want) <= TOL[kind], lo
+        _assert_close(to_np(out[part]), want, kind, lo)
     again, cnt2 = torch.full_like(out, float("nan")), torch.full((L,), 255, dtype=torch.uint8, device=dev())
     totals = torch.full((1,), -1, dtype=torch.int64, device=dev())
     b.or_fused_path_batched_monitored(b.make_buckets([(x, md, again, cnt2, L, seed, base)]), 1, N, k, not f32, totals, None)
     assert torch.equal(again.view(torch.uint8), out.view(torch.uint8)) and torch.equal(cnt2, cnt)
     assert totals.item() == cnt2.long().sum().item()
+
+
+@pytest.mark.parametrize("k,blocks", [(10, 2), (11, 2), (11, 600), (12, 2), (12, 600), (13, 2), (13, 600), (14, 2), (14, 300), (15, 2), (16, 1), (16, 66), (16, 130)])
+def test_bf16_subnormals_and_infinities(b, orc, k, blocks):
+    """What additions give, where the first stages are a matrix product: subnormal entries count, an infinite entry that arrived makes its
+    block infinite or NaN as it does in the oracle, and nothing else.
+
+    u = 2^-133, the lowest bf16.  The inputs are multiples of it up to 127 u, encoded values stay below 2^9 u, where bf16 is spaced 2 u: the
+    oracle and the kernel (which may scale after the rounding) each move an encoded value by at most u, i.e. by u / sqrt(3) rms.  A decoded
+    value is the mean of 3 with a sum of signs: the two differ by sqrt(2 / 9) u rms, 2.9 u at six times that, and by at most u more for each
+    of the results' own roundings."""
+    B, L, N, u = 1 << k, blocks << k, 3, 2.0 ** -133
+    gen = torch.Generator(device=dev()).manual_seed(50 + k)
+    x = torch.randint(-127, 128, (N, L), device=dev(), generator=gen).float().mul_(u).to(torch.bfloat16)
+    words = np.full((N, L // 32), 0xFFFFFFFF, dtype=np.uint32)
+    words[1, 1::7] = 0x0FFF0FFF
+    md, seed, base = masks_to_dev(words), 0x0FEDCBA987654321, (1 << 33) + 4 * B
+    out, cnt, enc = torch.empty_like(x[0]), torch.empty(L, dtype=torch.uint8, device=dev()), torch.empty_like(x[0])
+    ws = _workspace(b, L, k)
+
+    def both(j):
+        part = slice(j * B, (j + 1) * B)
+        want, wcnt = orc.fused_path(to_np(x[:, part].contiguous()), np.ascontiguousarray(words[:, j * B // 32:(j + 1) * B // 32]), k, seed, base + j * B)
+        assert np.array_equal(to_np(cnt[part]), wcnt)
+        wenc = orc.rht_encode(to_np(x[2, part].contiguous()), k, seed, base + j * B)
+        return as_f64(to_np(out[part])), as_f64(want), as_f64(to_np(enc[part])), as_f64(wenc)
+
+    def run():
+        b.or_fused_path_bf16(x, md, N, L, k, seed, base, out, cnt, ws)
+        b.or_rht_encode_bf16(x[2].contiguous(), L, k, seed, base, enc)
+
+    run()
+    for j in {0, blocks - 1}:
+        got, want, genc, wenc = both(j)
+        assert np.abs(want).max() > 40 * u and np.abs(got - want).max() <= 5 * u, j
+        assert np.abs(genc - wenc).max() <= 2 * u and (genc != wenc).mean() < 0.02, j      # the other side of a rounding boundary now and then
+    x.normal_(generator=gen)
+    x[2, 7], x[0, L - 1] = float("inf"), -float("inf")
+    run()
+    for j in {0, blocks - 1}:
+        for got, want in (both(j)[:2], both(j)[2:]):
+            assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[np.isinf(got)], want[np.isinf(want)]), j
+    if blocks > 2:
+        assert bool(torch.isfinite(out[B:-B]).all())
