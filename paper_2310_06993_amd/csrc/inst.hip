@@ -114,7 +114,8 @@ constexpr bool kMaySumFirst = K == 0 || K == 11;
   return tiles <= 512;
 }
 // The second tile buffer of k_fused_each (same bits with and without) pays up to three workgroups on a CU.  (Tiles of 8 or 16
-// wavefronts, at most two workgroups on a CU whatever the grid: always.)
+// wavefronts, at most two workgroups on a CU whatever the grid: always.  K = 0: launches that small encode workers side by side, which
+// leaves the case of one worker.  It has no next one, and yet this form is the shorter chain: fp32 2^8, 64 tiles 4.07 -> 3.95.)
 [[maybe_unused]] bool prefetch_wins(unsigned long long tiles) { return G::W >= 8 || tiles <= 3 * 256; }
 template <bool SPLIT>   // blocks below 2^10, several to a tile
 hipError_t sum_first(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
@@ -126,6 +127,9 @@ hipError_t sum_first(const PathArgs& a, unsigned long long units, hipStream_t s,
 // where the shorter chain is worth the trip of the encoded values through LDS.  us, without -> with:
 //   bf16 2^10 and below: 2^10, N = 8, 64 tiles 12.9 -> 6.0, 1024 tiles 16.8 -> 13.3, 2048 tiles 18.8 -> 24.8; N = 32, 1024 tiles 54.9 ->
 //     34.2 with eight groups (sixteen: 44.6); 2^9, N = 16, 50 tiles 22.0 -> 7.5 with sixteen (eight: 8.3); N = 2, 1024 tiles 6.2 -> 6.2
+//     Five to seven workers in more than 512 tiles: two rounds of four.  Eight -> four: N = 5, 600 / 1024 tiles 10.4 -> 9.1 / 12.5 -> 10.4,
+//     N = 7 10.8 -> 9.7 / 13.1 -> 11.0; with totals and 5 % loss N = 5 14.1 -> 13.8 / 17.5 -> 16.9 (eight tiles a workgroup one after the
+//     other 15.0 / 16.0: fewer atomics; with 1 % loss 15.8 against 12.8).
 //   fp32 below 2^10 (two to five workers): N = 4, 1024 tiles 8.3 -> 6.2, 2048 tiles 10.0 -> 7.8; N = 5, 3000 tiles 12.5 -> 16.9
 //   fp32 2^11 (two to five): N = 4, 64 tiles 6.3 -> 5.5, 256 tiles 6.6 -> 5.8; N = 3 5.6 -> 5.5; N = 2 5.0 -> 5.2; N = 5, 300 tiles 8.2 -> 9.4
 //   fp32 2^12: N = 16, 100 tiles 19.4 -> 16.3, 200 tiles 19.5 -> 17.9; N = 32, 8 tiles 34.5 -> 26.3; N = 8, 128 tiles 11.4 -> 10.8, 256 tiles
@@ -134,7 +138,7 @@ hipError_t sum_first(const PathArgs& a, unsigned long long units, hipStream_t s,
 constexpr int kEachGroups = K == 0 ? 16 : K == 11 || K == 12 ? 4 : 1;
 [[maybe_unused]] int each_groups(unsigned long long tiles, int N) {
   int most = 1;
-  if (K == 0) most = tiles <= 256 ? 16 : tiles <= 1024 ? 8 : 1;
+  if (K == 0) most = tiles <= 256 ? 16 : tiles <= 512 ? 8 : tiles <= 1024 ? (N <= 7 ? 4 : 8) : 1;
   if (K == 11 && (N == 3 || N == 4) && tiles <= 256) most = 4;
   if (K == 12 && tiles <= (N >= 12 ? 200 : 128) && N >= 8) most = 4;
   int g = 1;
@@ -192,7 +196,8 @@ hipError_t sum_first(const BatchArgs& a, unsigned long long units, hipStream_t s
 }
 template <class In, int SLOTS>
 hipError_t launch_each(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
-  if (prefetch_wins(units)) return launch_slots<SLOTS>(k_fused_each_batched<K, In, true, SLOTS>, G::THREADS, a, units, s, pos);
+  if constexpr (SLOTS != 4)   // launches of more tiles
+    if (prefetch_wins(units)) return launch_slots<SLOTS>(k_fused_each_batched<K, In, true, SLOTS>, G::THREADS, a, units, s, pos);
   if constexpr (G::W < 8) return launch_slots<SLOTS>(k_fused_each_batched<K, In, false, SLOTS>, G::THREADS, a, units, s, pos);
   return hipErrorInvalidValue;   // not reached
 }
@@ -210,11 +215,11 @@ hipError_t fused_batched(const BatchArgs& a, unsigned long long units, hipStream
   if constexpr (most > 1)
     if (const int g = each_groups(units, a.N); g > 1) return launch_each_groups<In, most>(g, a, units, s, pos);
   // K = 0 with totals, tiles a workgroup: eight share an atomic, four come and go more evenly, which is worth more in launches that
-  // fill the chip.  us, eight -> four: bf16 2^9, N = 2, 2049 / 51201 tiles 15.2 -> 12.2 / 165 -> 145, N = 8, 2049 / 12801 tiles 36.3 ->
-  // 28.4 / 124 -> 104, N = 16, 1025 / 6401 tiles 36.6 -> 40.1 / 128 -> 107;  fp32 2^9, N = 3, 17067 tiles 84 -> 68.  (Two: N = 5, 5 % loss, 3277
-  // tiles 30 -> 37; four 30 -> 31, the one size where eight were better.)
+  // leave an uneven number of eights on a CU.  us, eight -> four: bf16 2^9, N = 8, 1 % loss, 2048 / 2200 / 6400 / 12800 tiles 22.5 -> 22.7 / 30.6 ->
+  // 25.3 / 53.9 -> 48.5 / 88 -> 81, 5 % loss 23.2 -> 24.0 / 31.7 -> 27.6 / 55.7 -> 50.6 / 91 -> 84;  N = 4, 5 % loss, 2048 / 3277 / 12800 tiles
+  // 15.7 -> 17.0 / 21.0 -> 23.5 / 55 -> 53;  fp32 2^9, N = 3, 12800 tiles, 1 / 5 % loss 46 -> 44 / 47 -> 52.
   if constexpr (K == 0) {
-    if (a.totals && units >= 2048) return launch_each<In, 4>(a, units, s, pos);
+    if (a.totals && units > 2048) return launch_each<In, 4>(a, units, s, pos);
     if (a.totals) return launch_each<In, 8>(a, units, s, pos);
   }
   return launch_each<In, 1>(a, units, s, pos);

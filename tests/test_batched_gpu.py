@@ -276,7 +276,7 @@ def test_totals_of_shards_that_end_inside_a_tile(b, k, N, tiles, kind):
 @pytest.mark.parametrize("kind,k,N", [("bf16", 9, 4), ("bf16", 10, 3), ("bf16", 5, 1), ("f32", 8, 3), ("f32", 9, 5)])
 @pytest.mark.parametrize("tiles", [2047, 2048, 2049, 2050])
 def test_totals_where_tiles_share_a_workgroup(b, kind, k, N, tiles):
-    """Blocks of up to 2^10 with totals, every worker by itself: from 2048 tiles on four of them share a workgroup, below that other
+    """Blocks of up to 2^10 with totals, every worker by itself: above 2048 tiles four of them share a workgroup, up to there eight or other
     forms serve them.  Buckets of 1, 2 and 3 modulo 4 tiles, a bucket of one tile, last tiles cut short where blocks are smaller than a
     tile; two entries lost in every bucket, and in the largest something in nearly every tile.  Totals against the counts and against
     what was dropped; results and counts, bit for bit, as from a call for each bucket."""
