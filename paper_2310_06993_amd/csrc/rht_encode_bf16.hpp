@@ -2,7 +2,8 @@
 // and exchange as in rht_fused_bf16.hpp.
 //
 // Bound by memory (a large copy: 5.2 TB/s).  us, stages one by one with 2 bytes a lane per access -> this: 2^12, 13.1e6 entries 14.4 ->
-// 11.4 (4.6 TB/s), 210e6 153 -> 130 (6.5 TB/s);  2^11, 210e6 149 -> 131;  2^13 157 -> 130;  2^14, one ragged block 4.6 -> 3.9, 131e3 4.9 -> 4.1, 13.1e6 15.9 -> 12.4,
+// 11.4 (4.6 TB/s), 210e6 153 -> 130 (6.5 TB/s);  2^11, 210e6 149 -> 131;  2^13 157 -> 130;
+// one ragged block of 2^11 / 2^12 / 2^13 / 2^14 2.60 -> 2.70, 2.81 -> 2.87, 3.43 -> 3.20, 4.6 -> 3.9, 131e3 4.9 -> 4.1, 13.1e6 15.9 -> 12.4,
 // 210e6 167 -> 136.
 #pragma once
 #include "rht_fused_bf16.hpp"
@@ -57,8 +58,10 @@ __device__ __forceinline__ void encode_bf16_block(const PathArgs& a, u64 blk, fl
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(other, own, pick), out, at, (r >> 1) << (K - 3), kBufNt);
   }
 }
+// (four wavefronts: with more registers the compiler lets the products end in accumulation registers, and every value is copied from
+// there; one block of 2^11 / 2^12 / 2^13 2.52 -> 2.47, 2.74 -> 2.70, 3.20 -> 3.11)
 template <int K>
-__global__ __launch_bounds__(MTile<K>::THREADS) void k_encode_bf16(PathArgs a) {
+__global__ __launch_bounds__(MTile<K>::THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_encode_bf16(PathArgs a) {
   __shared__ __align__(16) float x[MTile<K>::T];
   if (blockIdx.x < a.unit0) encode_bf16_block<K, true>(a, blockIdx.x, x);
   else encode_bf16_block<K, false>(a, blockIdx.x, x);
