@@ -266,17 +266,21 @@ hipError_t fusb_f32(const BatchArgs& a, unsigned long long units, hipStream_t s,
 constexpr int kGroupsBf16 = K == 11 ? 8 : 16 / MTile<K>::W;
 // How many groups of wavefronts encode workers side by side (1: none; the same bits)?  As many as there are workers for, in launches
 // that leave CUs idle or leave room on them.  us, without -> with: 2^11, N = 8, 64 blocks 11.6 -> 6.9, 512 blocks 12.7 -> 9.6 (1024:
-// 13.9 -> 16.6), N = 3, 100 blocks 7.0 -> 6.3;  2^12, N = 8, 64 blocks 13.2 -> 8.9, 512 blocks 17.1 -> 13.9 with
-// four groups (eight: 18.2), N = 3, 100 blocks 7.8 -> 7.0;  2^13, N = 8, 64 blocks 15.9 -> 13.0, 512 blocks 20.1 ->
+// 13.9 -> 16.6), N = 3, 100 blocks 7.0 -> 6.3;  2^12, N = 8, 64 blocks 13.2 -> 8.9;  2^13, N = 8, 64 blocks 15.9 -> 13.0, 512 blocks 20.1 ->
 // 28.7;  2^14, N = 32, 2 blocks 65.5 -> 59.1, N = 8, 64 blocks 21.2 -> 20.5, 256 blocks 22.0 -> 23.2, N = 3, 100 blocks 11.7 -> 13.3.
-// Two groups, which share the decode too (mt_decode_shared): N = 2, 2^11, 65 blocks 6.0 -> 5.3, 2^12, 17 / 512 blocks 6.6 -> 5.7 / 8.8 ->
-// 7.4 (700: 9.3 -> 9.2), 2^13, 65 / 384 blocks 7.6 -> 7.3 / 9.9 -> 10.9;  N = 3, 2^13, 17 / 384 blocks 8.8 -> 8.7 / 11.6 -> 13.3;  instead of four
-// groups: 2^12, N = 3, 257 / 384 blocks 7.2 / 9.8 -> 7.5 / 9.0, N = 4, 384 / 512 blocks 10.5 / 11.0 -> 9.6 / 9.9, 2^11, N = 3, 384 blocks 7.0 -> 7.5.
+// Two groups, up to 2^13, have a form of their own (fused_bf16_pair), which is the shorter chain for few workers and leaves room for a third
+// workgroup on a CU.  us, 5 % loss: 2^11, N = 2, 65 blocks 5.3 -> 4.8, none -> it 512 blocks 6.5 -> 6.3;  2^12, four groups -> it, N = 3, 65 blocks 6.9 ->
+// 6.9 (nothing lost 5.6 -> 5.9), N = 4, 129 / 300 blocks 7.4 -> 7.3 / 9.1 -> 8.5, N = 8, 300 / 512 blocks 13.2 -> 13.1 / 15.1 -> 14.1, N = 16, 300 / 512 blocks 20.4 -> 22.7 / 22.1 -> 23.4, none -> it, N = 3, 513 /
+// 768 blocks 10.3 -> 9.4 / 10.9 -> 10.4, N = 16, 513 / 768 blocks 31.6 -> 26.4 / 33.4 -> 30.3;  2^13, four groups -> it, N = 4, 16 / 129 blocks 9.4 ->
+// 8.4 / 10.1 -> 8.9, N = 6, 64 / 256 blocks 12.2 -> 11.6 / 14.1 -> 12.2, N = 8, 64 / 256 blocks 13.4 -> 13.7 / 15.5 -> 14.4.
+bool pair_wins(unsigned long long blocks, int N) {
+  if (K == 11) return N <= 2 && blocks <= (N == 1 ? 256 : 512);
+  if (K == 12) return blocks <= 256 ? N <= 2 : blocks <= 512 ? N <= 8 : blocks <= 768 && N > 1;
+  return K == 13 && N <= 6 && blocks <= 256;
+}
 int groups_bf16(unsigned long long blocks, int N) {
   int most = kGroupsBf16;
-  if (K <= 13 && N == 2) return blocks <= (K == 13 ? 256 : 512) ? 2 : 1;
-  if (K == 13 && N == 3) return blocks <= 256 ? 2 : 1;
-  if (K == 12 && (N == 3 || N == 4) && blocks > 256) return blocks <= 512 ? 2 : 1;
+  if (pair_wins(blocks, N)) return 2;
   if (N < (K <= 12 ? 3 : K == 13 ? 4 : 6)) return 1;
   if (blocks > (K == 14 ? 128 : 256)) most = K == 11 ? 8 : K == 12 && blocks <= 512 ? 4 : 1;
   if (blocks > 512) most = 1;

@@ -19,8 +19,9 @@
 // by one -> this: 2^14, N = 8, 2556 blocks, 2 % loss in bursts 230 -> 165 (5.1 TB/s), 5 % in single packets 241 -> 177;  2^15, N = 8,
 // 1280 blocks 258 -> 196;  2^13, N = 8, 5000 blocks 209 -> 153;  2^12, N = 16, 10000 blocks 375 -> 271, N = 2 74 -> 54;  2^11, N = 8,
 // 20000 blocks 195 -> 142.  Two workers in flight instead of one: 164 -> 170.
-// The price is a longer decode, which has half as many wavefronts: with few workers launches of few blocks gain nothing (2^12, N = 2,
-// 129 blocks 5.9 -> 6.0 where both groups decode) or lose (2^12, N = 3, 512 blocks 9.0 -> 9.5; 2^13, N = 3, 65 blocks 8.4 -> 8.9).
+// The price is a longer decode, which has half as many wavefronts; in launches of few blocks and workers two groups share it
+// (fused_bf16_pair): 2^12, N = 2, 129 blocks 5.7 -> 5.6;  2^13, N = 3, 65 blocks 8.3 -> 8.2.  Those that still lose: 2^12, N = 3, 5 % loss, 512
+// blocks 8.7 -> 8.9 .. 9.2;  a single worker, 65 blocks of 2^11 / 2^12 / 2^13 3.9 -> 4.1 / 4.2 -> 4.4 / 5.1 -> 5.3.
 #pragma once
 #include "rht_fused.hpp"
 
@@ -162,7 +163,14 @@ __device__ __forceinline__ void mt_mask(float (&v)[32], uint32_t words) {   // z
     v[r] = in_mask(m) ? v[r] : 0.0f;
   }
 }
-// counts of the lane's 32 entries, a byte each, over the workers first, first + step ..
+// counts of the lane's 32 entries, a byte each, from the received bits of four workers
+__device__ __forceinline__ void mt_add_counts(const uint32_t (&w)[4], uint32_t (&c8)[8]) {
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) c8[q] += (((w[u] >> (4 * q)) & 0xFu) * 0x00204081u) & 0x01010101u;
+}
+// .. over the workers first, first + step ..
 template <int K>
 __device__ __forceinline__ void mt_recount(const PathArgs& a, u64 e0, int first, int step, int wave, int lane, uint32_t (&c8)[8]) {
 #pragma unroll
@@ -171,11 +179,24 @@ __device__ __forceinline__ void mt_recount(const PathArgs& a, u64 e0, int first,
     uint32_t w[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) w[u] = mt_words<K>(a, e0, i + u * step, wave, lane);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) c8[q] += (((w[u] >> (4 * q)) & 0xFu) * 0x00204081u) & 0x01010101u;
+    mt_add_counts(w, c8);
   }
+}
+// .. over all of them, where the received bits of the last four are at hand: with no more of them a chain without another trip to memory
+template <int K>
+__device__ __forceinline__ void mt_recount(const PathArgs& a, u64 e0, int wave, int lane, const uint32_t (&kept)[4], uint32_t (&c8)[8]) {
+  if (a.N > 4) {
+    mt_recount<K>(a, e0, 0, 1, wave, lane, c8);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) c8[q] = 0;
+    mt_add_counts(kept, c8);
+  }
+}
+__device__ __forceinline__ void mt_keep(uint32_t (&kept)[4], uint32_t words) {
+#pragma unroll
+  for (int u = 3; u > 0; --u) kept[u] = kept[u - 1];
+  kept[0] = words;
 }
 template <int K>
 __device__ __forceinline__ void mt_store_counts(const PathArgs& a, u64 e0, int wave, int lane, const uint32_t (&c8)[8]) {
@@ -399,22 +420,19 @@ __device__ __forceinline__ void fused_bf16_tile(const PathArgs& a, u64 unit) {
 
 // For launches that leave CUs idle: G groups of W wavefronts encode G workers side by side.  The encoded values go through LDS as
 // the bf16 pairs that they are, and group g adds those of its share of the registers over the workers, in order: the same
-// operations in the same order as above.  Group 0 decodes; of two groups (up to 2^13) both.
+// operations in the same order as above.  Group 0 decodes.  (Two groups up to 2^13: fused_bf16_pair.)
 template <int K, int G, bool TOTAL>
 __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
   typedef MTile<K> M;
   constexpr int W = M::W, T = M::T, R = M::R, D = 16 / G;   // D: pairs of a lane and a share
   static_assert(G >= 2 && G <= 16, "a share is at least a pair");
-  constexpr bool SHARED = G == 2 && K <= 13;
   __shared__ __align__(16) float x[G][T];
-  __shared__ __align__(16) uint8_t sign_bytes[SHARED ? T / 8 : 16];
   __shared__ uint32_t missing, lossy;   // lossy: something was lost somewhere in the block
   const int wave_all = wave_id(), lane = lane_id(), N = a.N, grp = wave_all / W, wave = wave_all % W;
   const u64 e0 = unit * T, ew = e0 + (u64)wave * 2048;
   InFlight f;
   mt_request<K>(a, e0, grp, wave, lane, f);
-  // (SHARED: both groups write the same bytes to the same place)
-  const uint32_t signs = mt_signs(a.seed, a.base + ew, SHARED ? sign_bytes + wave * 256 : (uint8_t*)(x[grp] + wave * 2048), lane);
+  const uint32_t signs = mt_signs(a.seed, a.base + ew, (uint8_t*)(x[grp] + wave * 2048), lane);
   Operand h = mt_operand(lane);
   if (TOTAL && threadIdx.x == 0) missing = 0;   // behind barriers when it is added to
   float acc[2 * D];
@@ -423,10 +441,10 @@ __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
   if (threadIdx.x == 0) lossy = 0;
   typedef uint32_t pairs_t __attribute__((ext_vector_type(D < 4 ? D : 4)));
   constexpr int V = D < 4 ? D : 4;   // pairs of one access to LDS
+  uint32_t words = 0;   // received bits of the group's worker in work
   for (int first = 0; first < N; first += G) {
     const bool works = first + grp < N;
     float v[R];
-    uint32_t words = 0;
     if (works) {
       mt_encode_s1(f.q, signs, h, v);
       words = f.words;
@@ -475,10 +493,7 @@ __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
   if (lossy == 0) {
     const float f = post * __builtin_amdgcn_rcpf((float)N);
 #pragma unroll
-    for (int r = 0; r < 2 * D; ++r) {
-      if constexpr (SHARED) acc[r] *= f;
-      else means[(wave * R + grp * 2 * D + r) * 64 + lane] = acc[r] * f;
-    }
+    for (int r = 0; r < 2 * D; ++r) means[(wave * R + grp * 2 * D + r) * 64 + lane] = acc[r] * f;
     if (grp == 0) {
       uint32_t c8[8];
 #pragma unroll
@@ -487,10 +502,15 @@ __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
     }
     if (TOTAL && a.total_out && threadIdx.x == 0) add_total(a, unit == 0, 0);
   } else {   // the group's workers, then all of them
-    uint32_t* counts = (uint32_t*)&x[SHARED ? 1 : 0][0];   // [group][wavefront][lane][8]
+    uint32_t* counts = (uint32_t*)&x[0][0];   // [group][wavefront][lane][8]
     static_assert(G * W * 512 + T <= G * T, "counts and means fit");
-    uint32_t c8[8];
-    mt_recount<K>(a, e0, grp, G, wave, lane, c8);
+    uint32_t c8[8] = {};
+    if (N <= G) {   // one round: they are at hand
+      const uint32_t one[4] = {words, 0, 0, 0};
+      mt_add_counts(one, c8);
+    } else {
+      mt_recount<K>(a, e0, grp, G, wave, lane, c8);
+    }
     *(uint4*)(counts + (wave_all * 64 + lane) * 8) = make_uint4(c8[0], c8[1], c8[2], c8[3]);
     *(uint4*)(counts + (wave_all * 64 + lane) * 8 + 4) = make_uint4(c8[4], c8[5], c8[6], c8[7]);
     lds_barrier<2>();
@@ -512,14 +532,8 @@ __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
 #pragma unroll
     for (int r = 0; r < 2 * D; ++r) {
       const int reg = grp * 2 * D + r;
-      const float m = mt_mean(acc[r], mt_count((const uint8_t*)(counts + wave * 512), reg, lane), post);
-      if constexpr (SHARED) acc[r] = m;
-      else means[(wave * R + reg) * 64 + lane] = m;
+      means[(wave * R + reg) * 64 + lane] = mt_mean(acc[r], mt_count((const uint8_t*)(counts + wave * 512), reg, lane), post);
     }
-  }
-  if constexpr (SHARED) {
-    mt_decode_shared<K>(acc, &x[0][0], sign_bytes, a, e0, grp, wave, lane);
-    return;
   }
   lds_barrier<2>();
   if (grp > 0) return;   // (a barrier waits for the wavefronts that are left)
@@ -529,6 +543,100 @@ __device__ __forceinline__ void fused_bf16_groups(const PathArgs& a, u64 unit) {
   lds_barrier<2>();
   mt_decode<K>(v, &x[0][0], wave, lane);
   mt_store(v, signs, a, ew, lane);
+}
+
+// Two groups of W wavefronts, for few workers (up to 2^13): a worker each at a time, half of the registers each in the sum and in the
+// decode, the same bits again.  A launch of few blocks is one chain from the first load to the last store, so every trip counts:
+// the pairs have a place in LDS of their own, which leaves two barriers a round, and every wavefront has the received bits of both
+// workers, so that counts and means need neither a barrier nor (up to four workers) another trip to memory.  us, four barriers a round and
+// the received bits read again -> this, 1 % loss: N = 2, 65 blocks, 2^11 5.3 -> 4.9, 2^12 5.9 -> 5.5, 2^13 7.2 -> 6.6.
+template <int K, bool TOTAL>
+__device__ __forceinline__ void fused_bf16_pair(const PathArgs& a, u64 unit) {
+  typedef MTile<K> M;
+  constexpr int W = M::W, T = M::T, R = M::R;
+  __shared__ __align__(16) float x[2][T];
+  __shared__ __align__(16) u32x4v pairs[2][W][4][64];
+  __shared__ __align__(16) uint8_t sign_bytes[T / 8];
+  __shared__ uint32_t missing;
+  const int wave_all = wave_id(), lane = lane_id(), N = a.N, grp = wave_all / W, wave = wave_all % W;
+  const u64 e0 = unit * T, ew = e0 + (u64)wave * 2048;
+  InFlight f;
+  mt_request<K>(a, e0, grp, wave, lane, f);
+  uint32_t other = mt_words<K>(a, e0, grp ^ 1, wave, lane);
+  // (both groups write the same bytes to the same place)
+  const uint32_t signs = mt_signs(a.seed, a.base + ew, sign_bytes + wave * 256, lane);
+  Operand h = mt_operand(lane);
+  if (TOTAL && threadIdx.x == 0) missing = 0;   // behind barriers when it is added to
+  float acc[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+  bool clean = true;   // nothing of this wavefront's S2 part was lost so far, from either group's workers
+  uint32_t kept[4] = {0, 0, 0, 0};
+  for (int first = 0; first < N; first += 2) {
+    const bool works = first + grp < N, whole = !works || all_arrived(f.words);
+    float v[R];
+    const uint32_t words = f.words;
+    clean = clean && whole && (first + (grp ^ 1) >= N || all_arrived(other));
+    mt_keep(kept, words);
+    mt_keep(kept, other);
+    if (works) mt_encode_s1(f.q, signs, h, v);
+    mt_request<K>(a, e0, first + 2 + grp, wave, lane, f);
+    other = mt_words<K>(a, e0, first + 2 + (grp ^ 1), wave, lane);
+    if (works) mt_store_s1(v, x[grp], wave, lane);
+    lds_barrier<2>();
+    if (works) {
+      mt_s2<K, false>(v, x[grp], wave, lane);
+      mt_encode_s2<K>(v, a.scale);
+      if (!whole) mt_mask(v, words);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        u32x4v t;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) t[d] = pack_bf16x2(v[8 * j + 2 * d], v[8 * j + 2 * d + 1]);
+        pairs[grp][wave][j][lane] = t;
+      }
+    }
+    lds_barrier<2>();   // the pairs are there; and everyone has read x
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      if (first + g < N) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const u32x4v t = pairs[g][wave][2 * grp + j][lane];
+#pragma unroll
+          for (int d = 0; d < 4; ++d) {
+            acc[8 * j + 2 * d] += bf16_lo(t[d]);
+            acc[8 * j + 2 * d + 1] += bf16_hi(t[d]);
+          }
+        }
+      }
+    }
+  }
+  // ---- counts, mean over what arrived
+  uint32_t c8[8];
+  const float post = K & 1 ? 1.0f : a.scale;
+  if (clean) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) c8[q] = (uint32_t)N * 0x01010101u;
+    const float f = post * __builtin_amdgcn_rcpf((float)N);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] *= f;
+  } else {
+    mt_recount<K>(a, e0, wave, lane, kept, c8);
+    uint8_t* mine = (uint8_t*)x[1] + wave_all * 2048;
+    *(uint4*)(mine + lane * 32) = make_uint4(c8[0], c8[1], c8[2], c8[3]);
+    *(uint4*)(mine + lane * 32 + 16) = make_uint4(c8[4], c8[5], c8[6], c8[7]);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = mt_mean(acc[r], mt_count(mine, grp * 16 + r, lane), post);
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (grp == 0) {
+    mt_store_counts<K>(a, e0, wave, lane, c8);
+    if (TOTAL && a.total_out && !clean) mt_add_missing(c8, N, &missing, lane);
+  }
+  mt_decode_shared<K>(acc, &x[0][0], sign_bytes, a, e0, grp, wave, lane);
+  if (TOTAL && a.total_out && threadIdx.x == 0) add_total(a, unit == 0, missing);   // (complete since the decode's barrier)
 }
 
 template <int K>
@@ -543,15 +651,18 @@ void k_fused_bf16_batched(BatchArgs ba) {
   const u64 unit = bucket_of(ba, a, blockIdx.x);
   fused_bf16_tile<K, true>(a, unit);
 }
+// 128 registers: with more the compiler lets the products end in accumulation registers, and every value is copied from there
 template <int K, int G>
-__global__ __launch_bounds__(MTile<K>::THREADS * G) void k_fused_bf16_groups(PathArgs a) {
-  fused_bf16_groups<K, G, false>(a, blockIdx.x);
+__global__ __launch_bounds__(MTile<K>::THREADS * G) __attribute__((amdgpu_num_vgpr(128))) void k_fused_bf16_groups(PathArgs a) {
+  if constexpr (G == 2 && K <= 13) fused_bf16_pair<K, false>(a, blockIdx.x);
+  else fused_bf16_groups<K, G, false>(a, blockIdx.x);
 }
 template <int K, int G>
-__global__ __launch_bounds__(MTile<K>::THREADS * G) void k_fused_bf16_groups_batched(BatchArgs ba) {
+__global__ __launch_bounds__(MTile<K>::THREADS * G) __attribute__((amdgpu_num_vgpr(128))) void k_fused_bf16_groups_batched(BatchArgs ba) {
   PathArgs a;
   const u64 unit = bucket_of(ba, a, blockIdx.x);
-  fused_bf16_groups<K, G, true>(a, unit);
+  if constexpr (G == 2 && K <= 13) fused_bf16_pair<K, true>(a, unit);
+  else fused_bf16_groups<K, G, true>(a, unit);
 }
 
 }  // namespace ordev
