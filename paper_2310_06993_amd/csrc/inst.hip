@@ -323,20 +323,33 @@ hipError_t fusb_bf16(const BatchArgs& a, unsigned long long units, hipStream_t s
 #if OR_K == 16
 // A workgroup per block, or two or four that meet in the workspace (the same bits)?  A workgroup takes 7 to 8 us a worker, and takes
 // 4.5 / 3.3 us for a half / a quarter of the encoded values.  us, four / two / one workgroups a block: N = 8, 16
-// blocks 48 / 64 / 91, 64 blocks 52 / 67 / 93, 100 blocks 86 / 68 / 93, 128 blocks 88 / 70 / 94, 160 blocks 122 / 118 / 94;  N = 2, 64
-// blocks 30 / 34 / 39, 128 blocks 44 / 37 / 40;  N = 32, 2 blocks 136 / 190 / 297.
+// blocks 48 / 64 / 91, 64 blocks 52 / 65 / 92, 100 blocks 86 / 67 / 92, 128 blocks 88 / 68 / 92, 160 blocks 122 / 118 / 94;  N = 2, 64
+// blocks 30 / 34 / 37, 128 blocks 44 / 36 / 38;  N = 32, 2 blocks 136 / 190 / 297.  (With nothing lost two of them, which both read the whole block,
+// take 4.3 us a worker: N = 8, 100 blocks 57.)
+// The same for the blocks that a walk has over in its last round, in launches of their own behind it.  us, in the walk -> that: N = 8, 300 / 384
+// / 600 / 1100 blocks 181 -> 147 / 181 -> 166 / 272 -> 253 / 440 -> 427;  N = 32, 257 / 300 blocks 600 -> 458 / 622 -> 470;  N = 2, 300 / 384 blocks
+// 74.5 -> 69.3 / 75.0 -> 77.6;  N = 1, 300 / 384 blocks 45.4 -> 48.8 / 46.0 -> 56.7.
 constexpr unsigned long long kFourSplit = 64, kTwoSplit = 128;
 constexpr unsigned long long kWalkers = 256;   // workgroups that walk over the blocks: one fills a CU
 hipError_t fus_bf16(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
   const unsigned long long blocks = units >> G::HB;
   if (blocks == 0) return hipSuccess;
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  if (blocks > kTwoSplit) return launch_kernel(k_fused_bf16_64k, dim3((unsigned)(blocks < kWalkers ? blocks : kWalkers)), dim3(512), s, pos, a);
-  const unsigned eights = (unsigned)(blocks + 7) / 8 * 8;
-  if (hipError_t e = blocks <= kFourSplit ? launch_kernel(k_fused_bf16_split_64k<1>, dim3(eights * 4), dim3(512), s, pos & LAUNCH_FIRST, a)
-                                  : launch_kernel(k_fused_bf16_split_64k<2>, dim3(eights * 2), dim3(512), s, pos & LAUNCH_FIRST, a))
+  const unsigned long long over = blocks > kWalkers && a.N > 1 ? blocks % kWalkers : 0;
+  const unsigned long long split = blocks <= kTwoSplit ? blocks : over <= (a.N == 2 ? kFourSplit : kTwoSplit) ? over : 0;
+  PathArgs w = a;
+  w.unit0 = blocks - split;
+  if (w.unit0) {
+    const dim3 grid((unsigned)(w.unit0 < kWalkers ? w.unit0 : kWalkers));
+    if (hipError_t e = launch_kernel(k_fused_bf16_64k, grid, dim3(512), s, split ? pos & LAUNCH_FIRST : pos, w)) return e;
+    pos &= LAUNCH_LAST;
+  }
+  if (split == 0) return hipSuccess;
+  const unsigned eights = (unsigned)(split + 7) / 8 * 8;
+  if (hipError_t e = split <= kFourSplit ? launch_kernel(k_fused_bf16_split_64k<1>, dim3(eights * 4), dim3(512), s, pos & LAUNCH_FIRST, w)
+                                         : launch_kernel(k_fused_bf16_split_64k<2>, dim3(eights * 2), dim3(512), s, pos & LAUNCH_FIRST, w))
     return e;
-  return launch_kernel(k_decode_64k, dim3((unsigned)blocks), dim3(512), s, pos & LAUNCH_LAST, a);
+  return launch_kernel(k_decode_64k, dim3((unsigned)split), dim3(512), s, pos & LAUNCH_LAST, w);
 }
 hipError_t fusb_bf16(const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
   const unsigned long long blocks = units >> G::HB;

@@ -117,7 +117,7 @@ __device__ __forceinline__ void decode_64k(float (&acc)[4][32], float* x, u32x4v
 }
 
 // next(x, a): the arguments of the x-th block's bucket; returns the block inside it.  NQ = 4: the whole path, workgroups walk over the
-// blocks first, first + step ..  NQ = 1, 2: for launches of few blocks, one block's quarters quarter0 .. quarter0 + NQ - 1 (a quarter
+// blocks first, first + step ..  NQ = 1, 2: for few blocks (alone or behind a walk), one block's quarters quarter0 .. quarter0 + NQ - 1 (a quarter
 // or a half of them), up to the mean, which goes to a.mean_out for k_decode_64k: by quarter, wavefront, four registers, lane.
 template <int NQ, class Next>
 __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blocks, uint32_t step, int quarter0, bool totals, const Next& next) {
@@ -128,6 +128,10 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
   __shared__ __align__(16) u32x4v signs[512];   // of the lane's 16 loads: pair_signs of four loads each
   const int wave = wave_id(), lane = lane_id();
 
+  // NQ = 2 has registers for the loads that do not go through LDS: all are asked for in the first half of a worker, and none has to wait until
+  // the entries in work have been used.  us, 1 % loss, N = 4 / 8 / 32, 100 blocks 45.2 -> 44.7 / 68.0 -> 66.6 / 205 -> 199
+  constexpr bool EARLY = NQ == 2;
+  [[maybe_unused]] u32x4v rest[6];
   u32x4v p[16];   // load q: 8 entries from 512 q + 8 lane of the wavefront's part
   auto part_of = [&](const PathArgs& a, u64 blk, int i) { return (const bf16_t*)a.in + (u64)i * a.n_pad + (blk << 16) + (u64)wave * 8192; };
   // The loads that write LDS are out of the compiler's sight, which would
@@ -143,12 +147,13 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
   u32x4v mw;   // received bits of the worker whose entries are on their way
   auto landed = [&]() {   // names what the compiler knows to be in flight: it waits for that here and not behind the loads that follow
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    asm volatile("" : "+v"(p[10]), "+v"(p[11]), "+v"(p[12]), "+v"(p[13]), "+v"(p[14]), "+v"(p[15]), "+v"(mw));
+    if constexpr (EARLY) asm volatile("" : "+v"(rest[0]), "+v"(rest[1]), "+v"(rest[2]), "+v"(rest[3]), "+v"(rest[4]), "+v"(rest[5]), "+v"(mw));
+    else asm volatile("" : "+v"(p[10]), "+v"(p[11]), "+v"(p[12]), "+v"(p[13]), "+v"(p[14]), "+v"(p[15]), "+v"(mw));
   };
   auto request_rest = [&](const bf16_t* part, int from, int to_q) {   // null: zeros, without touching memory
     const __amdgpu_buffer_rsrc_t rs = rsrc_of(part, part ? 16384 : 0);
 #pragma unroll
-    for (int q = from; q < to_q; ++q) p[q] = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, q * 1024, kBufNt));
+    for (int q = from; q < to_q; ++q) (EARLY ? rest[q - kStaged] : p[q]) = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, q * 1024, kBufNt));
   };
   // received bits in S2: the wavefront's 1024 entries of each eighth of the block; lane l holds 128 entries (four words, e5 e6) of
   // eighth l >> 3, from 128 (l & 7) on
@@ -202,6 +207,10 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
       }
 #pragma unroll
       for (int q = 0; q < kStaged; ++q) p[q] = stage[(wave * kStaged + q) * 64 + lane_t];
+      if constexpr (EARLY) {
+#pragma unroll
+        for (int q = kStaged; q < 16; ++q) p[q] = rest[q - kStaged];
+      }
       const u32x4v sg = signs[wave * 64 + lane_t];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -250,9 +259,10 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
         }
         __builtin_amdgcn_sched_barrier(0);
         // a few loads at a time: a CU takes one of them (1 KB) in 16 cycles, and all wavefronts would wait for the last one's
-        constexpr int per = NQ == 1 ? kStaged : 5;
-        if (per * turn < kStaged && after) request_staged(after, per * turn, per * turn + 3);   // (none on their way when the workgroup ends)
-        if (turn == NQ - 1) request_rest(after, kStaged, kStaged + 3);   // the entries have been used for the last time
+        constexpr int per = NQ <= 2 ? kStaged : 5, at_once = EARLY ? 4 : 3;
+        if (per * turn < kStaged && after) request_staged(after, per * turn, per * turn + at_once);   // (none on their way when the workgroup ends)
+        if (turn == NQ - 1) request_rest(after, kStaged, EARLY ? 16 : kStaged + 3);   // the entries have been used for the last time
+        if (EARLY && turn == NQ - 1) request_words(words_after);
         // half of the registers at a time after the stage between the halves: the second half's stages run under the first half's stores
         reg_stage<4>(v);
         auto& va = *(float (*)[16])&v[0];
@@ -278,8 +288,8 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
         // Everyone has read the quarter.  Here, where all wavefronts are together anyway: from here to the next stores they may drift
         // apart, so that one's accesses to LDS run under another's arithmetic.
         lds_barrier<8>();
-        if (per * turn < kStaged && after) request_staged(after, per * turn + 3, per * turn + per);
-        if (turn == NQ - 1) {
+        if (per * turn < kStaged && after) request_staged(after, per * turn + at_once, per * turn + per);
+        if (!EARLY && turn == NQ - 1) {
           request_rest(after, kStaged + 3, 16);
           request_words(words_after);
         }
@@ -400,7 +410,7 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
 }
 
 static __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_fused_bf16_64k(PathArgs args) {
-  fused_bf16_walk_64k<4>(blockIdx.x, (uint32_t)(args.n_pad >> 16), gridDim.x, 0, args.total_out != nullptr, [&](uint32_t at, PathArgs& a) {
+  fused_bf16_walk_64k<4>(blockIdx.x, (uint32_t)args.unit0, gridDim.x, 0, args.total_out != nullptr, [&](uint32_t at, PathArgs& a) {
     a = args;
     return (u64)at;
   });
@@ -413,11 +423,11 @@ static __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2
     return (u64)(at - ba.tile_start[j]);
   });
 }
-// 4 / NQ workgroups a block, on one XCD (blockIdx modulo 8) next to each other: they read the same entries
+// The blocks from args.unit0 on; 4 / NQ workgroups a block, on one XCD (blockIdx modulo 8) next to each other: they read the same entries
 template <int NQ>
 static __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_fused_bf16_split_64k(PathArgs args) {
   const unsigned slot = blockIdx.x >> 3;
-  const uint32_t blocks = (uint32_t)(args.n_pad >> 16), blk = slot / (4 / NQ) * 8 + (blockIdx.x & 7);
+  const uint32_t blocks = (uint32_t)(args.n_pad >> 16), blk = (uint32_t)args.unit0 + slot / (4 / NQ) * 8 + (blockIdx.x & 7);
   if (blk >= blocks) return;
   fused_bf16_walk_64k<NQ>(blk, blocks, 0, (int)(slot % (4 / NQ)) * NQ, args.total_out != nullptr, [&](uint32_t at, PathArgs& a) {
     a = args;
@@ -427,7 +437,7 @@ static __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2
 static __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_decode_64k(PathArgs a) {
   __shared__ __align__(16) float x[1 << 14];
   const int wave = wave_id(), lane = lane_id();
-  const u64 e0 = (u64)blockIdx.x << 16;
+  const u64 e0 = (a.unit0 + blockIdx.x) << 16;
   float acc[4][32];
   const float* from = a.mean_out + e0 + wave * 2048 + lane * 4;
 #pragma unroll

@@ -29,13 +29,13 @@ struct PathArgs {
   const uint32_t* masks;   // [N][L/32]
   void* out;               // result vector
   uint8_t* count_out;      // may be null
-  float* mean_out;         // fused bf16 in blocks of 2^16, launches of few blocks: the means on their way to the decode
+  float* mean_out;         // fused bf16 in blocks of 2^16, blocks that several workgroups share: the means on their way to the decode
   unsigned long long* total_out;   // may be null: receives the number of (worker, entry) arrivals (Sec. 3.4 loss monitoring)
   u64 n;                   // valid entries of the input (encode) / output (decode)
   u64 n_pad;               // padded length = vector length on the encoded side; shard_len for reduce/fused
   u64 seed;
   u64 base;                // index of entry 0 in the sign stream
-  u64 unit0;               // encode / decode: number of leading tiles that need no bounds checks
+  u64 unit0;               // encode / decode: number of leading tiles that need no bounds checks; fused bf16 in blocks of 2^16: of leading blocks that one workgroup serves each
   int N;                   // workers
   int k;                   // block_log2
   float scale;             // 2^(-k/2) rounded to fp32

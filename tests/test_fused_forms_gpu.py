@@ -37,7 +37,7 @@ def _assert_close(got, want, kind, where):
                                         (16, 1, 1), (16, 3, 64), (16, 2, 65), (16, 2, 129), (16, 5, 3), (16, 2, 258), (16, 40, 1),
                                         (11, 2, 512), (12, 2, 9), (12, 2, 513), (12, 4, 300), (13, 2, 1), (13, 3, 257),
                                         (11, 1, 5), (12, 1, 512), (13, 1, 3), (12, 8, 300), (12, 9, 257), (12, 12, 768), (12, 7, 769), (13, 6, 256),
-                                        (13, 7, 9)])
+                                        (13, 7, 9), (16, 3, 321), (16, 1, 300), (16, 4, 513)])
 def test_forms_against_the_oracle(b, orc, k, N, blocks, loss):
     """First, middle and last block against the oracle, and the same bits and the arrival total from the batched call.  loss 0: the
     shortcuts for wavefronts and blocks that have everything; 0.4: hardly a run of 32 entries is whole."""
@@ -105,7 +105,7 @@ def test_fp32_large_blocks_against_the_oracle(b, orc, k, N, blocks, loss):
 def test_bits_do_not_depend_on_the_size_of_the_launch(b, k, N):
     """A shard of blocks of 2^11 and more gives, bit for bit, what its beginning gives as a shard of its own or as a bucket among
     others: numbers of blocks on both sides of every change of form, and two rounds of 256 workgroups."""
-    B, sizes = 1 << k, (1, 64, 65, 128, 129, 256, 300) if k > 13 else (1, 65, 256, 257, 512, 513, 768, 769)
+    B, sizes = 1 << k, (1, 64, 65, 128, 129, 256, 300, 330, 513) if k > 13 else (1, 65, 256, 257, 512, 513, 768, 769)
     gen = torch.Generator(device=dev()).manual_seed(k + N)
     x = torch.randn((N, sizes[-1] * B), device=dev(), generator=gen).mul_(1e-3).to(torch.bfloat16)
     m = torch.where(torch.rand((N, sizes[-1] * B // 2048), device=dev(), generator=gen) < 0.002, 0, -1).to(torch.int32).repeat_interleave(64, 1)
