@@ -131,7 +131,8 @@ hipError_t sum_first(const PathArgs& a, unsigned long long units, hipStream_t s,
 //     N = 7 10.8 -> 9.7 / 13.1 -> 11.0; with totals and 5 % loss N = 5 14.1 -> 13.8 / 17.5 -> 16.9 (eight tiles a workgroup one after the
 //     other 15.0 / 16.0: fewer atomics; with 1 % loss 15.8 against 12.8).
 //   fp32 below 2^10 (two to five workers): N = 4, 1024 tiles 8.3 -> 6.2, 2048 tiles 10.0 -> 7.8; N = 5, 3000 tiles 12.5 -> 16.9
-//   fp32 2^11 (two to five): N = 4, 64 tiles 6.3 -> 5.5, 256 tiles 6.6 -> 5.8; N = 3 5.6 -> 5.5; N = 2 5.0 -> 5.2; N = 5, 300 tiles 8.2 -> 9.4
+//   fp32 2^11 (two to five): N = 4, 64 tiles 6.3 -> 5.5, 256 tiles 6.8 -> 6.6; N = 3, 1 / 16 / 64 / 256 tiles, 5 %
+//     loss 5.1 -> 4.8 / 5.5 -> 5.6 / 5.6 -> 5.8 / 5.8 -> 6.3, nothing lost 4.9 -> 4.5 / 5.1 -> 5.0 / 5.2 -> 5.2 / 5.5 -> 5.8; N = 2 5.0 -> 5.2; N = 5, 300 tiles 8.2 -> 9.4
 //   fp32 2^12: N = 16, 100 tiles 19.4 -> 16.3, 200 tiles 19.5 -> 17.9; N = 32, 8 tiles 34.5 -> 26.3; N = 8, 128 tiles 11.4 -> 10.8, 256 tiles
 //     11.6 -> 12.2; N = 6, 100 tiles 9.4 -> 10.1
 //   fp32 2^13: N = 32, 2 tiles 41.6 -> 48.9; N = 8, 64 tiles 13.9 -> 16.6
@@ -139,7 +140,7 @@ constexpr int kEachGroups = K == 0 ? 16 : K == 11 || K == 12 ? 4 : 1;
 [[maybe_unused]] int each_groups(unsigned long long tiles, int N) {
   int most = 1;
   if (K == 0) most = tiles <= 256 ? 16 : tiles <= 512 ? 8 : tiles <= 1024 ? (N <= 7 ? 4 : 8) : 1;
-  if (K == 11 && (N == 3 || N == 4) && tiles <= 256) most = 4;
+  if (K == 11 && (N == 3 || N == 4) && tiles <= (N == 3 ? 16 : 256)) most = 4;
   if (K == 12 && tiles <= (N >= 12 ? 200 : 128) && N >= 8) most = 4;
   int g = 1;
   while (g < most && g < N) g *= 2;
