@@ -60,11 +60,13 @@ enum {
 
 /* n rounded up to a whole number of blocks of 2^block_log2 entries (0 if block_log2 is invalid). */
 uint64_t or_padded_len(uint64_t n, int block_log2);
-/* Bytes of device workspace that or_reduce_decode* / or_fused_path* need for this shard length and
- * block size: 0 for block_log2 <= 14, else 5 bytes per shard entry (rounded up to 256-byte parts).  What
- * the kernels keep there (fp32 sums and counts; for the bf16 fused path with block_log2 = 16 fp32 means) is
- * written before it is read within one call: the workspace needs no initialisation, and calls that may
- * overlap in time need workspaces of their own. */
+/* Bytes of device workspace that or_reduce_decode* / or_fused_path* ask for with this shard length and
+ * block size: 0 for block_log2 <= 14, else 5 bytes per shard entry (rounded up to 256-byte parts).  One size
+ * for both types and both paths, an upper bound of what their kernels keep there: fp32 sums and counts for
+ * or_reduce_decode*, fp32 means for or_fused_path_bf16 with block_log2 = 16; or_fused_path, and
+ * or_fused_path_bf16 with block_log2 = 15, leave it untouched (and are refused without it all the same).
+ * What is kept there is written before it is read within one call: the workspace needs no initialisation,
+ * and calls that may overlap in time need workspaces of their own. */
 size_t or_workspace_bytes(uint64_t shard_len, int block_log2);
 const char* or_status_string(or_status s);
 int or_version(void);
@@ -147,13 +149,13 @@ or_status or_fused_path_bf16(const uint16_t* grads, const uint32_t* masks, int N
 
 /* or_fused_path_bf16_static: or_fused_path_bf16 for callers that cannot allocate device memory or must not
  * pass a workspace (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
- * The workspace of the kernels for block_log2 > 14 is a static array in device memory inside the library,
+ * The workspace for block_log2 > 14 is a static array in device memory inside the library,
  * (5 * OR_STATIC_MAX_SHARD_LEN bytes, 20 MiB, held by every GPU the library runs on until the process ends);
- * for block_log2 <= 14 no workspace is used.  Same arguments, checks, kernels and results as
+ * only kernels for block_log2 = 16 use it.  Same arguments, checks, kernels and results as
  * or_fused_path_bf16 otherwise.  block_log2 > 14 with shard_len > OR_STATIC_MAX_SHARD_LEN is rejected
  * with OR_ERR_WORKSPACE.  The call allocates nothing; its first call on a device looks the array's address
  * up (make that call outside a graph capture).  Every call on a GPU uses that GPU's one array: calls with
- * block_log2 > 14 that may overlap in time on one GPU (different streams, several host threads) race on
+ * block_log2 = 16 that may overlap in time on one GPU (different streams, several host threads) race on
  * it -- keep them on one stream or order them with events. */
 #define OR_STATIC_MAX_SHARD_LEN 4194304ull
 or_status or_fused_path_bf16_static(const uint16_t* grads, const uint32_t* masks, int N, uint64_t shard_len,

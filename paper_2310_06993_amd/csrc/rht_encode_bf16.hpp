@@ -1,10 +1,10 @@
 // Encode (OptiReduce Sec. 3.3) of bf16 gradients in blocks of 2^11 .. 2^14 entries: one workgroup per block, positions, products
 // and exchange as in rht_fused_bf16.hpp.
 //
-// Bound by memory (a large copy: 5.2 TB/s).  us, stages one by one with 2 bytes a lane per access -> this: 2^12, 13.1e6 entries 14.4 ->
-// 11.4 (4.6 TB/s), 210e6 153 -> 130 (6.5 TB/s);  2^11, 210e6 149 -> 131;  2^13 157 -> 130;
-// one ragged block of 2^11 / 2^12 / 2^13 / 2^14 2.60 -> 2.70, 2.81 -> 2.87, 3.43 -> 3.20, 4.6 -> 3.9, 131e3 4.9 -> 4.1, 13.1e6 15.9 -> 12.4,
-// 210e6 167 -> 136.
+// Bound by memory: inputs and outputs of 0.8 to 3.2 GB in turn, several times the last-level cache, 6.0 - 6.5 TB/s of both together (a plain
+// copy of the same buffers 4.7 - 5.1).  us, stages one by one with 2 bytes a lane per access -> this: 2^11, 210e6 entries 149 -> 131;  2^12, 13.1e6
+// 14.4 -> 10.9, 210e6 153 -> 130;  2^13, 210e6 157 -> 130;  2^14, 131e3 4.9 -> 4.1, 13.1e6 15.9 -> 11.5, 210e6 167 -> 136;  one ragged block of 2^11 / 2^12 /
+// 2^13 / 2^14 2.60 -> 2.70 / 2.81 -> 2.87 / 3.43 -> 3.20 / 4.6 -> 3.9.
 #pragma once
 #include "rht_fused_bf16.hpp"
 

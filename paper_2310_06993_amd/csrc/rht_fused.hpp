@@ -633,7 +633,10 @@ __global__ __launch_bounds__(kFusedThreads<K> * (MODE == GROUPS ? kGroups : 1)) 
 void k_fused(PathArgs a) {
   fused_tile<K, MODE, SPLIT>(a, blockIdx.x, gridDim.x);
 }
-// K = 0: a workgroup of the plain form serves kBatchSlots tiles of one bucket; ba.tile_start counts workgroups
+// K = 0: a workgroup of the plain form serves kBatchSlots tiles of one bucket; ba.tile_start counts workgroups.  With totals fewer tiles
+// mean more atomics: us, four / eight tiles a workgroup, 2^10, 5 % loss, N = 4, 4096 / 12800 tiles 26.0 / 22.3, 59.5 / 55.4, N = 16 60.6 / 55.9, 177 / 173;  1 %
+// loss, N = 2, 12800 tiles 35.1 / 37.7.  (Without totals, one / eight: N = 8, 1200 / 2048 / 12800 tiles 12.3 / 13.0, 16.6 / 16.3, 85.4 / 88.0, N = 2, 12800 tiles 33.1 /
+// 35.9.)
 template <int K, int MODE> constexpr int kBatchSlots = K == 0 && MODE != GROUPS ? 8 : 1;
 template <int K, int MODE, bool SPLIT>
 __global__ __launch_bounds__(kFusedThreads<K> * (MODE == GROUPS ? kGroups : kBatchSlots<K, MODE>)) __attribute__((amdgpu_waves_per_eu(4)))

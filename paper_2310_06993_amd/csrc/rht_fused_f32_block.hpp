@@ -14,8 +14,9 @@
 // side that goes first stores singly and the other loads 16 bytes a lane, which LDS serves twice as fast as the other way round.
 //
 // us, tile by tile with a table of signs and every worker by itself -> this: 2^15, N = 8, 1280 blocks, 1 % loss in packets 351 -> 288
-// (4.7 TB/s), 0.2 % in bursts 341 -> 265;  N = 32, 300 blocks, 5 % 454 -> 377, one block 177 -> 145;  2^16, N = 8, 640 blocks 543 -> 488, 16
-// blocks 82 -> 68;  N = 32, 150 blocks, 5 % 614 -> 512;  N = 2, 1000 blocks 352 -> 337.  Bound by memory where nearly every copy is whole, else
+// (5.5 TB/s of slices, masks, results and counts), 0.2 % in bursts 341 -> 265;  N = 32, 300 blocks, 5 % 454 -> 377, one block 177 -> 145;  2^16, N = 8, 640 blocks 543 -> 488, 16
+// blocks 82 -> 68;  N = 32, 150 blocks, 5 % 614 -> 512;  N = 2, 1000 blocks 352 -> 337.  (One to four blocks of two or three workers that
+// lost something: 2^15 18.9 -> 19.5, 2^16 31.6 -> 32.5.)  Bound by memory where nearly every copy is whole, else
 // by the encode (fifteen stages and two trips through LDS, on a CU with nothing else on it), 2^16 also by the second reading of the
 // slices, which the L2 serves in part: without the nontemporal hint 548 -> 488.
 #pragma once

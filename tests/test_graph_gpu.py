@@ -106,8 +106,8 @@ def test_three_calls_in_a_graph():
 
 def test_batched_monitored_and_static_calls_in_a_graph():
     """The batched fused call with its per-bucket arrival totals (zeroed by a kernel, not a memset) and the call
-    with the static workspace (blocks of 2^16: sign stream, hand-over flags and slots all live in the library's
-    array) recorded once and replayed with new inputs."""
+    with the static workspace (blocks of 2^16, few enough to be split between workgroups: their fp32 means meet in
+    the library's array) recorded once and replayed with new inputs."""
     import paper_2310_06993_amd.binding as b
     import oracle
     N, seed = 4, 31
