@@ -61,11 +61,21 @@ OR_LAUNCHER(enc_bf16, OR_ENC(bf16_t, bf16_t))
 #elif OR_K <= 14
 OR_LAUNCHER_T(enc_bf16, k_encode_bf16<K>, MTile<K>::THREADS)
 #else
-// workgroups that walk over the blocks: as many as 256 CUs hold at a time
+// Few blocks: a workgroup for each of the 2^14 values of a block, which all read the whole of it (the same bits).  Two of them fill a CU, and
+// beyond that they only read more.  us, a workgroup a block -> that: 2^15, 128 / 256 / 300 blocks 7.3 -> 5.4 / 8.1 -> 7.3 / 11.0 -> 12;  2^16,
+// 65 / 128 blocks 12.5 -> 8.7 / 13 -> 10.3, with two workgroups a block 9.7 / 11.0, 200 blocks with two of them 13.9 -> 19.
+// (In place a workgroup has to have read the whole block before anyone writes to it.)
+constexpr unsigned long long kEncodeSplit = K == 15 ? 256 : 128;
+template <int SPLIT>
+hipError_t enc_bf16_split(const PathArgs& a, unsigned long long blocks, hipStream_t s, int pos) {
+  const unsigned long long grid = SPLIT == 1 ? blocks : (blocks + 7) / 8 * 8 * SPLIT;
+  if (grid > 0x7FFFFFFFull) return hipErrorInvalidValue;
+  return launch_kernel(k_encode_block_bf16<K, SPLIT>, dim3((unsigned)grid), dim3(EBlock<K>::THREADS), s, pos, a);
+}
 hipError_t enc_bf16(const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
-  const unsigned long long blocks = units >> G::HB, resident = K == 15 ? 512 : 256;
+  const unsigned long long blocks = units >> G::HB;
   if (blocks == 0) return hipSuccess;
-  return launch_kernel(k_encode_block_bf16<K>, dim3((unsigned)(blocks < resident ? blocks : resident)), dim3(1024), s, pos, a);
+  return blocks <= kEncodeSplit && a.in != a.out ? enc_bf16_split<EBlock<K>::P>(a, blocks, s, pos) : enc_bf16_split<1>(a, blocks, s, pos);
 }
 #endif
 OR_XFORM_LAUNCHER(dec_f32, OR_DEC(float, false, false))

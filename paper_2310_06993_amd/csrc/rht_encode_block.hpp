@@ -1,123 +1,143 @@
-// Encode (OptiReduce Sec. 3.3) of bf16 gradients in blocks of 2^15 / 2^16 entries (P = 2 / 4 tiles of 2^14).
+// Encode (OptiReduce Sec. 3.3) of bf16 gradients in blocks of 2^15 / 2^16 entries: the first factor on the matrix cores and one exchange
+// through LDS, as in rht_fused_bf16_64k.hpp.
 //
-// A workgroup holds a whole block in registers.  2^16 blocks leave room for one workgroup on a CU, and nothing would run
-// under a block's loads and stores.  Hence: a workgroup walks over blocks and asks for the next one before it transforms
-// the current one.  (2^15: two workgroups on a CU do that for each other.)  The entries in flight stay packed pairs (8 registers a tile and lane beside 16 of data), 16 bytes a lane
-// per load.  Layouts and the 2^14 transform are those of rht_fused.hpp, the factor across tiles is add / subtract.
-// Bound by memory (a large copy: 5.2 TB/s): 1.0e9 entries 930 -> 777 us at 2^16 and 932 -> 749 at 2^15 (5.2 and 5.4 TB/s);
-// 3e6 entries at 2^16 28.9 -> 22.3, 30e6 at 2^15 46.5 -> 28.0.  Before: 2 bytes a lane per load, one block a workgroup.
+// A workgroup of 8 wavefronts makes 2^14 encoded values at a time, so 64 KB of LDS and 128 registers a lane are enough and two
+// workgroups share a CU: one's loads and stores run under the other's arithmetic.  The products make these parts: an operand holds the
+// columns of one value of the last bits of the first factor, H_32 (e0 e1 e2 e7 e8) of 2^15 and H_64 (e9 too, two accumulated products)
+// of 2^16.  Nothing is read twice.  Entry bits of the positions, T = K - 6:
+//   L   as loaded            regs e0 e1 e2, (e9) eT e(T+1) e(T+2)   lanes e3 .. e8               waves e(T+3) ..
+//   S1  after the products   regs e3 e4 eT e(T+1) e(T+2)            lanes e0 e1 e2 e7 e5 e6      waves e(T+3) ..   parts e8 (e9)
+//   S2  encoded              regs e5 e6 e(T+3) ..                   lanes e0 .. e4 e7            waves eT ..       parts e8 (e9)
+// (With the block's highest bits in the place of e8 and e9, which puts a part's results in a row: 3 to 5 % slower between 256 and 2000
+// blocks, the same above.)
+//
+// Bound by memory (a large copy: 5.2 TB/s).  us, stages one by one, 2^16 in one workgroup of 16 wavefronts that asks for the next block before
+// it transforms this one -> this: 2^16, 800e6 entries 659 -> 561 (5.7 TB/s), 700 / 512 / 256 blocks 44.1 -> 38.7 / 30.0 -> 26.7 / 15.4 -> 15.0;
+// 2^15, 800e6 entries 624 -> 536 (6.0 TB/s), 512 / 256 blocks 15.0 -> 13.8 / 9.2 -> 8.0.  One block of 2^15 / 2^16 7.6 -> 4.5 / 11.4 -> 5.6,
+// ragged 14.1 -> 4.6 / 23.8 -> 5.8.
 #pragma once
-#include "rht_fused.hpp"
+#include "rht_fused_bf16.hpp"
 
 namespace ordev {
 
-// Sign bits of this lane's 16 entries (in A) of each of the block's P tiles, from one Philox evaluation: lane 8 p + i holds
-// counter i of tile p.  `g` = sign-stream index of the wavefront's first entry in tile 0; x as in lane_signs.
-template <int P, class In>
-__device__ __forceinline__ void block_lane_signs(u64 seed, u64 g, float* x, int wave, int lane, uint32_t (&sg)[P]) {
-  typedef FTile<14, In> F;
-  const u64 ctr = ((g + (u64)((lane >> 3) & (P - 1)) * F::T) >> 7) + (u64)(lane & 7);
-  const u32x4 w = philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), 0u, 0u, (uint32_t)seed, (uint32_t)(seed >> 32));
-  uint32_t* words = (uint32_t*)(x + wave * F::PART);
-  if (lane < 8 * P) *(uint4*)(words + lane * 4) = make_uint4(w.a, w.b, w.c, w.d);
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    uint32_t bits = 0;
-#pragma unroll
-    for (int c = 0; c < F::C; ++c) {
-      const uint32_t t = words[p * 32 + c * 2 * F::V + (lane >> (5 - F::VB))] >> ((lane & ((32 >> F::VB) - 1)) << F::VB);
-      bits |= (t & ((1u << F::V) - 1)) << (c * F::V);
-    }
-    sg[p] = bits;
-  }
-  __builtin_amdgcn_wave_barrier();
-}
+template <int K>
+struct EBlock {
+  static constexpr int P = 1 << (K - 14), LOADS = 4 * P, C = LOADS / 8, THREADS = 512;   // C: products for a value
+  static_assert(K == 15 || K == 16, "blocks of 2^15 / 2^16");
+};
 
-// 16 registers of 64 consecutive entries each (register r: from entry `first` + r * STEP on) as bf16.  Two registers are packed
-// and exchanged with the neighbour lane, so that a lane stores two consecutive entries of one of them: 4 bytes a lane, not 2.
-template <int STEP>
-__device__ __forceinline__ void store_pairs_bf16(const float (&v)[16], __amdgpu_buffer_rsrc_t rs, int tile_byte, int first, int lane) {
+// SPLIT workgroups a block, on one XCD (blockIdx modulo 8) next to each other: they read the same entries
+template <int K, int SPLIT, bool FULL>
+__device__ __forceinline__ void encode_block_bf16(const PathArgs& a, u64 blk, int part0, float* x, uint8_t* bytes) {
+  typedef EBlock<K> E;
+  const int wave = wave_id(), lane = lane_id();
+  const u64 e0 = blk << K;
+  u32x4v p[E::LOADS];   // load q: 8 entries from at + step(q) of the block on
+  const int at = wave * 4096 * E::C + lane * 8;
+  auto step = [](int q) { return q * 512; };
+  const u64 left = FULL ? 1 << K : a.n - e0;   // of the block's entries; zeros past the end
+  if (FULL || left >= (u64)(wave * 4096 * E::C + 4096 * E::C)) {
+    const __amdgpu_buffer_rsrc_t rs = rsrc_of((const bf16_t*)a.in + e0, 2 << K);
+#pragma unroll
+    for (int q = 0; q < E::LOADS; ++q) p[q] = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, at * 2, step(q) * 2, kBufNt));
+  } else {   // the end of the input: pairs that lie inside, and the entry without a partner
+    const int inside = (int)left & ~1;
+    const __amdgpu_buffer_rsrc_t rs = rsrc_of((const bf16_t*)a.in + e0, inside * 2);
+#pragma unroll
+    for (int q = 0; q < E::LOADS; ++q)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) p[q][d] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (at + step(q) + d * 2) * 2, 0, 0);
+    if (left & 1) {
+      const uint32_t last = ((const uint16_t*)a.in)[e0 + inside];
+#pragma unroll
+      for (int q = 0; q < E::LOADS; ++q)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) p[q][d] = at + step(q) + d * 2 == inside ? last : p[q][d];
+    }
+  }
+  {   // signs: sixteen Philox counters for each of the P runs of 2048 entries, one a lane, spread through the wavefront's 1 KB
+    const u64 ctr = ((a.base + e0 + (u64)wave * 4096 * E::C) >> 7) + (u64)(lane & (32 * E::C - 1));
+    const u32x4 w = philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), 0u, 0u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
+    uint8_t* mine = bytes + wave * 1024;
+    *(uint4*)(mine + lane * 16) = make_uint4(w.a, w.b, w.c, w.d);
+    __builtin_amdgcn_wave_barrier();
+    auto byte = [&](int q) { return (uint32_t)mine[lane + q * 64]; };
+#pragma unroll
+    for (int q = 0; q < E::LOADS; q += 4) {
+      uint32_t word = pair_signs(byte(q) | byte(q + 1) << 8 | byte(q + 2) << 16 | byte(q + 3) << 24);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        flip_pairs(p[q + c], word);
+        asm volatile("" : "+v"(p[q + c]));   // here, not again in every part
+      }
+    }
+  }
+  const __amdgpu_buffer_rsrc_t out = rsrc_of((const bf16_t*)a.out + e0, 2 << K);
   const int odd = lane & 1;
   const uint32_t pick = odd ? 0x03020706u : 0x05040100u;   // bytes 0..3: our pair, 4..7: the neighbour's
-  const int at = (first + (lane & ~1) + odd * STEP) * 2;
 #pragma unroll
-  for (int r = 0; r < 16; r += 2) {
-    const uint32_t own = pack_bf16x2(v[r], v[r + 1]);
-    const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xf, 0xf, true);   // lane ^ 1
-    // even: (own.lo, other.lo); odd: (other.hi, own.hi)
-    const uint32_t x = __builtin_amdgcn_perm(other, own, pick);
-    __builtin_amdgcn_raw_buffer_store_b32(x, rs, at, tile_byte + r * STEP * 2, kBufNt);
+  for (int turn = 0; turn < E::P / SPLIT; ++turn) {
+    const int s = SPLIT == 1 ? turn ^ (turn >> 1) : part0 + turn;   // 0 1 3 2; bit 0: the block's highest entry bit
+    if (K == 16 && (SPLIT == 1 ? turn == 2 : turn == 0 && (part0 & 2))) {   // e14 changes: minus the entries of the second products
+#pragma unroll
+      for (int q = 1; q < E::LOADS; q += 2)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) p[q][d] ^= 0x80008000u;
+    }
+    // the +-1 operand: lane l holds column n = l & 15, rows 8 (l >> 4) + 0..7; n0 n1 n2 pair with the entry's place in the load, n3
+    // with lane bit 4 (e7), the part's highest entry bit with lane bit 5
+    int lane_t = lane;
+    asm volatile("" : "+v"(lane_t));   // formed here, not kept in registers all along
+    const uint32_t n1 = lane_t & 2 ? 0x80008000u : 0u, n2 = lane_t & 4 ? 0x80008000u : 0u;
+    uint32_t w = lane_t & 1 ? 0xBF803F80u : 0x3F803F80u;
+    w ^= (lane_t & 24) == 24 ? 0x80008000u : 0u;
+    if (s & 1) w ^= lane_t & 32 ? 0x80008000u : 0u;
+    const u32x4v h = {w, w ^ n1, w ^ n2, w ^ n1 ^ n2};
+    float v[32];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      f32x4v d = {0};
+#pragma unroll
+      for (int c = 0; c < E::C; ++c)
+        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8v, p[t * E::C + c]), __builtin_bit_cast(bf16x8v, h), d, 0, 0, 0);
+      v[4 * t] = d[0]; v[4 * t + 1] = d[1]; v[4 * t + 2] = d[2]; v[4 * t + 3] = d[3];
+    }
+    reg_stages(v, 0, 5);
+    // from the lowest address bit up: e5 e6 e0 e1 e2 e7 e3 e4 e8 ..
+    float* to = x + wave * 2048 + (lane_t & 7) * 4 + ((lane_t >> 3) & 1) * 32 + (lane_t >> 4);
+#pragma unroll
+    for (int r = 0; r < 32; ++r) to[(r & 3) * 64 + (r >> 2) * 256] = v[r];
+    lds_barrier<8>();
+    const float* from = x + (lane_t & 7) * 4 + ((lane_t >> 3) & 3) * 64 + (lane_t >> 5) * 32 + wave * 256;
+#pragma unroll
+    for (int r = 0; r < 32; r += 4) {
+      const f32x4v t = *(const f32x4v*)(from + (r >> 2) * 2048);
+      v[r] = t[0]; v[r + 1] = t[1]; v[r + 2] = t[2]; v[r + 3] = t[3];
+    }
+    if (turn + 1 < E::P / SPLIT) lds_barrier<8>();   // everyone has read.  Here, where all wavefronts are together anyway
+    reg_stages(v, 0, 5);
+    // Registers r and r + 1 are neighbouring runs of 32 entries: packed and exchanged with the neighbour lane, so that a lane stores two
+    // consecutive entries of one of them
+    const int to_entry = s * 256 + (wave << (K - 6)) + (lane_t >> 5) * 128 + odd * 32 + (lane_t & 30);
+#pragma unroll
+    for (int r = 0; r < 32; r += 2) {
+      const uint32_t own = pack_bf16x2(v[r] * a.scale, v[r + 1] * a.scale);
+      const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xf, 0xf, true);   // lane ^ 1
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(other, own, pick), out, to_entry * 2, (((r >> 1) & 1) * 64 + ((r >> 2) << (K - 3))) * 2, kBufNt);
+    }
   }
 }
 
-template <int K>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(K == 15 ? 8 : 4)))
-void k_encode_block_bf16(PathArgs a) {
-  typedef FTile<14, bf16_t> F;
-  constexpr int P = 1 << (K - 14), T = F::T, W = F::W, BUFS = K == 15 ? 1 : 2;
-  constexpr bool AHEAD = K == 16;
-  static_assert(F::reg_entry(1) == 1024 && F::reg_entry(8) == 8192, "register bits of B are entry bits 10 .. 13");
-  __shared__ __align__(16) float xbuf[BUFS][W * F::PART];
-  const int wave = wave_id(), lane = lane_id();
-  const u64 full = a.unit0 >> (K - 14), blocks = a.n_pad >> K;   // blocks that lie inside the input; with the cut one
-  Raw16<bf16_t> raw[P];
-  auto request = [&](u64 blk) {   // past the last block: zeros, without touching memory
-    const bool there = blk < blocks;
-    const u64 first = ((there ? blk : 0) << K) + (u64)wave * 1024, left = there && a.n > first ? a.n - first : 0;
-    const int valid = left < (P - 1) * T + 1024 ? (int)left : (P - 1) * T + 1024;
-    const __amdgpu_buffer_rsrc_t rs = rsrc_of((const bf16_t*)a.in + first, valid * 2);
-    if (!there || blk < full) {
-#pragma unroll
-      for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int c = 0; c < F::C; ++c)
-          raw[p].q[c] = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, p * (T * 2) + c * 1024, kBufNt));
-    } else {   // the block that the end of the input cuts short: entry by entry, zeros past the end
-#pragma unroll
-      for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int c = 0; c < F::C; ++c)
-#pragma unroll
-          for (int d = 0; d < 4; ++d) {
-            const int at = p * (T * 2) + c * 1024 + d * 4;
-            const uint32_t lo = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, lane * 16 + at, 0, 0);
-            const uint32_t hi = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, lane * 16 + at + 2, 0, 0);
-            raw[p].q[c][d] = lo | hi << 16;
-          }
-    }
-  };
-  if (AHEAD) request(blockIdx.x);
-  int flip = 0;
-  for (u64 blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
-    const u64 ew = (blk << K) + (u64)wave * 1024;
-    if (!AHEAD) request(blk);
-    int lane_t = lane;   // addresses formed here, not kept in registers all along
-    asm volatile("" : "+v"(lane_t));
-    if (BUFS == 1) __syncthreads();   // nobody still reads the last exchange
-    uint32_t sg[P];
-    block_lane_signs<P, bf16_t>(a.seed, a.base + ew, xbuf[flip], wave, lane_t, sg);
-    float v[P][16];
-#pragma unroll
-    for (int p = 0; p < P; ++p)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) v[p][r] = flip_sign(entry_of<bf16_t>(raw[p], r), sg[p], r);
-    __builtin_amdgcn_sched_barrier(0);
-    if (AHEAD) request(blk + gridDim.x);
-    __builtin_amdgcn_sched_barrier(0);
-    across_tiles<P, 16>(v);
-    const float c = a.scale * wire_sigma<14, bf16_t>(wave);
-    const __amdgpu_buffer_rsrc_t out = rsrc_of((const bf16_t*)a.out + (blk << K), P * T * 2);
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      if (BUFS == 1 && p > 0) __syncthreads();
-      to_wire<14, bf16_t>(v[p], xbuf[flip], wave, lane_t, 14);
-      flip ^= BUFS - 1;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) v[p][r] *= c;
-      store_pairs_bf16<F::reg_entry(1)>(v[p], out, p * (T * 2), wire_wave_entry<14, bf16_t>(wave), lane_t);
-    }
-  }
+template <int K, int SPLIT>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_encode_block_bf16(PathArgs a) {
+  __shared__ __align__(16) float x[1 << 14];
+  __shared__ __align__(16) uint8_t bytes[8 * 1024];
+  const unsigned slot = blockIdx.x >> 3;
+  const u64 blk = SPLIT == 1 ? blockIdx.x : slot / SPLIT * 8 + (blockIdx.x & 7), blocks = a.n_pad >> K;
+  if (SPLIT > 1 && blk >= blocks) return;
+  const int part0 = (int)(slot % SPLIT) * (EBlock<K>::P / SPLIT);
+  if (blk < (a.unit0 >> (K - 14))) encode_block_bf16<K, SPLIT, true>(a, blk, part0, x, bytes);
+  else encode_block_bf16<K, SPLIT, false>(a, blk, part0, x, bytes);
 }
 
 }  // namespace ordev

@@ -10,9 +10,26 @@
 // bf16 360 -> 241.  (With the 2^14 transform of rht_fused.hpp, which has no DPP stages for most bits and stores from its own
 // layout, 1 to 10 % less from four workers and 256 blocks on; its order of stages gave other bits than the two launches that small shards take.)
 #pragma once
-#include "rht_encode_block.hpp"
+#include "rht_fused.hpp"
 
 namespace ordev {
+
+// 16 registers of 64 consecutive entries each (register r: from entry `first` + r * STEP on) as bf16.  Two registers are packed
+// and exchanged with the neighbour lane, so that a lane stores two consecutive entries of one of them: 4 bytes a lane, not 2.
+template <int STEP>
+__device__ __forceinline__ void store_pairs_bf16(const float (&v)[16], __amdgpu_buffer_rsrc_t rs, int tile_byte, int first, int lane) {
+  const int odd = lane & 1;
+  const uint32_t pick = odd ? 0x03020706u : 0x05040100u;   // bytes 0..3: our pair, 4..7: the neighbour's
+  const int at = (first + (lane & ~1) + odd * STEP) * 2;
+#pragma unroll
+  for (int r = 0; r < 16; r += 2) {
+    const uint32_t own = pack_bf16x2(v[r], v[r + 1]);
+    const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xf, 0xf, true);   // lane ^ 1
+    // even: (own.lo, other.lo); odd: (other.hi, own.hi)
+    const uint32_t x = __builtin_amdgcn_perm(other, own, pick);
+    __builtin_amdgcn_raw_buffer_store_b32(x, rs, at, tile_byte + r * STEP * 2, kBufNt);
+  }
+}
 
 // Received bits of the lane's 16 entries in A (bit r = register r); `word`: lane l holds word l & 31 of the 32 words of the
 // wavefront's 1024 entries.

@@ -108,6 +108,28 @@ def test_encode_bf16_large_blocks_walked_over(b, orc, k, blocks, tail):
         assert torch.equal(xd.view(torch.int16), enc.view(torch.int16))
 
 
+@pytest.mark.parametrize("k,blocks,tail", [(15, 1, 0), (15, 9, 32767), (15, 256, 1), (15, 257, 0), (16, 1, 40001), (16, 7, 0), (16, 128, 3),
+                                           (16, 129, 65535)])
+def test_encode_bf16_large_blocks_in_parts(b, orc, k, blocks, tail):
+    """The bf16 encode of 2^15 / 2^16 blocks around the number of blocks up to which a workgroup makes a part of a block: the last block cut
+    short in each of its parts' inputs, and in place (where one workgroup makes the whole block), with the same bits."""
+    B = 1 << k
+    n = blocks * B - (B - tail if tail else 0)
+    rng = np.random.default_rng(900 + k + blocks)
+    x = _bf16_bits((rng.standard_normal(n) * 1e-4).astype(np.float32))
+    seed, base = 0xF00DFACE12345678, (1 << 33) + 5 * B
+    enc = torch.full((blocks * B,), float("nan"), dtype=torch.bfloat16, device=dev())
+    b.or_rht_encode_bf16(_dev_bf16(x), n, k, seed, base, enc)
+    for part in (slice(0, min(2, blocks) * B), slice((blocks - 1) * B, blocks * B)):
+        want = orc.rht_encode(x[part.start:min(part.stop, n)], k, seed, base + part.start)
+        assert rel_l2(to_np(enc[part]), want) <= TOL["bf16"]
+        assert (to_np(enc[part]) != want).mean() < 0.02      # as above
+    whole = torch.zeros(blocks * B, dtype=torch.bfloat16, device=dev())
+    whole[:n] = _dev_bf16(x)
+    b.or_rht_encode_bf16(whole, blocks * B, k, seed, base, whole)
+    assert torch.equal(whole.view(torch.int16), enc.view(torch.int16))
+
+
 @pytest.mark.parametrize("k,blocks,tail", [(11, 1, 1), (11, 1, 0), (11, 7, 2047), (12, 1, 2049), (12, 3, 0), (12, 2, 2048), (13, 2, 4097),
                                            (13, 5, 6145), (14, 1, 3), (14, 3, 0), (14, 2, 16383), (14, 600, 2047)])
 def test_encode_bf16_middle_blocks(b, orc, k, blocks, tail):
