@@ -5,6 +5,7 @@
 #include <math.h>
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "../../include/optireduce.h"
 #include "launch_table.hpp"
@@ -41,13 +42,11 @@ thread_local int g_last_hip_error = 0;
 // ------------------------------------------------------------------ streaming masked sum + count
 // Sec. 3.1.1 aggregation with no transform around it: each lane owns VEC consecutive entries (16
 // bytes of one worker's shard), reads the VEC mask bits of every worker and adds under select.
-#ifndef OR_NT_REDUCE
-#define OR_NT_REDUCE true
-#endif
-template <class Wire, int VEC>
+// U workers are asked for at once (the rule is launch_masked_reduce).  `keep`: the results stay in the L2 for who reads them next.
+template <class Wire, int VEC, int U>
 __device__ __forceinline__ void masked_reduce_at(const Wire* __restrict__ shards, const uint32_t* __restrict__ masks,
                                                  int N, u64 L, float* __restrict__ sum_out,
-                                                 uint8_t* __restrict__ count_out, u64 e) {
+                                                 uint8_t* __restrict__ count_out, u64 e, bool keep) {
   if (e >= L) return;
   typedef Wire vec_t __attribute__((ext_vector_type(VEC)));
   const u64 words = L >> 5;
@@ -57,60 +56,55 @@ __device__ __forceinline__ void masked_reduce_at(const Wire* __restrict__ shards
   for (int j = 0; j < VEC; ++j) { acc[j] = 0.0f; cnt[j] = 0; }
   const int sh = (int)(e & 31);
   int i = 0;
-  for (; i + 4 <= N; i += 4) {
-    vec_t x[4];
-    uint32_t m[4];
+  auto add = [&](auto at_once) {
+    constexpr int W = decltype(at_once)::value;
+    vec_t x[W];
+    uint32_t m[W];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      x[u] = OR_NT_REDUCE ? __builtin_nontemporal_load((const vec_t*)(shards + (u64)(i + u) * L + e))
-                          : *(const vec_t*)(shards + (u64)(i + u) * L + e);
-      m[u] = masks[(u64)(i + u) * words + (e >> 5)] >> sh;
+    for (int u = 0; u < W; ++u) {
+      x[u] = __builtin_nontemporal_load((const vec_t*)(shards + (u64)(i + u) * L + e));
+      m[u] = masks[(u64)(i + u) * words + (e >> 5)];
     }
+    __builtin_amdgcn_sched_barrier(0);   // all of them, before the first is added
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < W; ++u)
 #pragma unroll
       for (int j = 0; j < VEC; ++j) {
-        const bool got = (m[u] >> j) & 1u;
+        const bool got = (m[u] >> sh >> j) & 1u;
         float f;
         if constexpr (sizeof(Wire) == 4) f = x[u][j]; else f = __builtin_bit_cast(float, (uint32_t)x[u][j] << 16);
         acc[j] += got ? f : 0.0f;
         cnt[j] += got ? 1u : 0u;
       }
-  }
-  for (; i < N; ++i) {
-    vec_t x = OR_NT_REDUCE ? __builtin_nontemporal_load((const vec_t*)(shards + (u64)i * L + e))
-                           : *(const vec_t*)(shards + (u64)i * L + e);
-    uint32_t m = masks[(u64)i * words + (e >> 5)] >> sh;
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) {
-      const bool got = (m >> j) & 1u;
-      float f;
-      if constexpr (sizeof(Wire) == 4) f = x[j]; else f = __builtin_bit_cast(float, (uint32_t)x[j] << 16);
-      acc[j] += got ? f : 0.0f;
-      cnt[j] += got ? 1u : 0u;
-    }
-  }
-  // nontemporal: the results are not read again here and reads dominate the traffic
+    i += W;
+  };
+  while (i + U <= N) add(std::integral_constant<int, U>{});
+  if (U > 4 && i + 4 <= N) add(std::integral_constant<int, 4>{});
+  if (U > 2 && i + 2 <= N) add(std::integral_constant<int, 2>{});
+  if (U > 1 && i < N) add(std::integral_constant<int, 1>{});
   typedef float f4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-  for (int j = 0; j < VEC; j += 4)
-    __builtin_nontemporal_store(f4{acc[j], acc[j + 1], acc[j + 2], acc[j + 3]}, (f4*)(sum_out + e + j));
+  for (int j = 0; j < VEC; j += 4) {
+    const f4 s = {acc[j], acc[j + 1], acc[j + 2], acc[j + 3]};
+    if (keep) *(f4*)(sum_out + e + j) = s; else __builtin_nontemporal_store(s, (f4*)(sum_out + e + j));
+  }
   if (((uintptr_t)count_out & 3) == 0) {
 #pragma unroll
-    for (int j = 0; j < VEC; j += 4)
-      __builtin_nontemporal_store(cnt[j] | (cnt[j + 1] << 8) | (cnt[j + 2] << 16) | (cnt[j + 3] << 24),
-                                  (uint32_t*)(count_out + e + j));
+    for (int j = 0; j < VEC; j += 4) {
+      const uint32_t c = cnt[j] | (cnt[j + 1] << 8) | (cnt[j + 2] << 16) | (cnt[j + 3] << 24);
+      if (keep) *(uint32_t*)(count_out + e + j) = c; else __builtin_nontemporal_store(c, (uint32_t*)(count_out + e + j));
+    }
   } else {   // or_reduce_decode* takes counts at any address
 #pragma unroll
     for (int j = 0; j < VEC; ++j) count_out[e + j] = (uint8_t)cnt[j];
   }
 }
 
-template <class Wire, int VEC>
+template <class Wire, int VEC, int U>
 __global__ __launch_bounds__(256) void k_masked_reduce(const Wire* __restrict__ shards,
                                                        const uint32_t* __restrict__ masks, int N, u64 L,
-                                                       float* __restrict__ sum_out, uint8_t* __restrict__ count_out) {
-  masked_reduce_at<Wire, VEC>(shards, masks, N, L, sum_out, count_out, ((u64)blockIdx.x * 256 + threadIdx.x) * VEC);
+                                                       float* __restrict__ sum_out, uint8_t* __restrict__ count_out, bool keep) {
+  masked_reduce_at<Wire, VEC, U>(shards, masks, N, L, sum_out, count_out, ((u64)blockIdx.x * 256 + threadIdx.x) * VEC, keep);
 }
 
 // several buckets in one launch (a 25 MiB bucket is a few hundred workgroups here): descriptors in the kernel
@@ -133,10 +127,21 @@ __global__ __launch_bounds__(256) void k_masked_reduce_batched(ReduceBatch rb) {
   const uint32_t x = blockIdx.x;
   int j = 0;
   while (j + 1 < rb.n && rb.start[j + 1] <= x) ++j;
-  masked_reduce_at<Wire, VEC>((const Wire*)rb.b[j].shards, rb.b[j].masks, rb.N, rb.b[j].L, rb.b[j].sum, rb.b[j].count,
-                              ((u64)(x - rb.start[j]) * 256 + threadIdx.x) * VEC);
+  masked_reduce_at<Wire, VEC, 4>((const Wire*)rb.b[j].shards, rb.b[j].masks, rb.N, rb.b[j].L, rb.b[j].sum, rb.b[j].count,
+                              ((u64)(x - rb.start[j]) * 256 + threadIdx.x) * VEC, false);
 }
 
+// Workers asked for at once.  A launch of few workgroups waits for every batch: eight at once.  us, four -> eight, reduce + finalize,
+// bf16, 65536 entries, N = 16 / 32 6.7 -> 6.1 / 9.3 -> 8.2, 524288 entries 8.7 -> 8.0 / 12.8 -> 11.2, but 1048576 entries, N = 8 / 32 8.9 -> 9.2 /
+// 16.9 -> 17.8.  fp32 launches that fill the chip many times over do best with as few rows of memory open as
+// possible: one.  us, four -> one, 3194880 entries, N = 8 / 32 28.4 -> 28.0 / 83.7 -> 80.9, 12345664 entries 99.8 -> 97.0 / 306 -> 293, 8388608
+// entries (rows a power of two apart) 72.3 -> 66.6 / 213 -> 202, 2000000 entries 19.5 -> 19.0 / 52.6 -> 50.0, but 1000000 entries 11.8 -> 12.8 /
+// 28.0 -> 30.9; bf16, of half as many bytes, from 16 workers on
+// and later: 8388608 / 12345664 entries, N = 16 71.0 -> 65.6 / 98.2 -> 96.2, N = 32 131 -> 109 / 167 -> 161, but N = 8 44.2 -> 43.1 / 63.3 -> 64.6, 6000000
+// entries, N = 16 48.4 -> 50.2.
+// Sum and counts stay in the L2 (32 MB) where they fit: k_finalize reads every entry on the XCD that wrote it.  us, streamed past it -> kept, N =
+// 4, bf16, 524288 / 3194880 entries 5.3 -> 5.3 / 16.1 -> 15.0, fp32, 1048576 / 3194880 entries 9.5 -> 9.3 / 19.5 -> 18.9.
+constexpr u64 kReduceFew = 256, kReduceMany = 1900, kReduceManyBf16 = 4096, kKeepBytes = 24u << 20;
 template <class Wire, int VEC>
 hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N, u64 L, float* sum_out,
                                 uint8_t* count_out, hipStream_t s, int pos) {
@@ -144,34 +149,43 @@ hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N
   const u64 threads = (L + VEC - 1) / VEC;
   const u64 blocks = (threads + 255) / 256;
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  return orhost::launch_kernel(k_masked_reduce<Wire, VEC>, dim3((unsigned)blocks), dim3(256), s, pos,
-                               (const Wire*)shards, masks, N, L, sum_out, count_out);
+  const bool one = sizeof(Wire) == 4 ? blocks >= kReduceMany : N >= 16 && blocks >= kReduceManyBf16;
+  const auto kernel = blocks <= kReduceFew ? k_masked_reduce<Wire, VEC, 8> : one ? k_masked_reduce<Wire, VEC, 1> : k_masked_reduce<Wire, VEC, 4>;
+  return orhost::launch_kernel(kernel, dim3((unsigned)blocks), dim3(256), s, pos, (const Wire*)shards, masks, N, L, sum_out, count_out,
+                               L * 5 <= kKeepBytes);
 }
 
 // ------------------------------------------------------------------ small streaming kernels
-// mean = sum / count, 0 where count is 0 (Sec. 3.1.1 "averages" over what arrived); 4 entries per lane
+// mean = sum / count, 0 where count is 0 (Sec. 3.1.1 "averages" over what arrived); 16 bytes of it a lane, the entries of a workgroup of
+// k_masked_reduce for the same type.  us, reduce + finalize, bf16, 4 -> 8 entries a lane: N = 2, 524288 / 3194880 entries 5.6 -> 4.7 / 13.7 -> 13.5
 template <class Out>
 __global__ __launch_bounds__(256) void k_finalize(const float* __restrict__ sum, const uint8_t* __restrict__ count, u64 L,
                                                   Out* __restrict__ mean) {
-  const u64 e = ((u64)blockIdx.x * 256 + threadIdx.x) * 4;
+  constexpr int VEC = 16 / sizeof(Out);
+  const u64 e = ((u64)blockIdx.x * 256 + threadIdx.x) * VEC;
   if (e >= L) return;
   typedef float f4 __attribute__((ext_vector_type(4)));
-  const f4 s4 = *(const f4*)(sum + e);
-  const uint32_t c4 = *(const uint32_t*)(count + e);
-  float m[4];
+  f4 s4[VEC / 4];
+  uint32_t c4[VEC / 4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float c = (float)((c4 >> (8 * j)) & 0xFFu);
-    m[j] = c > 0.0f ? s4[j] / c : 0.0f;
+  for (int q = 0; q < VEC / 4; ++q) {
+    s4[q] = *(const f4*)(sum + e + 4 * q);
+    c4[q] = *(const uint32_t*)(count + e + 4 * q);
+  }
+  float m[VEC];
+#pragma unroll
+  for (int j = 0; j < VEC; ++j) {
+    const float c = (float)((c4[j / 4] >> (8 * (j % 4))) & 0xFFu);
+    m[j] = c > 0.0f ? s4[j / 4][j % 4] / c : 0.0f;
   }
   if constexpr (sizeof(Out) == 4) {
     *(f4*)(mean + e) = f4{m[0], m[1], m[2], m[3]};
   } else {
-    typedef uint16_t h4 __attribute__((ext_vector_type(4)));
-    h4 h;
+    typedef uint16_t h8 __attribute__((ext_vector_type(8)));
+    h8 h;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) h[j] = __builtin_bit_cast(uint16_t, (__bf16)m[j]);
-    *(h4*)(mean + e) = h;
+    for (int j = 0; j < 8; ++j) h[j] = __builtin_bit_cast(uint16_t, (__bf16)m[j]);
+    *(h8*)(mean + e) = h;
   }
 }
 
@@ -476,7 +490,7 @@ or_status finalize_impl(const float* sum, const uint8_t* count, u64 L, Out* mean
   if (ranges_overlap(mean, L * sizeof(Out), count, L)) return OR_ERR_SHAPE;
   if (ranges_overlap(mean, L * sizeof(Out), sum, L * 4) && !((const void*)mean == (const void*)sum && sizeof(Out) == 4))
     return OR_ERR_SHAPE;
-  const u64 blocks = (L / 4 + 255) / 256;
+  const u64 blocks = (L * sizeof(Out) / 16 + 255) / 256;
   if (blocks > 0x7FFFFFFFull) return OR_ERR_SHAPE;
   return finish(orhost::launch_kernel(k_finalize<Out>, dim3((unsigned)blocks), dim3(256), (hipStream_t)stream,
                                       orhost::LAUNCH_ONLY, sum, count, L, mean));

@@ -199,6 +199,31 @@ def test_integer_round_trip_is_bit_exact(b, k):
 
 
 # ------------------------------------------------------------------ aggregation
+@pytest.mark.parametrize("kind,N,L", [("f32", 11, 256 * 1024), ("f32", 7, 256 * 1024 + 32), ("f32", 5, 1899 * 1024), ("f32", 5, 1899 * 1024 + 32),
+                                      ("bf16", 11, 256 * 2048), ("bf16", 7, 256 * 2048 + 32), ("bf16", 16, 4095 * 2048), ("bf16", 16, 4095 * 2048 + 32),
+                                      ("bf16", 15, 4096 * 2048)])
+def test_masked_reduce_forms(b, kind, N, L):
+    """The masked reduce around the launch sizes where the number of workers asked for at once changes, and where sum and counts no longer
+    stay in the L2, then the mean: the same additions in the same order as a loop over the workers, so the same bits."""
+    gen = torch.Generator(device=dev()).manual_seed(L % 1000 + N)
+    x = torch.randn((N, L), device=dev(), generator=gen).to(torch.float32 if kind == "f32" else torch.bfloat16)
+    masks = torch.randint(-2**31, 2**31 - 1, (N, L // 32), device=dev(), generator=gen, dtype=torch.int64).to(torch.int32)
+    masks[1, ::3] = -1
+    total = torch.empty(L, device=dev())
+    count = torch.empty(L, dtype=torch.uint8, device=dev())
+    (b.or_masked_reduce if kind == "f32" else b.or_masked_reduce_bf16)(x, masks, N, L, total, count)
+    want, n = torch.zeros(L, device=dev()), torch.zeros(L, dtype=torch.int32, device=dev())
+    bit = torch.arange(32, device=dev(), dtype=torch.int32)
+    for i in range(N):
+        got = ((masks[i][:, None] >> bit) & 1).bool().view(-1)
+        want += torch.where(got, x[i].float(), torch.zeros((), device=dev()))
+        n += got
+    assert torch.equal(total, want) and torch.equal(count.int(), n)
+    mean = torch.empty(L, dtype=x.dtype, device=dev())
+    (b.or_finalize if kind == "f32" else b.or_finalize_bf16)(total, count, L, mean)
+    assert torch.equal(mean, torch.where(n > 0, want / n.clamp(min=1), torch.zeros((), device=dev())).to(x.dtype))
+
+
 @pytest.mark.parametrize("N,L", [(1, 32), (3, 96), (4, 32 * 257), (8, 32 * 1000 + 64), (16, 4096 * 3), (255, 64)])
 @pytest.mark.parametrize("kind", ["f32", "bf16"])
 def test_masked_reduce(b, orc, N, L, kind):
