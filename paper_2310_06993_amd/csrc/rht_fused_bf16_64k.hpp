@@ -32,10 +32,21 @@ namespace ordev {
 constexpr int kQuarterEntries = 1 << 14;
 constexpr int kStaged = 10;   // of a lane's 16 loads of a worker: through LDS
 
-// A quarter in LDS; entry bits from the lowest address bit up: e5 e6 e0 e1 e2 e7 e3 e4 e10 .. e15.  S1 stores singly (64 lanes, 64
-// banks), S2 loads 16 bytes a lane: LDS is read faster than it is written that way (64 KB: 0.33 + 0.12 us; the other way round
-// 0.35 + 0.22).
-__device__ __forceinline__ int quarter_s2(int wave, int lane) {   // + 2048 (r >> 2), registers e5 e6 together
+// A quarter in LDS.  S1 stores singly, S2 loads 16 bytes a lane: LDS is read faster than it is written that way.  Each half of a wavefront
+// stores to 32 banks of 4 bytes; a 16-byte load goes by 16 lanes, those of a half whose lane bits 2, 3, 4 have the same parity, which have to
+// cover 64 banks.  Entry bits from the lowest address bit up: e5 (e6^e7) e0 e1 e2 e3 e4 e7 e10 .. e15, with neither conflicts of the stores
+// (lanes e0 e1 e2 e7 e5 in a half) nor of the loads.  e7 is a lane bit of S2, where the XOR swaps two registers of the stage of e6: their sum is
+// the same, and their difference changes its sign (s2_sign), the same one for all workers, which the mean takes back.  us, 64 KB, with two
+// lanes on every bank 0.45 + 0.23 -> 0.36 + 0.14.
+__device__ __forceinline__ int quarter_s1(int wave, int lane) {   // + 32 e3 + 64 e4 + 256 (r >> 2)
+  return wave * 2048 + (lane & 7) * 4 + ((lane >> 4) & 1) + (((lane >> 5) ^ (lane >> 3)) & 1) * 2 + ((lane >> 3) & 1) * 128;
+}
+__device__ __forceinline__ int quarter_s2(int wave, int lane) {   // + 2048 (r >> 2), registers e5 (e6^e7) together
+  return (lane & 7) * 4 + ((lane >> 3) & 3) * 32 + (lane >> 5) * 128 + wave * 256;
+}
+__device__ __forceinline__ float s2_sign(float f, int r, int lane) { return (r & 2) && (lane & 32) ? -f : f; }
+// The same positions on the way into the decode, where registers e5 e6 are stored together: e5 e6 e0 e1 e2 e7 e3 e4 e10 .. e15
+__device__ __forceinline__ int decode_s2(int wave, int lane) {   // + 2048 (r >> 2)
   return (lane & 7) * 4 + ((lane >> 3) & 3) * 64 + (lane >> 5) * 32 + wave * 256;
 }
 
@@ -63,7 +74,7 @@ __device__ __forceinline__ void decode_64k(float (&acc)[4][32], float* x, u32x4v
     int lane_t = lane;
     asm volatile("" : "+v"(lane_t));
     if (s > 0) lds_barrier<8>();   // everyone has read the quarter before
-    float* to = x + quarter_s2(wave, lane_t);
+    float* to = x + decode_s2(wave, lane_t);
 #pragma unroll
     for (int r = 0; r < 32; r += 4) *(f32x4v*)(to + (r >> 2) * 2048) = f32x4v{acc[s][r], acc[s][r + 1], acc[s][r + 2], acc[s][r + 3]};
     lds_barrier<8>();
@@ -73,7 +84,7 @@ __device__ __forceinline__ void decode_64k(float (&acc)[4][32], float* x, u32x4v
     reg_stages(acc[s], 0, 5);
   }
   lds_barrier<8>();
-  // inside the wavefront, 2048 entries of one (e10, e11) at a time.  From the lowest address bit up: e0 e1 (e2^e3) (e4^e6) e5 e2 e6
+  // inside the wavefront, 2048 entries of one (e10, e11) at a time.  From the lowest address bit up: e0 e1 (e2^e3) (e4^e6) e5 (e2^e7) e6
   // e7 e8 e9 e12
   float* mine = x + wave * 2048;
   const __amdgpu_buffer_rsrc_t out = rsrc_of((const bf16_t*)a.out + e0 + (u64)wave * 8192, 16384);
@@ -87,14 +98,14 @@ __device__ __forceinline__ void decode_64k(float (&acc)[4][32], float* x, u32x4v
 #pragma unroll
       for (int s = 0; s < 4; ++s)   // e8, e9
 #pragma unroll
-        for (int r = 0; r < 8; ++r) mine[(to ^ ((r & 3) << 2)) + (r >> 2) * 128 + s * 256] = acc[s][f * 8 + r];
+        for (int r = 0; r < 8; ++r) mine[(to ^ ((r & 3) << 2 | (r >> 2) << 5)) + (r >> 2) * 128 + s * 256] = acc[s][f * 8 + r];
     }
     __builtin_amdgcn_wave_barrier();
     {
-      const int from = ((lane_t & 7) * 4 + ((lane_t >> 3) & 1) * 64 + ((lane_t >> 4) & 3) * 128) ^ (((lane_t >> 3) & 1) << 3);
+      const int from = ((lane_t & 7) * 4 + ((lane_t >> 3) & 1) * 64 + ((lane_t >> 4) & 3) * 128) ^ (((lane_t >> 3) & 1) << 3 | ((lane_t >> 4) & 1) << 5);
 #pragma unroll
       for (int g = 0; g < 8; ++g) {   // registers e0 e1 | e2 e9 e12
-        const f32x4v t = *(const f32x4v*)(mine + (from ^ ((g & 1) << 2)) + (g & 1) * 32 + (g >> 1) * 512);
+        const f32x4v t = *(const f32x4v*)(mine + (from ^ ((g & 1) * (4 + 32))) + (g >> 1) * 512);
         v[4 * g] = t[0]; v[4 * g + 1] = t[1]; v[4 * g + 2] = t[2]; v[4 * g + 3] = t[3];
       }
     }
@@ -267,15 +278,15 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
         reg_stage<4>(v);
         auto& va = *(float (*)[16])&v[0];
         auto& vb = *(float (*)[16])&v[16];
-        float* to = x + wave * 2048 + (lane_t & 7) * 4 + ((lane_t >> 3) & 1) * 32 + (lane_t >> 4);
+        float* to = x + quarter_s1(wave, lane_t);
         reg_stages(va, 0, 4);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) to[(r & 3) * 64 + (r >> 2) * 256] = va[r];
+        for (int r = 0; r < 16; ++r) to[(r & 1) * 32 + ((r >> 1) & 1) * 64 + (r >> 2) * 256] = va[r];
         __builtin_amdgcn_sched_barrier(0);
         reg_stages(vb, 0, 4);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) to[(r & 3) * 64 + (r >> 2) * 256 + 1024] = vb[r];
+        for (int r = 0; r < 16; ++r) to[(r & 1) * 32 + ((r >> 1) & 1) * 64 + (r >> 2) * 256 + 1024] = vb[r];
         lds_barrier<8>();
         {
           const float* from = x + quarter_s2(wave, lane_t);
@@ -317,6 +328,8 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
     } while (++i < N);
 
     // ---- counts (a byte for each of the 128 entries of the lane's words) and the mean over what arrived
+    int lane_m = lane;   // as above
+    asm volatile("" : "+v"(lane_m));
     const float post = a.scale;
     const __amdgpu_buffer_rsrc_t counts = rsrc_of(a.count_out + e0 + wave * 1024, a.count_out && quarter0 == 0 ? B - wave * 1024 : 0);   // none, or another workgroup's: stores are dropped
     const bool counts_aligned = ((uintptr_t)a.count_out & 15) == 0;
@@ -344,7 +357,7 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
 #pragma unroll
       for (int s = 0; s < NQ; ++s)
 #pragma unroll
-        for (int r = 0; r < 32; ++r) acc[s][r] *= f;
+        for (int r = 0; r < 32; ++r) acc[s][r] *= s2_sign(f, r, lane_m);
     }
     if (!clean) {
       uint8_t* mine = (uint8_t*)x + wave * 8192;   // the wavefront's counts, by word
@@ -369,18 +382,18 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
       }
       __builtin_amdgcn_wave_barrier();
       store_counts([&](int q) { return *(const u32x4v*)(mine + q * 1024 + lane * 16); });
-      const uint8_t* from = mine + (lane >> 5) * 128 + (lane & 31);
+      const uint8_t* from = mine + (lane_m >> 5) * 128 + (lane_m & 31);
 #pragma unroll
       for (int s = 0; s < NQ; ++s)
 #pragma unroll
         for (int r = 0; r < 32; ++r) {
           const uint32_t n = from[((r >> 2) * 8 + 2 * (quarter0 + s)) * 128 + (r & 3) * 32];
-          acc[s][r] = n ? acc[s][r] * (post * __builtin_amdgcn_rcpf((float)n)) : 0.0f;
+          acc[s][r] = n ? acc[s][r] * (s2_sign(post, r, lane_m) * __builtin_amdgcn_rcpf((float)n)) : 0.0f;
         }
     }
     if (totals && quarter0 == 0) {   // Sec. 3.4 loss monitoring: gathered in LDS, one atomic per workgroup
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) total += (uint32_t)__shfl_xor((int)total, o, 64);
+      for (int o = 32; o > 0; o >>= 1) total += (uint32_t)__builtin_amdgcn_ds_bpermute((lane_m ^ o) << 2, (int)total);   // (__shfl_xor keeps a lane number of its own)
       lds_barrier<8>();
       if (lane == 0) ((uint32_t*)x)[wave] = total;
       lds_barrier<8>();
