@@ -361,24 +361,29 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
     }
     if (!clean) {
       uint8_t* mine = (uint8_t*)x + wave * 8192;   // the wavefront's counts, by word
+      uint32_t c8[4][8];   // of a lane's four words
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) c8[j][q] = 0;
 #pragma unroll 1
-      for (int j = 0; j < 4; ++j) {   // a word of every lane at a time
-        uint32_t c8[8];
+      for (int i = 0; i < N; i += 4) {
+        u32x4v w[4];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) c8[q] = 0;
-        for (int i = 0; i < N; i += 4) {
-          uint32_t w[4];
+        for (int u = 0; u < 4; ++u) w[u] = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(words_of(a, blk, i + u), word_at, 0, 0));
 #pragma unroll
-          for (int u = 0; u < 4; ++u) w[u] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(words_of(a, blk, i + u), word_at + j * 4, 0, 0);
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
+          for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int q = 0; q < 8; ++q) c8[q] += (((w[u] >> (4 * q)) & 0xFu) * 0x00204081u) & 0x01010101u;
-        }
+            for (int q = 0; q < 8; ++q) c8[j][q] += (((w[u][j] >> (4 * q)) & 0xFu) * 0x00204081u) & 0x01010101u;
+      }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) total = __builtin_amdgcn_sad_u8(c8[q], 0u, total);
-        *(uint4*)(mine + lane * 128 + j * 32) = make_uint4(c8[0], c8[1], c8[2], c8[3]);
-        *(uint4*)(mine + lane * 128 + j * 32 + 16) = make_uint4(c8[4], c8[5], c8[6], c8[7]);
+      for (int j = 0; j < 4; ++j) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) total = __builtin_amdgcn_sad_u8(c8[j][q], 0u, total);
+        *(uint4*)(mine + lane_m * 128 + j * 32) = make_uint4(c8[j][0], c8[j][1], c8[j][2], c8[j][3]);
+        *(uint4*)(mine + lane_m * 128 + j * 32 + 16) = make_uint4(c8[j][4], c8[j][5], c8[j][6], c8[j][7]);
       }
       __builtin_amdgcn_wave_barrier();
       store_counts([&](int q) { return *(const u32x4v*)(mine + q * 1024 + lane * 16); });
