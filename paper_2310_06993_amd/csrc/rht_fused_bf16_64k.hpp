@@ -269,24 +269,32 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
           }
         }
         __builtin_amdgcn_sched_barrier(0);
-        // a few loads at a time: a CU takes one of them (1 KB) in 16 cycles, and all wavefronts would wait for the last one's
-        constexpr int per = NQ <= 2 ? kStaged : 5, at_once = EARLY ? 4 : 3;
+        // A few loads at a time where the launch fills the chip: a CU takes one of them (1 KB) in 16 cycles, and all wavefronts would wait for the
+        // last one's.  (All that are left at once, 15317 blocks of 8 workers 4694 -> 4790.)  Few blocks, whose reads the L2 serves for the most
+        // part, take as many as early as they can: us, 3 and 3 later -> 5, the rest at once, NQ = 1, 16 blocks, N = 8 / 32 47.4 -> 45.1 / 133.5 -> 123.4;  4 -> 10,
+        // NQ = 2, 128 blocks, N = 32 196 -> 192.
+        constexpr int per = NQ <= 2 ? kStaged : 5, at_once = NQ == 1 ? 5 : NQ == 2 ? kStaged : 3, rest_at_once = NQ <= 2 ? 16 : kStaged + 3;
         if (per * turn < kStaged && after) request_staged(after, per * turn, per * turn + at_once);   // (none on their way when the workgroup ends)
-        if (turn == NQ - 1) request_rest(after, kStaged, EARLY ? 16 : kStaged + 3);   // the entries have been used for the last time
-        if (EARLY && turn == NQ - 1) request_words(words_after);
-        // half of the registers at a time after the stage between the halves: the second half's stages run under the first half's stores
+        if (turn == NQ - 1) {   // the entries have been used for the last time
+          request_rest(after, kStaged, rest_at_once);
+          if (rest_at_once == 16) request_words(words_after);
+        }
+        // eight registers at a time after the stages between the eights: the others' stages run under their stores, and only the last
+        // stores are waited for
         reg_stage<4>(v);
-        auto& va = *(float (*)[16])&v[0];
-        auto& vb = *(float (*)[16])&v[16];
+        reg_stage<3>(v);
         float* to = x + quarter_s1(wave, lane_t);
-        reg_stages(va, 0, 4);
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) to[(r & 1) * 32 + ((r >> 1) & 1) * 64 + (r >> 2) * 256] = va[r];
-        __builtin_amdgcn_sched_barrier(0);
-        reg_stages(vb, 0, 4);
+        for (int h = 0; h < 4; ++h) {
+          auto& vh = *(float (*)[8])&v[8 * h];
+          reg_stage<0>(vh);
+          reg_stage<1>(vh);
+          reg_stage<2>(vh);
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) to[(r & 1) * 32 + ((r >> 1) & 1) * 64 + (r >> 2) * 256 + 1024] = vb[r];
+          for (int r = 0; r < 8; ++r) to[(r & 1) * 32 + ((r >> 1) & 1) * 64 + (r >> 2) * 256 + h * 512] = vh[r];
+          __builtin_amdgcn_sched_barrier(0);
+        }
         lds_barrier<8>();
         {
           const float* from = x + quarter_s2(wave, lane_t);
@@ -300,8 +308,8 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
         // apart, so that one's accesses to LDS run under another's arithmetic.
         lds_barrier<8>();
         if (per * turn < kStaged && after) request_staged(after, per * turn + at_once, per * turn + per);
-        if (!EARLY && turn == NQ - 1) {
-          request_rest(after, kStaged + 3, 16);
+        if (rest_at_once < 16 && turn == NQ - 1) {
+          request_rest(after, rest_at_once, 16);
           request_words(words_after);
         }
         reg_stages(v, 0, 5);
