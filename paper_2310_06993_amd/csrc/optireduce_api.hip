@@ -135,13 +135,13 @@ __global__ __launch_bounds__(256) void k_masked_reduce_batched(ReduceBatch rb) {
 // bf16, 65536 entries, N = 16 / 32 6.7 -> 6.1 / 9.3 -> 8.2, 524288 entries 8.7 -> 8.0 / 12.8 -> 11.2, but 1048576 entries, N = 8 / 32 8.9 -> 9.2 /
 // 16.9 -> 17.8.  fp32 launches that fill the chip many times over do best with as few rows of memory open as
 // possible: one.  us, four -> one, 3194880 entries, N = 8 / 32 28.4 -> 28.0 / 83.7 -> 80.9, 12345664 entries 99.8 -> 97.0 / 306 -> 293, 8388608
-// entries (rows a power of two apart) 72.3 -> 66.6 / 213 -> 202, 2000000 entries 19.5 -> 19.0 / 52.6 -> 50.0, but 1000000 entries 11.8 -> 12.8 /
-// 28.0 -> 30.9; bf16, of half as many bytes, from 16 workers on
+// entries (rows a power of two apart) 72.3 -> 66.6 / 213 -> 202, but 1000000 entries 11.8 -> 12.8 / 28.0 -> 30.9, and a few workgroups more than
+// run at once (2048) are a long chain: 2100000 entries, N = 12 25.5 -> 28.3; bf16, of half as many bytes, from 16 workers on
 // and later: 8388608 / 12345664 entries, N = 16 71.0 -> 65.6 / 98.2 -> 96.2, N = 32 131 -> 109 / 167 -> 161, but N = 8 44.2 -> 43.1 / 63.3 -> 64.6, 6000000
 // entries, N = 16 48.4 -> 50.2.
 // Sum and counts stay in the L2 (32 MB) where they fit: k_finalize reads every entry on the XCD that wrote it.  us, streamed past it -> kept, N =
 // 4, bf16, 524288 / 3194880 entries 5.3 -> 5.3 / 16.1 -> 15.0, fp32, 1048576 / 3194880 entries 9.5 -> 9.3 / 19.5 -> 18.9.
-constexpr u64 kReduceFew = 256, kReduceMany = 1900, kReduceManyBf16 = 4096, kKeepBytes = 24u << 20;
+constexpr u64 kReduceFew = 256, kReduceMany = 3000, kReduceManyBf16 = 4096, kKeepBytes = 24u << 20;
 template <class Wire, int VEC>
 hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N, u64 L, float* sum_out,
                                 uint8_t* count_out, hipStream_t s, int pos) {
@@ -150,7 +150,7 @@ hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N
   const u64 blocks = (threads + 255) / 256;
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
   const bool one = sizeof(Wire) == 4 ? blocks >= kReduceMany : N >= 16 && blocks >= kReduceManyBf16;
-  const auto kernel = blocks <= kReduceFew ? k_masked_reduce<Wire, VEC, 8> : one ? k_masked_reduce<Wire, VEC, 1> : k_masked_reduce<Wire, VEC, 4>;
+  const auto kernel = blocks <= kReduceFew && N >= 8 ? k_masked_reduce<Wire, VEC, 8> : one ? k_masked_reduce<Wire, VEC, 1> : k_masked_reduce<Wire, VEC, 4>;
   return orhost::launch_kernel(kernel, dim3((unsigned)blocks), dim3(256), s, pos, (const Wire*)shards, masks, N, L, sum_out, count_out,
                                L * 5 <= kKeepBytes);
 }

@@ -3,24 +3,6 @@
 #pragma once
 #include "rht_tile.hpp"
 
-// Which kernels read their inputs with nontemporal loads (each choice measured on MI355X; ENCB / DECB
-// are the encode / decode kernels for blocks above 2^14 entries, which came out slower with them).
-#ifndef OR_NT_RDEC
-#define OR_NT_RDEC true
-#endif
-#ifndef OR_NT_ENC
-#define OR_NT_ENC true
-#endif
-#ifndef OR_NT_ENCB
-#define OR_NT_ENCB false
-#endif
-#ifndef OR_NT_DECB
-#define OR_NT_DECB false
-#endif
-#ifndef OR_NT_DEC
-#define OR_NT_DEC true
-#endif
-
 namespace ordev {
 
 struct PathArgs {
@@ -92,6 +74,18 @@ __device__ __forceinline__ void across_tiles(float (&v)[PARTS][NR]) {
       }
 }
 
+// Encode and decode store past the caches: their results are not read again here, and their inputs stay.  us, plain -> nontemporal stores,
+// fp32 decode of 2^12, 3145728 / 5242880 / 31457280 / 209715200 entries 7.7 -> 5.8 / 9.9 -> 7.4 / 45.4 -> 43.7 / 287 -> 278, bf16 6.0 -> 5.5 / 8.5 -> 7.1 /
+// 32.9 -> 32.0 / 213 -> 205;  fp32 encode of 2^10 6.5 -> 4.9 / 8.8 -> 7.8 / 42.9 -> 41.9 / 272 -> 268.  Not where fp32 in- and output are larger than
+// the L2 and both fit the last-level cache (256 MB): 8388608 / 12582912 / 17825792 / 22020096 / 25493504 entries of 2^12 13.0 -> 13.0 / 19.1 -> 19.6 / 25.3 -> 26.3 /
+// 30.5 -> 31.4 / 37.8 -> 35.9.
+constexpr u64 kKeepFrom = 11u << 20, kKeepTo = 23u << 20;
+template <int K, bool LAYOUT_B, bool FULL, class T>
+__device__ __forceinline__ void store_result(T* p, u64 e0, u64 limit, u64 n_pad, int wave, int lane, const float (&v)[Geo<K>::R]) {
+  if (sizeof(T) == 4 && n_pad > kKeepFrom && n_pad <= kKeepTo) store_tile<K, LAYOUT_B, FULL, false>(p, e0, limit, wave, lane, v);
+  else store_tile<K, LAYOUT_B, FULL, true>(p, e0, limit, wave, lane, v);
+}
+
 // Sec. 3.3 encode: out = B^(-1/2) H D x, blockwise; pad of the last block is zero.
 // FULL: every access of the tile lies inside the vectors (no bounds checks).  The first a.unit0 tiles of a launch are
 // such tiles, the ragged end takes the checked form, in the same launch: as a launch of its own it cost 2.5 us of host
@@ -101,7 +95,7 @@ __device__ __forceinline__ void encode_tile(const PathArgs& a, u64 unit, float* 
   constexpr int T = Geo<K>::T, R = Geo<K>::R;
   const int wave = wave_id(), lane = lane_id(), kt = tile_bits<K>(a.k);
   float v[R];
-  load_tile<K, false, FULL, OR_NT_ENC>((const In*)a.in, unit * T, a.n, wave, lane, v);
+  load_tile<K, false, FULL, true>((const In*)a.in, unit * T, a.n, wave, lane, v);
   u64 sg[R];
   sign_masks(a.seed, a.base + unit * T + (u64)wave * Geo<K>::WAVE_ENTRIES, sg);
   apply_signs(v, sg);
@@ -109,7 +103,7 @@ __device__ __forceinline__ void encode_tile(const PathArgs& a, u64 unit, float* 
   const float c = a.scale * lane_sigma(lane, kt < 6 ? kt : 6);
 #pragma unroll
   for (int r = 0; r < R; ++r) v[r] *= c;
-  store_tile<K, true, FULL>((Wire*)a.out, unit * T, a.n_pad, wave, lane, v);
+  store_result<K, true, FULL>((Wire*)a.out, unit * T, a.n_pad, a.n_pad, wave, lane, v);
 }
 template <int K, class In, class Wire>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_encode(PathArgs a) {
@@ -119,6 +113,11 @@ __global__ __launch_bounds__(Geo<K>::THREADS) void k_encode(PathArgs a) {
   else encode_tile<K, In, Wire, false>(a, blockIdx.x, xbuf);
 }
 
+// Blocks above 2^14 load nontemporally too from kStreamFrom entries on: fp32 decode of 2^16, plain loads and stores -> nontemporal stores ->
+// both, 4194304 / 25493504 / 209715200 entries 18.0 -> 16.1 -> 17.6 / 54 -> 45 -> 43 / 361 -> 351 -> 335, of 2^15 11.2 -> 9.8 -> 10.7 / 56 -> 49 ->
+// 47 / 336 -> 347 -> 336.
+constexpr u64 kStreamFrom = 8u << 20;
+
 // The same for blocks above 2^14: workgroup x encodes block x (a.unit0 counts tiles).  FULL = false: the block is cut
 // short by the end of the input (its pad reads as zero); the output always holds whole blocks.
 template <int K, class In, class Wire, bool FULL>
@@ -127,8 +126,13 @@ __device__ __forceinline__ void encode_block(const PathArgs& a, float (*xbuf)[Ge
   const int wave = wave_id(), lane = lane_id(), kt = Geo<K>::KT;
   const u64 tile0 = (u64)blockIdx.x << HB;
   float v[PARTS][R];
+  if (a.n_pad > kStreamFrom) {
 #pragma unroll
-  for (int q = 0; q < PARTS; ++q) load_tile<K, false, FULL, OR_NT_ENCB>((const In*)a.in, (tile0 + q) * T, a.n, wave, lane, v[q]);
+    for (int q = 0; q < PARTS; ++q) load_tile<K, false, FULL, true>((const In*)a.in, (tile0 + q) * T, a.n, wave, lane, v[q]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < PARTS; ++q) load_tile<K, false, FULL, false>((const In*)a.in, (tile0 + q) * T, a.n, wave, lane, v[q]);
+  }
   uint32_t slo, shi;
   block_sign_words<K>(a.seed, a.base + tile0 * T + (u64)wave * Geo<K>::WAVE_ENTRIES, slo, shi);
 #pragma unroll
@@ -140,7 +144,7 @@ __device__ __forceinline__ void encode_block(const PathArgs& a, float (*xbuf)[Ge
     transform<K, true, false>(v[p], xbuf[p & 1], wave, lane, kt);
 #pragma unroll
     for (int r = 0; r < R; ++r) v[p][r] *= c;
-    store_tile<K, true, true>((Wire*)a.out, (tile0 + p) * T, a.n_pad, wave, lane, v[p]);
+    store_tile<K, true, true, true>((Wire*)a.out, (tile0 + p) * T, a.n_pad, wave, lane, v[p]);
   }
 }
 template <int K, class In, class Wire>
@@ -155,11 +159,10 @@ __global__ __launch_bounds__(Geo<K>::THREADS) void k_encode_block(PathArgs a) {
 // (the "averages" of Sec. 3.1.1 taken over the entries that arrived).  MASKED: second-stage loss
 // (the broadcast of the aggregated shard, Sec. 3.1.1): entries whose bit in a.masks is clear never
 // arrived and count as zero.
-template <int K, bool FINALIZE, bool FULL, bool MASKED>
+template <int K, bool FINALIZE, bool FULL, bool MASKED, bool NT>
 __device__ __forceinline__ void load_mean_tile(const PathArgs& a, u64 tile, int wave, int lane,
                                                float (&v)[Geo<K>::R]) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R;
-  constexpr bool NT = Geo<K>::PARTS == 1 ? OR_NT_DEC : OR_NT_DECB;
   load_tile<K, true, FULL, NT>((const float*)a.in, tile * T, a.n_pad, wave, lane, v);
   if constexpr (FINALIZE) {
     float c[R];
@@ -183,7 +186,7 @@ __device__ __forceinline__ void decode_tile(const PathArgs& a, u64 unit, float* 
   static_assert(Geo<K>::PARTS == 1, "larger blocks use k_decode_block");
   const int wave = wave_id(), lane = lane_id(), kt = tile_bits<K>(a.k);
   float v[R];
-  load_mean_tile<K, FINALIZE, FULL, MASKED>(a, unit, wave, lane, v);
+  load_mean_tile<K, FINALIZE, FULL, MASKED, true>(a, unit, wave, lane, v);
   transform<K, false>(v, xbuf, wave, lane, kt);
   const float c = a.scale * lane_sigma(lane, kt < 6 ? kt : 6);
   u64 sg[R];
@@ -191,7 +194,7 @@ __device__ __forceinline__ void decode_tile(const PathArgs& a, u64 unit, float* 
 #pragma unroll
   for (int r = 0; r < R; ++r) v[r] *= c;
   apply_signs(v, sg);
-  store_tile<K, false, FULL>((Out*)a.out, unit * T, a.n, wave, lane, v);
+  store_result<K, false, FULL>((Out*)a.out, unit * T, a.n, a.n_pad, wave, lane, v);
 }
 template <int K, class Out, bool FINALIZE, bool MASKED>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_decode(PathArgs a) {
@@ -208,8 +211,13 @@ __device__ __forceinline__ void decode_block(const PathArgs& a, u64 blk, float (
   const int wave = wave_id(), lane = lane_id(), kt = Geo<K>::KT;
   const u64 tile0 = blk << HB;
   float v[PARTS][R];
+  if (a.n_pad > kStreamFrom) {
 #pragma unroll
-  for (int q = 0; q < PARTS; ++q) load_mean_tile<K, FINALIZE, true, MASKED>(a, tile0 + q, wave, lane, v[q]);
+    for (int q = 0; q < PARTS; ++q) load_mean_tile<K, FINALIZE, true, MASKED, true>(a, tile0 + q, wave, lane, v[q]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < PARTS; ++q) load_mean_tile<K, FINALIZE, true, MASKED, false>(a, tile0 + q, wave, lane, v[q]);
+  }
   uint32_t slo, shi;
   block_sign_words<K>(a.seed, a.base + tile0 * T + (u64)wave * Geo<K>::WAVE_ENTRIES, slo, shi);
   across_tiles<PARTS, R>(v);
@@ -220,7 +228,7 @@ __device__ __forceinline__ void decode_block(const PathArgs& a, u64 blk, float (
 #pragma unroll
     for (int r = 0; r < R; ++r) v[p][r] *= c;
     apply_block_signs(v[p], slo, shi, p);
-    store_tile<K, false, FULL>((Out*)a.out, (tile0 + p) * T, a.n, wave, lane, v[p]);
+    store_tile<K, false, FULL, true>((Out*)a.out, (tile0 + p) * T, a.n, wave, lane, v[p]);
   }
 }
 template <int K, class Out, bool FINALIZE, bool MASKED>
@@ -341,17 +349,17 @@ __device__ __forceinline__ void reduce_decode_tile(const PathArgs& a, u64 unit) 
   for (int r = 0; r < R; ++r) acc[r] = 0.0f;
 #pragma unroll
   for (int r = 0; r < R / 4; ++r) cnt[r] = 0;
-  load_tile<K, true, FULL, OR_NT_RDEC>(shards, e0, L, wave, lane, va);
+  load_tile<K, true, FULL, true>(shards, e0, L, wave, lane, va);
   ma = load_mask_words<K, FULL>(a.masks, e0, L, moff);
   for (int i = 0; i < a.N; i += 2) {
     if (i + 1 < a.N) {
-      load_tile<K, true, FULL, OR_NT_RDEC>(shards + (u64)(i + 1) * L, e0, L, wave, lane, vb);
+      load_tile<K, true, FULL, true>(shards + (u64)(i + 1) * L, e0, L, wave, lane, vb);
       mb = load_mask_words<K, FULL>(a.masks + (u64)(i + 1) * mrow, e0, L, moff);
     }
     masked_accumulate(va, ma, acc, cnt, full);
     if (i + 1 < a.N) {
       if (i + 2 < a.N) {
-        load_tile<K, true, FULL, OR_NT_RDEC>(shards + (u64)(i + 2) * L, e0, L, wave, lane, va);
+        load_tile<K, true, FULL, true>(shards + (u64)(i + 2) * L, e0, L, wave, lane, va);
         ma = load_mask_words<K, FULL>(a.masks + (u64)(i + 2) * mrow, e0, L, moff);
       }
       masked_accumulate(vb, mb, acc, cnt, full);

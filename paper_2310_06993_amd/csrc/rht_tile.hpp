@@ -404,8 +404,7 @@ __device__ __forceinline__ void load_tile(const T* __restrict__ p, u64 e0, u64 l
   }
 }
 
-// NT = true: nontemporal stores.  Measured on MI355X: faster when reads dominate the kernel's traffic
-// (the N-to-1 shard kernels), slower for the 1:1 encode / decode kernels.
+// NT = true: nontemporal stores, for results that are not read again here.
 template <int K, bool LAYOUT_B, bool FULL, bool NT = false, class T>
 __device__ __forceinline__ void store_tile(T* __restrict__ p, u64 e0, u64 limit, int wave, int lane,
                                            const float (&v)[Geo<K>::R]) {
