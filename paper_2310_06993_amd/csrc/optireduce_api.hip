@@ -83,18 +83,32 @@ __device__ __forceinline__ void masked_reduce_at(const Wire* __restrict__ shards
   if (U > 2 && i + 2 <= N) add(std::integral_constant<int, 2>{});
   if (U > 1 && i < N) add(std::integral_constant<int, 1>{});
   typedef float f4 __attribute__((ext_vector_type(4)));
+  f4 s[VEC / 4];
+  uint32_t c[VEC / 4];
 #pragma unroll
-  for (int j = 0; j < VEC; j += 4) {
-    const f4 s = {acc[j], acc[j + 1], acc[j + 2], acc[j + 3]};
-    if (keep) *(f4*)(sum_out + e + j) = s; else __builtin_nontemporal_store(s, (f4*)(sum_out + e + j));
+  for (int q = 0; q < VEC / 4; ++q) {
+    s[q] = f4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    c[q] = cnt[4 * q] | (cnt[4 * q + 1] << 8) | (cnt[4 * q + 2] << 16) | (cnt[4 * q + 3] << 24);
   }
-  if (((uintptr_t)count_out & 3) == 0) {
+  const bool words_of_counts = ((uintptr_t)count_out & 3) == 0;
+  if (keep) {
+    ordev::keep_apart();
 #pragma unroll
-    for (int j = 0; j < VEC; j += 4) {
-      const uint32_t c = cnt[j] | (cnt[j + 1] << 8) | (cnt[j + 2] << 16) | (cnt[j + 3] << 24);
-      if (keep) *(uint32_t*)(count_out + e + j) = c; else __builtin_nontemporal_store(c, (uint32_t*)(count_out + e + j));
+    for (int q = 0; q < VEC / 4; ++q) *(f4*)(sum_out + e + 4 * q) = s[q];
+    if (words_of_counts) {
+#pragma unroll
+      for (int q = 0; q < VEC / 4; ++q) *(uint32_t*)(count_out + e + 4 * q) = c[q];
     }
-  } else {   // or_reduce_decode* takes counts at any address
+    ordev::keep_apart();
+  } else {
+#pragma unroll
+    for (int q = 0; q < VEC / 4; ++q) __builtin_nontemporal_store(s[q], (f4*)(sum_out + e + 4 * q));
+    if (words_of_counts) {
+#pragma unroll
+      for (int q = 0; q < VEC / 4; ++q) __builtin_nontemporal_store(c[q], (uint32_t*)(count_out + e + 4 * q));
+    }
+  }
+  if (!words_of_counts) {   // or_reduce_decode* takes counts at any address
 #pragma unroll
     for (int j = 0; j < VEC; ++j) count_out[e + j] = (uint8_t)cnt[j];
   }
@@ -139,9 +153,14 @@ __global__ __launch_bounds__(256) void k_masked_reduce_batched(ReduceBatch rb) {
 // run at once (2048) are a long chain: 2100000 entries, N = 12 25.5 -> 28.3; bf16, of half as many bytes, from 16 workers on
 // and later: 8388608 / 12345664 entries, N = 16 71.0 -> 65.6 / 98.2 -> 96.2, N = 32 131 -> 109 / 167 -> 161, but N = 8 44.2 -> 43.1 / 63.3 -> 64.6, 6000000
 // entries, N = 16 48.4 -> 50.2.
-// Sum and counts stay in the L2 (32 MB) where they fit: k_finalize reads every entry on the XCD that wrote it.  us, streamed past it -> kept, N =
-// 4, bf16, 524288 / 3194880 entries 5.3 -> 5.3 / 16.1 -> 15.0, fp32, 1048576 / 3194880 entries 9.5 -> 9.3 / 19.5 -> 18.9.
-constexpr u64 kReduceFew = 256, kReduceMany = 3000, kReduceManyBf16 = 4096, kKeepBytes = 24u << 20;
+// bf16 launches of 950 to 1300 workgroups (about four to five a CU) in between, from 12 workers on: two.  us, four -> two, N = 16 / 32, 2100000 entries
+// 21.5 -> 20.8 / 33.9 -> 32.5, 2300000 entries 23.2 -> 22.0 / 37.2 -> 35.3, but 1500000 entries, N = 16 15.1 -> 15.0, 3194880 entries 28.3 -> 29.7.
+// Sum and counts stay in the L2 (32 MB) where they fit: k_finalize reads every entry on the XCD that wrote it; and where the workers together are
+// at most 16 bytes an entry, for the last-level cache has room left.  us, streamed past it -> kept, bf16, N = 4, 5000000 / 14000000 entries 20.3 ->
+// 20.2 / 50.7 -> 46.7, N = 8 27.0 -> 27.1 / 69.5 -> 69.4 (with four at once; 8000000 entries 40.1 -> 38.8); fp32, N = 2 21.5 -> 21.7 / 55.2 -> 52.3, N =
+// 8 14000000 entries 111.9 -> 114.2; bf16, N = 4, 3194880 entries 16.1 -> 15.0.
+constexpr u64 kReduceFew = 256, kReduceTwoFrom = 950, kReduceTwoTo = 1300, kReduceMany = 3000, kReduceManyBf16 = 4096, kKeepBytes = 24u << 20;
+constexpr int kKeepRead = 16;   // bytes
 template <class Wire, int VEC>
 hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N, u64 L, float* sum_out,
                                 uint8_t* count_out, hipStream_t s, int pos) {
@@ -150,9 +169,13 @@ hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N
   const u64 blocks = (threads + 255) / 256;
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
   const bool one = sizeof(Wire) == 4 ? blocks >= kReduceMany : N >= 16 && blocks >= kReduceManyBf16;
-  const auto kernel = blocks <= kReduceFew && N >= 8 ? k_masked_reduce<Wire, VEC, 8> : one ? k_masked_reduce<Wire, VEC, 1> : k_masked_reduce<Wire, VEC, 4>;
+  const bool two = sizeof(Wire) == 2 && N >= 12 && blocks >= kReduceTwoFrom && blocks < kReduceTwoTo;
+  const auto kernel = blocks <= kReduceFew && N >= 8 ? k_masked_reduce<Wire, VEC, 8>
+                      : one                          ? k_masked_reduce<Wire, VEC, 1>
+                      : two                          ? k_masked_reduce<Wire, VEC, 2>
+                                                     : k_masked_reduce<Wire, VEC, 4>;
   return orhost::launch_kernel(kernel, dim3((unsigned)blocks), dim3(256), s, pos, (const Wire*)shards, masks, N, L, sum_out, count_out,
-                               L * 5 <= kKeepBytes);
+                               L * 5 <= kKeepBytes || N * (int)sizeof(Wire) <= kKeepRead);
 }
 
 // ------------------------------------------------------------------ small streaming kernels

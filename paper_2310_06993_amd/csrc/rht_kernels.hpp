@@ -75,15 +75,22 @@ __device__ __forceinline__ void across_tiles(float (&v)[PARTS][NR]) {
 }
 
 // Encode and decode store past the caches: their results are not read again here, and their inputs stay.  us, plain -> nontemporal stores,
-// fp32 decode of 2^12, 3145728 / 5242880 / 31457280 / 209715200 entries 7.7 -> 5.8 / 9.9 -> 7.4 / 45.4 -> 43.7 / 287 -> 278, bf16 6.0 -> 5.5 / 8.5 -> 7.1 /
-// 32.9 -> 32.0 / 213 -> 205;  fp32 encode of 2^10 6.5 -> 4.9 / 8.8 -> 7.8 / 42.9 -> 41.9 / 272 -> 268.  Not where fp32 in- and output are larger than
-// the L2 and both fit the last-level cache (256 MB): 8388608 / 12582912 / 17825792 / 22020096 / 25493504 entries of 2^12 13.0 -> 13.0 / 19.1 -> 19.6 / 25.3 -> 26.3 /
-// 30.5 -> 31.4 / 37.8 -> 35.9.
-constexpr u64 kKeepFrom = 11u << 20, kKeepTo = 23u << 20;
+// fp32 decode of 2^12, 3145728 / 5242880 / 31457280 / 67108864 entries 7.7 -> 5.8 / 9.9 -> 7.5 / 45.7 -> 43.1 / 92.8 -> 90.0, bf16 6.0 -> 5.4 / 8.3 -> 7.1 /
+// 33.5 -> 32.3 / 70.2 -> 65.3;  fp32 encode of 2^10 6.5 -> 5.0 / 8.7 -> 7.7 / 43.0 -> 42.0 / 89.6 -> 87.9.  Not where fp32 in- and output are larger than
+// the L2 and both fit the last-level cache (256 MB): 11534336 / 17825792 / 25165824 entries, decode of 2^12 17.5 -> 17.8 / 25.0 -> 26.2 / 36.2 -> 34.8,
+// encode 16.8 -> 17.2 / 25.2 -> 26.1 / 35.1 -> 33.9.  Blocks of 2^14, one a workgroup of 16 waves, gain for longer: encode, 12582912 / 17825792 /
+// 20971520 / 23068672 entries 20.2 -> 18.6 / 26.2 -> 26.2 / 31.4 -> 30.6 / 32.5 -> 33.6.
+template <int K> constexpr u64 kKeepFrom = (K == 14 ? 20u : 10u) << 20;
+constexpr u64 kKeepTo = 23u << 20;
 template <int K, bool LAYOUT_B, bool FULL, class T>
 __device__ __forceinline__ void store_result(T* p, u64 e0, u64 limit, u64 n_pad, int wave, int lane, const float (&v)[Geo<K>::R]) {
-  if (sizeof(T) == 4 && n_pad > kKeepFrom && n_pad <= kKeepTo) store_tile<K, LAYOUT_B, FULL, false>(p, e0, limit, wave, lane, v);
-  else store_tile<K, LAYOUT_B, FULL, true>(p, e0, limit, wave, lane, v);
+  if (sizeof(T) == 4 && n_pad > kKeepFrom<K> && n_pad <= kKeepTo) {
+    keep_apart();
+    store_tile<K, LAYOUT_B, FULL, false>(p, e0, limit, wave, lane, v);
+    keep_apart();
+  } else {
+    store_tile<K, LAYOUT_B, FULL, true>(p, e0, limit, wave, lane, v);
+  }
 }
 
 // Sec. 3.3 encode: out = B^(-1/2) H D x, blockwise; pad of the last block is zero.
@@ -130,8 +137,10 @@ __device__ __forceinline__ void encode_block(const PathArgs& a, float (*xbuf)[Ge
 #pragma unroll
     for (int q = 0; q < PARTS; ++q) load_tile<K, false, FULL, true>((const In*)a.in, (tile0 + q) * T, a.n, wave, lane, v[q]);
   } else {
+    keep_apart();
 #pragma unroll
     for (int q = 0; q < PARTS; ++q) load_tile<K, false, FULL, false>((const In*)a.in, (tile0 + q) * T, a.n, wave, lane, v[q]);
+    keep_apart();
   }
   uint32_t slo, shi;
   block_sign_words<K>(a.seed, a.base + tile0 * T + (u64)wave * Geo<K>::WAVE_ENTRIES, slo, shi);
@@ -215,8 +224,10 @@ __device__ __forceinline__ void decode_block(const PathArgs& a, u64 blk, float (
 #pragma unroll
     for (int q = 0; q < PARTS; ++q) load_mean_tile<K, FINALIZE, true, MASKED, true>(a, tile0 + q, wave, lane, v[q]);
   } else {
+    keep_apart();
 #pragma unroll
     for (int q = 0; q < PARTS; ++q) load_mean_tile<K, FINALIZE, true, MASKED, false>(a, tile0 + q, wave, lane, v[q]);
+    keep_apart();
   }
   uint32_t slo, shi;
   block_sign_words<K>(a.seed, a.base + tile0 * T + (u64)wave * Geo<K>::WAVE_ENTRIES, slo, shi);

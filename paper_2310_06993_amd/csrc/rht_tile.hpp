@@ -107,6 +107,9 @@ template <bool NT> __device__ __forceinline__ uint8_t load_one(const uint8_t* p)
 template <bool NT> __device__ __forceinline__ bf16_t load_one(const bf16_t* p) {
   return bf16_t{NT ? __builtin_nontemporal_load(&p->bits) : p->bits};
 }
+// Around accesses in one branch that differ from the other branch's only in their cache policy: the compiler makes one plain access of the two
+// otherwise.
+__device__ __forceinline__ void keep_apart() { asm volatile(""); }
 template <class T> __device__ __forceinline__ float round_to(float v) { return to_f32(from_f32<T>(v)); }
 
 // ------------------------------------------------------------------ Philox4x32-10 (Salmon et al., SC'11)
