@@ -158,7 +158,8 @@ __device__ __forceinline__ void fused_each(const PathArgs& a, u64 first_unit, u6
   if constexpr (kShardTilesFull<K>) {
     fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, true>(a, unit, wave, tiles, xbuf, missing);
   } else {
-    if ((unit + 1) * Geo<K>::T <= a.n_pad) fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, true>(a, unit, wave, tiles, xbuf, missing);
+    if ((unit + 1) * Geo<K>::T <= a.n_pad)
+      with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, true>(b, unit, wave, tiles, xbuf, missing); });
     else fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, false>(a, unit, wave, tiles, xbuf, missing);
   }
 }
@@ -335,7 +336,8 @@ __device__ __forceinline__ void fused_each_groups(const PathArgs& a, u64 unit) {
   if constexpr (kShardTilesFull<K>) {
     fused_each_groups_tile<K, In, G, TOTAL, true>(a, unit, grp, wave, x, y, &missing, &lossy);
   } else {
-    if ((unit + 1) * Geo<K>::T <= a.n_pad) fused_each_groups_tile<K, In, G, TOTAL, true>(a, unit, grp, wave, x, y, &missing, &lossy);
+    if ((unit + 1) * Geo<K>::T <= a.n_pad)
+      with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { fused_each_groups_tile<K, In, G, TOTAL, true>(b, unit, grp, wave, x, y, &missing, &lossy); });
     else fused_each_groups_tile<K, In, G, TOTAL, false>(a, unit, grp, wave, x, y, &missing, &lossy);
   }
 }

@@ -29,6 +29,25 @@ template <int K> constexpr bool kShardTilesFull = (K != 0);
 template <int K>
 __device__ __forceinline__ int tile_bits(int k) { return K ? Geo<K>::KT : k; }
 
+// Class 0 (tiles of 1024 entries for all blocks up to 2^10): the work of a whole tile compiled for each block size, so that its stages are one run
+// of code; a branch ahead of every stage kept the compiler from putting one stage's instructions between another's.  us, branches -> this: bf16
+// fused path of 2^10, N = 8 / 24, 3145728 entries 23.9 -> 19.2 / 59.8 -> 46.5, 1 M 13.6 -> 12.8 / 27.9 -> 25.8, 65536 5.95 -> 5.66 / 10.7 -> 9.7, of 2^8, N =
+// 8, 16.8 M 91.8 -> 75.7;  fp32, 2^9, N = 1 / 3, 3145728 entries 7.0 -> 6.3 / 12.7 -> 10.9;  encode, decode of 2^10, 65536 entries 2.67 -> 2.58, 2.81 -> 2.66,
+// bf16 encode, 16.8 M 16.6 -> 14.3;  reduce + decode 0 .. -3 %.  (Not the fp32 forms that add up whole workers first, rht_fused.hpp: they lose registers.)
+template <int K, class Tile>
+__device__ __forceinline__ void with_block_size(const PathArgs& a, Tile&& tile) {
+  if constexpr (K == 0) {
+    PathArgs known = a;
+    if (a.k == 10) { known.k = 10; return tile(known); }
+    if (a.k == 9) { known.k = 9; return tile(known); }
+    if (a.k == 8) { known.k = 8; return tile(known); }
+    if (a.k == 7) { known.k = 7; return tile(known); }
+    if (a.k == 6) { known.k = 6; return tile(known); }
+    if (a.k == 5) { known.k = 5; return tile(known); }
+  }
+  tile(a);
+}
+
 // ---- blocks above 2^14: one workgroup per block in encode / decode ----------------------------------
 // H_{2^k} = H_{2^(k-14)} (x) H_{2^14}: a workgroup holds the block's PARTS tiles in registers (PARTS*R per
 // lane), runs the small factor as add/sub between the tiles and the big one tile by tile.  Every input is
@@ -116,7 +135,7 @@ template <int K, class In, class Wire>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_encode(PathArgs a) {
   static_assert(Geo<K>::PARTS == 1, "larger blocks use k_encode_block");
   __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
-  if (blockIdx.x < a.unit0) encode_tile<K, In, Wire, true>(a, blockIdx.x, xbuf);
+  if (blockIdx.x < a.unit0) with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { encode_tile<K, In, Wire, true>(b, blockIdx.x, xbuf); });
   else encode_tile<K, In, Wire, false>(a, blockIdx.x, xbuf);
 }
 
@@ -208,7 +227,7 @@ __device__ __forceinline__ void decode_tile(const PathArgs& a, u64 unit, float* 
 template <int K, class Out, bool FINALIZE, bool MASKED>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_decode(PathArgs a) {
   __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
-  if (blockIdx.x < a.unit0) decode_tile<K, Out, FINALIZE, true, MASKED>(a, blockIdx.x, xbuf);
+  if (blockIdx.x < a.unit0) with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { decode_tile<K, Out, FINALIZE, true, MASKED>(b, blockIdx.x, xbuf); });
   else decode_tile<K, Out, FINALIZE, false, MASKED>(a, blockIdx.x, xbuf);
 }
 
@@ -394,7 +413,7 @@ __device__ __forceinline__ void reduce_decode_tile(const PathArgs& a, u64 unit) 
 }
 template <int K, class Wire, class Out>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_reduce_decode(PathArgs a) {
-  reduce_decode_tile<K, Wire, Out>(a, blockIdx.x);
+  with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { reduce_decode_tile<K, Wire, Out>(b, blockIdx.x); });
 }
 
 // Several buckets of one launch shape class (same N, block size and type) in ONE launch: small buckets
@@ -458,14 +477,14 @@ template <int K, class Wire>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_reduce_decode_batched(BatchArgs ba) {
   PathArgs a;
   const u64 unit = bucket_of<sizeof(Wire) == 4>(ba, a, blockIdx.x);
-  reduce_decode_tile<K, Wire, Wire>(a, unit);
+  with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { reduce_decode_tile<K, Wire, Wire>(b, unit); });
 }
 template <int K, class Out>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_finalize_decode_batched(BatchArgs ba) {
   PathArgs a;
   const u64 unit = bucket_of(ba, a, blockIdx.x);
   __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
-  decode_tile<K, Out, true, kShardTilesFull<K>, false>(a, unit, xbuf);
+  with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { decode_tile<K, Out, true, kShardTilesFull<K>, false>(b, unit, xbuf); });
 }
 
 }  // namespace ordev

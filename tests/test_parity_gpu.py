@@ -267,6 +267,38 @@ def test_finalize_decode(b, orc, k):
         <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("kind", ["f32", "bf16"])
+@pytest.mark.parametrize("k", [5, 6, 7, 8, 9, 10])
+def test_every_block_size_of_one_tile(b, orc, k, kind):
+    """Blocks of up to 2^10 share tiles of 1024 entries: whole tiles are compiled for each block size, a tile that is cut short for any.  Every
+    operation, launches of one tile and of several, with and without a last tile that is cut short."""
+    B, N, seed = 1 << k, 3, 0xF00DFACE12345678
+    base = 7 * max(B, 128)
+    np_dtype, dt = (np.float32, torch.float32) if kind == "f32" else (np.uint16, torch.bfloat16)
+    put = (lambda a: torch.from_numpy(a).to(dev())) if kind == "f32" else _dev_bf16
+    rng = np.random.default_rng(70 + k)
+    for L in (1024, 5 * 1024, 5 * 1024 + B if B < 1024 else 2 * 1024):
+        raw = (rng.standard_normal((N, L)) * 1e-3).astype(np.float32)
+        raw = raw if kind == "f32" else _bf16_bits(raw)
+        recv = rng.random((N, L)) > 0.05
+        masks = pack_mask_np(recv)
+        enc = np.stack([orc.rht_encode(raw[i], k, seed, base) for i in range(N)])
+        got = torch.zeros(L, dtype=dt, device=dev())
+        (b.or_rht_encode_at if kind == "f32" else b.or_rht_encode_bf16)(put(raw[0]), L, k, seed, base, got)
+        assert rel_l2(to_np(got), enc[0]) <= TOL[kind]
+        mean = (rng.standard_normal(L) * 1e-3).astype(np.float32)
+        (b.or_rht_decode_at if kind == "f32" else b.or_rht_decode_bf16)(torch.from_numpy(mean).to(dev()), L, k, seed, base, got)
+        assert rel_l2(to_np(got), orc.rht_decode(mean, L, k, seed, base, out_dtype=np_dtype)) <= TOL[kind]
+        want, want_count = orc.fused_path(raw, masks, k, seed, base)
+        count = torch.zeros(L, dtype=torch.uint8, device=dev())
+        sent = np.where(recv, enc, np.float32(np.nan) if kind == "f32" else np.uint16(0x7FC0)).astype(np_dtype)
+        for call, x in (("or_fused_path", raw), ("or_reduce_decode", sent)):
+            count.zero_()
+            getattr(b, call if kind == "f32" else call + "_bf16")(put(x), masks_to_dev(masks), N, L, k, seed, base, got, count, None)
+            assert np.array_equal(to_np(count), want_count)
+            assert rel_l2(to_np(got), want) <= TOL[kind]
+
+
 def _workspace(b, L, k):
     nbytes = b.or_workspace_bytes(L, k)
     return torch.empty(nbytes, dtype=torch.uint8, device=dev()) if nbytes else None
