@@ -332,11 +332,11 @@ hipError_t fusb_bf16(const BatchArgs& a, unsigned long long units, hipStream_t s
 }
 #endif
 #if OR_K == 16
-// A workgroup per block, or two or four that meet in the workspace (the same bits)?  A workgroup takes 7 to 8 us a worker, and takes
+// A workgroup per block, or two or four that meet in the workspace (the same bits)?  A workgroup takes 7 us a worker, and takes
 // 4.5 / 3.3 us for a half / a quarter of the encoded values.  us, four / two / one workgroups a block: N = 8, 16
 // blocks 48 / 64 / 91, 64 blocks 52 / 65 / 92, 100 blocks 86 / 67 / 92, 128 blocks 88 / 68 / 92, 160 blocks 122 / 118 / 94;  N = 2, 64
 // blocks 30 / 34 / 37, 128 blocks 44 / 36 / 38;  N = 32, 2 blocks 136 / 190 / 297.  (With nothing lost two of them, which both read the whole block,
-// take 4.3 us a worker: N = 8, 100 blocks 57.)
+// take 4.3 us a worker: N = 8, 100 blocks 57.)  That was with bank conflicts in the exchange; without them four take 45 at 16 and 48 at 64 blocks.
 // The same for the blocks that a walk has over in its last round, in launches of their own behind it.  us, in the walk -> that: N = 8, 300 / 384
 // / 600 / 1100 blocks 181 -> 147 / 181 -> 166 / 272 -> 253 / 440 -> 427;  N = 32, 257 / 300 blocks 600 -> 458 / 622 -> 470;  N = 2, 300 / 384 blocks
 // 74.5 -> 69.3 / 75.0 -> 77.6;  N = 1, 300 / 384 blocks 45.4 -> 48.8 / 46.0 -> 56.7.

@@ -155,12 +155,15 @@ __global__ __launch_bounds__(256) void k_masked_reduce_batched(ReduceBatch rb) {
 // entries, N = 16 48.4 -> 50.2.
 // bf16 launches of 950 to 1300 workgroups (about four to five a CU) in between, from 12 workers on: two.  us, four -> two, N = 16 / 32, 2100000 entries
 // 21.5 -> 20.8 / 33.9 -> 32.5, 2300000 entries 23.2 -> 22.0 / 37.2 -> 35.3, but 1500000 entries, N = 16 15.1 -> 15.0, 3194880 entries 28.3 -> 29.7.
-// Sum and counts stay in the L2 (32 MB) where they fit: k_finalize reads every entry on the XCD that wrote it; and where the workers together are
-// at most 16 bytes an entry, for the last-level cache has room left.  us, streamed past it -> kept, bf16, N = 4, 5000000 / 14000000 entries 20.3 ->
-// 20.2 / 50.7 -> 46.7, N = 8 27.0 -> 27.1 / 69.5 -> 69.4 (with four at once; 8000000 entries 40.1 -> 38.8); fp32, N = 2 21.5 -> 21.7 / 55.2 -> 52.3, N =
-// 8 14000000 entries 111.9 -> 114.2; bf16, N = 4, 3194880 entries 16.1 -> 15.0.
-constexpr u64 kReduceFew = 256, kReduceTwoFrom = 950, kReduceTwoTo = 1300, kReduceMany = 3000, kReduceManyBf16 = 4096, kKeepBytes = 24u << 20;
-constexpr int kKeepRead = 16;   // bytes
+// Sum and counts stay in the L2 (32 MB) where they fit: k_finalize reads every entry on the XCD that wrote it; and in the last-level cache
+// (256 MB) where the workers together are at most 12 bytes an entry, or 16 and sum and counts few enough to live next to them.  us, streamed past ->
+// kept, bf16, N = 4, 3194880 / 14000000 / 30000000 / 60000000 entries 16.1 -> 15.0 / 50.8 -> 46.8 / 106 -> 100 / 209 -> 221, N = 2, 18000000 entries
+// 56.9 -> 50.4, N = 8, 6000000 / 10000000 / 18000000 entries 32.0 -> 30.8 / 49.4 -> 48.2 / 90.6 -> 92.7; fp32, N = 2 / 3, 14000000 entries 55.4 -> 52.4 / 64.2
+// -> 62.1, N = 4, 10000000 entries 52.0 -> 50.9, N = 8, 14000000 entries 112 -> 114.
+constexpr u64 kReduceFew = 256, kReduceTwoFrom = 950, kReduceTwoTo = 1300, kReduceMany = 3000, kReduceManyBf16 = 4096;
+inline bool keep_results(u64 bytes, int bytes_read) {   // sum and counts; of all workers an entry
+  return bytes <= (bytes_read <= 12 ? 160u << 20 : bytes_read <= 16 ? 64u << 20 : 24u << 20);
+}
 template <class Wire, int VEC>
 hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N, u64 L, float* sum_out,
                                 uint8_t* count_out, hipStream_t s, int pos) {
@@ -175,7 +178,7 @@ hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N
                       : two                          ? k_masked_reduce<Wire, VEC, 2>
                                                      : k_masked_reduce<Wire, VEC, 4>;
   return orhost::launch_kernel(kernel, dim3((unsigned)blocks), dim3(256), s, pos, (const Wire*)shards, masks, N, L, sum_out, count_out,
-                               L * 5 <= kKeepBytes || N * (int)sizeof(Wire) <= kKeepRead);
+                               keep_results(L * 5, N * (int)sizeof(Wire)));
 }
 
 // ------------------------------------------------------------------ small streaming kernels

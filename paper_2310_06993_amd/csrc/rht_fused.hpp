@@ -10,13 +10,12 @@
 // others, in increasing order) in both modes below.  Blocks that share a tile (K = 0) are looked at one by one: a worker that lost
 // something in the tile is encoded with zeros in the blocks that it has whole, so no block's value depends on its neighbours'.
 //
-// Positions, also of the bf16 encode and the reduce + decode of larger blocks (V entries per 16 bytes: 4 fp32, 8 bf16; VB = log2 V; 16 entries a lane, 1024 a wavefront)
+// Positions (A also of the reduce + decode of larger blocks; V entries per 16 bytes: 4 fp32, 8 bf16; VB = log2 V; 16 entries a lane, 1024 a wavefront)
 //   A  as loaded and stored: register bits = entry bits 0 .. VB-1 and VB+6 .. 9, lane = VB .. VB+5, wavefront = 10 ..
 //   M  register bits = entry bits VB .. VB+3, lane bits (from 0) = VB+4, VB+5, 0 .. VB-1, VB+6 .. 9, wavefront = 10 ..
 //   B  ("wire") lane = entry bits 0 .. 5: a register is 64 consecutive entries, its received bits one lane mask;
 //      register bits = the entry bits not transformed in A and M (U0 = VB+4, U1 = VB+5 and the wavefront bits).
-// Every stage runs as a plain add / subtract between registers, except that tiles of 16 wavefronts have two bits more than
-// registers: U0, U1 are DPP stages on lane bits 0, 1 of M.  Going from A to M stays inside the
+// Every stage runs as a plain add / subtract between registers.  Going from A to M stays inside the
 // wavefront (no barrier), M to B is the exchange between wavefronts.  Entry e sits in LDS at e + (e >> (VB+4) << VB):
 // the 32 lanes of either half of a wavefront then fall into 32 different banks in M and B.
 #pragma once
@@ -28,19 +27,18 @@ template <int K, class In>
 struct FTile {
   static constexpr int VB = sizeof(In) == 4 ? 2 : 3, V = 1 << VB, C = 16 / V;   // C loads of 16 bytes a lane
   static constexpr int KT = K ? K : 10, T = 1 << KT, Q = KT - 10, W = 1 << Q;
-  static_assert(Q == 0 || Q == 1 || Q == 4, "tiles of 2^10, 2^11 and 2^14 entries");
+  static_assert(Q == 0 || Q == 1 || Q == 4, "tiles of 2^10, 2^11 and 2^14 entries; the last ones only in A");
   static constexpr int U0 = VB + 4, U1 = VB + 5;
   static constexpr int O0 = VB == 2 ? 8 : 6, O1 = 9;     // the bits of 6..9 other than U0, U1
   static constexpr int PART = 1024 + 64;                 // floats of a wavefront's entries in LDS
   static constexpr int ROW = (1 << U0) + V;              // floats from one value of entry bit U0 to the next
   static constexpr int reg_bit(int i) {                  // entry bit that register bit i stands for in B
-    return Q == 0 ? (i == 0 ? U0 : i == 1 ? U1 : i == 2 ? O0 : O1)
-         : Q == 1 ? (i == 0 ? U0 : i == 1 ? U1 : i == 2 ? 10 : O0) : i + 10;
+    return Q == 0 ? (i == 0 ? U0 : i == 1 ? U1 : i == 2 ? O0 : O1) : (i == 0 ? U0 : i == 1 ? U1 : i == 2 ? 10 : O0);
   }
-  static constexpr int wave_bit(int i) {                 // and bit i of the wavefront number
-    return Q == 1 ? O1 : i == 0 ? O0 : i == 1 ? O1 : i == 2 ? U0 : U1;
+  static constexpr int wave_bit(int) {                 // and bit i of the wavefront number
+    return O1;
   }
-  static constexpr int kLast = Q == 0 ? 2 : Q == 1 ? 3 : 4;   // register bits that are left to transform in B
+  static constexpr int kLast = Q == 0 ? 2 : 3;   // register bits that are left to transform in B
   static constexpr int reg_entry(int r) {
     int e = 0;
     for (int i = 0; i < 4; ++i) e |= ((r >> i) & 1) << reg_bit(i);
@@ -54,13 +52,6 @@ __device__ __forceinline__ int wire_wave_entry(int wave) {
 #pragma unroll
   for (int i = 0; i < FTile<K, In>::Q; ++i) e |= ((wave >> i) & 1) << FTile<K, In>::wave_bit(i);
   return e;
-}
-// the sign that the DPP stages leave: on the entry bits that took one (U0 and U1 for 16 wavefronts)
-template <int K, class In>
-__device__ __forceinline__ float wire_sigma(int wave) {
-  constexpr int Q = FTile<K, In>::Q;
-  const int odd = Q == 4 ? (wave >> 2) ^ (wave >> 3) : 0;
-  return odd & 1 ? -1.0f : 1.0f;
 }
 template <int W>
 __device__ __forceinline__ void tile_barrier() {   // tiles of one wavefront need none: its LDS accesses are in order
@@ -78,16 +69,12 @@ __device__ __forceinline__ void stages_a(float (&v)[16], int k) {
   if (K || k > 9) reg_stage<3>(v);
 }
 template <int K, class In>
-__device__ __forceinline__ void stages_m(float (&v)[16], int lane, int k) {
-  constexpr int VB = FTile<K, In>::VB, Q = FTile<K, In>::Q;
+__device__ __forceinline__ void stages_m(float (&v)[16], int k) {
+  constexpr int VB = FTile<K, In>::VB;
   reg_stage<0>(v);
   reg_stage<1>(v);
   if (VB == 2 || K || k > VB + 2) reg_stage<2>(v);
   if (K || k > VB + 3) reg_stage<3>(v);
-  if constexpr (Q == 4) {
-    lane_stage<0>(v, lane);
-    lane_stage<1>(v, lane);
-  }
 }
 template <int K, class In>
 __device__ __forceinline__ void stages_b(float (&v)[16], int k) {
@@ -95,7 +82,6 @@ __device__ __forceinline__ void stages_b(float (&v)[16], int k) {
   if (K || k > F::U0) reg_stage<0>(v);
   if (K || k > F::U1) reg_stage<1>(v);
   if constexpr (F::kLast > 2) reg_stage<2>(v);
-  if constexpr (F::kLast > 3) reg_stage<3>(v);
 }
 
 // ---- LDS accesses of the three layouts; x = the tile's buffer of W * PART floats
@@ -141,7 +127,7 @@ __device__ __forceinline__ void to_wire(float (&v)[16], float* x, int wave, int 
   lds_a<K, In, true>(v, x, wave, lane);
   __builtin_amdgcn_wave_barrier();
   lds_m<K, In, false>(v, x, wave, lane);
-  stages_m<K, In>(v, lane, k);
+  stages_m<K, In>(v, k);
   lds_m<K, In, true>(v, x, wave, lane);
   tile_barrier<FTile<K, In>::W>();
   lds_b<K, In, false>(v, x, wave, lane);
@@ -154,7 +140,7 @@ __device__ __forceinline__ void from_wire(float (&v)[16], float* x, int wave, in
   lds_b<K, In, true>(v, x, wave, lane);
   tile_barrier<FTile<K, In>::W>();
   lds_m<K, In, false>(v, x, wave, lane);
-  stages_m<K, In>(v, lane, k);
+  stages_m<K, In>(v, k);
   lds_m<K, In, true>(v, x, wave, lane);
   __builtin_amdgcn_wave_barrier();
   lds_a<K, In, false>(v, x, wave, lane);
@@ -508,7 +494,7 @@ __device__ __forceinline__ void fused_tile(const PathArgs& a, u64 first_unit, u6
         lds_a<K, In, true>(v, x, wave, lane);
         __builtin_amdgcn_wave_barrier();
         lds_m<K, In, false>(v, x, wave, lane);
-        stages_m<K, In>(v, lane, k);
+        stages_m<K, In>(v, k);
         lds_m<K, In, true>(v, x, wave, lane);
       }
       __syncthreads();

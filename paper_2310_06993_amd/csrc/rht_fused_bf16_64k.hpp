@@ -13,16 +13,16 @@
 // Decode: S2 all its registers and both bits of the quarters, S3 its registers, L e0 e1 e2 and e12.
 //
 // Bound by a wavefront's own chain: per worker 1400 additions, 330 other vector instructions and 64 products in each of two
-// wavefronts a SIMD, 4.5 us, and 2.3 us of exchange through LDS, which only partly run at the same time (7.0 to 7.5 us).  us, two
-// workgroups a block that read everything twice and met in memory -> this: N = 8, 15317 blocks 5980 - 6400 -> 4670 - 5030 (4.0 - 4.3 TB/s), 2560
-// blocks 970 -> 738, N = 2, 1000 blocks 240 -> 144.
+// wavefronts a SIMD, 4.5 us, and 2 us of exchange through LDS, which only partly run at the same time (7 us).  us, two
+// workgroups a block that read everything twice and met in memory -> this: N = 8, 15317 blocks 5980 - 6400 -> 4550 - 4700 (4.3 - 4.4 TB/s), 2560
+// blocks 970 -> 715, N = 2, 1000 blocks 240 -> 144.
 //
 // One workgroup is all that fits on a CU, so nothing but the kernel itself runs under its waits for memory.  Three quarters of the
 // next worker's entries are written to LDS by the loads themselves (no registers) from the start of a worker on, the last quarter
 // is asked for once the entries in registers have been used for the last time; and a workgroup walks over blocks, so that this
 // goes on through the decode of a block into the next one.  It does so only while nothing is spilled: the reload of a spilled register
 // waits for everything that was asked for before it.  Hence addresses and constants are formed where they are used (`lane_t`).  us,
-// 44 bytes of scratch a lane -> none: N = 1, 129 blocks 25.0 -> 22.9;  N = 2, 1000 blocks 151 -> 144;  N = 8, 2560 blocks 891 -> 879, nothing
+// 44 bytes of scratch a lane -> none, with the exchange as it was then: N = 1, 129 blocks 25.0 -> 22.9;  N = 2, 1000 blocks 151 -> 144;  N = 8, 2560 blocks 891 -> 879, nothing
 // lost 766 -> 738;  N = 32, 300 blocks 626 -> 624.
 #pragma once
 #include "rht_fused_bf16.hpp"

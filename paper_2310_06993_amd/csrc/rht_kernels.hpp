@@ -94,13 +94,14 @@ __device__ __forceinline__ void across_tiles(float (&v)[PARTS][NR]) {
 }
 
 // Encode and decode store past the caches: their results are not read again here, and their inputs stay.  us, plain -> nontemporal stores,
-// fp32 decode of 2^12, 3145728 / 5242880 / 31457280 / 67108864 entries 7.7 -> 5.8 / 9.9 -> 7.5 / 45.7 -> 43.1 / 92.8 -> 90.0, bf16 6.0 -> 5.4 / 8.3 -> 7.1 /
-// 33.5 -> 32.3 / 70.2 -> 65.3;  fp32 encode of 2^10 6.5 -> 5.0 / 8.7 -> 7.7 / 43.0 -> 42.0 / 89.6 -> 87.9.  Not where fp32 in- and output are larger than
-// the L2 and both fit the last-level cache (256 MB): 11534336 / 17825792 / 25165824 entries, decode of 2^12 17.5 -> 17.8 / 25.0 -> 26.2 / 36.2 -> 34.8,
-// encode 16.8 -> 17.2 / 25.2 -> 26.1 / 35.1 -> 33.9.  Blocks of 2^14, one a workgroup of 16 waves, gain for longer: encode, 12582912 / 17825792 /
-// 20971520 / 23068672 entries 20.2 -> 18.6 / 26.2 -> 26.2 / 31.4 -> 30.6 / 32.5 -> 33.6.
+// fp32 decode of 2^12, 3145728 / 5242880 / 44040192 / 67108864 entries 7.7 -> 5.8 / 9.9 -> 7.5 / 62.8 -> 59.5 / 92.8 -> 90.0, bf16 6.0 -> 5.4 / 8.3 -> 7.1 /
+// 33.5 -> 32.3 / 70.2 -> 65.3;  fp32 encode of 2^10 6.5 -> 5.0 / 8.7 -> 7.7 / 59.9 -> 58.6 / 89.6 -> 87.9.  Not where fp32 in- and output are larger than
+// the L2 and both fit the last-level cache (256 MB): 11534336 / 17825792 entries, decode of 2^12 17.5 -> 17.8 / 25.0 -> 26.2, encode 16.8 -> 17.2 / 25.2 -> 26.1;
+// towards its end the cards differ: 25493504 entries, decode 36.5 -> 35.4 on some, 36.6 -> 38.8 on another, encode of 26 M 37.9 -> 36.9 and 40.3 -> 41.5.
+// Blocks of 2^14, one a workgroup of 16 waves, gain for longer: encode, 12582912 / 17825792 / 20971520 / 23068672 entries 20.2 -> 18.6 / 26.2 -> 26.2 / 31.4
+// -> 30.6 / 32.5 -> 33.6.
 template <int K> constexpr u64 kKeepFrom = (K == 14 ? 20u : 10u) << 20;
-constexpr u64 kKeepTo = 23u << 20;
+constexpr u64 kKeepTo = 32u << 20;
 template <int K, bool LAYOUT_B, bool FULL, class T>
 __device__ __forceinline__ void store_result(T* p, u64 e0, u64 limit, u64 n_pad, int wave, int lane, const float (&v)[Geo<K>::R]) {
   if (sizeof(T) == 4 && n_pad > kKeepFrom<K> && n_pad <= kKeepTo) {
