@@ -14,8 +14,8 @@
 //
 // Bound by a wavefront's own chain: per worker 1400 additions, 330 other vector instructions and 64 products in each of two
 // wavefronts a SIMD, 4.5 us, and 2 us of exchange through LDS, which only partly run at the same time (7 us).  us, two
-// workgroups a block that read everything twice and met in memory -> this: N = 8, 15317 blocks 5980 - 6400 -> 4550 - 4700 (4.3 - 4.4 TB/s), 2560
-// blocks 970 -> 715, N = 2, 1000 blocks 240 -> 144.
+// workgroups a block that read everything twice and met in memory -> this: N = 8, 15317 blocks 5980 - 6400 -> 4600 - 4760 (4.2 - 4.4 TB/s), 2560
+// blocks 970 -> 743, N = 2, 1000 blocks 240 -> 144.
 //
 // One workgroup is all that fits on a CU, so nothing but the kernel itself runs under its waits for memory.  Three quarters of the
 // next worker's entries are written to LDS by the loads themselves (no registers) from the start of a worker on, the last quarter
@@ -36,7 +36,7 @@ constexpr int kStaged = 10;   // of a lane's 16 loads of a worker: through LDS
 // stores to 32 banks of 4 bytes; a 16-byte load goes by 16 lanes, those of a half whose lane bits 2, 3, 4 have the same parity, which have to
 // cover 64 banks.  Entry bits from the lowest address bit up: e5 (e6^e7) e0 e1 e2 e3 e4 e7 e10 .. e15, with neither conflicts of the stores
 // (lanes e0 e1 e2 e7 e5 in a half) nor of the loads.  e7 is a lane bit of S2, where the XOR swaps two registers of the stage of e6: their sum is
-// the same, and their difference changes its sign (s2_sign), the same one for all workers, which the mean takes back.  us, 64 KB, with two
+// the same, and their difference changes its sign, the same one for all workers, which the mean takes back (s2_sign).  us, 64 KB, with two
 // lanes on every bank 0.45 + 0.23 -> 0.36 + 0.14.
 __device__ __forceinline__ int quarter_s1(int wave, int lane) {   // + 32 e3 + 64 e4 + 256 (r >> 2)
   return wave * 2048 + (lane & 7) * 4 + ((lane >> 4) & 1) + (((lane >> 5) ^ (lane >> 3)) & 1) * 2 + ((lane >> 3) & 1) * 128;
@@ -279,21 +279,32 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
           request_rest(after, kStaged, rest_at_once);
           if (rest_at_once == 16) request_words(words_after);
         }
-        // eight registers at a time after the stages between the eights: the others' stages run under their stores, and only the last
-        // stores are waited for
+        // a half of the registers at a time after the stage between the halves, and eight of them once the stage between the eights has
+        // made them: the other half's stages run under their stores, and only the last stores are waited for.  (That stage before the other
+        // three, and four times eight registers by themselves: 2560 blocks of 8 workers, nothing lost, 743 -> 723 us, but other bits.)
         reg_stage<4>(v);
-        reg_stage<3>(v);
         float* to = x + quarter_s1(wave, lane_t);
 #pragma unroll
-        for (int h = 0; h < 4; ++h) {
-          auto& vh = *(float (*)[8])&v[8 * h];
-          reg_stage<0>(vh);
-          reg_stage<1>(vh);
-          reg_stage<2>(vh);
+        for (int h = 0; h < 2; ++h) {
+          auto& vh = *(float (*)[16])&v[16 * h];
+          reg_stages(vh, 0, 3);
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int r = 0; r < 8; ++r) to[(r & 1) * 32 + ((r >> 1) & 1) * 64 + (r >> 2) * 256 + h * 512] = vh[r];
-          __builtin_amdgcn_sched_barrier(0);
+          for (int g = 0; g < 2; ++g) {
+#pragma unroll
+            for (int r = 4 * g; r < 4 * g + 4; ++r) {
+              const float t = vh[r];
+              vh[r] = t + vh[r + 8];
+              vh[r + 8] = t - vh[r + 8];
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              float* at_r = to + (r & 1) * 32 + (r >> 1) * 64 + g * 256 + h * 1024;
+              at_r[0] = vh[4 * g + r];
+              at_r[512] = vh[4 * g + r + 8];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
         lds_barrier<8>();
         {

@@ -1,5 +1,7 @@
 """The fused path at the edges of the forms for launches of few blocks, and bf16 above 2^10: numbers of workers around the groups that encode side by side, numbers
 of blocks around the rules that choose them, with and without losses."""
+import zlib
+
 import numpy as np
 import pytest
 import torch
@@ -207,3 +209,32 @@ def test_bf16_subnormals_and_infinities(b, orc, k, blocks):
             assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[np.isinf(got)], want[np.isinf(want)]), j
     if blocks > 2:
         assert bool(torch.isfinite(out[B:-B]).all())
+
+
+# crc32 of results and counts, from the kernel as it was before its exchange through LDS was laid out without bank conflicts
+BITS_64K = {(2, 2): 3482775782, (9, 66): 52690716, (3, 259): 2449376446}
+
+
+@pytest.mark.parametrize("N,blocks", sorted(BITS_64K))
+def test_bits_of_the_largest_blocks_stay(b, N, blocks):
+    """bf16 blocks of 2^16: the order of the additions, and with it every bit of the results, in each split of a block and in the walk.  A
+    rounding of an encoded value that goes the other way changes results by a bf16 step, which no tolerance shows.  Values of
+    sixteen binades, blocks and halves of blocks of zeros, runs and single entries lost."""
+    k, B, L = 16, 1 << 16, blocks << 16
+
+    def noise(count, salt):   # whole numbers only: the same on every machine
+        h = torch.arange(count, device=dev(), dtype=torch.int64) * 0x5851F42D4C957F2D + salt * 0x14057B7EF767814F
+        h = (h ^ ((h >> 29) & 0x7FFFFFFFF)) * 0x2545F4914F6CDD1D
+        return (h >> 31) & 0xFFFFFFFF
+
+    h = noise(N * L, 1)
+    x = ((h & 0x807F) | ((108 + ((h >> 16) & 15)) << 7)).to(torch.int32).to(torch.int16).view(torch.bfloat16).view(N, L)
+    x[:, B // 2:B] = 0
+    x[:, -B:] = 0
+    h = noise(N * L // 32, 2).view(N, -1)
+    m = torch.where(h % 97 == 0, h, 0xFFFFFFFF)
+    m.view(N, -1, 16)[h.view(N, -1, 16)[:, :, 0] % 31 == 0] = 0
+    m[0, 2048 * (blocks // 2):2048 * (blocks // 2 + 1)] = 0xFFFFFFFF
+    out, cnt = torch.empty(L, dtype=torch.bfloat16, device=dev()), torch.empty(L, dtype=torch.uint8, device=dev())
+    b.or_fused_path_bf16(x, m.to(torch.int32), N, L, k, 0x0123456789ABCDEF, 5 * B, out, cnt, _workspace(b, L, k))
+    assert zlib.crc32(to_np(cnt).tobytes(), zlib.crc32(to_np(out).tobytes())) == BITS_64K[N, blocks]
