@@ -139,10 +139,6 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
   __shared__ __align__(16) u32x4v signs[512];   // of the lane's 16 loads: pair_signs of four loads each
   const int wave = wave_id(), lane = lane_id();
 
-  // NQ = 2 has registers for the loads that do not go through LDS: all are asked for in the first half of a worker, and none has to wait until
-  // the entries in work have been used.  us, 1 % loss, N = 4 / 8 / 32, 100 blocks 45.2 -> 44.7 / 68.0 -> 66.6 / 205 -> 199
-  constexpr bool EARLY = NQ == 2;
-  [[maybe_unused]] u32x4v rest[6];
   u32x4v p[16];   // load q: 8 entries from 512 q + 8 lane of the wavefront's part
   auto part_of = [&](const PathArgs& a, u64 blk, int i) { return (const bf16_t*)a.in + (u64)i * a.n_pad + (blk << 16) + (u64)wave * 8192; };
   // The loads that write LDS are out of the compiler's sight, which would
@@ -158,13 +154,12 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
   u32x4v mw;   // received bits of the worker whose entries are on their way
   auto landed = [&]() {   // names what the compiler knows to be in flight: it waits for that here and not behind the loads that follow
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if constexpr (EARLY) asm volatile("" : "+v"(rest[0]), "+v"(rest[1]), "+v"(rest[2]), "+v"(rest[3]), "+v"(rest[4]), "+v"(rest[5]), "+v"(mw));
-    else asm volatile("" : "+v"(p[10]), "+v"(p[11]), "+v"(p[12]), "+v"(p[13]), "+v"(p[14]), "+v"(p[15]), "+v"(mw));
+    asm volatile("" : "+v"(p[10]), "+v"(p[11]), "+v"(p[12]), "+v"(p[13]), "+v"(p[14]), "+v"(p[15]), "+v"(mw));
   };
   auto request_rest = [&](const bf16_t* part, int from, int to_q) {   // null: zeros, without touching memory
     const __amdgpu_buffer_rsrc_t rs = rsrc_of(part, part ? 16384 : 0);
 #pragma unroll
-    for (int q = from; q < to_q; ++q) (EARLY ? rest[q - kStaged] : p[q]) = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, q * 1024, kBufNt));
+    for (int q = from; q < to_q; ++q) p[q] = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, q * 1024, kBufNt));
   };
   // received bits in S2: the wavefront's 1024 entries of each eighth of the block; lane l holds 128 entries (four words, e5 e6) of
   // eighth l >> 3, from 128 (l & 7) on
@@ -218,10 +213,6 @@ __device__ __forceinline__ void fused_bf16_walk_64k(uint32_t first, uint32_t blo
       }
 #pragma unroll
       for (int q = 0; q < kStaged; ++q) p[q] = stage[(wave * kStaged + q) * 64 + lane_t];
-      if constexpr (EARLY) {
-#pragma unroll
-        for (int q = kStaged; q < 16; ++q) p[q] = rest[q - kStaged];
-      }
       const u32x4v sg = signs[wave * 64 + lane_t];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
