@@ -152,7 +152,8 @@ __global__ __launch_bounds__(256) void k_masked_reduce_batched(ReduceBatch rb) {
 // entries (rows a power of two apart) 72.3 -> 66.6 / 213 -> 202, but 1000000 entries 11.8 -> 12.8 / 28.0 -> 30.9, and a few workgroups more than
 // run at once (2048) are a long chain: 2100000 entries, N = 12 25.5 -> 28.3; bf16, of half as many bytes, from 16 workers on
 // and later: 8388608 / 12345664 entries, N = 16 71.0 -> 65.6 / 98.2 -> 96.2, N = 32 131 -> 109 / 167 -> 161, but N = 8 44.2 -> 43.1 / 63.3 -> 64.6, 6000000
-// entries, N = 16 48.4 -> 50.2.
+// entries, N = 16 48.4 -> 50.2; and with two workers where sum and counts go past the caches: us of the reduce by itself, a pair at once -> one,
+// 40000000 / 60000000 / 120000000 entries 72.2 -> 66.2 / 108 -> 97.5 / 218 -> 193, but kept, 14000000 entries 24.7 -> 26.0 (N = 3, 6: no difference).
 // bf16 launches of 950 to 1300 workgroups (about four to five a CU) in between, from 12 workers on: two.  us, four -> two, N = 16 / 32, 2100000 entries
 // 21.5 -> 20.8 / 33.9 -> 32.5, 2300000 entries 23.2 -> 22.0 / 37.2 -> 35.3, but 1500000 entries, N = 16 15.1 -> 15.0, 3194880 entries 28.3 -> 29.7.
 // Sum and counts stay in the L2 (32 MB) where they fit: k_finalize reads every entry on the XCD that wrote it; and in the last-level cache
@@ -171,14 +172,14 @@ hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N
   const u64 threads = (L + VEC - 1) / VEC;
   const u64 blocks = (threads + 255) / 256;
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  const bool one = sizeof(Wire) == 4 ? blocks >= kReduceMany : N >= 16 && blocks >= kReduceManyBf16;
+  const bool keep = keep_results(L * 5, N * (int)sizeof(Wire));
+  const bool one = sizeof(Wire) == 4 ? blocks >= kReduceMany : (N >= 16 && blocks >= kReduceManyBf16) || (N == 2 && !keep);
   const bool two = sizeof(Wire) == 2 && N >= 12 && blocks >= kReduceTwoFrom && blocks < kReduceTwoTo;
   const auto kernel = blocks <= kReduceFew && N >= 8 ? k_masked_reduce<Wire, VEC, 8>
                       : one                          ? k_masked_reduce<Wire, VEC, 1>
                       : two                          ? k_masked_reduce<Wire, VEC, 2>
                                                      : k_masked_reduce<Wire, VEC, 4>;
-  return orhost::launch_kernel(kernel, dim3((unsigned)blocks), dim3(256), s, pos, (const Wire*)shards, masks, N, L, sum_out, count_out,
-                               keep_results(L * 5, N * (int)sizeof(Wire)));
+  return orhost::launch_kernel(kernel, dim3((unsigned)blocks), dim3(256), s, pos, (const Wire*)shards, masks, N, L, sum_out, count_out, keep);
 }
 
 // ------------------------------------------------------------------ small streaming kernels
