@@ -183,12 +183,10 @@ hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N
 }
 
 // ------------------------------------------------------------------ small streaming kernels
-// mean = sum / count, 0 where count is 0 (Sec. 3.1.1 "averages" over what arrived); 16 bytes of it a lane, the entries of a workgroup of
-// k_masked_reduce for the same type.  us, reduce + finalize, bf16, 4 -> 8 entries a lane: N = 2, 524288 / 3194880 entries 5.6 -> 4.7 / 13.7 -> 13.5
-template <class Out>
+// mean = sum / count, 0 where count is 0 (Sec. 3.1.1 "averages" over what arrived); VEC entries a lane
+template <class Out, int VEC>
 __global__ __launch_bounds__(256) void k_finalize(const float* __restrict__ sum, const uint8_t* __restrict__ count, u64 L,
                                                   Out* __restrict__ mean) {
-  constexpr int VEC = 16 / sizeof(Out);
   const u64 e = ((u64)blockIdx.x * 256 + threadIdx.x) * VEC;
   if (e >= L) return;
   typedef float f4 __attribute__((ext_vector_type(4)));
@@ -208,11 +206,11 @@ __global__ __launch_bounds__(256) void k_finalize(const float* __restrict__ sum,
   if constexpr (sizeof(Out) == 4) {
     *(f4*)(mean + e) = f4{m[0], m[1], m[2], m[3]};
   } else {
-    typedef uint16_t h8 __attribute__((ext_vector_type(8)));
-    h8 h;
+    typedef uint16_t hv __attribute__((ext_vector_type(VEC)));
+    hv h;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) h[j] = __builtin_bit_cast(uint16_t, (__bf16)m[j]);
-    *(h8*)(mean + e) = h;
+    for (int j = 0; j < VEC; ++j) h[j] = __builtin_bit_cast(uint16_t, (__bf16)m[j]);
+    *(hv*)(mean + e) = h;
   }
 }
 
@@ -507,6 +505,10 @@ or_status path_impl(bool fused, const T* in, const uint32_t* masks, int N, u64 L
   return run_path<T>(fused, in, masks, N, L, k, seed, base, out, count_out, ws, stream, bf16);
 }
 
+// Entries a lane.  bf16: eight, 16 bytes of the mean and the entries of a workgroup of k_masked_reduce, whose results are then on the XCD that
+// reads them; but four where sum and counts are read from memory (keep_results).  us, reduce + finalize, four -> eight: N = 2, 524288 / 20000000 /
+// 30000000 entries 5.8 -> 4.7 / 57.3 -> 56.7 / 82.6 -> 80.8, but 60000000 / 120000000 entries, N = 2 181 -> 184 / 362 -> 370, N = 4 205 -> 208 / 404 -> 412.
+constexpr u64 kFinalizeNarrowFrom = 160u << 20;   // bytes of sum and counts
 template <class Out>
 or_status finalize_impl(const float* sum, const uint8_t* count, u64 L, Out* mean, void* stream) {
   DisarmOnExit disarm;
@@ -517,9 +519,12 @@ or_status finalize_impl(const float* sum, const uint8_t* count, u64 L, Out* mean
   if (ranges_overlap(mean, L * sizeof(Out), count, L)) return OR_ERR_SHAPE;
   if (ranges_overlap(mean, L * sizeof(Out), sum, L * 4) && !((const void*)mean == (const void*)sum && sizeof(Out) == 4))
     return OR_ERR_SHAPE;
-  const u64 blocks = (L * sizeof(Out) / 16 + 255) / 256;
+  const bool wide = sizeof(Out) == 2 && L * 5 <= kFinalizeNarrowFrom;
+  const u64 blocks = (L / (wide ? 8 : 4) + 255) / 256;
   if (blocks > 0x7FFFFFFFull) return OR_ERR_SHAPE;
-  return finish(orhost::launch_kernel(k_finalize<Out>, dim3((unsigned)blocks), dim3(256), (hipStream_t)stream,
+  auto kernel = k_finalize<Out, 4>;
+  if constexpr (sizeof(Out) == 2) if (wide) kernel = k_finalize<Out, 8>;
+  return finish(orhost::launch_kernel(kernel, dim3((unsigned)blocks), dim3(256), (hipStream_t)stream,
                                       orhost::LAUNCH_ONLY, sum, count, L, mean));
 }
 
