@@ -160,10 +160,12 @@ __global__ __launch_bounds__(256) void k_masked_reduce_batched(ReduceBatch rb) {
 // (256 MB) where the workers together are at most 12 bytes an entry, or 16 and sum and counts few enough to live next to them.  us, streamed past ->
 // kept, bf16, N = 4, 3194880 / 14000000 / 30000000 / 60000000 entries 16.1 -> 15.0 / 50.8 -> 46.8 / 106 -> 100 / 209 -> 221, N = 2, 18000000 entries
 // 56.9 -> 50.4, N = 8, 6000000 / 10000000 / 18000000 entries 32.0 -> 30.8 / 49.4 -> 48.2 / 90.6 -> 92.7; fp32, N = 2 / 3, 14000000 entries 55.4 -> 52.4 / 64.2
-// -> 62.1, N = 4, 10000000 entries 52.0 -> 50.9, N = 8, 14000000 entries 112 -> 114.
+// -> 62.1, N = 4, 10000000 entries 52.0 -> 50.9, N = 8, 14000000 entries 112 -> 114.  From 32 bytes read an entry on, where the workers go through the L2 too,
+// only up to 10 MB: bf16, N = 16, 2700000 entries 25.6 -> 26.2, N = 24, 4000000 44.9 -> 46.0;  fp32, N = 8 / 24, 3194880 entries 27.1 -> 27.8 / 59.9 -> 62.9, 4600000
+// 39.1 -> 39.5 / 91.0 -> 92.9, but 2100000 entries 19.6 -> 19.3 / 42.3 -> 41.6, and with fewer, fp32, N = 5, 2700000 entries 19.2 -> 18.8.
 constexpr u64 kReduceFew = 256, kReduceTwoFrom = 950, kReduceTwoTo = 1300, kReduceMany = 3000, kReduceManyBf16 = 4096;
 inline bool keep_results(u64 bytes, int bytes_read) {   // sum and counts; of all workers an entry
-  return bytes <= (bytes_read <= 12 ? 160u << 20 : bytes_read <= 16 ? 64u << 20 : 24u << 20);
+  return bytes <= (bytes_read <= 12 ? 160u << 20 : bytes_read <= 16 ? 64u << 20 : bytes_read < 32 ? 24u << 20 : 10u << 20);
 }
 template <class Wire, int VEC>
 hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N, u64 L, float* sum_out,

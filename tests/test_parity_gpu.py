@@ -201,7 +201,8 @@ def test_integer_round_trip_is_bit_exact(b, k):
 # ------------------------------------------------------------------ aggregation
 @pytest.mark.parametrize("kind,N,L", [("f32", 11, 256 * 1024), ("f32", 7, 256 * 1024 + 32), ("f32", 5, 2999 * 1024), ("f32", 5, 2999 * 1024 + 32),
                                       ("bf16", 11, 256 * 2048), ("bf16", 7, 256 * 2048 + 32), ("bf16", 16, 4095 * 2048), ("bf16", 16, 4095 * 2048 + 32),
-                                      ("bf16", 15, 4096 * 2048), ("bf16", 2, 1 << 25), ("bf16", 2, (1 << 25) + 32)])
+                                      ("bf16", 15, 4096 * 2048), ("bf16", 2, 1 << 25), ("bf16", 2, (1 << 25) + 32),
+                                      ("bf16", 16, 1 << 21), ("bf16", 16, (1 << 21) + 32), ("f32", 8, 1 << 21), ("f32", 8, (1 << 21) + 32)])
 def test_masked_reduce_forms(b, kind, N, L):
     """The masked reduce around the launch sizes where the number of workers asked for at once changes, and where sum and counts no longer
     stay in the L2, then the mean: the same additions in the same order as a loop over the workers, so the same bits."""
