@@ -154,8 +154,9 @@ __global__ __launch_bounds__(256) void k_masked_reduce_batched(ReduceBatch rb) {
 // and later: 8388608 / 12345664 entries, N = 16 71.0 -> 65.6 / 98.2 -> 96.2, N = 32 131 -> 109 / 167 -> 161, but N = 8 44.2 -> 43.1 / 63.3 -> 64.6, 6000000
 // entries, N = 16 48.4 -> 50.2; and with two workers where sum and counts go past the caches: us of the reduce by itself, a pair at once -> one,
 // 40000000 / 60000000 / 120000000 entries 72.2 -> 66.2 / 108 -> 97.5 / 218 -> 193, but kept, 14000000 entries 24.7 -> 26.0 (N = 3, 6: no difference).
-// bf16 launches of 950 to 1300 workgroups (about four to five a CU) in between, from 12 workers on: two.  us, four -> two, N = 16 / 32, 2100000 entries
-// 21.5 -> 20.8 / 33.9 -> 32.5, 2300000 entries 23.2 -> 22.0 / 37.2 -> 35.3, but 1500000 entries, N = 16 15.1 -> 15.0, 3194880 entries 28.3 -> 29.7.
+// bf16 launches of 950 to 1300 workgroups (about four to five a CU) in between, from 12 workers on: two.  us, four -> two, 2100000 entries, N = 12 / 13 / 16 /
+// 17 / 24 18.4 -> 17.9 / 19.4 -> 18.7 / 21.7 -> 21.1 / 22.8 -> 21.4 / 27.6 -> 26.3, 2300000 entries 19.9 -> 19.3 / 20.5 -> 20.0 / 22.7 -> 22.1 / 24.4 -> 23.2 / 30.2 ->
+// 28.7, but 1500000 entries, N = 16 15.1 -> 15.0, 3194880 entries 28.3 -> 29.7.
 // Sum and counts stay in the L2 (32 MB) where they fit: k_finalize reads every entry on the XCD that wrote it; and in the last-level cache
 // (256 MB) where the workers together are at most 12 bytes an entry, or 16 and sum and counts few enough to live next to them.  us, streamed past ->
 // kept, bf16, N = 4, 3194880 / 14000000 / 30000000 / 60000000 entries 16.1 -> 15.0 / 50.8 -> 46.8 / 106 -> 100 / 209 -> 221, N = 2, 18000000 entries
@@ -176,11 +177,10 @@ hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
   const bool keep = keep_results(L * 5, N * (int)sizeof(Wire));
   const bool one = sizeof(Wire) == 4 ? blocks >= kReduceMany : (N >= 16 && blocks >= kReduceManyBf16) || (N == 2 && !keep);
-  const bool two = sizeof(Wire) == 2 && N >= 12 && blocks >= kReduceTwoFrom && blocks < kReduceTwoTo;
-  const auto kernel = blocks <= kReduceFew && N >= 8 ? k_masked_reduce<Wire, VEC, 8>
-                      : one                          ? k_masked_reduce<Wire, VEC, 1>
-                      : two                          ? k_masked_reduce<Wire, VEC, 2>
-                                                     : k_masked_reduce<Wire, VEC, 4>;
+  auto kernel = k_masked_reduce<Wire, VEC, 4>;
+  if (blocks <= kReduceFew && N >= 8) kernel = k_masked_reduce<Wire, VEC, 8>;
+  else if (one) kernel = k_masked_reduce<Wire, VEC, 1>;
+  else if constexpr (sizeof(Wire) == 2) if (N >= 12 && blocks >= kReduceTwoFrom && blocks < kReduceTwoTo) kernel = k_masked_reduce<Wire, VEC, 2>;
   return orhost::launch_kernel(kernel, dim3((unsigned)blocks), dim3(256), s, pos, (const Wire*)shards, masks, N, L, sum_out, count_out, keep);
 }
 

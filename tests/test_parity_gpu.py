@@ -202,10 +202,13 @@ def test_integer_round_trip_is_bit_exact(b, k):
 @pytest.mark.parametrize("kind,N,L", [("f32", 11, 256 * 1024), ("f32", 7, 256 * 1024 + 32), ("f32", 5, 2999 * 1024), ("f32", 5, 2999 * 1024 + 32),
                                       ("bf16", 11, 256 * 2048), ("bf16", 7, 256 * 2048 + 32), ("bf16", 16, 4095 * 2048), ("bf16", 16, 4095 * 2048 + 32),
                                       ("bf16", 15, 4096 * 2048), ("bf16", 2, 1 << 25), ("bf16", 2, (1 << 25) + 32),
-                                      ("bf16", 16, 1 << 21), ("bf16", 16, (1 << 21) + 32), ("f32", 8, 1 << 21), ("f32", 8, (1 << 21) + 32)])
+                                      ("bf16", 16, 1 << 21), ("bf16", 16, (1 << 21) + 32), ("f32", 8, 1 << 21), ("f32", 8, (1 << 21) + 32),
+                                      ("f32", 11, 256 * 1024 + 32), ("bf16", 11, 256 * 2048 + 32), ("f32", 5, 5033152), ("f32", 5, 5033184),
+                                      ("bf16", 8, 13421760), ("bf16", 8, 13421792), ("bf16", 11, 1000 * 2048), ("bf16", 13, 949 * 2048),
+                                      ("bf16", 13, 949 * 2048 + 32), ("bf16", 14, 1299 * 2048), ("bf16", 13, 1299 * 2048), ("bf16", 13, 1299 * 2048 + 32)])
 def test_masked_reduce_forms(b, kind, N, L):
-    """The masked reduce around the launch sizes where the number of workers asked for at once changes, and where sum and counts no longer
-    stay in the L2, then the mean: the same additions in the same order as a loop over the workers, so the same bits."""
+    """The masked reduce around the launch sizes where the number of workers asked for at once changes (256, 950, 1300, 3000, 4096 workgroups), and
+    where sum and counts no longer stay in the caches (10, 24, 64, 160 MB, by the bytes read an entry), then the mean: the same additions in the same order as a loop over the workers, so the same bits."""
     gen = torch.Generator(device=dev()).manual_seed(L % 1000 + N)
     x = torch.randn((N, L), device=dev(), generator=gen).to(torch.float32 if kind == "f32" else torch.bfloat16)
     masks = torch.randint(-2**31, 2**31 - 1, (N, L // 32), device=dev(), generator=gen, dtype=torch.int64).to(torch.int32)
