@@ -101,12 +101,18 @@ __device__ __forceinline__ void across_tiles(float (&v)[PARTS][NR]) {
 
 // Encode and decode store past the caches: their results are not read again here, and their inputs stay.  us, plain -> nontemporal stores,
 // fp32 decode of 2^12, 3145728 / 5242880 / 44040192 / 67108864 entries 7.7 -> 5.8 / 9.9 -> 7.5 / 62.8 -> 59.5 / 92.8 -> 90.0, bf16 6.0 -> 5.4 / 8.3 -> 7.1 /
-// 33.5 -> 32.3 / 70.2 -> 65.3;  fp32 encode of 2^10 6.5 -> 5.0 / 8.7 -> 7.7 / 59.9 -> 58.6 / 89.6 -> 87.9.  Not where fp32 in- and output are larger than
-// the L2 and both fit the last-level cache (256 MB): 11534336 / 17825792 entries, decode of 2^12 17.5 -> 17.8 / 25.0 -> 26.2, encode 16.8 -> 17.2 / 25.2 -> 26.1;
-// towards its end the cards differ: 25493504 entries, decode 36.5 -> 35.4 on some, 36.6 -> 38.8 on another, encode of 26 M 37.9 -> 36.9 and 40.3 -> 41.5.
-// Blocks of 2^14, one a workgroup of 16 waves, gain for longer: encode, 12582912 / 17825792 / 20971520 / 23068672 entries 20.2 -> 18.6 / 26.2 -> 26.2 / 31.4
-// -> 30.6 / 32.5 -> 33.6.
-template <int K> constexpr u64 kKeepFrom = (K == 14 ? 20u : 10u) << 20;
+// 33.5 -> 32.3 / 70.2 -> 65.3;  fp32 encode of 2^10 6.5 -> 5.0 / 8.7 -> 7.7 / 59.9 -> 58.6 / 89.6 -> 87.9.
+// Part of that is lost again by who reads the results next; call and reader (p += out) together, fp32 encode / decode of 2^12, 2 sets of buffers
+// in turn, 4194304 entries 15.1 -> 14.1 / 16.0 -> 14.5, 44040192 150 -> 135 / 151 -> 139.  Hence not where fp32 in- and output are larger than the L2 and both
+// fit the last-level cache (256 MB): together, 7340032 / 10485760 entries 24.6 -> 26.0 / 33.6 -> 35.7 and 24.7 -> 26.1 / 34.5 -> 36.0 (by themselves 11.1 -> 10.4 /
+// 15.8 -> 15.4 and 11.5 -> 10.3 / 16.5 -> 15.4, of 16 sets 12.0 -> 12.4 / 16.9 -> 17.0 and 12.1 -> 12.5 / 17.4 -> 17.4);  by themselves, 11534336 / 17825792
+// entries, decode 17.5 -> 17.8 / 25.0 -> 26.2, encode 16.8 -> 17.2 / 25.2 -> 26.1;  towards its end the cards differ: 25493504 entries, decode 36.5 -> 35.4 on some,
+// 36.6 -> 38.8 on another, encode of 26 M 37.9 -> 36.9 and 40.3 -> 41.5.
+// 2^13 gains up to 6 M: together, 6291456 / 7340032 entries 21.8 -> 22.0 / 24.7 -> 26.3 and 22.7 -> 21.6 / 25.6 -> 27.0.  Blocks of 2^14, one a workgroup of 16 waves,
+// gain for longer: encode, 12582912 / 17825792 / 20971520 / 23068672 entries 20.2 -> 18.6 / 26.2 -> 26.2 / 31.4 -> 30.6 / 32.5 -> 33.6, together 41.4 -> 42.2 / 60.3 -> 62.2
+// (12 and 18 M).  bf16 results: by themselves, decode of 2^12, 12 / 20 / 30 M 15.4 -> 14.7 / 23.5 -> 22.1 / 33.3 -> 32.1, together 26.9 -> 27.4 / 40.9 -> 42.2 / 58.4
+// -> 60.2: left past the caches.
+template <int K> constexpr u64 kKeepFrom = K == 14 ? 16u << 20 : K == 13 ? 13u << 19 : 6u << 20;
 constexpr u64 kKeepTo = 32u << 20;
 template <int K, bool LAYOUT_B, bool FULL, class T>
 __device__ __forceinline__ void store_result(T* p, u64 e0, u64 limit, u64 n_pad, int wave, int lane, const float (&v)[Geo<K>::R]) {
