@@ -47,17 +47,28 @@ typedef Geo<K> G;
   }
 
 #if OR_K <= 14
-#define OR_ENC(In, Wire) (k_encode<K, In, Wire>)
-#define OR_DEC(Out, FIN, MASKED) (k_decode<K, Out, FIN, MASKED>)
+#define OR_F32_LAUNCHER(name, Args, keep, kernel, ...)                                         \
+  hipError_t name(const Args& a, unsigned long long units, hipStream_t s, int pos) {           \
+    if (units == 0) return hipSuccess;                                                         \
+    if (units > 0x7FFFFFFFull) return hipErrorInvalidValue;                                    \
+    return launch_kernel(keep ? kernel<K, __VA_ARGS__, true> : kernel<K, __VA_ARGS__, false>, dim3((unsigned)units), dim3(G::THREADS), s, pos, a); \
+  }
+OR_LAUNCHER(enc_f32, (k_encode<K, float, float>))
+OR_F32_LAUNCHER(dec_f32, PathArgs, keeps_results<K>(a.n_pad), k_decode, float, false, false)
+OR_F32_LAUNCHER(fdec_f32, PathArgs, keeps_finalized<K>(a.n_pad), k_decode, float, true, false)
+OR_F32_LAUNCHER(mdec_f32, PathArgs, keeps_results<K>(a.n_pad), k_decode, float, false, true)
+#define OR_DEC(Out, FIN, MASKED) (k_decode<K, Out, FIN, MASKED, false>)
 #define OR_XFORM_LAUNCHER OR_LAUNCHER
 #else
-#define OR_ENC(In, Wire) (k_encode_block<K, In, Wire>)
 #define OR_DEC(Out, FIN, MASKED) (k_decode_block<K, Out, FIN, MASKED>)
 #define OR_XFORM_LAUNCHER OR_BLOCK_LAUNCHER
+OR_BLOCK_LAUNCHER(enc_f32, (k_encode_block<K, float, float>))
+OR_BLOCK_LAUNCHER(dec_f32, OR_DEC(float, false, false))
+OR_BLOCK_LAUNCHER(fdec_f32, OR_DEC(float, true, false))
+OR_BLOCK_LAUNCHER(mdec_f32, OR_DEC(float, false, true))
 #endif
-OR_XFORM_LAUNCHER(enc_f32, OR_ENC(float, float))
 #if OR_K == 0
-OR_LAUNCHER(enc_bf16, OR_ENC(bf16_t, bf16_t))
+OR_LAUNCHER(enc_bf16, (k_encode<K, bf16_t, bf16_t>))
 #elif OR_K <= 14
 OR_LAUNCHER_T(enc_bf16, k_encode_bf16<K>, MTile<K>::THREADS)
 #else
@@ -78,11 +89,8 @@ hipError_t enc_bf16(const PathArgs& a, unsigned long long units, hipStream_t s, 
   return blocks <= kEncodeSplit && a.in != a.out ? enc_bf16_split<EBlock<K>::P>(a, blocks, s, pos) : enc_bf16_split<1>(a, blocks, s, pos);
 }
 #endif
-OR_XFORM_LAUNCHER(dec_f32, OR_DEC(float, false, false))
 OR_XFORM_LAUNCHER(dec_bf16, OR_DEC(bf16_t, false, false))
-OR_XFORM_LAUNCHER(fdec_f32, OR_DEC(float, true, false))
 OR_XFORM_LAUNCHER(fdec_bf16, OR_DEC(bf16_t, true, false))
-OR_XFORM_LAUNCHER(mdec_f32, OR_DEC(float, false, true))
 OR_XFORM_LAUNCHER(mdec_bf16, OR_DEC(bf16_t, false, true))
 #if OR_K <= 14
 // reduce+decode of 2^13 and 2^14 blocks keeps 32 entries per lane
@@ -98,8 +106,8 @@ OR_LAUNCHER_T(rdec_bf16, (k_reduce_decode<KR, bf16_t, bf16_t>), Geo<KR>::THREADS
   }
 OR_BATCH_LAUNCHER(rdecb_f32, (k_reduce_decode_batched<KR, float>), Geo<KR>::THREADS)
 OR_BATCH_LAUNCHER(rdecb_bf16, (k_reduce_decode_batched<KR, bf16_t>), Geo<KR>::THREADS)
-OR_BATCH_LAUNCHER(fdecb_f32, (k_finalize_decode_batched<K, float>), G::THREADS)
-OR_BATCH_LAUNCHER(fdecb_bf16, (k_finalize_decode_batched<K, bf16_t>), G::THREADS)
+OR_F32_LAUNCHER(fdecb_f32, BatchArgs, keeps_finalized<K>(units * G::T), k_finalize_decode_batched, float)
+OR_BATCH_LAUNCHER(fdecb_bf16, (k_finalize_decode_batched<K, bf16_t, false>), G::THREADS)
 // Which workers are added before they are encoded is a matter of type, block size and number of workers alone: the two ways
 // round differently, and a bucket gives the same bits alone, in a batch and as part of a longer shard.
 //   bf16: every worker is encoded by itself (its encoded value is rounded); above 2^10 in a kernel of its own (rht_fused_bf16.hpp).

@@ -114,15 +114,15 @@ __device__ __forceinline__ void across_tiles(float (&v)[PARTS][NR]) {
 // -> 60.2: left past the caches.
 template <int K> constexpr u64 kKeepFrom = K == 14 ? 16u << 20 : K == 13 ? 13u << 19 : 6u << 20;
 constexpr u64 kKeepTo = 32u << 20;
-template <int K, bool LAYOUT_B, bool FULL, class T>
-__device__ __forceinline__ void store_result(T* p, u64 e0, u64 limit, u64 n_pad, int wave, int lane, const float (&v)[Geo<K>::R]) {
-  if (sizeof(T) == 4 && n_pad > kKeepFrom<K> && n_pad <= kKeepTo) {
-    keep_apart();
-    store_tile<K, LAYOUT_B, FULL, false>(p, e0, limit, wave, lane, v);
-    keep_apart();
-  } else {
-    store_tile<K, LAYOUT_B, FULL, true>(p, e0, limit, wave, lane, v);
-  }
+// Few entries, where nothing is gained: together with the reader, decode of 2^12 / 2^13, 219933 entries 5.28 -> 5.44 / 5.89 -> 6.12, but 1048576 8.4 -> 8.2 / 8.9 -> 8.6
+// (2^10: no difference).
+template <int K> constexpr u64 kKeepFew = K == 0 ? 0 : 3u << 18;
+template <int K> constexpr bool keeps_results(u64 n_pad) { return n_pad <= kKeepFew<K> || (n_pad > kKeepFrom<K> && n_pad <= kKeepTo); }
+// Decode from sums and counts, one bucket or all buckets of a launch together: by itself, 2^8 / 2^12, 6144000 entries 12.3 -> 12.5 / 11.7 -> 12.4, 9830400 17.4 -> 18.0 /
+// 17.5 -> 18.5, 14745600 23.6 -> 25.0 / 23.8 -> 25.4, 18022400 28.6 -> 29.9 / 29.4 -> 30.1, but 4096000 9.4 -> 9.4 / 9.4 -> 8.2, 21299200 36.6 -> 34.6 / 35.6 -> 34.6, 24576000
+// 42.1 -> 39.3 / 41.9 -> 39.2;  2^14, 12288000 / 18874368 23.3 -> 21.8 / 32.7 -> 31.8.
+template <int K> constexpr bool keeps_finalized(u64 entries) {
+  return entries <= kKeepFew<K> || (K < 14 && entries > 11u << 19 && entries <= 19u << 20);
 }
 
 // Sec. 3.3 encode: out = B^(-1/2) H D x, blockwise; pad of the last block is zero.
@@ -142,7 +142,13 @@ __device__ __forceinline__ void encode_tile(const PathArgs& a, u64 unit, float* 
   const float c = a.scale * lane_sigma(lane, kt < 6 ? kt : 6);
 #pragma unroll
   for (int r = 0; r < R; ++r) v[r] *= c;
-  store_result<K, true, FULL>((Wire*)a.out, unit * T, a.n_pad, a.n_pad, wave, lane, v);
+  if (sizeof(Wire) == 4 && keeps_results<K>(a.n_pad)) {   // one kernel for both: encode of 2^14, 487689 entries 5.06, a kernel each 5.18
+    keep_apart();
+    store_tile<K, true, FULL, false>((Wire*)a.out, unit * T, a.n_pad, wave, lane, v);
+    keep_apart();
+  } else {
+    store_tile<K, true, FULL, true>((Wire*)a.out, unit * T, a.n_pad, wave, lane, v);
+  }
 }
 template <int K, class In, class Wire>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_encode(PathArgs a) {
@@ -221,7 +227,7 @@ __device__ __forceinline__ void load_mean_tile(const PathArgs& a, u64 tile, int 
 }
 
 // Sec. 3.3 / Sec. 4 decode: out = D B^(-1/2) H mean, first n entries kept.  FULL as in encode_tile.
-template <int K, class Out, bool FINALIZE, bool FULL, bool MASKED = false>
+template <int K, class Out, bool FINALIZE, bool FULL, bool MASKED, bool KEEP>
 __device__ __forceinline__ void decode_tile(const PathArgs& a, u64 unit, float* xbuf) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R;
   static_assert(Geo<K>::PARTS == 1, "larger blocks use k_decode_block");
@@ -235,13 +241,14 @@ __device__ __forceinline__ void decode_tile(const PathArgs& a, u64 unit, float* 
 #pragma unroll
   for (int r = 0; r < R; ++r) v[r] *= c;
   apply_signs(v, sg);
-  store_result<K, false, FULL>((Out*)a.out, unit * T, a.n, a.n_pad, wave, lane, v);
+  store_tile<K, false, FULL, !KEEP>((Out*)a.out, unit * T, a.n, wave, lane, v);
 }
-template <int K, class Out, bool FINALIZE, bool MASKED>
+// KEEP is chosen on the host: a kernel for both takes longer, 2^13, 65536 entries 3.83, a kernel each 3.79
+template <int K, class Out, bool FINALIZE, bool MASKED, bool KEEP>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_decode(PathArgs a) {
   __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
-  if (blockIdx.x < a.unit0) with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { decode_tile<K, Out, FINALIZE, true, MASKED>(b, blockIdx.x, xbuf); });
-  else decode_tile<K, Out, FINALIZE, false, MASKED>(a, blockIdx.x, xbuf);
+  if (blockIdx.x < a.unit0) with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { decode_tile<K, Out, FINALIZE, true, MASKED, KEEP>(b, blockIdx.x, xbuf); });
+  else decode_tile<K, Out, FINALIZE, false, MASKED, KEEP>(a, blockIdx.x, xbuf);
 }
 
 // The same for blocks above 2^14 (see k_encode_block).  The input holds whole blocks; FULL = false: the
@@ -492,12 +499,12 @@ __global__ __launch_bounds__(Geo<K>::THREADS) void k_reduce_decode_batched(Batch
   const u64 unit = bucket_of<sizeof(Wire) == 4>(ba, a, blockIdx.x);
   with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { reduce_decode_tile<K, Wire, Wire>(b, unit); });
 }
-template <int K, class Out>
+template <int K, class Out, bool KEEP>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_finalize_decode_batched(BatchArgs ba) {
   PathArgs a;
   const u64 unit = bucket_of(ba, a, blockIdx.x);
   __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
-  with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { decode_tile<K, Out, true, kShardTilesFull<K>, false>(b, unit, xbuf); });
+  with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { decode_tile<K, Out, true, kShardTilesFull<K>, false, KEEP>(b, unit, xbuf); });
 }
 
 }  // namespace ordev

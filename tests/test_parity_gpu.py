@@ -271,11 +271,12 @@ def test_finalize_decode(b, orc, k):
         <= TOL["bf16"]
 
 
-@pytest.mark.parametrize("k,edge", [(9, 6 << 20), (9, 32 << 20), (12, 6 << 20), (12, 32 << 20), (13, 13 << 19), (13, 32 << 20), (14, 16 << 20),
+@pytest.mark.parametrize("k,edge", [(9, 11 << 19), (9, 6 << 20), (9, 19 << 20), (9, 32 << 20), (11, 3 << 18), (12, 3 << 18), (12, 11 << 19), (12, 6 << 20),
+                                    (12, 19 << 20), (12, 32 << 20), (13, 3 << 18), (13, 13 << 19), (13, 32 << 20), (14, 3 << 18), (14, 16 << 20),
                                     (14, 32 << 20), (15, 8 << 20), (16, 8 << 20)])
 def test_sizes_where_the_caches_are_passed_by(b, orc, k, edge):
-    """Encode, decode and decode after second-stage loss on both sides of the sizes where stores (blocks of up to 2^14) and loads (above) begin
-    or end to go past the caches, with a last block cut short: bit for bit what parts of 512 K entries give as calls of their own, and the
+    """Encode, decode, decode after second-stage loss and from sums and counts on both sides of the sizes where stores (blocks of up to 2^14) and
+    loads (above) begin or end to go past the caches, with a last block cut short: bit for bit what parts of 512 K entries give as calls of their own, and the
     first, a middle and the last block against the oracle."""
     B, seed, base, part = 1 << k, 0xF00DFACE12345678, (1 << 33) + 5 * (1 << k), 1 << 19
     for n in (edge - 3, edge + 7):
@@ -283,12 +284,15 @@ def test_sizes_where_the_caches_are_passed_by(b, orc, k, edge):
         gen = torch.Generator(device=dev()).manual_seed(k)
         x = torch.randn(pad, device=dev(), generator=gen).mul_(1e-3)
         m = torch.randint(-2**31, 2**31 - 1, (pad // 32,), device=dev(), generator=gen, dtype=torch.int64).to(torch.int32)
-        for op in ("encode", "decode", "masked"):
+        counts = torch.randint(0, 9, (pad,), device=dev(), generator=gen, dtype=torch.uint8)
+        for op in ("encode", "decode", "masked", "finalize"):
             def call(lo, count, out):
                 if op == "encode":
                     b.or_rht_encode_at(x[lo:], count, k, seed, base + lo, out)
                 elif op == "decode":
                     b.or_rht_decode_at(x[lo:], count, k, seed, base + lo, out)
+                elif op == "finalize":
+                    b.or_finalize_decode(x[lo:], counts[lo:], count, k, seed, base + lo, out)
                 else:
                     b.or_rht_decode_masked(x[lo:], m[lo // 32:], count, k, seed, base + lo, out)
             whole = torch.full((pad if op == "encode" else n,), float("nan"), device=dev())
@@ -297,12 +301,20 @@ def test_sizes_where_the_caches_are_passed_by(b, orc, k, edge):
             for lo in range(0, n, part):
                 call(lo, min(part, n - lo), parts[lo:])
             assert torch.equal(whole, parts), (op, n)
+            if op == "finalize":   # as two buckets of one launch, with the last block whole
+                cut, batched = pad // 3 // B * B, torch.full((pad,), float("nan"), device=dev())
+                b.or_finalize_decode_batched(b.make_stage_buckets([(None, None, x[lo:hi], counts[lo:hi], batched[lo:hi], hi - lo, seed, base + lo)
+                                                                   for lo, hi in ((0, cut), (cut, pad))]), 2, k, False)
+                assert torch.equal(batched[:n], whole), n
             for lo in (0, n // 2 // B * B, (n - 1) // B * B):
                 here = min(B, n - lo)
                 if op == "encode":
                     got, want = whole[lo:lo + B], orc.rht_encode(to_np(x[lo:lo + here]), k, seed, base + lo)
                 else:
                     agg = to_np(x[lo:lo + B])
+                    if op == "finalize":
+                        c = to_np(counts[lo:lo + B]).astype(np.float32)
+                        agg = np.where(c > 0, agg / np.maximum(c, np.float32(1)), np.float32(0))
                     if op == "masked":
                         agg = np.where(np.unpackbits(to_np(m[lo // 32:(lo + B) // 32]).view(np.uint8), bitorder="little").astype(bool), agg, np.float32(0))
                     got, want = whole[lo:lo + here], orc.rht_decode(agg, here, k, seed, base + lo)
