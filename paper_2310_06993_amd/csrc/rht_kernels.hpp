@@ -34,20 +34,29 @@ __device__ __forceinline__ int tile_bits(int k) { return K ? Geo<K>::KT : k; }
 // fused path of 2^10, N = 8 / 24, 3145728 entries 23.9 -> 19.2 / 59.8 -> 46.5, 1 M 13.6 -> 12.8 / 27.9 -> 25.8, 65536 5.95 -> 5.66 / 10.7 -> 9.7, of 2^8, N =
 // 8, 16.8 M 91.8 -> 75.7;  fp32, 2^9, N = 1 / 3, 3145728 entries 7.0 -> 6.3 / 12.7 -> 10.9;  encode, decode of 2^10, 65536 entries 2.67 -> 2.58, 2.81 -> 2.66,
 // bf16 encode, 16.8 M 16.6 -> 14.3;  reduce + decode 0 .. -3 %.  (Not the fp32 forms that add up whole workers first, rht_fused.hpp: they lose registers.)
-// A switch: comparisons one after the other, each behind the code of the size before it, miss in the instruction cache.  us, those -> this, bf16 fused path, N = 8
-// / 24, 2^6, 1 M entries 12.2 -> 12.0 / 24.9 -> 24.6, 2^8, 65536 entries 5.73 -> 5.68 / 9.52 -> 9.35, 2^10, 1 M 12.8 -> 12.5 / 26.0 -> 25.9;  with totals, N = 8, eight buckets
-// of 131072 entries, 2^6 16.7 -> 16.4 (without sizes 16.2), 2^9 16.6 -> 16.9.
-template <int K, class Tile>
+// FIRST = 10: comparisons one after the other, each behind the code of the size before it, for the short kernels of encode and decode; else a switch, where
+// that code is long and a small size would miss in the instruction cache at every comparison.  us, comparisons -> switch, bf16 fused path, N = 8 / 24, 2^6, 1 M entries
+// 12.2 -> 12.0 / 24.9 -> 24.6, 2^8, 65536 entries 5.73 -> 5.68 / 9.52 -> 9.35, 2^10, 1 M 12.8 -> 12.5 / 26.0 -> 25.9;  with totals, N = 8, eight buckets of 131072 entries, 2^6
+// 16.7 -> 16.4 (without sizes 16.2), 2^9 16.6 -> 16.9;  but fp32 encode / decode of 65536 entries, 2^10 2.56 -> 2.62 / 2.66 -> 2.68, 2^8 2.48 -> 2.52 / 2.58 -> 2.62.
+template <int K, int FIRST = 0, class Tile>
 __device__ __forceinline__ void with_block_size(const PathArgs& a, Tile&& tile) {
   if constexpr (K == 0) {
     PathArgs known = a;
-    switch (a.k) {
-      case 5: known.k = 5; return tile(known);
-      case 6: known.k = 6; return tile(known);
-      case 7: known.k = 7; return tile(known);
-      case 8: known.k = 8; return tile(known);
-      case 9: known.k = 9; return tile(known);
-      default: known.k = 10; return tile(known);
+    if constexpr (FIRST > 5) {
+      if (a.k == FIRST) { known.k = FIRST; return tile(known); }
+      with_block_size<K, FIRST - 1>(a, (Tile&&)tile);
+    } else if constexpr (FIRST == 5) {
+      known.k = 5;
+      tile(known);
+    } else {
+      switch (a.k) {
+        case 5: known.k = 5; return tile(known);
+        case 6: known.k = 6; return tile(known);
+        case 7: known.k = 7; return tile(known);
+        case 8: known.k = 8; return tile(known);
+        case 9: known.k = 9; return tile(known);
+        default: known.k = 10; return tile(known);
+      }
     }
   } else {
     tile(a);
@@ -154,7 +163,7 @@ template <int K, class In, class Wire>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_encode(PathArgs a) {
   static_assert(Geo<K>::PARTS == 1, "larger blocks use k_encode_block");
   __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
-  if (blockIdx.x < a.unit0) with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { encode_tile<K, In, Wire, true>(b, blockIdx.x, xbuf); });
+  if (blockIdx.x < a.unit0) with_block_size<K, 10>(a, [&](const PathArgs& b) __attribute__((always_inline)) { encode_tile<K, In, Wire, true>(b, blockIdx.x, xbuf); });
   else encode_tile<K, In, Wire, false>(a, blockIdx.x, xbuf);
 }
 
@@ -247,7 +256,7 @@ __device__ __forceinline__ void decode_tile(const PathArgs& a, u64 unit, float* 
 template <int K, class Out, bool FINALIZE, bool MASKED, bool KEEP>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_decode(PathArgs a) {
   __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
-  if (blockIdx.x < a.unit0) with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { decode_tile<K, Out, FINALIZE, true, MASKED, KEEP>(b, blockIdx.x, xbuf); });
+  if (blockIdx.x < a.unit0) with_block_size<K, 10>(a, [&](const PathArgs& b) __attribute__((always_inline)) { decode_tile<K, Out, FINALIZE, true, MASKED, KEEP>(b, blockIdx.x, xbuf); });
   else decode_tile<K, Out, FINALIZE, false, MASKED, KEEP>(a, blockIdx.x, xbuf);
 }
 
@@ -504,7 +513,7 @@ __global__ __launch_bounds__(Geo<K>::THREADS) void k_finalize_decode_batched(Bat
   PathArgs a;
   const u64 unit = bucket_of(ba, a, blockIdx.x);
   __shared__ float xbuf[Geo<K>::Q > 0 ? Geo<K>::T : 1];
-  with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { decode_tile<K, Out, true, kShardTilesFull<K>, false, KEEP>(b, unit, xbuf); });
+  with_block_size<K, 10>(a, [&](const PathArgs& b) __attribute__((always_inline)) { decode_tile<K, Out, true, kShardTilesFull<K>, false, KEEP>(b, unit, xbuf); });
 }
 
 }  // namespace ordev
