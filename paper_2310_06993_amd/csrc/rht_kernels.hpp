@@ -33,7 +33,7 @@ __device__ __forceinline__ int tile_bits(int k) { return K ? Geo<K>::KT : k; }
 // of code; a branch ahead of every stage kept the compiler from putting one stage's instructions between another's.  us, branches -> this: bf16
 // fused path of 2^10, N = 8 / 24, 3145728 entries 23.9 -> 19.2 / 59.8 -> 46.5, 1 M 13.6 -> 12.8 / 27.9 -> 25.8, 65536 5.95 -> 5.66 / 10.7 -> 9.7, of 2^8, N =
 // 8, 16.8 M 91.8 -> 75.7;  fp32, 2^9, N = 1 / 3, 3145728 entries 7.0 -> 6.3 / 12.7 -> 10.9;  encode, decode of 2^10, 65536 entries 2.67 -> 2.58, 2.81 -> 2.66,
-// bf16 encode, 16.8 M 16.6 -> 14.3;  reduce + decode 0 .. -3 %.  (Not the fp32 forms that add up whole workers first, rht_fused.hpp: they lose registers.)
+// bf16 encode, 16.8 M 16.6 -> 14.3;  bf16 reduce + decode 0 .. -3 %.  (Not the fp32 forms that add up whole workers first, rht_fused.hpp: they lose registers.)
 // FIRST = 10: comparisons one after the other, each behind the code of the size before it, for the short kernels of encode and decode; else a switch, where
 // that code is long and a small size would miss in the instruction cache at every comparison.  us, comparisons -> switch, bf16 fused path, N = 8 / 24, 2^6, 1 M entries
 // 12.2 -> 12.0 / 24.9 -> 24.6, 2^8, 65536 entries 5.73 -> 5.68 / 9.52 -> 9.35, 2^10, 1 M 12.8 -> 12.5 / 26.0 -> 25.9;  with totals, N = 8, eight buckets of 131072 entries, 2^6
@@ -442,7 +442,10 @@ __device__ __forceinline__ void reduce_decode_tile(const PathArgs& a, u64 unit) 
 }
 template <int K, class Wire, class Out>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_reduce_decode(PathArgs a) {
-  with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { reduce_decode_tile<K, Wire, Out>(b, blockIdx.x); });
+  // fp32 by itself: for any size.  us, that -> compiled for each, 2^10, N = 12 / 24 / 32, 901120 entries 11.0 -> 11.5 / 17.8 -> 19.4 / 22.1 -> 24.6, 1 M 11.9 -> 12.2 / 19.6 -> 21.0
+  // / 24.3 -> 26.7, but N = 2, 65536 entries 3.54 -> 3.51, N = 4, 1.2 M 7.3 -> 7.2.  (bf16 and buckets: no such loss.)
+  if constexpr (sizeof(Wire) == 4) reduce_decode_tile<K, Wire, Out>(a, blockIdx.x);
+  else with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { reduce_decode_tile<K, Wire, Out>(b, blockIdx.x); });
 }
 
 // Several buckets of one launch shape class (same N, block size and type) in ONE launch: small buckets
