@@ -42,8 +42,9 @@ thread_local int g_last_hip_error = 0;
 // ------------------------------------------------------------------ streaming masked sum + count
 // Sec. 3.1.1 aggregation with no transform around it: each lane owns VEC consecutive entries (16
 // bytes of one worker's shard), reads the VEC mask bits of every worker and adds under select.
-// U workers are asked for at once (the rule is launch_masked_reduce).  `keep`: the results stay in the L2 for who reads them next.
-template <class Wire, int VEC, int U>
+// U workers are asked for at once, those that are left over two at once, PAIR, or one by one (the rules are at launch_masked_reduce and where
+// k_masked_reduce_batched is launched).  `keep`: the results stay in the L2 for who reads them next.
+template <class Wire, int VEC, int U, bool PAIR>
 __device__ __forceinline__ void masked_reduce_at(const Wire* __restrict__ shards, const uint32_t* __restrict__ masks,
                                                  int N, u64 L, float* __restrict__ sum_out,
                                                  uint8_t* __restrict__ count_out, u64 e, bool keep) {
@@ -63,14 +64,16 @@ __device__ __forceinline__ void masked_reduce_at(const Wire* __restrict__ shards
 #pragma unroll
     for (int u = 0; u < W; ++u) {
       x[u] = __builtin_nontemporal_load((const vec_t*)(shards + (u64)(i + u) * L + e));
-      m[u] = masks[(u64)(i + u) * words + (e >> 5)];
+      m[u] = masks[(u64)(i + u) * words + (e >> 5)] >> sh;
     }
-    __builtin_amdgcn_sched_barrier(0);   // all of them, before the first is added
+    // bf16: all of them, before the first is added; the compiler mixes them otherwise (fp32: it does not, and its own order is 2 to 4 % better in
+    // launches of few entries).  us, with the mean, without -> with, N = 4 / 8 / 24, 20000 entries 4.50 -> 4.13 / 5.30 -> 4.58 / 8.83 -> 6.48
+    if (sizeof(Wire) == 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < W; ++u)
 #pragma unroll
       for (int j = 0; j < VEC; ++j) {
-        const bool got = (m[u] >> sh >> j) & 1u;
+        const bool got = (m[u] >> j) & 1u;
         float f;
         if constexpr (sizeof(Wire) == 4) f = x[u][j]; else f = __builtin_bit_cast(float, (uint32_t)x[u][j] << 16);
         acc[j] += got ? f : 0.0f;
@@ -80,8 +83,8 @@ __device__ __forceinline__ void masked_reduce_at(const Wire* __restrict__ shards
   };
   while (i + U <= N) add(std::integral_constant<int, U>{});
   if (U > 4 && i + 4 <= N) add(std::integral_constant<int, 4>{});
-  if (U > 2 && i + 2 <= N) add(std::integral_constant<int, 2>{});
-  if (U > 1 && i < N) add(std::integral_constant<int, 1>{});
+  if (U > 2 && PAIR && i + 2 <= N) add(std::integral_constant<int, 2>{});
+  if (U > 1) while (i < N) add(std::integral_constant<int, 1>{});
   typedef float f4 __attribute__((ext_vector_type(4)));
   f4 s[VEC / 4];
   uint32_t c[VEC / 4];
@@ -118,7 +121,7 @@ template <class Wire, int VEC, int U>
 __global__ __launch_bounds__(256) void k_masked_reduce(const Wire* __restrict__ shards,
                                                        const uint32_t* __restrict__ masks, int N, u64 L,
                                                        float* __restrict__ sum_out, uint8_t* __restrict__ count_out, bool keep) {
-  masked_reduce_at<Wire, VEC, U>(shards, masks, N, L, sum_out, count_out, ((u64)blockIdx.x * 256 + threadIdx.x) * VEC, keep);
+  masked_reduce_at<Wire, VEC, U, true>(shards, masks, N, L, sum_out, count_out, ((u64)blockIdx.x * 256 + threadIdx.x) * VEC, keep);
 }
 
 // several buckets in one launch (a 25 MiB bucket is a few hundred workgroups here): descriptors in the kernel
@@ -136,12 +139,16 @@ struct ReduceBatch {
   ReduceBucket b[ordev::kMaxBatch];
 };
 static_assert(sizeof(ReduceBatch) <= 4096, "kernel arguments are limited to 4 KB");
-template <class Wire, int VEC>
+// Four workers at once and results past the caches, whatever the size.  What is left over, pair -> one by one, us, bf16: N = 2 / 3 / 7, 24 buckets of 16384
+// entries 3.98 -> 4.22 / 4.65 -> 4.99 / 5.68 -> 6.14, 24 of 819200 34.4 -> 33.5 / 39.3 -> 39.3 / 63.6 -> 63.1, N = 2, two of 26188800 97.2 -> 86.1;  fp32: N = 2 / 6, 24 of 819200
+// 42.1 -> 44.1 / 95.5 -> 95.8.
+constexpr u64 kBatchPairTo = 2048;   // workgroups
+template <class Wire, int VEC, bool PAIR>
 __global__ __launch_bounds__(256) void k_masked_reduce_batched(ReduceBatch rb) {
   const uint32_t x = blockIdx.x;
   int j = 0;
   while (j + 1 < rb.n && rb.start[j + 1] <= x) ++j;
-  masked_reduce_at<Wire, VEC, 4>((const Wire*)rb.b[j].shards, rb.b[j].masks, rb.N, rb.b[j].L, rb.b[j].sum, rb.b[j].count,
+  masked_reduce_at<Wire, VEC, 4, PAIR>((const Wire*)rb.b[j].shards, rb.b[j].masks, rb.N, rb.b[j].L, rb.b[j].sum, rb.b[j].count,
                               ((u64)(x - rb.start[j]) * 256 + threadIdx.x) * VEC, false);
 }
 
@@ -840,8 +847,9 @@ or_status stage_batched_impl(bool reduce, const or_stage_bucket* buckets, int n,
     seen += m;
     hipError_t e;
     if (!reduce) e = f(ba, wgs, s, pos);
-    else if (bf16) e = orhost::launch_kernel(k_masked_reduce_batched<uint16_t, 8>, dim3((unsigned)wgs), dim3(256), s, pos, rb);
-    else e = orhost::launch_kernel(k_masked_reduce_batched<float, 4>, dim3((unsigned)wgs), dim3(256), s, pos, rb);
+    else if (bf16) e = orhost::launch_kernel(wgs <= kBatchPairTo ? k_masked_reduce_batched<uint16_t, 8, true> : k_masked_reduce_batched<uint16_t, 8, false>,
+                                             dim3((unsigned)wgs), dim3(256), s, pos, rb);
+    else e = orhost::launch_kernel(k_masked_reduce_batched<float, 4, true>, dim3((unsigned)wgs), dim3(256), s, pos, rb);
     if (e) return finish(e);
   }
   return OR_OK;

@@ -157,6 +157,26 @@ def test_empty_buckets_among_many_and_totals(b, orc, k, kind):
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("kind,N,last", [("bf16", 2, 1024 * 2048), ("bf16", 2, 1024 * 2048 + 32), ("bf16", 7, 1024 * 2048), ("bf16", 7, 1024 * 2048 + 32),
+                                         ("bf16", 1, 1024 * 2048 + 32), ("f32", 3, 1024 * 1024 + 32)])
+def test_masked_reduce_batched_forms(b, kind, N, last):
+    """Two buckets of 1024 workgroups and of as many or one more, where the way changes in which the workers past the last four are asked for:
+    the bits of the single call."""
+    dt = torch.float32 if kind == "f32" else torch.bfloat16
+    gen = torch.Generator(device=dev()).manual_seed(N + last)
+    items, refs = [], []
+    for L in (1024 * (1024 if kind == "f32" else 2048), last):
+        x = torch.randn((N, L), device=dev(), generator=gen).to(dt)
+        m = torch.randint(-2**31, 2**31 - 1, (N, L // 32), device=dev(), generator=gen, dtype=torch.int64).to(torch.int32)
+        ref = torch.empty(L, device=dev()), torch.empty(L, dtype=torch.uint8, device=dev())
+        (b.or_masked_reduce if kind == "f32" else b.or_masked_reduce_bf16)(x, m, N, L, *ref)
+        refs.append(ref)
+        items.append((x, m, torch.full_like(ref[0], float("nan")), torch.full_like(ref[1], 255), None, L, 0, 0))
+    b.or_masked_reduce_batched(b.make_stage_buckets(items), 2, N, kind == "bf16")
+    for item, (total, count) in zip(items, refs):
+        assert torch.equal(item[2].view(torch.int32), total.view(torch.int32)) and torch.equal(item[3], count)
+
+
 @pytest.mark.parametrize("k,kind", [(12, "f32"), (12, "bf16"), (9, "f32"), (14, "f32"), (15, "bf16")])
 def test_masked_reduce_and_finalize_decode_batched(b, orc, k, kind):
     """or_masked_reduce_batched and or_finalize_decode_batched on many buckets (some empty) equal the single
