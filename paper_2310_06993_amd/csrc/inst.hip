@@ -60,7 +60,7 @@ OR_F32_LAUNCHER(mdec_f32, PathArgs, keeps_results<K>(a.n_pad), k_decode, float, 
 #define OR_DEC(Out, FIN, MASKED) (k_decode<K, Out, FIN, MASKED, false>)
 #define OR_XFORM_LAUNCHER OR_LAUNCHER
 #else
-#define OR_DEC(Out, FIN, MASKED) (k_decode_block<K, Out, FIN, MASKED>)
+#define OR_DEC(Out, FIN, MASKED) (a.n_pad > kStreamFrom ? k_decode_block<K, Out, FIN, MASKED, true> : k_decode_block<K, Out, FIN, MASKED, false>)
 #define OR_XFORM_LAUNCHER OR_BLOCK_LAUNCHER
 OR_BLOCK_LAUNCHER(enc_f32, (k_encode_block<K, float, float>))
 OR_BLOCK_LAUNCHER(dec_f32, OR_DEC(float, false, false))
@@ -275,7 +275,9 @@ hipError_t fusb_f32(const BatchArgs& a, unsigned long long units, hipStream_t s,
   const dim3 grid((unsigned)half_grid(blocks));
   if (K == 15) return launch_kernel(k_fused_f32_half_batched<K>, grid, dim3(1024), s, pos, b);
   if (hipError_t e = launch_kernel(k_fused_f32_half_batched<K>, grid, dim3(1024), s, pos & LAUNCH_FIRST, b)) return e;
-  if constexpr (K == 16) return launch_kernel(k_decode_block_batched<K>, dim3((unsigned)blocks), dim3(G::THREADS), s, pos & LAUNCH_LAST, b);
+  if constexpr (K == 16)
+    return launch_kernel(blocks << K > kStreamFrom ? k_decode_block_batched<K, true> : k_decode_block_batched<K, false>, dim3((unsigned)blocks),
+                         dim3(G::THREADS), s, pos & LAUNCH_LAST, b);
   return hipErrorInvalidValue;   // not reached
 }
 #endif

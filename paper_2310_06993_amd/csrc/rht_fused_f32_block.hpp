@@ -272,13 +272,13 @@ __global__ __launch_bounds__(1024) void k_fused_f32_half_batched(BatchArgs ba) {
   fused_f32_half<K, true>(a, unit << K, h);
 }
 // the means of 2^16 blocks in the buckets' outputs, decoded in place
-template <int K>
+template <int K, bool STREAM>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_decode_block_batched(BatchArgs ba) {
   __shared__ float xbuf[2][Geo<K>::T];
   PathArgs a;
   const u64 unit = bucket_of(ba, a, blockIdx.x);
   a.in = a.out;
-  decode_block<K, float, false, true, false>(a, unit, xbuf);
+  decode_block<K, float, false, true, false, STREAM>(a, unit, xbuf);
 }
 
 }  // namespace ordev

@@ -262,21 +262,14 @@ __global__ __launch_bounds__(Geo<K>::THREADS) void k_decode(PathArgs a) {
 
 // The same for blocks above 2^14 (see k_encode_block).  The input holds whole blocks; FULL = false: the
 // output is cut short inside this block.
-template <int K, class Out, bool FINALIZE, bool FULL, bool MASKED>
+template <int K, class Out, bool FINALIZE, bool FULL, bool MASKED, bool STREAM>
 __device__ __forceinline__ void decode_block(const PathArgs& a, u64 blk, float (*xbuf)[Geo<K>::T]) {
   constexpr int T = Geo<K>::T, R = Geo<K>::R, HB = Geo<K>::HB, PARTS = Geo<K>::PARTS;
   const int wave = wave_id(), lane = lane_id(), kt = Geo<K>::KT;
   const u64 tile0 = blk << HB;
   float v[PARTS][R];
-  if (a.n_pad > kStreamFrom) {
 #pragma unroll
-    for (int q = 0; q < PARTS; ++q) load_mean_tile<K, FINALIZE, true, MASKED, true>(a, tile0 + q, wave, lane, v[q]);
-  } else {
-    keep_apart();
-#pragma unroll
-    for (int q = 0; q < PARTS; ++q) load_mean_tile<K, FINALIZE, true, MASKED, false>(a, tile0 + q, wave, lane, v[q]);
-    keep_apart();
-  }
+  for (int q = 0; q < PARTS; ++q) load_mean_tile<K, FINALIZE, true, MASKED, STREAM>(a, tile0 + q, wave, lane, v[q]);
   uint32_t slo, shi;
   block_sign_words<K>(a.seed, a.base + tile0 * T + (u64)wave * Geo<K>::WAVE_ENTRIES, slo, shi);
   across_tiles<PARTS, R>(v);
@@ -290,12 +283,14 @@ __device__ __forceinline__ void decode_block(const PathArgs& a, u64 blk, float (
     store_tile<K, false, FULL, true>((Out*)a.out, (tile0 + p) * T, a.n, wave, lane, v[p]);
   }
 }
-template <int K, class Out, bool FINALIZE, bool MASKED>
+// STREAM is chosen on the host: a kernel for both takes longer, 2^15, one block with sums and counts 9.30, a kernel each 9.16, reduce + decode of 16 blocks of
+// three workers 14.3, 14.0
+template <int K, class Out, bool FINALIZE, bool MASKED, bool STREAM>
 __global__ __launch_bounds__(Geo<K>::THREADS) void k_decode_block(PathArgs a) {
   static_assert(Geo<K>::PARTS > 1, "blocks above 2^14");
   __shared__ float xbuf[2][Geo<K>::T];
-  if ((u64)blockIdx.x << Geo<K>::HB < a.unit0) decode_block<K, Out, FINALIZE, true, MASKED>(a, blockIdx.x, xbuf);
-  else decode_block<K, Out, FINALIZE, false, MASKED>(a, blockIdx.x, xbuf);
+  if ((u64)blockIdx.x << Geo<K>::HB < a.unit0) decode_block<K, Out, FINALIZE, true, MASKED, STREAM>(a, blockIdx.x, xbuf);
+  else decode_block<K, Out, FINALIZE, false, MASKED, STREAM>(a, blockIdx.x, xbuf);
 }
 
 // acc += value where the worker's copy arrived.  Arrivals are counted as `full` (workers whose whole
