@@ -172,17 +172,19 @@ __global__ __launch_bounds__(256) void k_masked_reduce_batched(ReduceBatch rb) {
 // only up to 10 MB: bf16, N = 16, 2700000 entries 25.6 -> 26.2, N = 24, 4000000 44.9 -> 46.0;  fp32, N = 8 / 24, 3194880 entries 27.1 -> 27.8 / 59.9 -> 62.9, 4600000
 // 39.1 -> 39.5 / 91.0 -> 92.9, but 2100000 entries 19.6 -> 19.3 / 42.3 -> 41.6, and with fewer, fp32, N = 5, 2700000 entries 19.2 -> 18.8.
 constexpr u64 kReduceFew = 256, kReduceTwoFrom = 950, kReduceTwoTo = 1300, kReduceMany = 3000, kReduceManyBf16 = 4096;
-inline bool keep_results(u64 bytes, int bytes_read) {   // sum and counts; of all workers an entry
-  return bytes <= (bytes_read <= 12 ? 160u << 20 : bytes_read <= 16 ? 64u << 20 : bytes_read < 32 ? 24u << 20 : 10u << 20);
+// (Not where the decode of larger blocks comes next, which gains from what it finds in the caches: up to 24 MB there.  us, reduce + decode of 2^16, 45 blocks, fp32,
+// N = 8 / 24 40.3 -> 38.6 / 72.5 -> 70.7, bf16, N = 16 / 32 40.4 -> 39.1 / 56.5 -> 54.9.)
+inline bool keep_results(u64 bytes, int bytes_read, bool for_decode) {   // sum and counts; of all workers an entry
+  return bytes <= (bytes_read <= 12 ? 160u << 20 : bytes_read <= 16 ? 64u << 20 : bytes_read < 32 || for_decode ? 24u << 20 : 10u << 20);
 }
 template <class Wire, int VEC>
 hipError_t launch_masked_reduce(const void* shards, const uint32_t* masks, int N, u64 L, float* sum_out,
-                                uint8_t* count_out, hipStream_t s, int pos) {
+                                uint8_t* count_out, hipStream_t s, int pos, bool for_decode) {
   if (L == 0) return hipSuccess;
   const u64 threads = (L + VEC - 1) / VEC;
   const u64 blocks = (threads + 255) / 256;
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  const bool keep = keep_results(L * 5, N * (int)sizeof(Wire));
+  const bool keep = keep_results(L * 5, N * (int)sizeof(Wire), for_decode);
   const bool one = sizeof(Wire) == 4 ? blocks >= kReduceMany : (N >= 16 && blocks >= kReduceManyBf16) || (N == 2 && !keep);
   auto kernel = k_masked_reduce<Wire, VEC, 4>;
   if (blocks <= kReduceFew && N >= 8) kernel = k_masked_reduce<Wire, VEC, 8>;
@@ -408,7 +410,7 @@ or_status masked_reduce_impl(const T* shards, const uint32_t* masks, int N, u64 
     return OR_ERR_SHAPE;
   constexpr int VEC = 16 / sizeof(T);
   return finish(launch_masked_reduce<T, VEC>(shards, masks, N, L, sum_out, count_out, (hipStream_t)stream,
-                                             orhost::LAUNCH_ONLY));
+                                             orhost::LAUNCH_ONLY, false));
 }
 
 size_t workspace_bytes(u64 L, int k) {
@@ -494,7 +496,7 @@ or_status run_path(bool fused, const T* in, const uint32_t* masks, int N, u64 L,
     return finish((bf16 ? t->reduce_decode_bf16 : t->reduce_decode_f32)(a, units, s, first | last));
   uint8_t* cnt = count_out ? count_out : ws_cnt;
   constexpr int VEC = 16 / sizeof(T);
-  if (hipError_t e = launch_masked_reduce<T, VEC>(in, masks, N, L, ws_f32, cnt, s, first)) return finish(e);
+  if (hipError_t e = launch_masked_reduce<T, VEC>(in, masks, N, L, ws_f32, cnt, s, first, true)) return finish(e);
   d.count_in = cnt;
   if (total) {
     u64 blocks = (L / 16 + 255) / 256;
