@@ -160,6 +160,8 @@ __device__ __forceinline__ void fused_each(const PathArgs& a, u64 first_unit, u6
   } else {
     if ((unit + 1) * Geo<K>::T <= a.n_pad)
       with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, true>(b, unit, wave, tiles, xbuf, missing); });
+    else if constexpr (sizeof(In) == 2)   // the tile that is cut short too (figures below); fp32, 2^8, N = 2 / 3, 3146496 entries, for any size -> this 10.8 -> 11.6 / 13.0 -> 14.5
+      with_block_size<K, 0, 9>(a, [&](const PathArgs& b) __attribute__((always_inline)) { fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, false>(b, unit, wave, tiles, xbuf, missing); });
     else fused_each_tile<K, In, PREFETCH, TOTAL, SLOTS, false>(a, unit, wave, tiles, xbuf, missing);
   }
 }
@@ -338,7 +340,10 @@ __device__ __forceinline__ void fused_each_groups(const PathArgs& a, u64 unit) {
   } else {
     if ((unit + 1) * Geo<K>::T <= a.n_pad)
       with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { fused_each_groups_tile<K, In, G, TOTAL, true>(b, unit, grp, wave, x, y, &missing, &lossy); });
-    else fused_each_groups_tile<K, In, G, TOTAL, false>(a, unit, grp, wave, x, y, &missing, &lossy);
+    else   // For any size its chain was the launch's.  us, before whole tiles were compiled for each size -> for any size -> this, 2^8: bf16, N = 3 / 12, 27392 entries
+           // 5.36 -> 5.60 -> 5.14 / 7.92 -> 8.23 -> 7.31, N = 8, 1 M 19.3 -> 18.8 -> 15.9;  fp32, N = 3, 27392 entries 5.24 -> 5.39 -> 5.22, 262912 5.72 -> 5.85 -> 5.94, 1 M 9.4
+           // -> 9.1 -> 8.3
+      with_block_size<K, 0, 9>(a, [&](const PathArgs& b) __attribute__((always_inline)) { fused_each_groups_tile<K, In, G, TOTAL, false>(b, unit, grp, wave, x, y, &missing, &lossy); });
   }
 }
 template <int K, class In, int G>

@@ -38,7 +38,7 @@ __device__ __forceinline__ int tile_bits(int k) { return K ? Geo<K>::KT : k; }
 // that code is long and a small size would miss in the instruction cache at every comparison.  us, comparisons -> switch, bf16 fused path, N = 8 / 24, 2^6, 1 M entries
 // 12.2 -> 12.0 / 24.9 -> 24.6, 2^8, 65536 entries 5.73 -> 5.68 / 9.52 -> 9.35, 2^10, 1 M 12.8 -> 12.5 / 26.0 -> 25.9;  with totals, N = 8, eight buckets of 131072 entries, 2^6
 // 16.7 -> 16.4 (without sizes 16.2), 2^9 16.6 -> 16.9;  but fp32 encode / decode of 65536 entries, 2^10 2.56 -> 2.62 / 2.66 -> 2.68, 2^8 2.48 -> 2.52 / 2.58 -> 2.62.
-template <int K, int FIRST = 0, class Tile>
+template <int K, int FIRST = 0, int LAST = 10, class Tile>
 __device__ __forceinline__ void with_block_size(const PathArgs& a, Tile&& tile) {
   if constexpr (K == 0) {
     PathArgs known = a;
@@ -55,7 +55,7 @@ __device__ __forceinline__ void with_block_size(const PathArgs& a, Tile&& tile) 
         case 7: known.k = 7; return tile(known);
         case 8: known.k = 8; return tile(known);
         case 9: known.k = 9; return tile(known);
-        default: known.k = 10; return tile(known);
+        default: known.k = LAST; return tile(known);
       }
     }
   } else {
