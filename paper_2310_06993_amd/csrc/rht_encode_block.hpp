@@ -77,15 +77,15 @@ __device__ __forceinline__ void encode_block_bf16(const PathArgs& a, u64 blk, in
   const uint32_t pick = odd ? 0x03020706u : 0x05040100u;   // bytes 0..3: our pair, 4..7: the neighbour's
 #pragma unroll
   for (int turn = 0; turn < E::P / SPLIT; ++turn) {
-    const int s = SPLIT == 1 ? turn ^ (turn >> 1) : part0 + turn;   // 0 1 3 2; bit 0: the block's highest entry bit
-    if (K == 16 && (SPLIT == 1 ? turn == 2 : turn == 0 && (part0 & 2))) {   // e14 changes: minus the entries of the second products
+    const int s = SPLIT == 1 ? turn ^ (turn >> 1) : part0 + turn;   // 0 1 3 2; bit 0: e8, bit 1: e9
+    if (K == 16 && (SPLIT == 1 ? turn == 2 : turn == 0 && (part0 & 2))) {   // e9 changes: minus the entries of the second products
 #pragma unroll
       for (int q = 1; q < E::LOADS; q += 2)
 #pragma unroll
         for (int d = 0; d < 4; ++d) p[q][d] ^= 0x80008000u;
     }
     // the +-1 operand: lane l holds column n = l & 15, rows 8 (l >> 4) + 0..7; n0 n1 n2 pair with the entry's place in the load, n3
-    // with lane bit 4 (e7), the part's highest entry bit with lane bit 5
+    // with lane bit 4 (e7), e8 of the part with lane bit 5
     int lane_t = lane;
     asm volatile("" : "+v"(lane_t));   // formed here, not kept in registers all along
     const uint32_t n1 = lane_t & 2 ? 0x80008000u : 0u, n2 = lane_t & 4 ? 0x80008000u : 0u;

@@ -103,6 +103,7 @@ __device__ __forceinline__ void lds_a(float (&v)[16], float* x, int wave, int la
 }
 template <int K, class In, bool STORE>
 __device__ __forceinline__ void lds_m(float (&v)[16], float* x, int wave, int lane) {
+  static_assert(FTile<K, In>::Q <= 1, "tiles of 2^14 entries have no layouts but A");
   typedef FTile<K, In> F;
   float* p = x + wave * F::PART + (lane & 3) * F::ROW + ((lane >> 2) & (F::V - 1)) + (lane >> (2 + F::VB)) * (4 * F::ROW);
 #pragma unroll
@@ -112,6 +113,7 @@ __device__ __forceinline__ void lds_m(float (&v)[16], float* x, int wave, int la
 }
 template <int K, class In, bool STORE>
 __device__ __forceinline__ void lds_b(float (&v)[16], float* x, int wave, int lane) {
+  static_assert(FTile<K, In>::Q <= 1, "tiles of 2^14 entries have no layouts but A");
   typedef FTile<K, In> F;
   float* p = x + F::padded(wire_wave_entry<K, In>(wave)) + lane;
 #pragma unroll

@@ -87,9 +87,9 @@ def test_encode_decode_bf16(b, orc, k):
 
 @pytest.mark.parametrize("k,blocks,tail", [(16, 1, 1), (16, 2, 0), (16, 3, -1), (16, 258, 0), (16, 513, 16385), (15, 1, 7),
                                            (15, 514, 0), (15, 515, 1025)])
-def test_encode_bf16_large_blocks_walked_over(b, orc, k, blocks, tail):
-    """The bf16 encode of 2^15 / 2^16 blocks: one block, more blocks than workgroups (256 / 512 of them walk over the
-    blocks), a last block cut short at an odd entry in different tiles and wavefronts, and in place."""
+def test_encode_bf16_large_blocks(b, orc, k, blocks, tail):
+    """The bf16 encode of 2^15 / 2^16 blocks, one workgroup each: one block, more blocks than are on the GPU at a time (512), a last block cut
+    short at an odd entry in different parts and wavefronts, and in place."""
     B = 1 << k
     n = blocks * B - (B - tail if tail > 0 else -tail)
     rng = np.random.default_rng(500 + k + blocks)
@@ -208,7 +208,8 @@ def test_integer_round_trip_is_bit_exact(b, k):
                                       ("bf16", 13, 949 * 2048 + 32), ("bf16", 14, 1299 * 2048), ("bf16", 13, 1299 * 2048), ("bf16", 13, 1299 * 2048 + 32)])
 def test_masked_reduce_forms(b, kind, N, L):
     """The masked reduce around the launch sizes where the number of workers asked for at once changes (256, 950, 1300, 3000, 4096 workgroups), and
-    where sum and counts no longer stay in the caches (10, 24, 64, 160 MB, by the bytes read an entry), then the mean: the same additions in the same order as a loop over the workers, so the same bits."""
+    where sum and counts no longer stay in the caches (10, 24, 64, 160 MB, by the bytes read an entry), then the mean: the same additions in the
+    same order as a loop over the workers, so the same bits."""
     gen = torch.Generator(device=dev()).manual_seed(L % 1000 + N)
     x = torch.randn((N, L), device=dev(), generator=gen).to(torch.float32 if kind == "f32" else torch.bfloat16)
     masks = torch.randint(-2**31, 2**31 - 1, (N, L // 32), device=dev(), generator=gen, dtype=torch.int64).to(torch.int32)
