@@ -168,11 +168,13 @@ constexpr int kEachGroups = K == 0 ? 16 : K == 11 || K == 12 ? 4 : 1;
 constexpr int kFewestGroups = K == 0 ? 2 : 4;
 template <class In, int GR>
 hipError_t launch_each_groups(int g, const PathArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  if (K == 0 && sizeof(In) == 4 && a.k > 9) return hipErrorInvalidValue;   // cannot happen (sum_first_wins): the kernel knows no other sizes
   if constexpr (GR > kFewestGroups) if (g < GR) return launch_each_groups<In, GR / 2>(g, a, units, s, pos);
   return launch_kernel(k_fused_each_groups<K, In, GR>, dim3((unsigned)units), dim3(G::THREADS * GR), s, pos, a);
 }
 template <class In, int GR>
 hipError_t launch_each_groups(int g, const BatchArgs& a, unsigned long long units, hipStream_t s, int pos) {
+  if (K == 0 && sizeof(In) == 4 && a.k > 9) return hipErrorInvalidValue;   // cannot happen (sum_first_wins): the kernel knows no other sizes
   if constexpr (GR > kFewestGroups) if (g < GR) return launch_each_groups<In, GR / 2>(g, a, units, s, pos);
   return launch_kernel(k_fused_each_groups_batched<K, In, GR>, dim3((unsigned)units), dim3(G::THREADS * GR), s, pos, a);
 }

@@ -338,11 +338,16 @@ __device__ __forceinline__ void fused_each_groups(const PathArgs& a, u64 unit) {
   if constexpr (kShardTilesFull<K>) {
     fused_each_groups_tile<K, In, G, TOTAL, true>(a, unit, grp, wave, x, y, &missing, &lossy);
   } else {
+    // The tile that is cut short too, bf16: for any size its chain was the launch's.  us, before whole tiles were compiled for each size -> for any size ->
+    // this, 2^8, N = 3 / 12, 27392 entries 5.36 -> 5.60 -> 5.14 / 7.92 -> 8.23 -> 7.31, N = 8, 1 M 19.3 -> 18.8 -> 15.9.
+    // fp32 (blocks below 2^10, two to five workers): the fewest code.  As a share of what it took before there were sizes, 2^6 .. 2^9, N = 4, whole tiles of several
+    // buckets / of one / cut tiles of several / of one: bf16's way 1.03 / 0.98 / 1.10 / 1.04, a switch and one form for cut tiles 1.03 / 0.98 / 1.03 / 1.02, this 0.99 / 0.96 /
+    // 1.03 / 1.01.
+    constexpr bool F32 = sizeof(In) == 4;
     if ((unit + 1) * Geo<K>::T <= a.n_pad)
-      with_block_size<K>(a, [&](const PathArgs& b) __attribute__((always_inline)) { fused_each_groups_tile<K, In, G, TOTAL, true>(b, unit, grp, wave, x, y, &missing, &lossy); });
-    else   // For any size its chain was the launch's.  us, before whole tiles were compiled for each size -> for any size -> this, 2^8: bf16, N = 3 / 12, 27392 entries
-           // 5.36 -> 5.60 -> 5.14 / 7.92 -> 8.23 -> 7.31, N = 8, 1 M 19.3 -> 18.8 -> 15.9;  fp32, N = 3, 27392 entries 5.24 -> 5.39 -> 5.22, 262912 5.72 -> 5.85 -> 5.94, 1 M 9.4
-           // -> 9.1 -> 8.3
+      with_block_size<K, F32 ? 9 : 0>(a, [&](const PathArgs& b) __attribute__((always_inline)) { fused_each_groups_tile<K, In, G, TOTAL, true>(b, unit, grp, wave, x, y, &missing, &lossy); });
+    else if constexpr (F32) fused_each_groups_tile<K, In, G, TOTAL, false>(a, unit, grp, wave, x, y, &missing, &lossy);
+    else
       with_block_size<K, 0, 9>(a, [&](const PathArgs& b) __attribute__((always_inline)) { fused_each_groups_tile<K, In, G, TOTAL, false>(b, unit, grp, wave, x, y, &missing, &lossy); });
   }
 }
